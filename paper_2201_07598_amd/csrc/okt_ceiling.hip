@@ -83,7 +83,7 @@ __global__ __launch_bounds__(CEIL_BLOCK) void stream_sum_kernel(
 // The memory traffic of the batched sparse reduce without its arithmetic.  Same
 // launch shape (one 512-thread workgroup per tile, grid = tiles x regions) and the
 // same slice table, so the same pieces of the same arrays are read by the same
-// number of waves, in the same way: the slice starts and lengths of up to 256
+// number of waves: the slice starts and lengths of up to 256
 // contributions are staged in LDS, slice q goes to wave q mod 8, a wave reads a
 // slice 64 consecutive entries at a time and keeps ten such blocks, across its
 // slices, in flight, index and value together; every entry is then written to the

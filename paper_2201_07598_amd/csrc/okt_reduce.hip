@@ -9,17 +9,15 @@
 //     of a call run side by side, so their latency is paid once.
 //  2. reduce_tile_kernel: a workgroup owns one tile.  Its slice of every
 //     contribution is known from the table, so all its entries are addressed up
-//     front: the slices go round-robin to the waves, a wave reads a slice 64
-//     consecutive entries at a time and keeps several such blocks, across its
-//     slices, in flight.  Entries are summed with LDS fp64 atomic adds.  Where the region is densely hit the accumulator of a slot is
-//     the slot itself.  Where it is sparsely hit the tile is wider than the
-//     accumulator array: a first sweep marks the hit slots in a bitmap, the
-//     popcount prefix of the bitmap ranks them, and the second sweep sums into
-//     accumulator [rank].  The tile is then written out in index order; its place
-//     in the output comes from the two-level chained scan over tile counts.
-// Traffic: every input entry is read once from HBM (the second sweep hits in
-// cache), every output entry is written once, plus 4 B per slot if the dense
-// region is requested.
+//     front, read with 16-byte loads all in flight and kept in registers.  Entries are
+//     summed with LDS fp64 atomic adds.  Where the region is densely hit the
+//     accumulator of a slot is the slot itself.  Where it is sparsely hit the tile is
+//     wider than the accumulator array: the hit slots are marked in a bitmap, the popcount prefix
+//     of the bitmap ranks them, and the entries are summed into accumulator [rank].
+//     The tile is then written out in index order; its place in the output comes from the two-level chained scan over tile counts.
+// Traffic: every input entry is read once (tiles with more entries than registers
+// hold read them twice), every output entry is written once, plus 4 B per slot if
+// the dense region is requested.
 #include "okt_device.h"
 #include "okt_search.h"
 #include "okt_sizes.h"
@@ -27,8 +25,6 @@
 #include <type_traits>
 
 namespace okt {
-
-constexpr int RED_WAVES = RED_BLOCK / WAVE;
 
 struct RegionView {
     uint32_t lo, hi, width, ntiles;
@@ -48,14 +44,17 @@ __device__ __forceinline__ RegionView region_view(const uint32_t* lo_hi, uint32_
 
 // table[region][t][p] = number of entries of contribution p with index below
 // lo + t * slots (clipped to hi), for t = 0 .. ntiles.
-// from_guess: a launch with so many boundaries that it is bound by the number of
-// probes, not by the latency of one search, starts every search from a guess.
+// Every search starts from a guess, which makes it two or three waits and lines of
+// memory instead of a bisection's fifteen: 35 boundaries x 16 contributions x 490
+// regions in 33 us against 49 with a gallop of single probes from the same guess, 102
+// against 129 us for 55 x 64 x 373; a lone region (317 x 32), reduced in 26.1 us
+// instead of 26.9 with plain bisections.
 __global__ __launch_bounds__(256) void reduce_slices_kernel(
     const uint32_t* __restrict__ idx_cat, const uint64_t* __restrict__ seg_begin,
     const uint64_t* __restrict__ seg_end, uint32_t seg_stride,
     const uint32_t* __restrict__ lo_hi, uint32_t lo0, uint32_t hi0, uint32_t P,
     uint32_t max_width, uint32_t slots, char* ws, uint32_t ws_region_bytes,
-    uint32_t table_offset, uint32_t spin_limit, uint32_t from_guess) {
+    uint32_t table_offset, uint32_t spin_limit) {
     const uint32_t region = blockIdx.y;
     const RegionView r = region_view(lo_hi, lo0, hi0, region, max_width, slots);
     uint32_t* table = (uint32_t*)(ws + (size_t)region * ws_region_bytes + table_offset);
@@ -80,8 +79,7 @@ __global__ __launch_bounds__(256) void reduce_slices_kernel(
         // over the region (both factors are below 2^32)
         const uint64_t guess = cb + (r.width ? (ce - cb) * (bound - r.lo) / r.width : 0);
         table[(size_t)t * P + p] =
-            (uint32_t)((from_guess ? lower_bound_near(idx_cat, cb, ce, (uint32_t)bound, guess)
-                                   : lower_bound_idx(idx_cat, cb, ce, (uint32_t)bound)) - cb);
+            (uint32_t)(lower_bound_near(idx_cat, cb, ce, (uint32_t)bound, guess) - cb);
     }
 }
 
@@ -134,14 +132,26 @@ __global__ __launch_bounds__(256) void reduce_slices_wave_kernel(
     }
 }
 
+// From one count per wave of the workgroup in LDS: the counts of the waves before
+// the calling one, and of all.
+struct WaveSums { uint32_t before, total; };
+template <int WAVES>
+__device__ __forceinline__ WaveSums sum_of_waves(const uint32_t* s_wave) {
+    const int lane = threadIdx.x & (WAVE - 1), wave = (int)uniform(threadIdx.x >> 6);
+    const uint32_t incl = wave_inclusive_scan_u32(lane < WAVES ? s_wave[lane] : 0u);
+    return WaveSums{wave ? (uint32_t)__builtin_amdgcn_readlane((int)incl, wave - 1) : 0u,
+                    (uint32_t)__builtin_amdgcn_readlane((int)incl, WAVES - 1)};
+}
+
 // Exclusive prefix over the popcounts of `words` bitmap words into s_wprefix;
 // returns the total (to every thread).  Called by the whole workgroup.
-template <uint32_t WORDS_MAX>
+// A tile of more than 65,536 slots may have prefixes that 16 bits do not hold: the
+// first word with such a prefix goes to *s_wrap (all ones if there is none).
+template <int BLOCK, uint32_t WORDS_MAX>
 __device__ __forceinline__ uint32_t bitmap_prefix(const uint32_t* s_bits, uint16_t* s_wprefix,
-                                                  uint32_t words, uint32_t* s_wave) {
-    static_assert(WORDS_MAX % RED_BLOCK == 0 || WORDS_MAX < RED_BLOCK,
-                  "every thread owns the same number of bitmap words");
-    constexpr uint32_t PER = (WORDS_MAX + RED_BLOCK - 1) / RED_BLOCK;   // words per thread (1 to 3)
+                                                  uint32_t words, uint32_t* s_wave, uint32_t* s_wrap) {
+    static_assert(WORDS_MAX * 32 < 2 * 65536, "prefixes wrap once at most");
+    constexpr uint32_t PER = (WORDS_MAX + BLOCK - 1) / BLOCK;           // words per thread (1 to 3)
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid >> 6;
     uint32_t c[PER], sum = 0;
 #pragma unroll
@@ -150,74 +160,95 @@ __device__ __forceinline__ uint32_t bitmap_prefix(const uint32_t* s_bits, uint16
         c[j] = w < words ? (uint32_t)__popc(s_bits[w]) : 0u;
         sum += c[j];
     }
-    const uint32_t incl = wave_inclusive_scan<uint32_t>(sum);
+    const uint32_t incl = wave_inclusive_scan_u32(sum);
     if (lane == WAVE - 1) s_wave[wave] = incl;
     __syncthreads();
-    uint32_t before = incl - sum, total = 0;
-#pragma unroll
-    for (int w = 0; w < RED_WAVES; ++w) {
-        if (w < wave) before += s_wave[w];
-        total += s_wave[w];
-    }
+    const WaveSums sums = sum_of_waves<BLOCK / WAVE>(s_wave);
+    uint32_t before = sums.before + incl - sum;
 #pragma unroll
     for (uint32_t j = 0; j < PER; ++j) {
         const uint32_t w = tid * PER + j;
-        if (w < words) s_wprefix[w] = (uint16_t)before;       // < 32 * WORDS_MAX <= 65536
+        if (w < words) s_wprefix[w] = (uint16_t)before;
+        if (WORDS_MAX > 2048 && w < words && before > 0xffffu) atomicMin(s_wrap, w);
         before += c[j];
     }
     __syncthreads();
-    return total;
+    return sums.total;
 }
 
-// grid = (tiles of the widest region, B).  Region j: chunk offsets at
-// seg_begin / seg_end + j * seg_stride; bounds from lo_hi[2j..] if lo_hi != NULL else
-// (lo0, hi0).
-// C accumulators, a bitmap of S_MAX slots: (RED_C, RED_S_MAX); (RED_C_SPARSE,
-// RED_S_SPARSE) for very sparsely hit regions; (RED_C_DENSE, RED_C_DENSE) for
-// densely hit ones, where the accumulator of a slot is the slot itself.
-template <uint32_t C, uint32_t S_MAX>
-__global__ __launch_bounds__(RED_BLOCK) void reduce_tile_kernel(
-    const uint32_t* __restrict__ idx_cat, const float* __restrict__ val_cat,
-    const uint64_t* __restrict__ seg_begin, uint32_t seg_stride,
-    const uint32_t* __restrict__ lo_hi, uint32_t lo0,
-    uint32_t hi0, uint32_t P, uint32_t max_width, uint32_t slots, uint32_t* __restrict__ idx_out,
-    float* __restrict__ val_out, uint64_t capacity, uint64_t* __restrict__ nnz_out,
-    float* __restrict__ dense_out, char* ws, uint32_t ws_region_bytes, uint32_t table_offset,
-    uint32_t span_blocks) {
-    constexpr uint32_t WORDS_MAX = S_MAX / 32;
-    static_assert(S_MAX <= 65536, "slots and ranks are kept in 16 bits");
-    __shared__ double s_sum[C];
-    __shared__ uint32_t s_bits[WORDS_MAX];
-    __shared__ uint16_t s_wprefix[WORDS_MAX];
-    constexpr bool CAN_RANK = S_MAX > C;          // else: accumulator = slot, always
-    __shared__ uint16_t s_slot[CAN_RANK ? C : 1]; // ranked tiles: slot of accumulator [rank]
-    __shared__ uint64_t s_start[RED_CHUNKS];      // slice starts of the current sweep
-    __shared__ uint32_t s_len[RED_CHUNKS];        // slice lengths
-    __shared__ uint32_t s_loaded_p0;              // which sweep they belong to
-    __shared__ uint32_t s_wave[RED_WAVES];
-    __shared__ uint32_t s_tile, s_before[2];
+struct __attribute__((packed, aligned(4))) Quad32 { uint32_t v[4]; };   // four words at any word address
 
-    const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid >> 6;
+// grid = (tiles of the widest region, B).  Region j: chunk offsets at seg_begin /
+// seg_end + j * seg_stride; bounds from lo_hi[2j..] if lo_hi != NULL else (lo0, hi0).
+//
+// A tile's entries are read in UNITS of RED_UNIT consecutive entries of one slice:
+// a unit belongs to four lanes, each of which reads four entries of it with one
+// 16-byte load, so a wave reads sixteen units - of as many slices, if they are
+// short - with one load instruction, and only the last unit of a slice is partly
+// empty.  The threads that hold the slice table write the units' places to LDS, so
+// that finding a thread's entries is one LDS read.  ROUNDS units per four
+// threads make a chunk.  A tile that is one chunk (the host sizes tiles so that
+// this is the rule) keeps all its entries in registers: they are read from memory
+// once, both arrays at once, and the marking, the summing and the writing of the
+// indices need nothing more from memory.  A tile with more entries (many
+// contributions that hit the same slots) goes chunk by chunk, twice.
+//
+// What bounds it: a tile is a chain of phases - ticket, slice table, entries, marks,
+// ranks, sums, place, output - of some 14 us with two tiles of 8,000 entries to a
+// CU, of which about half wait for memory and half are LDS work (two reads and an
+// fp64 atomic add at random places an entry), and LDS (ten bytes a hit slot) is what
+// limits the tiles in flight.  490 regions of 16 contributions (1.9 GB in and out):
+// 575 us with slices read in blocks of 64 entries, twice, by 8-wave workgroups of
+// half this size, 500 us as it is here; 373 regions of 64 contributions: 734 and
+// 555 us, the longer slices of the wider tile counting for as much as the rest.
+// Tried and not kept: 16 waves with 8 entries a thread and the same tile (spills at
+// 64 registers, 526 us without them), three or four smaller tiles to a CU (540, 530
+// us), several regions' tiles in turn per workgroup with the next slice table
+// fetched ahead (500 us: what it hides, its registers and the extra barriers cost).
+template <int BLOCK, int ROUNDS, uint32_t C, uint32_t S_MAX>
+__global__ __launch_bounds__(BLOCK, 4) void reduce_tile_kernel(
+    const uint32_t* __restrict__ idx_cat, const float* __restrict__ val_cat,
+    const uint64_t* __restrict__ seg_begin, const uint64_t* __restrict__ seg_end,
+    uint32_t seg_stride, const uint32_t* __restrict__ lo_hi, uint32_t lo0,
+    uint32_t hi0, uint32_t P, uint32_t max_width, uint32_t slots,
+    uint32_t* __restrict__ idx_out, float* __restrict__ val_out, uint64_t capacity,
+    uint64_t* __restrict__ nnz_out, float* __restrict__ dense_out, char* ws,
+    uint32_t ws_region_bytes, uint32_t table_offset) {
+    constexpr int WAVES = BLOCK / WAVE;
+    constexpr bool DENSE = S_MAX == C;            // accumulator = slot, always
+    constexpr uint32_t WORDS_MAX = S_MAX / 32;
+    constexpr uint32_t UNITS = BLOCK / 4 * ROUNDS;
+    // Lanes without an entry work on a slot, a rank and an accumulator of their own
+    // past the end (one of SPARE), so that the loops over the entries have no branch.
+    constexpr uint32_t SPARE = 32, SLOT_BITS = 17, SLOT_MASK = (1u << SLOT_BITS) - 1u;
+    static_assert(S_MAX + 32 * SPARE <= SLOT_MASK && C + SPARE <= 1u << (32 - SLOT_BITS), "a slot and a rank share a word");
+    static_assert(C % 2 == 0 && WORDS_MAX % 4 == 0, "cleared 16 bytes at a time");
+    __shared__ __attribute__((aligned(16))) double s_sum[C + SPARE];
+    __shared__ __attribute__((aligned(16))) uint32_t s_bits[WORDS_MAX + SPARE];
+    __shared__ uint16_t s_wprefix[WORDS_MAX + SPARE];
+    __shared__ uint64_t s_unit[UNITS];            // first entry << 6 | whole unit readable << 5 | entries
+    __shared__ uint32_t s_wave[3][WAVES];
+    __shared__ uint32_t s_tile, s_before[2], s_wrap;
+
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1);
+    const int wave = (int)uniform((uint32_t)tid >> 6);
     const uint32_t region = blockIdx.y;
     char* region_ws = ws + (size_t)region * ws_region_bytes;
     ScanHeader* hdr = (ScanHeader*)region_ws;
     uint64_t* tile_desc = (uint64_t*)(region_ws + SCAN_HEADER_BYTES);
     uint64_t* group_desc = tile_desc + gridDim.x;
-    const uint32_t* table = (const uint32_t*)(region_ws + table_offset);
     if (tid == 0) {
         s_tile = atomicAdd(&hdr->ticket, 1u);
-        s_loaded_p0 = ~0u;
+        s_wrap = ~0u;
     }
-
+    if (tid < (int)SPARE) s_wprefix[WORDS_MAX + tid] = (uint16_t)(C + tid);
     const RegionView r = region_view(lo_hi, lo0, hi0, region, max_width, slots);
     uint64_t* nnz = nnz_out + 2 * (size_t)region;
-    const bool ranked = CAN_RANK && slots > C;   // accumulators indexed by rank, not by slot
-    const uint32_t words_all = slots / 32;       // slots is a multiple of 32
     // the bitmap and the accumulators are cleared while the ticket is under way
-    for (uint32_t w = tid; w < words_all; w += RED_BLOCK) s_bits[w] = 0;
-    for (uint32_t s = tid; s < C; s += RED_BLOCK) s_sum[s] = 0.0;
+    for (uint32_t w = tid; w < WORDS_MAX / 4; w += BLOCK) reinterpret_cast<uint4*>(s_bits)[w] = uint4{0, 0, 0, 0};
+    for (uint32_t s = tid; s < C / 2; s += BLOCK) reinterpret_cast<double2*>(s_sum)[s] = double2{0.0, 0.0};
     __syncthreads();
-    const uint32_t tile = s_tile;
+    const uint32_t tile = uniform(s_tile);
     if (r.ntiles == 0) {
         if (tile == 0 && tid == 0) {
             nnz[0] = r.bad ? ~0ull : 0ull;
@@ -229,135 +260,208 @@ __global__ __launch_bounds__(RED_BLOCK) void reduce_tile_kernel(
     const uint32_t a = r.lo + tile * slots;                       // first index of the tile
     const uint32_t tslots = (r.hi - a) < slots ? (r.hi - a) : slots;
     const uint32_t words = (tslots + 31) / 32;
+    const uint32_t* row = (const uint32_t*)(region_ws + table_offset) + (size_t)tile * P;   // slice starts, then ends
     const uint64_t* off = seg_begin + (size_t)region * seg_stride;
-    const uint32_t* row0 = table + (size_t)tile * P;              // slice starts
-    const uint32_t* row1 = row0 + P;                              // slice ends
+    const uint64_t* off_end = seg_end + (size_t)region * seg_stride;
     idx_out += (size_t)region * capacity;
     val_out += (size_t)region * capacity;
+    float* const dense = dense_out ? dense_out + (size_t)region * max_width + (size_t)tile * slots : nullptr;
+    if (dense && !DENSE)
+        for (uint32_t s = tid; s < tslots; s += BLOCK) dense[s] = 0.0f;   // the sums go on top, several barriers later
 
-    // Hands every entry of the tile to body(index, value).  Contributions are
-    // taken RED_CHUNKS at a time; slice q of a sweep belongs to wave q mod WAVES,
-    // whose lanes read it in spans of G x 64 consecutive entries (G coalesced loads
-    // that share one address and one piece of bookkeeping).  A wave first names up
-    // to UNITS such spans, across its slices, then issues all their loads, then
-    // consumes them: enough loads in flight to cover the memory latency, no
-    // per-entry search, and only wave-uniform bookkeeping.  Long slices (few
-    // contributions) take G = 4 or 2; short ones G = 1, where a longer span would
-    // be mostly empty (the host picks from the expected slice length).
-    auto for_each_entry_in = [&](auto with_values, auto span, auto units, auto&& body) {
+    // ---- the slice table: 2^share threads hold one slice ----
+    // (several where contributions are few, so that the units of long slices are
+    // written by many threads); BLOCK contributions at most at a time
+    uint32_t share = 0;
+    while (share < 6 && (P << (share + 1)) <= (uint32_t)BLOCK) ++share;
+    const uint32_t member = (uint32_t)tid & ((1u << share) - 1u);
+    uint64_t sl_start = 0;              // this thread's slice: its place in the input,
+    uint32_t sl_len = 0, sl_readable = 0, sl_unit0 = 0;   // entries, entries up to the end of the contribution, first unit
+    auto fetch_slices = [&](uint32_t p0) {
+        const uint32_t q = p0 + ((uint32_t)tid >> share);
+        sl_start = 0;
+        sl_len = sl_readable = 0;
+        if (q < P) {
+            const uint32_t b = row[q], e = row[P + q];
+            const uint64_t begin = off[q], end = off_end[q];
+            sl_start = begin + b;
+            sl_len = e > b ? e - b : 0u;                          // e < b, or a slice without end, only for
+            if (sl_len > (1u << 26)) sl_len = 1u << 26;           // unsorted input: the units' numbers stay in 32 bits
+            const uint64_t readable = end > sl_start ? end - sl_start : 0ull;
+            sl_readable = readable < 0xffffffffull ? (uint32_t)readable : 0xffffffffu;
+        }
+    };
+    uint32_t units = 0, entries = 0;    // of the contributions fetched last
+    auto number_slices = [&]() {                                  // one barrier
+        const uint32_t mine = (sl_len + RED_UNIT - 1) / RED_UNIT;
+        const uint32_t incl = wave_inclusive_scan_u32(member == 0 ? mine : 0u);
+        const uint32_t incl_entries = wave_inclusive_scan_u32(member == 0 ? sl_len : 0u);
+        if (lane == WAVE - 1) {
+            s_wave[0][wave] = incl_entries;
+            s_wave[1][wave] = incl;
+        }
+        __syncthreads();
+        entries = sum_of_waves<WAVES>(s_wave[0]).total;
+        const WaveSums sums = sum_of_waves<WAVES>(s_wave[1]);
+        sl_unit0 = sums.before + incl - mine;                     // the members of a slice agree
+        units = sums.total;
+    };
+    auto write_units = [&](uint32_t u0) {                         // units u0 .. u0 + UNITS - 1
+        const uint32_t mine = (sl_len + RED_UNIT - 1) / RED_UNIT;
+        uint32_t i = member;
+        if (sl_unit0 + i < u0) i += (u0 - sl_unit0 - i + (1u << share) - 1u) >> share << share;
+        for (; i < mine && sl_unit0 + i < u0 + UNITS; i += 1u << share) {
+            const uint32_t o = i * RED_UNIT, left = sl_len - o;
+            const uint64_t whole = o + RED_UNIT <= sl_readable ? 1u : 0u;
+            s_unit[sl_unit0 + i - u0] =
+                (sl_start + o) << 6 | whole << 5 | (left < RED_UNIT ? left : RED_UNIT);
+        }
+    };
+    // ---- this thread's entries of a chunk ----
+    struct Chunk {
+        uint32_t slot[ROUNDS][4];    // slot in the tile, later rank << SLOT_BITS | slot; from S_MAX on: no entry
+        float value[ROUNDS][4];
+    };
+    auto load_chunk = [&](Chunk& c, uint32_t in_chunk, auto with_values) {
         constexpr bool VALUES = decltype(with_values)::value;
-        constexpr int G = decltype(span)::value, UNITS = decltype(units)::value;
-        for (uint32_t p0 = 0; p0 < P; p0 += RED_CHUNKS) {
-            const uint32_t np = (P - p0) < (uint32_t)RED_CHUNKS ? (P - p0) : (uint32_t)RED_CHUNKS;
-            // Every thread must take the same branch here.  The note of what is
-            // loaded is therefore written between the two barriers: each thread has
-            // read it (before the first) when it changes, and sees the new value
-            // (after the second) when it next looks.  Written after the second
-            // barrier instead, a wave that ran ahead could still read the value an
-            // earlier sweep left for this very chunk and skip the reload alone.
-            if (p0 != s_loaded_p0) {            // slice table of this sweep not in LDS yet
-                __syncthreads();
-                for (uint32_t q = tid; q < np; q += RED_BLOCK) {
-                    const uint32_t b = row0[p0 + q], e = row1[p0 + q];
-                    s_start[q] = off[p0 + q] + b;
-                    s_len[q] = e > b ? e - b : 0u;      // e < b only for unsorted input
-                }
-                if (tid == 0) s_loaded_p0 = p0;
-                __syncthreads();
+        uint32_t left[ROUNDS];
+        const uint32_t nowhere = S_MAX + 32u * ((uint32_t)lane % SPARE);
+#pragma unroll
+        for (int u = 0; u < ROUNDS; ++u) {
+            const uint32_t unit = ((uint32_t)tid >> 2) + u * (BLOCK / 4);
+            const uint64_t d = unit < in_chunk ? s_unit[unit] : 0ull;
+            const uint32_t len = (uint32_t)d & 31u, first = 4u * ((uint32_t)tid & 3u);
+            left[u] = len > first ? len - first : 0u;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                c.slot[u][j] = 0;
+                c.value[u][j] = 0.0f;
             }
-            uint32_t q = (uint32_t)__builtin_amdgcn_readfirstlane(wave), o = 0;   // next span: slice q, from entry o
-            while (q < np) {
-                uint64_t pos[UNITS];
-                uint32_t left[UNITS];            // entries of the slice from the span's start on (wave-uniform)
+            if (left[u] != 0) {
+                const uint64_t from = (d >> 6) + first;
+                if ((uint32_t)d & 32u) {                      // past the slice's end, not the contribution's
+                    const Quad32 i4 = *reinterpret_cast<const Quad32*>(idx_cat + from);
 #pragma unroll
-                for (int u = 0; u < UNITS; ++u) {
-                    // skip empty slices
-                    while (q < np && s_len[q] == 0) q += RED_WAVES;
-                    const bool have = q < np;
-                    const uint32_t len =
-                        have ? (uint32_t)__builtin_amdgcn_readfirstlane(s_len[q]) : 0u;
-                    left[u] = have ? len - o : 0u;
-                    pos[u] = have ? s_start[q] + o + lane : 0;
-                    if (have) {
-                        o += G * WAVE;
-                        if (o >= len) { q += RED_WAVES; o = 0; }
+                    for (int j = 0; j < 4; ++j) c.slot[u][j] = i4.v[j];
+                    if (VALUES) {
+                        const Quad32 v4 = *reinterpret_cast<const Quad32*>(val_cat + from);
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) c.value[u][j] = __uint_as_float(v4.v[j]);
                     }
-                }
-                uint32_t index[UNITS][G];
-                float value[UNITS][G];
+                } else {
 #pragma unroll
-                for (int u = 0; u < UNITS; ++u) {
-#pragma unroll
-                    for (int j = 0; j < G; ++j) {
-                        if ((uint32_t)lane + (uint32_t)(j * WAVE) < left[u]) {
-                            index[u][j] = idx_cat[pos[u] + j * WAVE];
-                            if (VALUES) value[u][j] = val_cat[pos[u] + j * WAVE];
+                    for (int j = 0; j < 4; ++j)
+                        if ((uint32_t)j < left[u]) {
+                            c.slot[u][j] = idx_cat[from + j];
+                            if (VALUES) c.value[u][j] = val_cat[from + j];
                         }
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < UNITS; ++u) {
-#pragma unroll
-                    for (int j = 0; j < G; ++j)
-                        if ((uint32_t)lane + (uint32_t)(j * WAVE) < left[u])
-                            body(index[u][j], VALUES ? value[u][j] : 0.0f);
                 }
             }
         }
+#pragma unroll
+        for (int u = 0; u < ROUNDS; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t s = c.slot[u][j] - a;
+                c.slot[u][j] = (uint32_t)j < left[u] && s < tslots ? s : nowhere;   // beyond tslots: unsorted input only
+            }
     };
-    auto for_each_entry = [&](auto with_values, auto&& body) {
-        if (span_blocks == 4)
-            for_each_entry_in(with_values, std::integral_constant<int, 4>{},
-                              std::integral_constant<int, 3>{}, body);
-        else if (span_blocks == 2)
-            for_each_entry_in(with_values, std::integral_constant<int, 2>{},
-                              std::integral_constant<int, 6>{}, body);
-        else
-            for_each_entry_in(with_values, std::integral_constant<int, 1>{},
-                              std::integral_constant<int, RED_UNROLL>{}, body);
+    using Yes = std::true_type;
+    using No = std::false_type;
+    auto for_each_chunk = [&](auto with_values, auto&& body) {
+        for (uint32_t p0 = 0; p0 < P; p0 += BLOCK) {
+            fetch_slices(p0);
+            number_slices();
+            for (uint32_t u0 = 0; u0 < units; u0 += UNITS) {
+                write_units(u0);
+                __syncthreads();
+                Chunk c;
+                load_chunk(c, units - u0 < UNITS ? units - u0 : UNITS, with_values);
+                body(c);
+                __syncthreads();                              // s_unit and s_wave are free again
+            }
+            if (units == 0) __syncthreads();
+        }
     };
-    using Yes = std::true_type;      // sweep needs the values too
-    using No = std::false_type;      // sweep needs the indices only
+    auto mark = [&](const Chunk& c) {
+#pragma unroll
+        for (int u = 0; u < ROUNDS; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                __hip_atomic_fetch_or(&s_bits[c.slot[u][j] >> 5], 1u << (c.slot[u][j] & 31), __ATOMIC_RELAXED,
+                                      __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    // Hit slots of the tile below bitmap word w.  MAY_WRAP: there may be more than
+    // 65,535 of them (a chunk's entries alone never make as many).
+    auto hits_below = [&](uint32_t w, auto may_wrap) -> uint32_t {
+        return (uint32_t)s_wprefix[w] + (decltype(may_wrap)::value && WORDS_MAX > 2048 && w >= s_wrap ? 65536u : 0u);
+    };
+    // Sums the entries and notes every entry's rank.  GENERAL: only those whose rank
+    // lies in [r0, r0 + C).
+    auto add = [&](Chunk& c, uint32_t r0, auto general) {
+        constexpr bool GENERAL = decltype(general)::value;
+#pragma unroll
+        for (int u = 0; u < ROUNDS; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t s = c.slot[u][j];
+                const uint32_t below = s_bits[s >> 5] & ((1u << (s & 31)) - 1u);
+                uint32_t rank = hits_below(s >> 5, general) + (uint32_t)__popc(below);
+                if (GENERAL) rank = s < S_MAX ? rank - r0 : C;
+                else c.slot[u][j] = rank << SLOT_BITS | s;
+                float x = c.value[u][j];
+                asm volatile("" : "+v"(x));      // widened here, not where it was loaded: registers
+                if (!GENERAL || rank < C)
+                    __hip_atomic_fetch_add(&s_sum[rank], (double)x, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+    };
 
     // Both waves of the chained scan; every thread gets the count of all tiles
-    // before this one.
+    // before this one.  What the two waves look at first is asked for early
+    // (look_back) and, as a rule, there by the time it is needed.
+    const uint32_t group = tile / SCAN_GROUP;
+    uint64_t seen = 0;
+    auto look_back = [&]() {
+        seen = 0;
+        if (wave == 0 && (uint32_t)lane < tile % SCAN_GROUP) seen = desc_load(tile_desc + group * SCAN_GROUP + lane);
+        if (wave == 1 && (uint32_t)lane < group) seen = desc_load(group_desc + (group - 1 - lane));
+    };
     auto place_tile = [&](uint32_t count) -> uint32_t {
-        const uint32_t group = tile / SCAN_GROUP;
         if (wave == 0) {
-            const uint32_t before = scan_within_group(hdr, tile_desc, group_desc, tile, count);
+            const uint32_t before = scan_within_group(hdr, tile_desc, group_desc, tile, count, seen);
             if (lane == 0) s_before[0] = before;
         } else if (wave == 1) {
-            const uint32_t before = scan_across_groups(hdr, group_desc, group);
+            const uint32_t before = scan_across_groups(hdr, group_desc, group, seen);
             if (lane == 0) s_before[1] = before;
         }
         __syncthreads();
-        const uint32_t before = s_before[0] + s_before[1];
+        const uint32_t before = uniform(s_before[0] + s_before[1]);
         if (tid == 0 && group != 0 && tile % SCAN_GROUP == SCAN_GROUP - 1)
             scan_close_group(group_desc, group, before + count);
         return before;
     };
-    float* dense = dense_out ? dense_out + (size_t)region * max_width + (size_t)tile * slots
-                             : nullptr;
-    uint32_t distinct, exclusive;
+    uint32_t distinct = 0, exclusive = 0;
 
-    if (!ranked) {
+    if constexpr (DENSE) {
         // ---- densely hit region: accumulator = slot, one sweep ----
-        for_each_entry(Yes{}, [&](uint32_t index, float x) {
-            const uint32_t slot = index - a;
-            if (slot >= tslots) return;          // only reachable with unsorted input
-            __hip_atomic_fetch_add(&s_sum[slot], (double)x, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_WORKGROUP);
-            __hip_atomic_fetch_or(&s_bits[slot >> 5], 1u << (slot & 31), __ATOMIC_RELAXED,
-                                  __HIP_MEMORY_SCOPE_WORKGROUP);
+        for_each_chunk(Yes{}, [&](Chunk& c) {
+#pragma unroll
+            for (int u = 0; u < ROUNDS; ++u)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (c.slot[u][j] < S_MAX)
+                        __hip_atomic_fetch_add(&s_sum[c.slot[u][j]], (double)c.value[u][j], __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_WORKGROUP);
+            mark(c);
         });
-        __syncthreads();
-        distinct = bitmap_prefix<WORDS_MAX>(s_bits, s_wprefix, words, s_wave);
+        distinct = bitmap_prefix<BLOCK, WORDS_MAX>(s_bits, s_wprefix, words, s_wave[2], &s_wrap);
         exclusive = place_tile(distinct);
         // a thread writes out the hit slots of one EMIT_BITS-wide piece of a bitmap
         // word: a tile has fewer words than the workgroup has threads, a word up
         // to 32 hits, and the slowest thread sets the pace
         constexpr uint32_t EMIT_BITS = 4, EMIT_PER = 32 / EMIT_BITS;   // bits of a bitmap word per thread
-        for (uint32_t u = tid; u < words * EMIT_PER; u += RED_BLOCK) {
+        for (uint32_t u = tid; u < words * EMIT_PER; u += BLOCK) {
             const uint32_t w = u / EMIT_PER, shift = (u % EMIT_PER) * EMIT_BITS;
             const uint32_t word = s_bits[w];
             uint32_t bits = (word >> shift) & ((1u << EMIT_BITS) - 1u);
@@ -365,69 +469,99 @@ __global__ __launch_bounds__(RED_BLOCK) void reduce_tile_kernel(
             while (bits) {
                 const int bit = __ffs(bits) - 1;
                 bits &= bits - 1;
-                const uint32_t slot = w * 32u + shift + bit;
+                const uint32_t hit = w * 32u + shift + bit;
                 if (pos < capacity) {
-                    idx_out[pos] = a + slot;
-                    val_out[pos] = (float)s_sum[slot];
+                    idx_out[pos] = a + hit;
+                    val_out[pos] = (float)s_sum[hit];
                 }
                 ++pos;
             }
         }
         if (dense)
-            for (uint32_t s = tid; s < tslots; s += RED_BLOCK) dense[s] = (float)s_sum[s];
-    } else if constexpr (CAN_RANK) {
+            for (uint32_t s = tid; s < tslots; s += BLOCK) dense[s] = (float)s_sum[s];
+    } else {
         // ---- sparsely hit region: mark, rank, then sum into accumulator [rank] ----
-        for_each_entry(No{}, [&](uint32_t index, float) {
-            const uint32_t slot = index - a;
-            if (slot < tslots)
-                __hip_atomic_fetch_or(&s_bits[slot >> 5], 1u << (slot & 31), __ATOMIC_RELAXED,
-                                      __HIP_MEMORY_SCOPE_WORKGROUP);
-        });
-        __syncthreads();
-        distinct = bitmap_prefix<WORDS_MAX>(s_bits, s_wprefix, words, s_wave);
-        // the count is known before the sums: publish it now, wait for the others later
-        if (tid == 0) scan_publish_early(tile_desc, tile, distinct);
-        exclusive = 0;
-        const uint32_t rounds = (distinct + C - 1) / C;             // 1, unless the estimate was off
-        if (dense) {
-            for (uint32_t s = tid; s < tslots; s += RED_BLOCK) dense[s] = 0.0f;
-            __syncthreads();                     // zeros land before the values below
-        }
-        for (uint32_t round = 0; round < rounds; ++round) {
-            const uint32_t r0 = round * C;                           // first rank of this round
-            if (round) {                                             // the first round starts cleared
-                __syncthreads();                                     // previous round fully read
-                for (uint32_t s = tid; s < C; s += RED_BLOCK) s_sum[s] = 0.0;
-                __syncthreads();
+        uint32_t* s_idx = reinterpret_cast<uint32_t*>(s_sum);   // takes over once the sums are read
+        auto rank_tile = [&]() {
+            distinct = bitmap_prefix<BLOCK, WORDS_MAX>(s_bits, s_wprefix, words, s_wave[2], &s_wrap);
+            // the count is known before the sums: publish it now, wait for the others later
+            if (tid == 0) scan_publish_early(tile_desc, tile, distinct);
+        };
+        // The sums of ranks r0 .. r0 + in_round - 1 leave LDS, the indices take their
+        // place, and both go out in output order; the wait for the tiles before this
+        // one lies in between.
+        auto write_out = [&](uint32_t r0, uint32_t in_round, auto&& put_indices) {
+            constexpr int PER = (int)((C + BLOCK - 1) / BLOCK);
+            float x[PER];
+            uint32_t k0 = (uint32_t)tid;
+            asm volatile("" : "+v"(k0));             // addresses are formed here, not kept from before
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                const uint32_t k = k0 + i * BLOCK;
+                x[i] = k < in_round ? (float)s_sum[k] : 0.0f;
             }
-            auto add = [&](uint32_t index, float x) {
-                const uint32_t slot = index - a;
-                if (slot >= tslots) return;
-                const uint32_t below = s_bits[slot >> 5] & ((1u << (slot & 31)) - 1u);
-                const uint32_t rank = (uint32_t)s_wprefix[slot >> 5] + (uint32_t)__popc(below) - r0;
-                if (rank < C) {
-                    __hip_atomic_fetch_add(&s_sum[rank], (double)x, __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_WORKGROUP);
-                    s_slot[rank] = (uint16_t)slot;       // every hit of the slot writes the same
-                }
-            };
-            for_each_entry(Yes{}, add);
             __syncthreads();
-            if (round == 0) exclusive = place_tile(distinct);
-            // accumulators and their slots are already in output order
-            const uint32_t in_round = distinct - r0 < C ? distinct - r0 : C;
-            for (uint32_t k = tid; k < in_round; k += RED_BLOCK) {
-                const uint64_t pos = (uint64_t)exclusive + r0 + k;
-                const uint32_t slot = s_slot[k];
-                const float x = (float)s_sum[k];
-                if (pos < capacity) {
-                    idx_out[pos] = a + slot;
-                    val_out[pos] = x;
+            put_indices();
+            if (r0 == 0) exclusive = place_tile(distinct);
+            else __syncthreads();
+            const uint64_t first = (uint64_t)exclusive + r0, room = capacity > first ? capacity - first : 0;
+            const uint32_t out = in_round < room ? in_round : (uint32_t)room;
+            uint32_t* const to_idx = idx_out + first;
+            float* const to_val = val_out + first;
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                const uint32_t k = k0 + i * BLOCK;
+                if (k < out) {
+                    to_idx[k] = s_idx[k];
+                    to_val[k] = x[i];
                 }
-                if (dense) dense[slot] = x;
+                if (dense && k < in_round) dense[s_idx[k] - a] = x[i];
             }
+        };
+        fetch_slices(0);
+        number_slices();
+        if (P <= (uint32_t)BLOCK && units <= UNITS && entries <= C) {
+            // all entries in registers, and no more hit slots than accumulators
+            write_units(0);
+            __syncthreads();
+            Chunk mine;
+            load_chunk(mine, units, Yes{});
+            mark(mine);
+            __syncthreads();
+            rank_tile();
+            add(mine, 0, No{});
+            __syncthreads();
+            look_back();
+            write_out(0, distinct, [&]() {
+#pragma unroll
+                for (int u = 0; u < ROUNDS; ++u)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)               // every hit of a slot writes the same
+                        s_idx[mine.slot[u][j] >> SLOT_BITS] = a + (mine.slot[u][j] & SLOT_MASK);
+            });
+        } else {
+            __syncthreads();                                      // s_wave read by all
+            for_each_chunk(No{}, mark);
+            rank_tile();
+            uint32_t r0 = 0;
+            do {                                              // one round, unless the estimate was off
+                if (r0) {                                     // the first round starts cleared
+                    __syncthreads();                          // previous round fully read
+                    for (uint32_t s = tid; s < C; s += BLOCK) s_sum[s] = 0.0;
+                    __syncthreads();
+                }
+                for_each_chunk(Yes{}, [&](Chunk& c) { add(c, r0, Yes{}); });
+                if (r0 == 0) look_back();
+                write_out(r0, distinct - r0 < C ? distinct - r0 : C, [&]() {
+                    for (uint32_t w = tid; w < words; w += BLOCK) {
+                        uint32_t bits = s_bits[w], rank = hits_below(w, Yes{}) - r0;
+                        for (; bits; bits &= bits - 1, ++rank)
+                            if (rank < C) s_idx[rank] = a + w * 32u + (uint32_t)(__ffs(bits) - 1);
+                    }
+                });
+                r0 += C;
+            } while (r0 < distinct);
         }
-        if (rounds == 0) exclusive = place_tile(0u);   // an empty tile is still a link of the chain
     }
     if (tile == r.ntiles - 1 && tid == 0) {
         const uint64_t total = (uint64_t)exclusive + distinct;
@@ -457,12 +591,15 @@ int reduce_launch(const uint32_t* d_idx_cat, const float* d_val_cat,
         !aligned(d_dense, 4) || !aligned(d_lo_hi, 4))
         return OKT_ERR_INVALID_ARG;
     // the caller's bound on the size of the union doubles as the density estimate
-    ReduceShape shape = reduce_tile_shape(max_width, capacity);
-    // The wide dense tile is for throughput.  A launch that cannot fill the chip
-    // anyway is nothing but the latency of its tiles: it takes the narrower dense
-    // tile of the ranked shape (more, shorter tiles).
-    if (shape.kind == RED_DENSE && (uint64_t)B * reduce_tiles(max_width, RED_C) <= 3 * (uint64_t)device_cus())
-        shape = ReduceShape{RED_C, RED_RANKED};
+    const ReduceShape wide = reduce_tile_shape(max_width, capacity, P, true);
+    ReduceShape shape = wide;
+    // The wide tiles are for throughput.  A launch that cannot fill the chip with them
+    // is nothing but the latency of its tiles: it takes tiles of half the size.
+    if ((uint64_t)B * reduce_tiles(max_width, wide.slots) < RED_WIDE_TILES_PER_CU * (uint64_t)device_cus()) {
+        shape = reduce_tile_shape(max_width, capacity, P, false);
+        // twice the tiles need twice the table: not with a workspace sized for less
+        if (ws_bytes < reduce_ws_bytes_region(max_width, P, shape.slots) * B) shape = wide;
+    }
     const uint32_t slots = shape.slots;
     const size_t region_bytes = reduce_ws_bytes_region(max_width, P, slots);
     if (region_bytes > 0xffffffffull) return OKT_ERR_INVALID_ARG;
@@ -483,15 +620,11 @@ int reduce_launch(const uint32_t* d_idx_cat, const float* d_val_cat,
         hipLaunchKernelGGL(reduce_slices_kernel, dim3((unsigned)sblocks, B), dim3(256), 0, s,
                            d_idx_cat, d_seg_begin, d_seg_end, seg_stride, d_lo_hi, lo, hi, P,
                            max_width, slots, (char*)d_ws, (uint32_t)region_bytes, table_offset,
-                           spin_limit_setting(), cells * B >= (1u << 17) ? 1u : 0u);
+                           spin_limit_setting());
     }
-    // entries a contribution is expected to have in a tile: longer slices are read
-    // in spans of two or four blocks of 64
-    const uint64_t per_slice = capacity / tiles / P;
-    const uint32_t span_blocks = per_slice >= 128 ? 4u : per_slice >= 64 ? 2u : 1u;
     if (traffic_only) {
         timing_before(s);
-        hipLaunchKernelGGL(gather_ceiling_kernel, dim3((unsigned)tiles, B), dim3(RED_BLOCK), 0, s,
+        hipLaunchKernelGGL(gather_ceiling_kernel, dim3((unsigned)tiles, B), dim3(512), 0, s,
                            d_idx_cat, d_val_cat, d_seg_begin, seg_stride, d_lo_hi, P, max_width, slots,
                            d_idx_out, d_val_out, capacity, (const char*)d_ws, (uint32_t)region_bytes,
                            table_offset);
@@ -499,14 +632,23 @@ int reduce_launch(const uint32_t* d_idx_cat, const float* d_val_cat,
         return launch_status();
     }
     timing_before(s);
-    auto* tile_kernel = shape.kind == RED_SPARSE  ? reduce_tile_kernel<RED_C_SPARSE, RED_S_SPARSE>
-                        : shape.kind == RED_DENSE ? reduce_tile_kernel<RED_C_DENSE, RED_C_DENSE>
-                                                  : reduce_tile_kernel<RED_C, RED_S_MAX>;
-    hipLaunchKernelGGL(tile_kernel, dim3((unsigned)tiles, B), dim3(RED_BLOCK), 0, s,
-                       d_idx_cat, d_val_cat, d_seg_begin, seg_stride, d_lo_hi, lo, hi, P, max_width,
-                       slots,
-                       d_idx_out, d_val_out, capacity, d_nnz_out, d_dense, (char*)d_ws,
-                       (uint32_t)region_bytes, table_offset, span_blocks);
+    auto launch = [&](auto* tile_kernel, uint32_t block) {
+        hipLaunchKernelGGL(tile_kernel, dim3((unsigned)tiles, B), dim3(block), 0, s, d_idx_cat, d_val_cat,
+                           d_seg_begin, d_seg_end, seg_stride, d_lo_hi, lo, hi, P, max_width, slots,
+                           d_idx_out, d_val_out, capacity, d_nnz_out, d_dense, (char*)d_ws,
+                           (uint32_t)region_bytes, table_offset);
+    };
+    using W = ReduceWide;
+    using N = ReduceNarrow;
+    if (shape.wide) {
+        if (shape.kind == RED_DENSE) launch(reduce_tile_kernel<W::BLOCK, W::ROUNDS, W::C_DENSE, W::C_DENSE>, W::BLOCK);
+        else if (shape.kind == RED_RANKED) launch(reduce_tile_kernel<W::BLOCK, W::ROUNDS, W::C_RANKED, W::S_RANKED>, W::BLOCK);
+        else launch(reduce_tile_kernel<W::BLOCK, W::ROUNDS, W::C_SPARSE, W::S_SPARSE>, W::BLOCK);
+    } else {
+        if (shape.kind == RED_DENSE) launch(reduce_tile_kernel<N::BLOCK, N::ROUNDS, N::C_DENSE, N::C_DENSE>, N::BLOCK);
+        else if (shape.kind == RED_RANKED) launch(reduce_tile_kernel<N::BLOCK, N::ROUNDS, N::C_RANKED, N::S_RANKED>, N::BLOCK);
+        else launch(reduce_tile_kernel<N::BLOCK, N::ROUNDS, N::C_SPARSE, N::S_SPARSE>, N::BLOCK);
+    }
     timing_after(s);
     return launch_status();
 }

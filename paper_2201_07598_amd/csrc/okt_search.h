@@ -22,37 +22,41 @@ OKT_SEARCH_FN uint64_t lower_bound_idx(const uint32_t* a, uint64_t lo, uint64_t 
     return lo;
 }
 
+// Sixteen consecutive entries at any word address, read together.
+struct __attribute__((packed, aligned(4))) SearchWindow { uint32_t v[16]; };
+
 // The same answer - the first position in [lo, hi) whose entry is not below x, or
-// hi - found from a guess: one probe at the guess, then steps of doubling length
-// away from it until x is bracketed, then the bisection inside the bracket.  With
-// indices spread evenly over the region the guess is a few dozen entries off, so
-// a boundary costs about half the probes of a bisection over the whole list, all
-// but the first in two or three neighbouring cache lines; with any other spread
-// it costs at most about twice the bisection.
+// hi - found from a guess: sixteen entries around the guess are read at once (one
+// line of memory, or two) and, if x does not fall among them, the next guess is
+// extrapolated from their spacing.  With indices spread evenly over the region the
+// first guess is a few dozen entries off and the second one hits, so a boundary
+// costs two or three lines and as many waits, where probes of one entry each (steps
+// of doubling length from the guess, then a bisection) take eight waits in three or
+// four lines.  After SEARCH_GUESSES misses, and in lists shorter than a window, what
+// is left is bisected: any input ends.
+constexpr int SEARCH_GUESSES = 4;
 OKT_SEARCH_FN uint64_t lower_bound_near(const uint32_t* a, uint64_t lo, uint64_t hi, uint32_t x,
                                         uint64_t guess) {
-    if (lo >= hi) return lo;
-    uint64_t g = guess < lo ? lo : (guess >= hi ? hi - 1 : guess);
-    uint64_t step = 16;
-    if (a[g] < x) {                              // the answer lies in (g, hi]
-        uint64_t first = g + 1;
-        for (;;) {
-            const uint64_t p = g + step;
-            if (p >= hi) return lower_bound_idx(a, first, hi, x);
-            if (!(a[p] < x)) return lower_bound_idx(a, first, p, x);
-            first = p + 1;
-            g = p;
-            step *= 2;
+    for (int miss = 0; miss < SEARCH_GUESSES; ++miss) {
+        if (hi <= lo || hi - lo < 16) break;                 // the answer lies in [lo, hi]
+        uint64_t w = guess < lo + 8 ? lo : guess - 8;
+        if (w > hi - 16) w = hi - 16;
+        const SearchWindow win = *reinterpret_cast<const SearchWindow*>(a + w);
+        uint32_t below = 0;
+        for (int j = 0; j < 16; ++j) below += win.v[j] < x ? 1u : 0u;
+        if (below != 0 && below != 16) return w + below;
+        const uint32_t first = win.v[0], last = win.v[15];
+        const float per = 15.0f / (float)(last > first ? last - first : 1u);   // entries per index
+        if (below == 0) {                                    // a[w] is not below x
+            hi = w;
+            const uint64_t back = (uint64_t)((float)(first - x) * per);
+            guess = back < w ? w - back : 0;
+        } else {
+            lo = w + 16;
+            guess = lo + (uint64_t)((float)(x - last) * per);
         }
     }
-    uint64_t last = g;                           // a[last] is not below x: the answer lies in [lo, last]
-    for (;;) {
-        if (last - lo < step) return lower_bound_idx(a, lo, last, x);
-        const uint64_t p = last - step;
-        if (a[p] < x) return lower_bound_idx(a, p + 1, last, x);
-        last = p;
-        step *= 2;
-    }
+    return lower_bound_idx(a, lo, hi, x);
 }
 
 // Boundary r (0 <= r <= R) of the balanced split of [0, n) by a sorted index list

@@ -152,55 +152,72 @@ inline size_t refresh_ws_bytes(uint64_t n) {
 }
 
 // ---- sparse reduce ----
-// A workgroup of RED_BLOCK threads owns a tile of `slots` consecutive index
-// slots of the region and sums into RED_C fp64 accumulators in LDS.  In a region
-// that is densely hit a tile is RED_C slots wide and slot = accumulator.  In a
-// sparsely hit region a tile is up to RED_S_MAX slots wide: a first sweep marks
-// the hit slots in a bitmap, the popcount prefix of the bitmap ranks them, and
-// the accumulators are indexed by rank, so the LDS holds hit slots only.
-constexpr int RED_BLOCK = 512;
-constexpr int RED_UNROLL = 10;                  // blocks of 64 entries a wave keeps in flight (short slices)
-constexpr uint32_t RED_C = 4096;                // accumulators per tile and round
-constexpr uint32_t RED_S_MAX = 32768;           // widest tile (bits in the bitmap)
-constexpr int RED_CHUNKS = 256;                 // contributions handled per sweep
-
-// Two more shapes of the same kernel spend the same LDS differently.  Very
-// sparsely hit regions: a wider bitmap paid for with fewer accumulators, so that
-// a tile is not cut short by the bitmap with half of its accumulators unused.
-// Densely hit regions (accumulator = slot): no rank-to-slot array and a bitmap
-// only as wide as the accumulators, which leaves room for more of them.
-constexpr uint32_t RED_C_SPARSE = 3840;
-constexpr uint32_t RED_S_SPARSE = 49152;
-constexpr uint32_t RED_C_DENSE = 6016;                 // a multiple of 32
+// A workgroup owns a tile of `slots` consecutive index slots of the region and
+// sums into C fp64 accumulators in LDS.  In a region that is densely hit slot =
+// accumulator.  In a sparsely hit region a tile is wider than that, up to S slots:
+// the hit slots are marked in a bitmap, the popcount prefix of the bitmap ranks
+// them, and the accumulators are indexed by rank, so the LDS holds hit slots only.
+// Very sparsely hit regions trade accumulators for bitmap.
+constexpr uint32_t RED_UNIT = 16;               // entries read by four lanes with one 16-byte load each
+// Two wide tiles to a CU (80 KB of LDS each), or four narrow ones.
+struct ReduceWide {
+    static constexpr int BLOCK = 512, ROUNDS = 4;   // ROUNDS: units per four threads that stay in registers
+    static constexpr uint32_t C_DENSE = 9216, C_RANKED = 8064, S_RANKED = 65536, C_SPARSE = 7168, S_SPARSE = 98304;
+};
+struct ReduceNarrow {
+    static constexpr int BLOCK = 512, ROUNDS = 2;
+    static constexpr uint32_t C_DENSE = 4096, C_RANKED = 3968, S_RANKED = 32768, C_SPARSE = 3584, S_SPARSE = 49152;
+};
+constexpr uint32_t RED_SLOTS_MIN = 4096;        // no tile is narrower
+// Launches with fewer tiles than this take the narrow form: more, shorter tiles.
+constexpr uint64_t RED_WIDE_TILES_PER_CU = 2;
+// From this share of its slots hit on, a region is taken as densely hit: of a tile of
+// C_DENSE slots only that share of the accumulators is used, but one sweep does.
+// Measured over 8 to 256 contributions in batches: at 0.3 ranked tiles are ahead
+// (135 against 179 us), at 0.4 dense ones (168 against 147 us), and where
+// contributions collide (more entries per hit slot) dense ones from less on.
+constexpr double RED_DENSE_FROM = 0.35;
 
 // Tile shape for a region `width` wide whose union is expected to hold at most
-// `expected` entries.  Densely hit (at most RED_C_DENSE / RED_C slots per expected
-// entry and accumulator): RED_C_DENSE slots, accumulator = slot, one sweep.  Else
-// ranked tiles as wide - any multiple of 32 slots - as keeps the expected number
-// of hit slots per tile at RED_FILL of the accumulators: up to RED_S_MAX
-// slots with RED_C accumulators, beyond that up to RED_S_SPARSE slots with
-// RED_C_SPARSE accumulators.
-constexpr double RED_FILL = 0.9;
+// `expected` entries, from P contributions.  A tile is as wide - any multiple of
+// 32 slots - as keeps the expected number of hit slots at RED_FILL of the
+// accumulators, and the units the entries make (about one entry per hit slot, and
+// half a unit lost at the end of every slice) within what a chunk holds, unless
+// that would leave more than half the accumulators idle.
+constexpr double RED_FILL = 0.9, RED_FILL_UNITS = 0.95;
 enum ReduceKind { RED_DENSE = 0, RED_RANKED = 1, RED_SPARSE = 2 };
 struct ReduceShape {
     uint32_t slots;
     ReduceKind kind;
+    bool wide;
 };
-inline ReduceShape reduce_tile_shape(uint64_t width, uint64_t expected) {
+template <typename Form>
+inline ReduceShape reduce_tile_shape_of(uint64_t width, uint64_t expected, uint32_t P, bool wide) {
     if (width == 0 || expected == 0)
-        return expected == 0 && width > RED_C_DENSE ? ReduceShape{RED_S_SPARSE, RED_SPARSE}
-                                                    : ReduceShape{RED_C_DENSE, RED_DENSE};
-    const double per_acc = RED_FILL * (double)width / (double)expected;   // slots per accumulator
-    const double want = per_acc * RED_C;
-    if (want <= RED_C_DENSE) return ReduceShape{RED_C_DENSE, RED_DENSE};
-    if (want > RED_S_MAX) {
-        const double wide = per_acc * RED_C_SPARSE;
-        if (wide >= RED_S_SPARSE) return ReduceShape{RED_S_SPARSE, RED_SPARSE};
-        const uint32_t slots = (uint32_t)wide / 32 * 32;
+        return expected == 0 && width > Form::C_DENSE ? ReduceShape{Form::S_SPARSE, RED_SPARSE, wide}
+                                                      : ReduceShape{Form::C_DENSE, RED_DENSE, wide};
+    const double units = RED_FILL_UNITS * (Form::BLOCK / 4 * Form::ROUNDS) - 0.5 * P;
+    auto hits = [&](uint32_t c) {
+        const double most = RED_FILL * c;
+        return units * RED_UNIT < most && units * RED_UNIT > 0.5 * c ? units * RED_UNIT : most;
+    };
+    const double per_hit = (double)width / (double)expected;          // slots per hit
+    const double want = per_hit * hits(Form::C_RANKED);
+    if ((double)expected >= RED_DENSE_FROM * (double)width) return ReduceShape{Form::C_DENSE, RED_DENSE, wide};
+    if (want > Form::S_RANKED) {
+        const double sparse = per_hit * hits(Form::C_SPARSE);
+        if (sparse >= Form::S_SPARSE) return ReduceShape{Form::S_SPARSE, RED_SPARSE, wide};
+        const uint32_t slots = (uint32_t)sparse / 32 * 32;
         // narrower than the other shape's widest tile: that one holds more per tile
-        return slots > RED_S_MAX ? ReduceShape{slots, RED_SPARSE} : ReduceShape{RED_S_MAX, RED_RANKED};
+        return slots > Form::S_RANKED ? ReduceShape{slots, RED_SPARSE, wide}
+                                      : ReduceShape{Form::S_RANKED, RED_RANKED, wide};
     }
-    return ReduceShape{(uint32_t)want / 32 * 32, RED_RANKED};
+    const uint32_t slots = (uint32_t)want / 32 * 32;
+    return ReduceShape{slots < RED_SLOTS_MIN ? RED_SLOTS_MIN : slots, RED_RANKED, wide};
+}
+inline ReduceShape reduce_tile_shape(uint64_t width, uint64_t expected, uint32_t P, bool wide) {
+    return wide ? reduce_tile_shape_of<ReduceWide>(width, expected, P, true)
+                : reduce_tile_shape_of<ReduceNarrow>(width, expected, P, false);
 }
 inline uint64_t reduce_tiles(uint64_t width, uint32_t slots) { return (width + slots - 1) / slots; }
 // per region: a 64-byte header, one descriptor per tile and one per 64 tiles,
@@ -212,7 +229,7 @@ inline size_t reduce_ws_bytes_region(uint64_t max_width, uint32_t P, uint32_t sl
     return (bytes + 63) & ~(size_t)63;
 }
 inline size_t reduce_ws_bytes(uint64_t B, uint64_t max_width, uint32_t P) {
-    return (size_t)B * reduce_ws_bytes_region(max_width, P, RED_C);     // no tile is narrower: largest
+    return (size_t)B * reduce_ws_bytes_region(max_width, P, RED_SLOTS_MIN);     // largest
 }
 
 }  // namespace okt

@@ -1,0 +1,98 @@
+"""The reduce's tiles where they can go wrong: the wide form (a launch with enough
+regions to fill the chip), contribution counts around the number of threads, units
+that end a slice, a contribution or the input, tiles with more entries than
+registers hold, more hit slots than accumulators, and more than 16 bits count.
+
+Sums are of dyadic values small enough that fp64 adds them exactly in any order, so
+the oracle's result is the only correct one, bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2201_07598_amd as okt
+from oracle import okt_oracle as orc
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def dev(a):
+    view = {np.dtype(np.uint32): np.int32, np.dtype(np.uint64): np.int64}.get(a.dtype)
+    return torch.from_numpy(np.ascontiguousarray(a).view(view) if view else a).to(DEV)
+
+
+def run_batch(regions, P, width, capacity, lead=0):
+    """regions: list of (lo, hi, [P index arrays]); checks every region against the oracle."""
+    B = len(regions)
+    parts = [p for _, _, ps in regions for p in ps]
+    lens = np.array([p.size for p in parts], dtype=np.int64).reshape(B, P)
+    idx = np.concatenate(parts + [np.zeros(0, np.uint32)]).astype(np.uint32)
+    rng = np.random.default_rng(idx.size + P)
+    val = (rng.integers(-2048, 2048, idx.size) * 2.0 ** -12).astype(np.float32)
+    off = np.zeros((B, P + 1), dtype=np.uint64)
+    starts = np.concatenate([[0], np.cumsum(lens.reshape(-1))]).astype(np.uint64)
+    for b in range(B):
+        off[b] = starts[b * P:b * P + P + 1]
+    # `lead` words in front: slices start at every word address, the input ends with the buffer
+    d_idx = torch.zeros(lead + idx.size, dtype=torch.int32, device=DEV)[lead:]
+    d_val = torch.zeros(lead + idx.size, device=DEV)[lead:]
+    d_idx.copy_(dev(idx)), d_val.copy_(dev(val))
+    lo_hi = dev(np.array([(a, b) for a, b, _ in regions], dtype=np.uint32).reshape(-1))
+    o_idx = torch.full((B * max(capacity, 1),), -1, dtype=torch.int32, device=DEV)
+    o_val = torch.zeros(B * max(capacity, 1), device=DEV)
+    nnz = torch.zeros(2 * B, dtype=torch.int64, device=DEV)
+    ws = torch.empty(okt.okt_sparse_reduce_batch_workspace_bytes(B, P, width), dtype=torch.uint8, device=DEV)
+    okt.okt_sparse_reduce_batch(d_idx, d_val, dev(off.reshape(-1)), lo_hi, B, P, width, o_idx, o_val,
+                                capacity, nnz, ws)
+    torch.cuda.synchronize()
+    got_i, got_v = o_idx.cpu().numpy().view(np.uint32), o_val.cpu().numpy()
+    nnz = nnz.cpu().numpy().reshape(B, 2)
+    for b, (lo, hi, _) in enumerate(regions):
+        s, e = int(off[b, 0]), int(off[b, P])
+        ref = orc.sparse_reduce(idx[s:e], val[s:e], off[b] - off[b, 0], lo, hi)
+        U = ref["idx"].size
+        n = min(U, capacity)
+        assert tuple(nnz[b]) == (n, U), (b, nnz[b], U)
+        at = b * capacity
+        assert np.array_equal(got_i[at:at + n], ref["idx"][:n]), b
+        assert np.array_equal(got_v[at:at + n], ref["val"][:n].astype(np.float32)), b
+
+
+def some(rng, lo, width, m):
+    return (np.sort(rng.choice(width, min(m, width), replace=False)) + lo).astype(np.uint32)
+
+
+@pytest.mark.parametrize("P,m,share", [
+    (1, 700, 0.05), (3, 333, 0.2), (16, 16, 0.1), (16, 17, 0.34), (16, 95, 0.36), (64, 40, 0.05),
+    (65, 3, 0.02), (256, 60, 0.3), (511, 5, 0.1), (512, 5, 0.1), (513, 5, 0.1), (700, 30, 0.9)])
+def test_wide_tiles_in_batches(P, m, share):
+    """At least two wide tiles to a compute unit.  `share`: what the capacity claims of
+    the region is hit, which picks the kind of tile, right or wrong."""
+    rng = np.random.default_rng(P * 1000 + m)
+    width, B = 40_003, 530
+    kinds = [some(rng, 0, width, m) for _ in range(P)]
+    regions = []
+    for b in range(B):
+        lo = b * 7_919
+        if b < 6:
+            ps = [some(rng, lo, width, int(rng.integers(0, 2 * m))) for _ in range(P)]
+        else:                                        # cheap for the host: one set, shifted
+            ps = [kinds[(p + b) % P] + np.uint32(lo) for p in range(P)]
+        regions.append((lo, lo + width - (b % 3) * 37, ps))
+    check = [0, 1, 2, 3, 4, 5, 6, 7, B - 2, B - 1]
+    keep = [r if i in check else (r[0], r[1], [p[:1] for p in r[2]]) for i, r in enumerate(regions)]
+    run_batch(keep, P, width, int(share * width), lead=P % 4)
+
+
+def test_wide_tiles_with_more_hits_than_they_have_room_for():
+    """Estimated very sparse, in fact every slot hit: tiles of 98,304 slots, all of them
+    hit (more than 16 bits count), by one contribution and by three."""
+    width, B, P = 98_304 + 1_000, 300, 3
+    full = np.arange(width, dtype=np.uint32)
+    none = np.zeros(0, np.uint32)
+    regions = [(b * 10, b * 10 + width, [none, none, none]) for b in range(B)]
+    regions[0] = (0, width, [full, none, none])
+    regions[7] = (70, 70 + width, [full + np.uint32(70), full[::2] + np.uint32(70), full + np.uint32(70)])
+    regions[B - 1] = (5, 5 + width, [none, none, full[5:]])
+    run_batch(regions, P, width, 4_000)
+    run_batch(regions, P, width, width // 20)
