@@ -33,8 +33,9 @@
  *     thread, okt_debug_spin_limit and okt_debug_slot_min_n on the whole
  *     process.
  *   - The kernels that place their output through a scan across workgroups
- *     (the select family, the reduce family, the index intersection) wait for
- *     one another through device memory.  Every such wait ends by construction
+ *     (the select family, the reduce family, the index intersection), and those
+ *     that find the exact threshold digit by digit, wait for one another through
+ *     device memory.  Every such wait ends by construction
  *     and is bounded all the same; should one run out, the kernel still exits
  *     normally, every count the call writes (d_nnz_out, d_count_out) is set to
  *     UINT64_MAX and the other outputs are unspecified (all stores stay inside
@@ -69,7 +70,8 @@ const char* okt_last_hip_error(void);
 /*
  * Test hook: the number of polls a wait between workgroups may take before it
  * gives up, for every call made after this one, process-wide (0 = the built-in
- * limit, about 2^24).  With a limit of 1 a call either completes as usual or
+ * limit, about 2^24); the digits of the exact threshold keep the built-in limit.
+ * With a limit of 1 a call either completes as usual or
  * reports UINT64_MAX counts as described above; it never hangs or faults.
  */
 void okt_debug_spin_limit(uint32_t polls);
@@ -99,8 +101,8 @@ uint64_t okt_slot_min_n(int accumulating);
  * family, okt_accumulate_select, the pass of okt_accumulate_topk_select that
  * forms the accumulator, okt_region_partition, the tile kernel of the reduce
  * family, the collect pass of okt_topk_threshold_exact (not recorded when that
- * call takes its unsampled path), the intersect kernel.  The pair is used
- * once and forgotten; a call that launches no such kernel (an argument error, an
+ * call makes none: up to two million elements, a large k, a small workspace), the
+ * intersect kernel.  The pair is used once and forgotten; a call that launches no such kernel (an argument error, an
  * empty input) leaves it armed for the next one.  For benchmarks: so that an
  * event time can be compared with a profiler's kernel duration.
  */
@@ -175,7 +177,7 @@ int okt_residual_accumulate(const float* d_grad, float* d_residual_inout, float 
  *                                   only when values tie with the k-th)
  * Integer work only: the result is exact and run-to-run identical.
  * Workspace: okt_workspace_bytes(n, 0); a smaller one (>= 64 KiB) still gives
- * the same result, with more passes over d_acc.
+ * the same result, with more passes over d_acc.  One to three launches.
  */
 int okt_topk_threshold_exact(const float* d_acc, uint64_t n, uint64_t k,
                              float* d_threshold_out, uint64_t* d_count_ge_out,
@@ -274,12 +276,12 @@ int okt_accumulate_select(const float* d_grad, float* d_residual_inout, float lr
  *   d_idx_out, d_val_out, d_nnz_out   as in okt_threshold_select
  *   d_residual_inout                  ends as acc with +0.0f at the emitted entries
  * 1 <= k <= n < 2^32; d_grad and d_residual_inout must not overlap.
- * With a workspace of okt_workspace_bytes(n, .) and n of four million or more,
- * the pass that forms the accumulator also sets aside, in index order, every
+ * With a workspace of okt_workspace_bytes(n, .), n of 131,072 or more and k up to
+ * some percent of n, the pass that forms the accumulator also sets aside, in index order, every
  * element above a bound read off a sample; the exact selection and the final
  * select then run over those candidates (a few percent of the vector), and only
  * the emitted entries are zeroed in the residual with scattered stores: 12 B per
- * element instead of 20.  A shorter vector, a smaller workspace (the minimum is
+ * element instead of 20, three launches (five for a long vector).  A shorter vector, a smaller workspace (the minimum is
  * what the three calls need), or a sample that misled take the three steps over
  * the whole vector: the results are the same.
  */

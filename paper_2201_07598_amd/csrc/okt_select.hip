@@ -60,8 +60,8 @@ static bool slots_apply(uint64_t n, size_t ws_bytes, bool accumulating) {
 }
 
 int launch_slot_finish(float* d_acc, uint64_t n, const float* d_threshold, const SlotPlan& plan,
-                       char* ws, int after, bool dense_zero, uint32_t* d_idx_out, float* d_val_out,
-                       uint64_t capacity, uint64_t* d_nnz_out, hipStream_t s) {
+                       char* ws, int after, uint32_t* d_idx_out, float* d_val_out,
+                       uint64_t capacity, uint64_t* d_nnz_out, hipStream_t s, int bounds) {
     ScanHeader* hdr = (ScanHeader*)ws;
     uint64_t* seg_desc = (uint64_t*)(ws + SCAN_HEADER_BYTES);
     uint64_t* group_desc = seg_desc + plan.nseg;
@@ -77,10 +77,10 @@ int launch_slot_finish(float* d_acc, uint64_t n, const float* d_threshold, const
     constexpr uint32_t per_wg = (SLOT_EMIT_BLOCK / WAVE) * SLOT_EMIT_TILES;
     uint32_t grid = (plan.ntiles + per_wg - 1) / per_wg;
     if (grid < 8 * device_cus()) grid = 8 * device_cus();
-    auto* emit = after == SLOT_ZERO      ? slot_emit_kernel<SLOT_ZERO, true>
-                 : after == SLOT_RESTORE ? slot_emit_kernel<SLOT_RESTORE, true>
-                 : dense_zero            ? slot_emit_kernel<SLOT_KEEP, true>
-                                         : slot_emit_kernel<SLOT_KEEP, false>;
+    auto* emit = after == SLOT_ZERO      ? slot_emit_kernel<SLOT_ZERO, true, 1>
+                 : after == SLOT_RESTORE ? slot_emit_kernel<SLOT_RESTORE, true, 1>
+                 : bounds > 1            ? slot_emit_kernel<SLOT_KEEP, false, SLOT_BOUNDS>
+                                         : slot_emit_kernel<SLOT_KEEP, false, 1>;
     hipLaunchKernelGGL(emit, dim3(grid), dim3(SLOT_EMIT_BLOCK), 0, s, d_acc, (uint32_t)n, d_threshold,
                        counts, place, slots, dense_list, hdr, plan.ntiles, d_idx_out, d_val_out,
                        capacity);
@@ -115,7 +115,7 @@ static int launch_dense_select(float* d_acc, uint64_t n, const float* d_threshol
                            (uint32_t)(scan_ws_bytes(plan.nseg) / 8), spin_limit_setting());
         timing_after(s);
         return launch_slot_finish(d_acc, n, d_threshold, plan, ws, zero ? SLOT_ZERO : SLOT_KEEP,
-                                  zero, d_idx_out, d_val_out, capacity, d_nnz_out, s);
+                                  d_idx_out, d_val_out, capacity, d_nnz_out, s);
     }
     ScanHeader* hdr = (ScanHeader*)d_ws;
     uint64_t* seg_desc = (uint64_t*)((char*)d_ws + SCAN_HEADER_BYTES);
@@ -240,7 +240,7 @@ extern "C" int okt_accumulate_select(const float* d_grad, float* d_residual_inou
                            plan.ntiles, (uint64_t*)ws, (uint32_t)(scan_ws_bytes(plan.nseg) / 8),
                            spin_limit_setting());
         timing_after(s);
-        return launch_slot_finish(d_residual_inout, n, d_threshold, plan, ws, SLOT_RESTORE, true,
+        return launch_slot_finish(d_residual_inout, n, d_threshold, plan, ws, SLOT_RESTORE,
                                   d_idx_out, d_val_out, capacity, d_nnz_out, s);
     }
     ScanHeader* hdr = (ScanHeader*)d_ws;

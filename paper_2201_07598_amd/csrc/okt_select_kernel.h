@@ -170,6 +170,7 @@ __device__ __forceinline__ uint32_t select_walk(const float* acc, uint64_t start
 //                             output position holding index o
 //   walk_emit(walked, i, o)   the same for an entry written by the second walk of
 //                             a piece that overflowed its stash
+//   gathers                   the output index is read from memory
 //   restore                   the first pass already zeroed the stashed entries
 //                             (the fused kernel's dense write-back): those that
 //                             do not fit the output are put back
@@ -181,24 +182,28 @@ __device__ __forceinline__ uint32_t select_walk(const float* acc, uint64_t start
 // candidates drawn from a dense residual (idx_in set), or that residual itself
 // (idx_in null); an entry's place in the residual is zeroed when it goes out.
 struct DenseSource {
+    static constexpr bool gathers = false;
     static constexpr bool restore = false;
     __device__ __forceinline__ uint32_t out_index(uint32_t i) const { return i; }
     __device__ __forceinline__ void stash_emit(float* walked, uint32_t i, uint32_t) const { walked[i] = 0.0f; }
     __device__ __forceinline__ void walk_emit(float* walked, uint32_t i, uint32_t) const { walked[i] = 0.0f; }
 };
 struct DenseZeroedSource {
+    static constexpr bool gathers = false;
     static constexpr bool restore = true;
     __device__ __forceinline__ uint32_t out_index(uint32_t i) const { return i; }
     __device__ __forceinline__ void stash_emit(float*, uint32_t, uint32_t) const {}
     __device__ __forceinline__ void walk_emit(float* walked, uint32_t i, uint32_t) const { walked[i] = 0.0f; }
 };
 struct DenseCopySource {
+    static constexpr bool gathers = false;
     static constexpr bool restore = false;
     __device__ __forceinline__ uint32_t out_index(uint32_t i) const { return i; }
     __device__ __forceinline__ void stash_emit(float*, uint32_t, uint32_t) const {}
     __device__ __forceinline__ void walk_emit(float*, uint32_t, uint32_t) const {}
 };
 struct CooSource {
+    static constexpr bool gathers = true;
     static constexpr bool restore = false;
     const uint32_t* idx_in;
     __device__ __forceinline__ uint32_t out_index(uint32_t i) const { return idx_in[i]; }
@@ -206,6 +211,7 @@ struct CooSource {
     __device__ __forceinline__ void walk_emit(float*, uint32_t, uint32_t) const {}
 };
 struct CandidateSource {
+    static constexpr bool gathers = true;
     static constexpr bool restore = false;
     const uint32_t* idx_in;
     float* res;                              // used only when idx_in is set
@@ -265,16 +271,33 @@ __device__ __forceinline__ void select_finish(
     const uint64_t first = (uint64_t)exclusive + wave_first;
     const bool all_stashed = count == stashed;
     const uint32_t final_entries = all_stashed ? count : resume_count;   // of the stash
-    for (uint32_t j = lane; j < final_entries; j += WAVE) {
-        const uint64_t pos = first + j;
-        const StashEntry e = mine[j];
-        if (pos < capacity) {
-            const uint32_t o = source.out_index(e.idx);
-            idx_out[pos] = o;
-            val_out[pos] = e.val;
-            source.stash_emit(acc, e.idx, o);
-        } else if (Source::restore) {
-            acc[e.idx] = e.val;             // output full: the entry stays in the residual
+    // four turns at a time where the output index is gathered (a COO list): a turn is
+    // then a round trip to memory (15 segments of 250,000 entries: 10.1 -> 8.8 us)
+    constexpr int TURNS = Source::gathers ? 4 : 1;
+    for (uint32_t j0 = lane; j0 < final_entries; j0 += TURNS * WAVE) {
+        StashEntry e[TURNS];
+        uint32_t o[TURNS];
+#pragma unroll
+        for (int t = 0; t < TURNS; ++t) {
+            const uint32_t j = j0 + t * WAVE;
+            if (j < final_entries) {
+                e[t] = mine[j];
+                if (first + j < capacity) o[t] = source.out_index(e[t].idx);
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < TURNS; ++t) {
+            const uint32_t j = j0 + t * WAVE;
+            const uint64_t pos = first + j;
+            if (j < final_entries) {
+                if (pos < capacity) {
+                    idx_out[pos] = o[t];
+                    val_out[pos] = e[t].val;
+                    source.stash_emit(acc, e[t].idx, o[t]);
+                } else if (Source::restore) {
+                    acc[e[t].idx] = e[t].val;             // output full: the entry stays in the residual
+                }
+            }
         }
     }
     if (!all_stashed) {

@@ -132,9 +132,11 @@ inline size_t restore_ws_bytes(uint64_t max_local) {
 constexpr int RS_BITS1 = 11, RS_BITS2 = 11, RS_BITS3 = 9;   // 11 + 11 + 9 = 31
 constexpr int RS_MAX_BINS = 1 << 11;
 constexpr size_t RS_STATE_BYTES = 256;
-constexpr size_t RS_HIST_BYTES = 4 * RS_MAX_BINS * sizeof(uint32_t);   // sample + three digits
-constexpr uint64_t RS_SAMPLE_MIN_N = 4u << 20;   // shorter vectors are simply read three times
-constexpr uint64_t RS_SAMPLE_BLOCKS = 1024;      // sample: about this many blocks of 1024 elements
+constexpr size_t RS_HIST_BYTES = 4 * RS_MAX_BINS * sizeof(uint32_t);   // the digits'
+constexpr uint64_t RS_SAMPLE_MIN_N = 4u << 20;   // vectors whose workspace has room for slots
+constexpr uint64_t RS_SAMPLE_FROM_N = 1u << 17;  // shorter vectors are simply read three times
+constexpr uint64_t COLLECT_FROM_N = 2u << 20;    // up to here the digits run over the vector, bound or not
+constexpr uint32_t TINY_N = 16384;               // up to here one workgroup finds the threshold
 inline size_t threshold_ws_min_bytes() { return RS_STATE_BYTES + RS_HIST_BYTES; }
 inline size_t threshold_ws_bytes(uint64_t n) {
     // state + histograms + room for the candidate keys (a few percent of the vector)
@@ -146,9 +148,9 @@ inline size_t threshold_ws_bytes(uint64_t n) {
 // collected.  A shorter vector takes the three steps one after the other.
 inline size_t refresh_scan_bytes(uint64_t n) { return (select_ws_bytes(n) + 255) & ~(size_t)255; }
 inline size_t refresh_ws_bytes(uint64_t n) {
-    if (n < RS_SAMPLE_MIN_N) return 0;
+    if (n < RS_SAMPLE_FROM_N) return 0;
     return threshold_ws_min_bytes() + 2 * refresh_scan_bytes(n) + 8 * (size_t)(n / 8 + 1024) +
-           round_up_256(slot_ws_bytes(n));
+           (n < RS_SAMPLE_MIN_N ? 0 : round_up_256(slot_ws_bytes(n)));
 }
 
 // ---- sparse reduce ----

@@ -142,6 +142,21 @@ __device__ __forceinline__ void slot_clear_scan_state(uint64_t* __restrict__ sta
         state[i] = i == SCAN_SPIN_WORD ? (uint64_t)spin_limit : 0ull;
 }
 
+// What the passes test against: the caller's threshold, or the least of `bounds`
+// magnitude keys (a refresh iteration's sample leaves several).
+template <int BOUNDS>
+__device__ __forceinline__ float slot_threshold(const float* __restrict__ d_threshold) {
+    if (BOUNDS == 1) return *d_threshold;
+    uint32_t lo = __float_as_uint(d_threshold[0]);
+#pragma unroll
+    for (int i = 1; i < BOUNDS; ++i) {
+        const uint32_t b = __float_as_uint(d_threshold[i]);
+        lo = b < lo ? b : lo;
+    }
+    return __uint_as_float(lo);
+}
+constexpr int SLOT_BOUNDS = 16;
+
 // ---- first pass over a vector that is only read ----
 template <bool NT, typename Test>
 __device__ __forceinline__ void slot_fill_tile(const float* __restrict__ acc, uint32_t n, Test test,
@@ -237,7 +252,7 @@ __global__ __launch_bounds__(SLOT_FILL_BLOCK) void slot_fill_accumulate_kernel(
     slot_clear_scan_state(scan_state, scan_words, spin_limit);
     const uint32_t tile = blockIdx.x * (SLOT_FILL_BLOCK / WAVE) + (threadIdx.x >> 6);
     if (tile >= ntiles) return;
-    const float th = *d_threshold;
+    const float th = slot_threshold<ZERO ? 1 : SLOT_BOUNDS>(d_threshold);   // candidates: the sample's bounds
     if (th == th)
         slot_fill_accumulate_tile<ZERO, NT>(grad, res, lr, n, TestFloat{__builtin_fabsf(th)}, counts,
                                             slots, tile, s_stage[threadIdx.x >> 6], ntiles);
@@ -488,14 +503,14 @@ __device__ __forceinline__ void slot_emit_tiles(float* __restrict__ acc, uint32_
     }
 }
 
-template <int AFTER, bool DENSE_ZERO>
+template <int AFTER, bool DENSE_ZERO, int BOUNDS>
 __global__ __launch_bounds__(SLOT_EMIT_BLOCK) void slot_emit_kernel(
     float* __restrict__ acc, uint32_t n, const float* __restrict__ d_threshold,
     const uint16_t* __restrict__ counts, const uint32_t* __restrict__ place,
     const SlotEntry* __restrict__ slots, const uint32_t* __restrict__ list,
     const ScanHeader* __restrict__ hdr, uint32_t ntiles, uint32_t* __restrict__ idx_out,
     float* __restrict__ val_out, uint64_t capacity) {
-    const float th = *d_threshold;
+    const float th = slot_threshold<BOUNDS>(d_threshold);
     if (th == th)
         slot_emit_tiles<AFTER, DENSE_ZERO>(acc, n, TestFloat{__builtin_fabsf(th)}, counts, place,
                                            slots, list, hdr, ntiles, idx_out, val_out, capacity);
@@ -511,12 +526,11 @@ __global__ __launch_bounds__(SLOT_EMIT_BLOCK) void slot_emit_kernel(
 uint64_t slot_min_n(bool accumulating);
 // Second and third pass of a select through slots; the first pass has filled the
 // counts and the slots of the workspace `ws` (laid out by `plan`, scan state
-// cleared).  `d_threshold`: what the first pass tested against.  `after`: what the
-// entries of the slots still need done to the vector; `dense_zero`: the walk over
-// a dense tile zeroes what it writes out.
+// cleared).  `d_threshold`: what the first pass tested against (the least of `bounds`).  `after`: what the
+// entries of the slots still need done to the vector.
 int launch_slot_finish(float* d_acc, uint64_t n, const float* d_threshold, const SlotPlan& plan,
-                       char* ws, int after, bool dense_zero, uint32_t* d_idx_out, float* d_val_out,
-                       uint64_t capacity, uint64_t* d_nnz_out, hipStream_t s);
+                       char* ws, int after, uint32_t* d_idx_out, float* d_val_out,
+                       uint64_t capacity, uint64_t* d_nnz_out, hipStream_t s, int bounds = 1);
 
 }  // namespace okt
 #endif

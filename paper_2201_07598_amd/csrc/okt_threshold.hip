@@ -2,20 +2,18 @@
 // 2-4, th_re_evaluate; Sec. 3.1.3).  The paper sorts; this is an exact
 // selection on the 31-bit magnitude key that reads the vector about once.
 //
-//   1. A histogram of the first digit (exponent and three mantissa bits) over a
-//      strided sample of about a million elements gives a key that lies, with a
-//      wide margin, below the k-th largest one.
+//   1. A strided sample gives a key that lies, with a margin, below the k-th largest.
 //   2. One streaming pass over the whole vector copies every key at or above
 //      that bound, a little more than k of them, to the workspace (the select
 //      kernel's loop: one compare per element, per-wave LDS stash, one global
 //      atomic per workgroup for what the stashes hold at the end).
 //   3. If at least k keys were collected (always, unless the sample misled),
-//      rank k is among them, and an exact MSD radix select, digits of
-//      11 + 11 + 9 bits, runs over the candidates only.  Otherwise, or when the
-//      vector is short or the workspace small, the same radix select runs over
-//      the whole vector (three more passes).
-// Six launches at most: wherever a complete histogram has to be read, the
-// workgroup that added its counts last does the reading, in the same launch.
+//      rank k is among them, and an exact MSD radix select of two digits from the
+//      bound up runs over the candidates only.  Otherwise, or when the vector is
+//      very short or the workspace small, a radix select of 11 + 11 + 9 bits runs over
+//      the whole vector (three more passes).  A vector of up to COLLECT_FROM_N elements
+//      skips step 2: the two digits run over all of it.
+// Three launches at most (two without step 2, one up to TINY_N elements).
 // Either way the answer is the exact order statistic: all arithmetic is integer
 // counting, the sample only decides how much is read.  State lives in the
 // workspace on the device; the host never waits.
@@ -26,8 +24,8 @@
 // candidates is the fused accumulate+select kernel run against the sample's
 // bound, writing the accumulator over the residual and the candidates, in index
 // order with their indices, to the workspace; the radix select runs over the
-// candidate values; and the final select walks the candidates instead of the
-// vector, zeroing the residual where an entry goes out.  If the sample misled,
+// candidate values; and the final select, in the same launch, walks the candidates
+// instead of the vector, zeroing the residual where an entry goes out.  If the sample misled,
 // the last two steps run over the whole vector instead: same results.
 #include "okt_device.h"
 #include "okt_select_kernel.h"
@@ -36,252 +34,139 @@
 
 namespace okt {
 
+constexpr int PHASES_MAX = 4;      // digits of resolve_kernel: one from a bound and three general ones at most
+constexpr int BOUNDS = 16;         // workgroups of the sample
+constexpr uint32_t HIST_WORDS = 4 * RS_MAX_BINS;
+
 struct RadixState {
-    uint32_t prefix;       // digits found so far (the high bits of the answer)
-    uint32_t use_cand;     // 1: the radix passes run over the candidate keys
-    uint64_t k_rem;        // rank still to find inside the current prefix
-    uint64_t above;        // keys strictly above the current prefix
-    uint64_t m;            // number of 32-bit words the radix passes run over
-    uint32_t cand_lo;      // every key >= cand_lo is a candidate
-    uint32_t pad;
-    unsigned long long cand_count;    // number of candidates found by the counting pass
-    uint32_t done[4];      // workgroups that have handed in their histogram: sample, digits 1-3
-    uint64_t collected[2]; // ordered collection (refresh iteration): candidates written, found
+    uint32_t bound[BOUNDS];           // the sample's: every key >= their least is a candidate
+    unsigned long long cand_count;    // candidates found by the collect pass
+    uint64_t collected[2];            // ordered collection (refresh iteration): candidates written, found
+    uint32_t done[PHASES_MAX];        // shares of a phase of resolve_kernel that are finished
+    uint32_t ticket;
 };
 static_assert(sizeof(RadixState) <= RS_STATE_BYTES, "state fits its slot");
 
-constexpr int HIST_BLOCK = 256;
-constexpr int HIST_ITERS = 4;                              // float4 per thread per step
-constexpr int HIST_STEP4 = HIST_BLOCK * HIST_ITERS;        // float4 per workgroup per step
-
-// Find the bin that holds rank k_rem counting from the top bin down: 256 threads,
-// thread t owns the PER bins below the (t * PER) highest ones; an inclusive scan
-// over the threads' sums names the owner, who walks its own few bins.  The
-// owner (exactly one thread) stores (bin, keys above the bin) to s_result.
-template <int BITS>
-__device__ __forceinline__ void pick_bin(const uint32_t* __restrict__ hist, uint64_t k_rem,
-                                         uint64_t* s_wave_total, uint64_t* s_result) {
-    constexpr int BINS = 1 << BITS;
-    constexpr int PER = BINS / 256;                  // bins per thread (8 or 2)
-    const int t = threadIdx.x, lane = t & (WAVE - 1), wave = t >> 6;
-    uint32_t c[PER];
-    uint64_t mine = 0;
+__device__ __forceinline__ uint32_t cand_bound(const RadixState* state) {
+    uint32_t lo = state->bound[0];
 #pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        // j = 0 is the thread's highest bin; the counts were added by other workgroups
-        c[j] = __hip_atomic_load(&hist[BINS - 1 - (t * PER + j)], __ATOMIC_RELAXED,
-                                 __HIP_MEMORY_SCOPE_AGENT);
+    for (int i = 1; i < BOUNDS; ++i) lo = state->bound[i] < lo ? state->bound[i] : lo;
+    return lo;
+}
+
+// Find the bin that holds rank k_rem counting from the top bin down.  1024 threads,
+// thread t owns the `per` bins below the t * per highest ones; an inclusive scan
+// over the threads' sums names the owner, who walks its own few bins.  The
+// owner (exactly one thread, if the bins hold that many) stores (bin, keys above the
+// bin, keys in it) to s_result, whose first word is all ones otherwise.
+template <bool ELSEWHERE>             // the counts were added by other workgroups
+__device__ __forceinline__ void pick_bin(const uint32_t* hist, uint32_t bins, uint32_t k_rem,
+                                         uint32_t* s_wave, uint32_t* s_result) {
+    constexpr int PER_MAX = 8;
+    const int t = threadIdx.x, lane = t & (WAVE - 1), wave = t >> 6;
+    const uint32_t per = bins > 1024 ? bins / 1024 : 1;               // bins is a power of two, at most 8192
+    const bool owner = (uint32_t)t * per < bins;
+    uint32_t c[PER_MAX], mine = 0;
+#pragma unroll
+    for (int j = 0; j < PER_MAX; ++j) {
+        c[j] = 0;
+        if (owner && (uint32_t)j < per) {
+            const uint32_t* at = hist + (bins - 1 - ((uint32_t)t * per + j));   // j = 0 is the thread's highest bin
+            c[j] = ELSEWHERE ? __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *at;
+        }
         mine += c[j];
     }
-    const uint64_t incl = wave_inclusive_scan<uint64_t>(mine);
-    if (lane == WAVE - 1) s_wave_total[wave] = incl;
+    const uint32_t incl = wave_inclusive_scan_u32(mine);
+    if (lane == WAVE - 1) s_wave[wave] = incl;
+    if (t == 0) s_result[0] = ~0u;
     __syncthreads();
-    uint64_t before = incl - mine;
-    for (int w = 0; w < wave; ++w) before += s_wave_total[w];
-    if (before < k_rem && k_rem <= before + mine) {  // true for exactly one thread
-        uint64_t above = before;
-        int j = 0;
-        while (j < PER - 1 && above + c[j] < k_rem) above += c[j++];
-        s_result[0] = (uint64_t)(BINS - 1 - (t * PER + j));
-        s_result[1] = above;                         // above < k_rem <= above + hist[bin]
-    }
-    __syncthreads();
-}
-
-// Adds a workgroup's counts to the global histogram and waits for the answers: an
-// atomic that has returned has been carried out where every CU sees it, which a
-// release fence would only achieve by writing the whole L2 back.
-template <int BINS>
-__device__ __forceinline__ void add_counts(uint32_t* __restrict__ hist, const uint32_t* s_hist) {
-    uint32_t seen = 0;
+    uint32_t before = incl - mine;
 #pragma unroll
-    for (int b = threadIdx.x; b < BINS; b += HIST_BLOCK) {     // all out first, then one wait
-        const uint32_t c = s_hist[b];
-        if (c) seen |= atomicAdd(&hist[b], c);
-    }
-    asm volatile("" ::"v"(seen));
-}
-// True in exactly one workgroup of the grid: the one that comes last.  Called by
-// every workgroup once add_counts has returned; the last one may then
-// read the complete histogram (with device-scope loads).
-__device__ __forceinline__ bool last_workgroup(uint32_t* counter, uint32_t* s_flag) {
-    __syncthreads();
-    if (threadIdx.x == 0) *s_flag = atomicAdd(counter, 1u) == gridDim.x - 1 ? 1u : 0u;
-    __syncthreads();
-    return *s_flag != 0;
-}
-
-// ---------------------------------------------------------------------------
-// radix passes (over the candidates, or over the whole vector)
-// ---------------------------------------------------------------------------
-// One digit pass.  SHIFT/BITS select the digit; a key takes part if its bits
-// above the digit equal state->prefix (always, for the first digit).  The source
-// is the candidate array or the vector itself, as the state says; both are
-// arrays of 32-bit words whose low 31 bits are the key.
-// The first pass also decides what the passes run over: the candidates, if the
-// counting pass ran and rank k is among them, else the whole vector.  The
-// workgroup that hands in its counts last picks the digit (the bin that holds
-// the rank still sought) and leaves the state for the next pass; after the last
-// digit it writes the threshold and its count.
-template <int SHIFT, int BITS, int PASS>
-__global__ __launch_bounds__(HIST_BLOCK) void radix_hist_kernel(
-    const float* __restrict__ acc, const uint32_t* __restrict__ cand, RadixState* state,
-    uint32_t* __restrict__ hist, uint64_t n, uint64_t k, uint64_t cand_cap, int sampled,
-    float* threshold_out, uint64_t* count_ge_out) {
-    constexpr int BINS = 1 << BITS;
-    constexpr bool FIRST = PASS == 1, LAST = PASS == 3;
-    static_assert(HIST_BLOCK == 256, "pick_bin is written for 256 threads");
-    __shared__ uint32_t s_hist[BINS];
-    __shared__ uint64_t s_wave_total[4], s_result[2];
-    __shared__ uint32_t s_flag;
-    uint32_t use_cand;
-    uint64_t m64;
-    if (FIRST) {
-        // keys at or above cand_lo: counted by the collect pass, or by the ordered
-        // collection of a refresh iteration (all ones if one of its waits gave up)
-        const uint64_t found = sampled == 2 ? state->collected[1] : state->cand_count;
-        use_cand = sampled && k <= found && found <= cand_cap ? 1u : 0u;   // rank k is among them
-        m64 = use_cand ? found : n;
-    } else {
-        use_cand = state->use_cand;
-        m64 = state->m;
-    }
-    const uint32_t* src = use_cand ? cand : reinterpret_cast<const uint32_t*>(acc);
-    const uint32_t m = (uint32_t)m64;
-    const uint32_t m4 = m >> 2;
-    uint32_t base4 = blockIdx.x * (uint32_t)HIST_STEP4;
-    for (int b = threadIdx.x; b < BINS; b += HIST_BLOCK) s_hist[b] = 0;
-    const uint32_t prefix = FIRST ? 0u : state->prefix;
-    const uint64_t k_rem = FIRST ? k : state->k_rem;
-    const uint64_t above_so_far = FIRST ? 0ull : state->above;
-    __syncthreads();
-
-    auto take = [&](uint32_t word) {
-        const uint32_t key = word & ABS_MASK;
-        if (FIRST || (key >> (SHIFT + BITS)) == prefix)
-            atomicAdd(&s_hist[(key >> SHIFT) & (BINS - 1)], 1u);
-    };
-    const uint4* src4 = reinterpret_cast<const uint4*>(src);
-    const uint32_t stride = gridDim.x * (uint32_t)HIST_STEP4;
-    // m4 < 2^30 and stride <= 2^21, so base4 never wraps
-    // a pass over the whole of a vector longer than the last-level cache finds nothing
-    // of it there (wave-uniform choice)
-    const bool around_cache = !use_cand && m64 >= STREAM_PAST_CACHE_N;
-    for (; base4 + HIST_STEP4 <= m4; base4 += stride) {
-        uint4 v[HIST_ITERS];
+    for (int w = 0; w < 1024 / WAVE; ++w)
+        if (w < wave) before += s_wave[w];
+    if (before < k_rem && k_rem <= before + mine) {  // true for at most one thread
+        uint32_t above = before, in_bin = c[0], j = 0;
 #pragma unroll
-        for (int it = 0; it < HIST_ITERS; ++it) {
-            const uint4* at = src4 + base4 + it * HIST_BLOCK + threadIdx.x;
-            if (around_cache) {
-                typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-                const v4u q = __builtin_nontemporal_load(reinterpret_cast<const v4u*>(at));
-                v[it] = make_uint4(q.x, q.y, q.z, q.w);
-            } else {
-                v[it] = *at;
+        for (int i = 0; i < PER_MAX - 1; ++i)
+            if ((uint32_t)i == j && above + c[i] < k_rem) {
+                above += c[i];
+                in_bin = c[i + 1];
+                ++j;
             }
-        }
-#pragma unroll
-        for (int it = 0; it < HIST_ITERS; ++it) {
-            take(v[it].x); take(v[it].y); take(v[it].z); take(v[it].w);
-        }
+        s_result[0] = bins - 1 - ((uint32_t)t * per + j);
+        s_result[1] = above;                         // above < k_rem <= above + in_bin
+        s_result[2] = in_bin;
     }
-    if (base4 < m4) {       // ragged remainder: one partial step, owned by one workgroup
-        for (int it = 0; it < HIST_ITERS; ++it) {
-            const uint32_t i = base4 + it * HIST_BLOCK + threadIdx.x;
-            if (i < m4) {
-                const uint4 x = src4[i];
-                take(x.x); take(x.y); take(x.z); take(x.w);
-            }
-        }
-    }
-    if (blockIdx.x == 0 && threadIdx.x < (m & 3u)) take(src[(m4 << 2) + threadIdx.x]);
     __syncthreads();
-    add_counts<BINS>(hist, s_hist);
-    if (!last_workgroup(&state->done[PASS], &s_flag)) return;
-
-    // ---- the complete histogram: pick the digit ----
-    pick_bin<BITS>(hist, k_rem, s_wave_total, s_result);
-    if (threadIdx.x != 0) return;
-    const int bin = (int)s_result[0];
-    const uint64_t above = s_result[1];
-    const uint32_t found = (prefix << BITS) | (uint32_t)bin;
-    state->prefix = found;
-    state->k_rem = k_rem - above;
-    state->above = above_so_far + above;
-    if (FIRST) {
-        state->use_cand = use_cand;
-        state->m = m64;
-    }
-    if (LAST) {
-        *threshold_out = __uint_as_float(found);
-        *count_ge_out = above_so_far + above +
-                        __hip_atomic_load(&hist[bin], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
 }
 
 // ---------------------------------------------------------------------------
-// sampling, candidate range, counting pass
+// the sample
 // ---------------------------------------------------------------------------
-// First-digit histogram over every `stride`-th block of 1024 elements.  A
-// workgroup takes SAMPLE_PER_WG sampled blocks with all their loads in flight,
-// so that few workgroups (few global atomics per hot bin) still cover the
-// sample at memory latency.  The workgroup that comes last reads the bound off
-// the complete histogram: the first-digit bin that holds the sample rank
-// k' + margin, k' = k * sample / n; every key from the bottom of that bin up is
-// a candidate.
-constexpr int SAMPLE_PER_WG = 8;
-// With `grad` set the sampled values are eps + lr * G formed on the fly (`acc` is
-// then the residual before the accumulate).
-__global__ __launch_bounds__(HIST_BLOCK) void sample_hist_kernel(
-    const float* __restrict__ acc, const float* __restrict__ grad, float lr,
-    uint32_t nblocks_sampled, uint32_t stride, uint32_t* __restrict__ hist, RadixState* state,
-    uint64_t n, uint64_t k) {
-    constexpr int BINS = 1 << RS_BITS1;
-    __shared__ uint32_t s_hist[BINS];
-    __shared__ uint64_t s_wave_total[4], s_result[2];
-    __shared__ uint32_t s_flag;
-    for (int b = threadIdx.x; b < BINS; b += HIST_BLOCK) s_hist[b] = 0;
-    __syncthreads();
-    // sampled blocks are whole: the host only samples the first floor(n/1024) blocks
-    float4 v[SAMPLE_PER_WG];
-#pragma unroll
-    for (int u = 0; u < SAMPLE_PER_WG; ++u) {
-        const uint32_t j = blockIdx.x * SAMPLE_PER_WG + u;
-        v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (j < nblocks_sampled) {
-            const size_t at = (size_t)j * stride * 256 + threadIdx.x;
-            v[u] = reinterpret_cast<const float4*>(acc)[at];
-            if (grad) {
-                const float4 g = reinterpret_cast<const float4*>(grad)[at];
-                v[u].x = __fadd_rn(v[u].x, __fmul_rn(lr, g.x));
-                v[u].y = __fadd_rn(v[u].y, __fmul_rn(lr, g.y));
-                v[u].z = __fadd_rn(v[u].z, __fmul_rn(lr, g.z));
-                v[u].w = __fadd_rn(v[u].w, __fmul_rn(lr, g.w));
-            }
-        }
-    }
-#pragma unroll
-    for (int u = 0; u < SAMPLE_PER_WG; ++u) {
-        if (blockIdx.x * SAMPLE_PER_WG + u < nblocks_sampled) {
-            atomicAdd(&s_hist[magnitude_key(v[u].x) >> 20], 1u);
-            atomicAdd(&s_hist[magnitude_key(v[u].y) >> 20], 1u);
-            atomicAdd(&s_hist[magnitude_key(v[u].z) >> 20], 1u);
-            atomicAdd(&s_hist[magnitude_key(v[u].w) >> 20], 1u);
-        }
-    }
-    __syncthreads();
-    add_counts<BINS>(hist, s_hist);
-    if (!last_workgroup(&state->done[0], &s_flag)) return;
+// A bound that lies, with a margin, below the k-th largest key, from a sample of
+// 131,072 elements: 8192 blocks of 16 (a line of memory each), spread evenly.  Each
+// of the BOUNDS workgroups histograms every sixteenth of them (13 bits of the key: a
+// bin is a thirty-second of an octave), and its own bound is the bottom of the bin
+// that holds the sample rank k' + sqrt(k'), k' = 8192 k / n: one standard
+// deviation below the target rank.  The least of the sixteen is the one that counts:
+// all of them lie above the k-th largest key with a probability of 0.16 ^ 16, and
+// still one in a hundred million where neighbours are so alike that a count
+// deviates twice as far.  About 1.3 k elements pass it at k = 1 % of a vector, 2 k at
+// 0.1 %.  (One histogram over all the workgroups needs cleared memory and a last
+// workgroup to read it: two launches, 16 us, against 6 us for this one.)
+//
+// The same launch clears what the later ones need cleared: the radix state, the
+// histograms and up to two scan states.  With `grad` set the sampled values are
+// eps + lr * G formed on the fly (`acc` is then the residual before the accumulate).
+constexpr int SAMPLE_BLOCK = 1024;
+constexpr uint32_t SAMPLE_RUN = 16, SAMPLE_RUNS = 8192, SAMPLE_RUNS_PER_WG = SAMPLE_RUNS / BOUNDS;
+constexpr uint32_t SAMPLE_BINS = 8192;
+constexpr int SAMPLE_SHIFT = 31 - 13;
+static_assert(RS_SAMPLE_FROM_N >= SAMPLE_RUN * SAMPLE_RUNS, "the sampled blocks are distinct");
 
-    const uint64_t sample = (uint64_t)nblocks_sampled * 1024;
-    // k' rounded up; margin of 16 standard deviations of a binomial count, and some
-    const uint64_t kp = (k * sample + n - 1) / n;      // k, sample < 2^32: no overflow
-    uint64_t margin = 64;
-    while (margin * margin < 256 * kp) margin += margin / 2 + 1;     // ~ 16 sqrt(k')
-    uint64_t r_lo = kp + margin;                                     // a sample rank safely below the target
-    if (r_lo > sample) r_lo = sample;
-    pick_bin<RS_BITS1>(hist, r_lo, s_wave_total, s_result);
-    if (threadIdx.x == 0) state->cand_lo = (uint32_t)s_result[0] << 20;
+__global__ __launch_bounds__(SAMPLE_BLOCK) void sample_bound_kernel(
+    const float* __restrict__ acc, const float* __restrict__ grad, float lr, uint32_t n, uint32_t k,
+    RadixState* state, uint32_t* __restrict__ hist, uint64_t* __restrict__ scan_a, uint32_t words_a,
+    uint64_t* __restrict__ scan_b, uint32_t words_b, uint32_t spin_limit) {
+    __shared__ __attribute__((aligned(16))) uint32_t s_hist[SAMPLE_BINS];
+    __shared__ uint32_t s_wave[SAMPLE_BLOCK / WAVE], s_result[3];
+    const uint32_t tid = threadIdx.x, wg = blockIdx.x;
+    constexpr uint32_t PER = SAMPLE_RUNS_PER_WG * 4 / SAMPLE_BLOCK;
+    float4 v[PER], g[PER];
+#pragma unroll
+    for (uint32_t u = 0; u < PER; ++u) {
+        const uint32_t run = wg + BOUNDS * (u * (SAMPLE_BLOCK / 4) + (tid >> 2));
+        const uint64_t at = (uint64_t)run * (n / SAMPLE_RUN) / SAMPLE_RUNS * 4 + (tid & 3u);   // in quads
+        v[u] = reinterpret_cast<const float4*>(acc)[at];
+        if (grad) g[u] = reinterpret_cast<const float4*>(grad)[at];
+    }
+    for (uint32_t b = tid; b < SAMPLE_BINS / 4; b += SAMPLE_BLOCK) reinterpret_cast<uint4*>(s_hist)[b] = uint4{0, 0, 0, 0};
+    const uint32_t i = wg * SAMPLE_BLOCK + tid;
+    for (uint32_t w = i; w < HIST_WORDS; w += BOUNDS * SAMPLE_BLOCK) hist[w] = 0;
+    for (uint32_t w = i; w < words_a; w += BOUNDS * SAMPLE_BLOCK) scan_a[w] = w == SCAN_SPIN_WORD ? (uint64_t)spin_limit : 0ull;
+    for (uint32_t w = i; w < words_b; w += BOUNDS * SAMPLE_BLOCK) scan_b[w] = w == SCAN_SPIN_WORD ? (uint64_t)spin_limit : 0ull;
+    if (i >= BOUNDS && i < sizeof(RadixState) / 4) reinterpret_cast<uint32_t*>(state)[i] = 0;   // behind the bounds
+    __syncthreads();
+#pragma unroll
+    for (uint32_t u = 0; u < PER; ++u) {
+        if (grad) {
+            v[u].x = __fadd_rn(v[u].x, __fmul_rn(lr, g[u].x));
+            v[u].y = __fadd_rn(v[u].y, __fmul_rn(lr, g[u].y));
+            v[u].z = __fadd_rn(v[u].z, __fmul_rn(lr, g[u].z));
+            v[u].w = __fadd_rn(v[u].w, __fmul_rn(lr, g[u].w));
+        }
+        atomicAdd(&s_hist[magnitude_key(v[u].x) >> SAMPLE_SHIFT], 1u);
+        atomicAdd(&s_hist[magnitude_key(v[u].y) >> SAMPLE_SHIFT], 1u);
+        atomicAdd(&s_hist[magnitude_key(v[u].z) >> SAMPLE_SHIFT], 1u);
+        atomicAdd(&s_hist[magnitude_key(v[u].w) >> SAMPLE_SHIFT], 1u);
+    }
+    __syncthreads();
+    constexpr uint32_t sample = SAMPLE_RUNS_PER_WG * SAMPLE_RUN;
+    const uint32_t kp = (uint32_t)(((uint64_t)k * sample + n / 2) / n);       // at most `sample`
+    uint32_t rank = kp + (uint32_t)(__builtin_sqrtf((float)kp) + 0.5f);
+    rank = rank < 1 ? 1 : rank > sample ? sample : rank;
+    pick_bin<false>(s_hist, SAMPLE_BINS, rank, s_wave, s_result);
+    if (tid == 0) state->bound[wg] = s_result[0] << SAMPLE_SHIFT;
 }
 
 constexpr int CNT_BLOCK = SEL_BLOCK;
@@ -290,7 +175,7 @@ constexpr int CNT_STASH = 1024;                  // keys per wave between flushe
 constexpr int CNT_U = 4;
 
 // The counting pass: one contiguous piece per wave, as in the select kernel,
-// with the same one-compare-per-element test.  Every key at or above cand_lo is
+// with the same one-compare-per-element test.  Every key at or above the bound is
 // a candidate and is copied to `cand`, in any order (per-wave LDS stash; a stash
 // that fills up is flushed with an atomic of its own, the rest of a workgroup
 // with one atomic at the end).
@@ -373,42 +258,403 @@ __global__ __launch_bounds__(CNT_BLOCK) void collect_kernel(
     __shared__ uint32_t s_stash[CNT_WAVES][CNT_STASH];
     __shared__ uint32_t s_left[CNT_WAVES];
     __shared__ unsigned long long s_base;
-    const float lo = __uint_as_float(state->cand_lo);       // a key below the Inf/NaN range, or NaN
+    const uint32_t lo_key = cand_bound(state);
+    const float lo = __uint_as_float(lo_key);               // a key below the Inf/NaN range, or NaN
     if (lo == lo)
         collect_body<NT>(acc, n, piece, state, cand, cand_cap, TestFloat{lo}, s_stash, s_left, &s_base);
     else
-        collect_body<NT>(acc, n, piece, state, cand, cand_cap, TestKey{state->cand_lo}, s_stash, s_left,
-                         &s_base);
+        collect_body<NT>(acc, n, piece, state, cand, cand_cap, TestKey{lo_key}, s_stash, s_left, &s_base);
 }
 
-__global__ void radix_init_kernel(RadixState* state, uint32_t* hist, uint32_t words) {
+__global__ void radix_init_kernel(RadixState* state, uint32_t* hist) {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < words) hist[i] = 0;
-    if (i == 0) {
-        RadixState z = {};
-        *state = z;
+    if (i < HIST_WORDS) hist[i] = 0;
+    if (i < sizeof(RadixState) / 4) reinterpret_cast<uint32_t*>(state)[i] = 0;
+}
+
+// ---------------------------------------------------------------------------
+// the exact threshold, and the select that uses it, in one launch
+// ---------------------------------------------------------------------------
+// An MSD radix select on the magnitude key, digit by digit, and (SELECT) the
+// compaction of what lies at or above the result, as phases of one kernel.  A phase
+// is cut into equal shares; a workgroup takes tickets, and ticket t is share t mod
+// shares of phase t / shares.  A digit's counts go to a histogram in memory; who has
+// a ticket of a later phase waits until all shares of the digit are counted, reads
+// the complete histogram and works out for itself what the next phase is.  All
+// shares of earlier phases are held by running workgroups that wait only for still
+// earlier ones, so every wait ends, with however few workgroups running; the waits
+// are bounded all the same (built-in limit).
+//
+// With a bound from the sample two digits do: the keys up to an octave above it in
+// 2048 bins (and one for all that lie higher), then the 4096 keys of one of those
+// bins.  If the answer lies higher, or the bound was not below it, the digits are the
+// general ones, 11 + 11 + 9 bits from the top; they run over the candidates if rank k
+// is among them, else over the whole vector.  The counts go out with atomics whose
+// result is waited for: an atomic that has returned has been carried out where every
+// compute unit sees it, which a release fence would only achieve by writing the whole
+// L2 back.
+//
+// One launch takes the place of four (three digits of 6 to 14 us and a select of 10
+// to 17 us; 31 us in all at 14.7 M elements and 2 %, 41 us at 336 M and 0.1 %, 28 and
+// 34 us here; with the sample's two launches made one, a refresh iteration of 1 Mi
+// elements went from 45 to 27 us, of 14.7 M from 84 to 74).  A phase boundary costs about four microseconds (counts out, last share
+// noticed, histogram read), a launch five.  Tickets on one counter are served one at
+// a time, some 30 ns each, so candidates are cut into SHARES_AIM shares or so (510
+// shares: 33 us for two digits over 1.7 M candidates, 21 us with 69), and one
+// workgroup does alone, from registers, what fits into a single share.
+constexpr uint32_t BOUND_SHIFT = 12, BOUND_LOG_BINS = 11;   // first digit from a bound: 2^12 keys a bin
+constexpr uint32_t SHARES_AIM = 64;
+constexpr int RES_BLOCK = SEL_BLOCK;
+constexpr int RES_WAVES = RES_BLOCK / WAVE;
+static_assert(RES_BLOCK == 1024, "pick_bin is written for 1024 threads");
+constexpr int ROWS_MAX = 6;                        // quads of a thread in a share of candidates
+constexpr uint32_t ROW = RES_BLOCK * 4;
+
+// What the digits run over: nothing known (the whole vector); the keys of candidates
+// in any order (cand_count of them); the values of candidates in index order, with
+// their indices (collected); the whole vector, with a bound.
+enum ResolveOver { OVER_ALL = 0, OVER_KEYS = 1, OVER_COLLECTED = 2, OVER_BOUNDED = 3 };
+
+struct Digit {                                     // a digit, or its result
+    uint32_t base, shift, bins;                    // keys base .. base + (bins << shift) - 1
+    bool higher;                                   // keys above those are counted too
+    uint32_t k_rem, above;                         // rank to find among them and higher ones; keys above all that
+    bool found;                                    // base is the key of the answer,
+    uint32_t equal;                                // which so many keys share
+};
+__device__ __forceinline__ Digit general_digit(uint32_t k) { return Digit{0u, 20u, 1u << RS_BITS1, false, k, 0u, false, 0u}; }
+__device__ __forceinline__ Digit bound_digit(uint32_t bound, uint32_t k) {
+    return Digit{bound, BOUND_SHIFT, 1u << BOUND_LOG_BINS, true, k, 0u, false, 0u};
+}
+// What follows a digit whose histogram is complete (`higher`: its count of higher
+// keys).  Called by the whole workgroup; uniform.
+template <bool ELSEWHERE>
+__device__ __forceinline__ Digit next_digit(const Digit& d, const uint32_t* hist, uint32_t higher, uint32_t k,
+                                            uint32_t* s_wave, uint32_t* s_result) {
+    const uint32_t beyond = d.higher ? higher : 0u;
+    const uint32_t want = d.k_rem > beyond ? d.k_rem - beyond : 0u;
+    pick_bin<ELSEWHERE>(hist, d.bins, want, s_wave, s_result);
+    const uint32_t bin = uniform(s_result[0]), above = uniform(s_result[1]);
+    if (bin == ~0u) return general_digit(k);      // more than an octave above the bound, or below it
+    Digit r = d;
+    r.base += bin << d.shift;
+    r.k_rem = want - above;
+    r.above += beyond + above;
+    r.equal = uniform(s_result[2]);
+    r.found = d.shift == 0;
+    r.higher = false;
+    r.bins = d.shift == BOUND_SHIFT ? 1u << BOUND_SHIFT : d.shift == 20 ? 1u << RS_BITS2 : 1u << RS_BITS3;
+    r.shift = d.shift == 20 ? 9u : 0u;
+    return r;
+}
+
+// A share of candidates in registers: rows of 4096, four consecutive ones a thread.
+template <bool INDICES>
+struct CandRows {
+    uint32_t key[ROWS_MAX][4];                     // the value's bits
+    uint32_t idx[INDICES ? ROWS_MAX : 1][4];
+    uint32_t have;                                 // bit 4 row + c: there is one
+    __device__ __forceinline__ void load(const uint32_t* __restrict__ vals, const uint32_t* __restrict__ indices,
+                                         uint32_t start, uint32_t end) {
+        // No branch between the loads: rows past the end read the last quad again (the
+        // arrays have room for whole quads).
+        const uint32_t last = (end - 1) / 4 * 4;
+        have = 0;
+#pragma unroll
+        for (int r = 0; r < ROWS_MAX; ++r) {
+            const uint32_t i = start + r * ROW + 4u * threadIdx.x, q = i < last ? i : last;
+            const uint4 v = *reinterpret_cast<const uint4*>(vals + q);
+            key[r][0] = v.x; key[r][1] = v.y; key[r][2] = v.z; key[r][3] = v.w;
+            if (INDICES) {
+                const uint4 j = *reinterpret_cast<const uint4*>(indices + q);
+                idx[r][0] = j.x; idx[r][1] = j.y; idx[r][2] = j.z; idx[r][3] = j.w;
+            }
+            const uint32_t n = i < end ? (end - i < 4 ? end - i : 4u) : 0u;
+            have |= ((1u << n) - 1u) << (4 * r);
+        }
+    }
+};
+
+// `vec`: the whole vector; the residual if SELECT.
+template <bool SELECT>
+__global__ __launch_bounds__(RES_BLOCK) void resolve_kernel(
+    float* __restrict__ vec, uint32_t n, uint32_t k, RadixState* state, uint32_t* __restrict__ hist,
+    const uint32_t* __restrict__ cand_idx, float* __restrict__ cand, uint64_t cand_cap, int over,
+    float* threshold_out, uint64_t* count_ge_out, uint32_t* __restrict__ idx_out,
+    float* __restrict__ val_out, uint64_t capacity, uint64_t* __restrict__ nnz_out, ScanHeader* hdr,
+    uint64_t* seg_desc, uint64_t* group_desc, uint32_t nseg, uint32_t piece) {
+    constexpr uint32_t BINS_MAX = 4096;
+    constexpr int STASH = SELECT ? SEL_STASH : 1;
+    // the histogram of a digit and the stashes of the select are never in use together
+    constexpr size_t LDS = SELECT ? sizeof(StashMemory<RES_WAVES, STASH>) : BINS_MAX * 4;
+    static_assert(LDS >= BINS_MAX * 4, "room for a histogram");
+    __shared__ __attribute__((aligned(16))) unsigned char s_memory[LDS];
+    __shared__ uint32_t s_count[RES_WAVES], s_result[3], s_before[2], s_rows[ROWS_MAX][RES_WAVES];
+    __shared__ uint32_t s_ticket, s_last, s_higher, s_give_up;
+    uint32_t* s_hist = reinterpret_cast<uint32_t*>(s_memory);
+    const uint32_t tid = threadIdx.x;
+
+    // ---- alike in every workgroup ----
+    const uint32_t bound = over != OVER_ALL ? cand_bound(state) : 0u;
+    const uint64_t found = over == OVER_COLLECTED ? state->collected[1]
+                         : over == OVER_KEYS ? (uint64_t)state->cand_count : 0ull;
+    const bool use_cand = k <= found && found <= cand_cap;                   // rank k is among the candidates
+    const bool bounded = use_cand || over == OVER_BOUNDED;
+    const uint32_t len = use_cand ? (uint32_t)found : n;
+    float* walked = use_cand ? cand : vec;
+    uint32_t per_share = piece * (uint32_t)RES_WAVES;                        // the launch's, for the whole vector
+    if (bounded) {
+        // whole rows: as many as make SHARES_AIM shares; of candidates ROWS_MAX, which
+        // registers hold, and all of them in one share if that holds them
+        uint32_t rows = (uint32_t)(((uint64_t)len + SHARES_AIM * ROW - 1) / (SHARES_AIM * ROW));
+        if (use_cand && (rows > (uint32_t)ROWS_MAX || len <= ROWS_MAX * ROW)) rows = ROWS_MAX;
+        // no more shares than the launch has descriptors for
+        const uint32_t least = (uint32_t)(((uint64_t)len + (uint64_t)nseg * ROW - 1) / ((uint64_t)nseg * ROW));
+        if (rows < least) rows = least;
+        per_share = rows * ROW;
+    }
+    const uint32_t used = (uint32_t)(((uint64_t)len + per_share - 1) / per_share);
+    // there is work for as many workgroups as there are shares
+    if (blockIdx.x >= used) return;
+    Digit d = bounded ? bound_digit(bound, k) : general_digit(k);
+
+    // this share's counts of a digit
+    uint32_t higher = 0;
+    auto clear_hist = [&]() {
+        higher = 0;
+        for (uint32_t b = tid; b < d.bins; b += RES_BLOCK) s_hist[b] = 0;
+        if (tid == 0) s_higher = 0;
+        __syncthreads();
+    };
+    auto take = [&](uint32_t key) {
+        const uint32_t bin = (key - d.base) >> d.shift;              // below the base: wraps to the far end
+        if (bin < d.bins) atomicAdd(&s_hist[bin], 1u);
+        else if (key >= d.base) ++higher;
+    };
+    auto counted = [&]() {
+        if (d.higher) {
+            higher = wave_sum(higher);
+            if ((tid & (WAVE - 1)) == 0 && higher) atomicAdd(&s_higher, higher);
+        }
+        __syncthreads();
+    };
+    // The candidates of a share at or above the threshold: their places from a scan over
+    // rows and waves, and over the shares before; stores straight from registers.
+    auto compact = [&](const auto& rows, uint32_t share) {
+        uint32_t chosen = 0, packed[2] = {0, 0};                     // per row: ten bits hold a wave's 256
+#pragma unroll
+        for (int r = 0; r < ROWS_MAX; ++r) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if ((rows.key[r][c] & ABS_MASK) >= d.base) chosen |= 1u << (4 * r + c);
+        }
+        chosen &= rows.have;
+#pragma unroll
+        for (int r = 0; r < ROWS_MAX; ++r) packed[r / 3] += (uint32_t)__popc(chosen >> (4 * r) & 15u) << (10 * (r % 3));
+        const uint32_t incl[2] = {wave_inclusive_scan_u32(packed[0]), wave_inclusive_scan_u32(packed[1])};
+        const int wave = (int)uniform(tid >> 6), lane = tid & (WAVE - 1);
+        if (lane == WAVE - 1)
+#pragma unroll
+            for (int r = 0; r < ROWS_MAX; ++r) s_rows[r][wave] = incl[r / 3] >> (10 * (r % 3)) & 1023u;
+        __syncthreads();
+        if (wave == 0) {
+            constexpr int CELLS = ROWS_MAX * RES_WAVES;
+            static_assert(CELLS <= 2 * WAVE && CELLS % 2 == 0, "two cells a lane");
+            uint32_t* cells = &s_rows[0][0];
+            const bool in = 2 * lane < CELLS;
+            const uint32_t c0 = in ? cells[2 * lane] : 0u, c1 = in ? cells[2 * lane + 1] : 0u;
+            const uint32_t upto = wave_inclusive_scan_u32(c0 + c1);
+            const uint32_t aggregate = (uint32_t)__builtin_amdgcn_readlane((int)upto, WAVE - 1);
+            const uint32_t before = used == 1 ? 0u : scan_within_group(hdr, seg_desc, group_desc, share, aggregate);
+            if (lane == 0) {
+                s_before[0] = before;
+                s_count[0] = aggregate;
+            }
+            if (in) {
+                cells[2 * lane] = upto - c0 - c1;
+                cells[2 * lane + 1] = upto - c1;
+            }
+        } else if (wave == 1) {
+            const uint32_t before = used == 1 ? 0u : scan_across_groups(hdr, group_desc, share / SCAN_GROUP);
+            if (lane == 0) s_before[1] = before;
+        }
+        __syncthreads();
+        const uint32_t exclusive = uniform(s_before[0] + s_before[1]), aggregate = uniform(s_count[0]);
+        if (used != 1 && tid == 0 && share / SCAN_GROUP != 0 && share % SCAN_GROUP == SCAN_GROUP - 1)
+            scan_close_group(group_desc, share / SCAN_GROUP, exclusive + aggregate);
+#pragma unroll
+        for (int r = 0; r < ROWS_MAX; ++r) {
+            uint64_t pos = (uint64_t)exclusive + s_rows[r][wave] +
+                           ((incl[r / 3] - packed[r / 3]) >> (10 * (r % 3)) & 1023u);
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (chosen >> (4 * r + c) & 1u) {
+                    if (pos < capacity) {
+                        idx_out[pos] = rows.idx[r][c];
+                        val_out[pos] = __uint_as_float(rows.key[r][c]);
+                        vec[rows.idx[r][c]] = 0.0f;
+                    }
+                    ++pos;
+                }
+        }
+        if (share == used - 1 && tid == 0) {
+            const uint64_t total = (uint64_t)exclusive + aggregate;
+            const bool failed =
+                __hip_atomic_load(&hdr->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+            nnz_out[0] = failed ? ~0ull : (total < capacity ? total : capacity);
+            nnz_out[1] = failed ? ~0ull : total;
+        }
+    };
+
+    if (use_cand && used == 1) {
+        // ---- one share: no exchange with other workgroups ----
+        CandRows<SELECT> rows;
+        rows.load(reinterpret_cast<const uint32_t*>(cand), cand_idx, 0, len);
+        while (!d.found) {
+            __syncthreads();
+            clear_hist();
+#pragma unroll
+            for (int r = 0; r < ROWS_MAX; ++r)
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if (rows.have >> (4 * r + c) & 1u) take(rows.key[r][c] & ABS_MASK);
+            counted();
+            d = next_digit<false>(d, s_hist, s_higher, k, s_count, s_result);
+        }
+        if (tid == 0) {
+            *threshold_out = __uint_as_float(d.base);
+            *count_ge_out = (uint64_t)d.above + d.equal;
+        }
+        if constexpr (SELECT) {
+            __syncthreads();
+            compact(rows, 0);
+        }
+        return;
+    }
+
+    // phase q's histogram: RS_MAX_BINS words, the last digit from a bound twice that; the
+    // last word of all counts the keys above a bound's octave
+    uint32_t* const total_higher = hist + HIST_WORDS - 1;
+    auto next_of = [&](uint32_t q) {
+        const uint32_t up = d.higher ? __hip_atomic_load(total_higher, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+        d = next_digit<true>(d, hist + RS_MAX_BINS * q, up, k, s_count, s_result);
+    };
+    uint32_t at = 0, ticket = 0;                           // the phase that d is
+    if (tid == 0) ticket = atomicAdd(&state->ticket, 1u);
+    for (;;) {
+        __syncthreads();                                   // LDS of the share before is free
+        if (tid == 0) {
+            s_ticket = ticket;
+            s_give_up = 0;
+            ticket = atomicAdd(&state->ticket, 1u);        // asked for while this one is worked on
+        }
+        __syncthreads();
+        const uint32_t p = uniform(s_ticket) / used, share = uniform(s_ticket) % used;
+        while (at < p && !d.found) {
+            if (!SELECT && d.shift == 0) return;           // nothing follows the last digit
+            if (tid == 0) {
+                uint32_t polls = 0;
+                while (__hip_atomic_load(&state->done[at], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != used) {
+                    if (++polls > SPIN_LIMIT) {            // give up: every count says so
+                        *count_ge_out = ~0ull;
+                        if (SELECT) {
+                            __hip_atomic_store(&hdr->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            nnz_out[0] = nnz_out[1] = ~0ull;
+                        }
+                        s_give_up = 1;
+                        break;
+                    }
+                    __builtin_amdgcn_s_sleep(1);
+                }
+            }
+            __syncthreads();
+            if (uniform(s_give_up)) return;
+            next_of(at++);
+        }
+        if (d.found) {
+            // phase `at` is the select; a ticket beyond it is the end
+            if (!SELECT || p > at) return;
+            if constexpr (SELECT) {
+                if (share == 0 && tid == 0) {
+                    *threshold_out = __uint_as_float(d.base);
+                    *count_ge_out = (uint64_t)d.above + d.equal;
+                }
+                if (use_cand && per_share <= ROWS_MAX * ROW) {
+                    CandRows<true> rows;
+                    const uint32_t start = share * per_share;
+                    rows.load(reinterpret_cast<const uint32_t*>(cand), cand_idx, start,
+                              len - start < per_share ? len : start + per_share);
+                    compact(rows, share);
+                } else {
+                    StashMemory<RES_WAVES, STASH>& s_stash = *reinterpret_cast<StashMemory<RES_WAVES, STASH>*>(s_memory);
+                    const CandidateSource source{use_cand ? cand_idx : nullptr, vec};
+                    select_body<RES_BLOCK, SEL_U, STASH, false>(
+                        walked, len, TestKey{d.base}, source, idx_out, val_out, capacity, nnz_out, hdr, seg_desc,
+                        group_desc, used, per_share / RES_WAVES, share, s_stash, s_count, s_before);
+                }
+            }
+            continue;
+        }
+
+        // ---- a digit ----
+        clear_hist();
+        const uint64_t start = (uint64_t)share * per_share;
+        const uint64_t end = start + per_share < len ? start + per_share : len;
+        // a pass over the whole of a vector longer than the last-level cache finds nothing
+        // of it there
+        const bool around_cache = !use_cand && len >= STREAM_PAST_CACHE_N;
+        uint64_t r = start;
+        for (; r + 4 * ROW <= end; r += 4 * ROW) {
+            const float4* src = reinterpret_cast<const float4*>(walked + r) + tid;
+            float4 v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                v[u] = around_cache ? load_quad<true>(src + u * RES_BLOCK) : load_quad<false>(src + u * RES_BLOCK);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                take(magnitude_key(v[u].x)); take(magnitude_key(v[u].y));
+                take(magnitude_key(v[u].z)); take(magnitude_key(v[u].w));
+            }
+        }
+        for (; r < end; r += ROW) {
+            const uint64_t i = r + 4u * tid;
+            if (i + 4 <= end) {
+                const float4 v = *reinterpret_cast<const float4*>(walked + i);
+                take(magnitude_key(v.x)); take(magnitude_key(v.y));
+                take(magnitude_key(v.z)); take(magnitude_key(v.w));
+            } else {
+                for (uint64_t j = i; j < end; ++j) take(magnitude_key(walked[j]));
+            }
+        }
+        counted();
+        uint32_t* total = hist + RS_MAX_BINS * p;
+        uint32_t seen = 0;
+        for (uint32_t b = tid; b < d.bins; b += RES_BLOCK) {           // all out first, then one wait
+            const uint32_t c = s_hist[b];
+            if (c) seen |= atomicAdd(&total[b], c);
+        }
+        if (d.higher && tid == 0 && s_higher) seen |= atomicAdd(total_higher, s_higher);
+        asm volatile("" ::"v"(seen));
+        __syncthreads();
+        if (tid == 0) s_last = atomicAdd(&state->done[p], 1u) == used - 1 ? 1u : 0u;
+        if (!SELECT) {
+            // nothing follows the last digit: the workgroup that finishes it writes the answer
+            __syncthreads();
+            if (uniform(s_last) && d.shift == 0) {
+                next_of(p);
+                if (tid == 0) {
+                    *threshold_out = __uint_as_float(d.base);
+                    *count_ge_out = (uint64_t)d.above + d.equal;
+                }
+                return;
+            }
+        }
     }
 }
 
 // ---------------------------------------------------------------------------
 // refresh iteration in one pass over the gradient
 // ---------------------------------------------------------------------------
-// Clears the radix state, the histograms and the two scan states (collection,
-// final select) of a refresh iteration.
-__global__ void refresh_init_kernel(RadixState* state, uint32_t* hist, uint32_t hist_words,
-                                    uint64_t* scan_a, uint32_t words_a, uint64_t* scan_b,
-                                    uint32_t words_b, uint32_t spin_limit) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < hist_words) hist[i] = 0;
-    const uint64_t w = i == SCAN_SPIN_WORD ? (uint64_t)spin_limit : 0ull;
-    if (i < words_a) scan_a[i] = w;
-    if (i < words_b) scan_b[i] = w;
-    if (i == 0) {
-        RadixState z = {};
-        *state = z;
-    }
-}
-
 // The fused accumulate+select kernel run against the sample's bound: the
 // residual becomes the accumulator (no zeros), every element at or above the
 // bound goes, in index order, to the candidate list, whose length (written,
@@ -426,7 +672,7 @@ __global__ __launch_bounds__(BLOCK) void accumulate_collect_kernel(
     if (threadIdx.x == 0) s_seg = atomicAdd(&hdr->ticket, 1u);
     __syncthreads();
     const uint32_t seg = s_seg;
-    const uint32_t lo_key = state->cand_lo;
+    const uint32_t lo_key = cand_bound(state);
     const float lo = __uint_as_float(lo_key);               // a key below the Inf/NaN range, or NaN
     if (lo == lo) {
         accumulate_select_body<BLOCK, U, STASH, false, NT>(
@@ -439,61 +685,84 @@ __global__ __launch_bounds__(BLOCK) void accumulate_collect_kernel(
     }
 }
 
-// The select of a refresh iteration.  If the radix passes ran over the
-// candidates, so does this: the candidates hold every element at or above the
-// threshold, in index order, so the walk over them emits what a walk over the
-// vector would, and the residual is zeroed where an entry is written out.  The
-// candidates are shared out over all the workgroups of the launch.  Otherwise
-// the walk runs over the residual itself.
-template <int BLOCK, int U, int STASH>
-__global__ __launch_bounds__(BLOCK) void candidate_select_kernel(
-    float* __restrict__ res, uint32_t n, const RadixState* __restrict__ state,
-    const uint32_t* __restrict__ cand_idx, float* __restrict__ cand_val,
-    const float* __restrict__ d_threshold, uint32_t* __restrict__ idx_out,
-    float* __restrict__ val_out, uint64_t capacity, uint64_t* __restrict__ nnz_out,
-    ScanHeader* hdr, uint64_t* seg_desc, uint64_t* group_desc, uint32_t nseg, uint32_t piece) {
-    constexpr int WAVES = BLOCK / WAVE;
-    __shared__ StashMemory<WAVES, STASH> s_stash;
-    __shared__ uint32_t s_count[WAVES];
-    __shared__ uint32_t s_seg;
-    __shared__ uint32_t s_before[2];
-    const bool use_cand = state->use_cand != 0;
-    float* walked = res;
-    uint32_t len = n;
-    CandidateSource source{nullptr, res};
-    if (use_cand) {
-        walked = cand_val;
-        len = (uint32_t)state->m;                           // candidates found: at most n
-        source.idx_in = cand_idx;
-        const uint32_t waves = nseg * (uint32_t)WAVES;
-        uint32_t share = ((len + waves - 1) / waves + 255u) / 256u * 256u;   // whole rounds
-        if (share == 0) share = 256u;
-        if (share < piece) piece = share;                   // never longer than the launch's piece
-        // The launch is sized for a walk over the whole residual; the candidates
-        // fill only the first few segments.  The workgroups beyond them leave before
-        // they take a ticket (tickets on one counter are served one after the other,
-        // some 30 ns each: over a thousand idle workgroups queuing for theirs took
-        // longer than the selection itself), so the tickets 0 .. used - 1 go to the
-        // `used` workgroups that stay, all of them running.
-        const uint32_t per_seg = piece * (uint32_t)WAVES;
-        uint32_t used = (len + per_seg - 1) / per_seg;
-        if (used == 0) used = 1;
-        if (used < nseg) nseg = used;
-        if (blockIdx.x >= nseg) return;
+// The exact threshold of a short array in one workgroup and one launch: the keys stay
+// in registers, the digits' histograms in LDS.  (TINY_N elements at most; at 11,700 this one
+// launch takes 7.3 us, the four it replaces took 19.)
+constexpr int TINY_BLOCK = 1024;
+constexpr uint32_t TINY_PER = TINY_N / TINY_BLOCK;
+__global__ __launch_bounds__(TINY_BLOCK) void tiny_threshold_kernel(const float* __restrict__ acc, uint32_t n,
+                                                                    uint32_t k, float* threshold_out,
+                                                                    uint64_t* count_ge_out) {
+    __shared__ uint32_t s_hist[RS_MAX_BINS];
+    __shared__ uint32_t s_wave[TINY_BLOCK / WAVE], s_result[3];
+    const uint32_t tid = threadIdx.x;
+    uint32_t key[TINY_PER];                        // all ones: no element
+#pragma unroll
+    for (uint32_t u = 0; u < TINY_PER / 4; ++u) {
+        const uint32_t i = 4 * (u * TINY_BLOCK + tid);
+        if (i + 4 <= n) {
+            const float4 v = *reinterpret_cast<const float4*>(acc + i);
+            key[4 * u] = magnitude_key(v.x);
+            key[4 * u + 1] = magnitude_key(v.y);
+            key[4 * u + 2] = magnitude_key(v.z);
+            key[4 * u + 3] = magnitude_key(v.w);
+        } else {
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j) key[4 * u + j] = i + j < n ? magnitude_key(acc[i + j]) : ~0u;
+        }
     }
-    if (threadIdx.x == 0) s_seg = atomicAdd(&hdr->ticket, 1u);
-    __syncthreads();
-    const uint32_t seg = s_seg;
-    const float th = *d_threshold;
-    if (th == th) {
-        select_body<BLOCK, U, STASH, false>(walked, len, TestFloat{__builtin_fabsf(th)}, source, idx_out,
-                                           val_out, capacity, nnz_out, hdr, seg_desc, group_desc,
-                                           nseg, piece, seg, s_stash, s_count, s_before);
-    } else {
-        select_body<BLOCK, U, STASH, false>(walked, len, TestKey{magnitude_key(th)}, source, idx_out,
-                                           val_out, capacity, nnz_out, hdr, seg_desc, group_desc,
-                                           nseg, piece, seg, s_stash, s_count, s_before);
+    uint32_t base = 0, above = 0, k_rem = k;
+#pragma unroll
+    for (int digit = 0; digit < 3; ++digit) {
+        const uint32_t shift = digit == 0 ? 20u : digit == 1 ? 9u : 0u;
+        const uint32_t bins = digit == 2 ? 1u << RS_BITS3 : 1u << RS_BITS1;
+        for (uint32_t b = tid; b < bins; b += TINY_BLOCK) s_hist[b] = 0;
+        __syncthreads();
+#pragma unroll
+        for (uint32_t j = 0; j < TINY_PER; ++j) {
+            const uint32_t bin = (key[j] - base) >> shift;           // no element: beyond every bin
+            if (bin < bins) atomicAdd(&s_hist[bin], 1u);
+        }
+        __syncthreads();
+        pick_bin<false>(s_hist, bins, k_rem, s_wave, s_result);
+        base += s_result[0] << shift;
+        above += s_result[1];
+        k_rem -= s_result[1];
+        if (digit == 2 && tid == 0) {
+            *threshold_out = __uint_as_float(base);
+            *count_ge_out = (uint64_t)above + s_result[2];
+        }
+        __syncthreads();
     }
+}
+
+}  // namespace okt
+
+namespace okt {
+
+// Whether the candidates of a sampled bound are worth collecting: a vector long
+// enough for the sample, and room for them - about 1.1 k where k is some percent of n,
+// 2 k where it is a thousandth.  A larger share than a workspace of
+// okt_workspace_bytes holds (9 % of n) is found as quickly by digits over the whole.
+static bool sample_pays(uint64_t n, uint64_t k, uint64_t cand_cap) {
+    return n >= RS_SAMPLE_FROM_N && cand_cap >= k + k / 4 + n / 64;
+}
+
+template <bool SELECT>
+static void launch_resolve(float* vec, uint64_t n, uint64_t k, RadixState* state, uint32_t* hist,
+                           const uint32_t* cand_idx, float* cand, uint64_t cand_cap, int over,
+                           float* d_threshold_out, uint64_t* d_count_ge_out, uint32_t* d_idx_out,
+                           float* d_val_out, uint64_t capacity, uint64_t* d_nnz_out, char* scan,
+                           const SelectShape& shape, hipStream_t s) {
+    ScanHeader* hdr = (ScanHeader*)scan;
+    uint64_t* seg_desc = scan ? (uint64_t*)(scan + SCAN_HEADER_BYTES) : nullptr;
+    uint64_t* group_desc = scan ? seg_desc + shape.nseg : nullptr;
+    // workgroups stay and take tickets: one per compute unit is all that LDS has room for
+    const uint32_t grid = shape.nseg < device_cus() ? shape.nseg : device_cus();
+    hipLaunchKernelGGL(resolve_kernel<SELECT>, dim3(grid), dim3(RES_BLOCK), 0, s, vec, (uint32_t)n, (uint32_t)k,
+                       state, hist, cand_idx, cand, cand_cap, over, d_threshold_out, d_count_ge_out,
+                       d_idx_out, d_val_out, capacity, d_nnz_out, hdr, seg_desc, group_desc, shape.nseg,
+                       shape.piece);
 }
 
 }  // namespace okt
@@ -509,56 +778,37 @@ extern "C" int okt_topk_threshold_exact(const float* d_acc, uint64_t n, uint64_t
         return OKT_ERR_INVALID_ARG;
     if (!d_ws || !aligned(d_ws, 256) || ws_bytes < threshold_ws_min_bytes())
         return OKT_ERR_WORKSPACE;
+    if (n <= TINY_N) {
+        hipLaunchKernelGGL(tiny_threshold_kernel, dim3(1), dim3(TINY_BLOCK), 0, s, d_acc, (uint32_t)n, (uint32_t)k,
+                           d_threshold_out, d_count_ge_out);
+        return launch_status();
+    }
     RadixState* state = (RadixState*)d_ws;
-    uint32_t* hist_sample = (uint32_t*)((char*)d_ws + RS_STATE_BYTES);
-    uint32_t* hist1 = hist_sample + RS_MAX_BINS;
-    uint32_t* hist2 = hist1 + RS_MAX_BINS;
-    uint32_t* hist3 = hist2 + RS_MAX_BINS;
-    uint32_t* cand = hist3 + RS_MAX_BINS;
-    const uint64_t cand_cap = (ws_bytes - threshold_ws_min_bytes()) / 4;
-
-    hipLaunchKernelGGL(radix_init_kernel, dim3(4 * RS_MAX_BINS / 256), dim3(256), 0, s, state,
-                       hist_sample, 4u * RS_MAX_BINS);
-
-    // sampling pays once the vector is long and the workspace can hold the candidates
-    const uint64_t blocks = n / 1024;                       // whole blocks of 1024 elements
-    const bool sampled = n >= RS_SAMPLE_MIN_N && cand_cap >= n / 16;
-    if (sampled) {
-        uint64_t stride = blocks / RS_SAMPLE_BLOCKS;
-        if (stride < 1) stride = 1;
-        const uint64_t nsamp = (blocks + stride - 1) / stride;
-        hipLaunchKernelGGL(sample_hist_kernel,
-                           dim3((unsigned)((nsamp + SAMPLE_PER_WG - 1) / SAMPLE_PER_WG)),
-                           dim3(HIST_BLOCK), 0, s, d_acc, (const float*)nullptr, 0.0f,
-                           (uint32_t)nsamp, (uint32_t)stride, hist_sample, state, n, k);
+    uint32_t* hist = (uint32_t*)((char*)d_ws + RS_STATE_BYTES);
+    uint32_t* cand = hist + HIST_WORDS;
+    const uint64_t cand_cap = ((ws_bytes - threshold_ws_min_bytes()) / 4) & ~(uint64_t)3;   // whole quads
+    const SelectShape shape = select_shape(n, device_cus());
+    int over = OVER_ALL;
+    if (n >= RS_SAMPLE_FROM_N && n <= COLLECT_FROM_N) over = OVER_BOUNDED;
+    else if (sample_pays(n, k, cand_cap)) over = OVER_KEYS;
+    if (over != OVER_ALL) {
+        hipLaunchKernelGGL(sample_bound_kernel, dim3(BOUNDS), dim3(SAMPLE_BLOCK), 0, s, d_acc,
+                           (const float*)nullptr, 0.0f, (uint32_t)n, (uint32_t)k, state, hist,
+                           (uint64_t*)nullptr, 0u, (uint64_t*)nullptr, 0u, 0u);
+    } else {
+        hipLaunchKernelGGL(radix_init_kernel, dim3(HIST_WORDS / 256), dim3(256), 0, s, state, hist);
+    }
+    if (over == OVER_KEYS) {
         static_assert(CNT_WAVES == SEL_WAVES, "the collect pass is cut like the select");
-        const SelectShape shape = select_shape(n, device_cus());
         timing_before(s);
         hipLaunchKernelGGL(stream_past_cache(n) ? collect_kernel<true> : collect_kernel<false>,
                            dim3(shape.nseg), dim3(CNT_BLOCK), 0, s, d_acc, (uint32_t)n, shape.piece,
                            state, cand, cand_cap);
         timing_after(s);
     }
-
-    // the radix passes are sized for the candidates when sampling ran (a failed
-    // check makes them walk the whole vector with the same, smaller grid)
-    const uint64_t expect = sampled ? n / 16 : n;
-    const uint64_t steps = ((expect >> 2) + HIST_STEP4 - 1) / HIST_STEP4;
-    // every workgroup ends with up to 2048 returning atomics on the shared histogram:
-    // over the candidates (a few MB) a workgroup per CU is plenty, over a whole
-    // vector the passes want the memory parallelism of many more
-    const uint64_t grid_max = sampled ? device_cus() : 8 * device_cus();
-    const unsigned grid = (unsigned)(steps < grid_max ? (steps ? steps : 1) : grid_max);
-    const int was_sampled = sampled ? 1 : 0;
-    hipLaunchKernelGGL((radix_hist_kernel<20, RS_BITS1, 1>), dim3(grid), dim3(HIST_BLOCK), 0, s,
-                       d_acc, cand, state, hist1, n, k, cand_cap, was_sampled, d_threshold_out,
-                       d_count_ge_out);
-    hipLaunchKernelGGL((radix_hist_kernel<9, RS_BITS2, 2>), dim3(grid), dim3(HIST_BLOCK), 0, s,
-                       d_acc, cand, state, hist2, n, k, cand_cap, was_sampled, d_threshold_out,
-                       d_count_ge_out);
-    hipLaunchKernelGGL((radix_hist_kernel<0, RS_BITS3, 3>), dim3(grid), dim3(HIST_BLOCK), 0, s,
-                       d_acc, cand, state, hist3, n, k, cand_cap, was_sampled, d_threshold_out,
-                       d_count_ge_out);
+    launch_resolve<false>(const_cast<float*>(d_acc), n, k, state, hist, nullptr, (float*)cand, cand_cap,
+                          over, d_threshold_out, d_count_ge_out, nullptr, nullptr, 0, nullptr, nullptr,
+                          shape, s);
     return launch_status();
 }
 
@@ -598,8 +848,8 @@ extern "C" int okt_accumulate_topk_select(const float* d_grad, float* d_residual
         fixed = threshold_ws_min_bytes() + 2 * scan_bytes;
         cand_cap = ws_bytes > fixed ? ((ws_bytes - fixed) / 8) & ~(uint64_t)63 : 0;
     }
-    if (n < RS_SAMPLE_MIN_N || cand_cap < n / 16) {
-        // short vector (or a workspace without room for candidates): the three steps
+    if (!sample_pays(n, k, cand_cap)) {
+        // short vector, large k, or a workspace without room for candidates: the three steps
         // one after the other, each with the workspace to itself
         int rc = okt_residual_accumulate(d_grad, d_residual_inout, lr, n, stream);
         if (rc != OKT_OK) return rc;
@@ -611,10 +861,7 @@ extern "C" int okt_accumulate_topk_select(const float* d_grad, float* d_residual
     }
 
     RadixState* state = (RadixState*)d_ws;
-    uint32_t* hist_sample = (uint32_t*)((char*)d_ws + RS_STATE_BYTES);
-    uint32_t* hist1 = hist_sample + RS_MAX_BINS;
-    uint32_t* hist2 = hist1 + RS_MAX_BINS;
-    uint32_t* hist3 = hist2 + RS_MAX_BINS;
+    uint32_t* hist = (uint32_t*)((char*)d_ws + RS_STATE_BYTES);
     char* scan_b = (char*)d_ws + threshold_ws_min_bytes();          // the final select's
     char* scan_a = scan_b + scan_bytes;                             // the collection's, or the slots
     float* cand_val = (float*)(scan_a + (slots ? slot_bytes : scan_bytes));
@@ -624,25 +871,13 @@ extern "C" int okt_accumulate_topk_select(const float* d_grad, float* d_residual
 
     const uint32_t words_b = (uint32_t)(scan_ws_bytes(shape.nseg) / 8);
     const uint32_t words_a = slots ? (uint32_t)(scan_ws_bytes(plan.nseg) / 8) : words_b;
-    uint32_t init_words = 4u * RS_MAX_BINS;
-    if (words_a > init_words) init_words = words_a;
-    if (words_b > init_words) init_words = words_b;
-    hipLaunchKernelGGL(refresh_init_kernel, dim3((init_words + 255) / 256), dim3(256), 0, s, state,
-                       hist_sample, 4u * RS_MAX_BINS, (uint64_t*)scan_a, words_a, (uint64_t*)scan_b,
+    hipLaunchKernelGGL(sample_bound_kernel, dim3(BOUNDS), dim3(SAMPLE_BLOCK), 0, s, d_residual_inout, d_grad, lr,
+                       (uint32_t)n, (uint32_t)k, state, hist, (uint64_t*)scan_a, words_a, (uint64_t*)scan_b,
                        words_b, spin_limit_setting());
-
-    const uint64_t blocks = n / 1024;
-    uint64_t stride = blocks / RS_SAMPLE_BLOCKS;
-    if (stride < 1) stride = 1;
-    const uint64_t nsamp = (blocks + stride - 1) / stride;
-    hipLaunchKernelGGL(sample_hist_kernel,
-                       dim3((unsigned)((nsamp + SAMPLE_PER_WG - 1) / SAMPLE_PER_WG)),
-                       dim3(HIST_BLOCK), 0, s, d_residual_inout, d_grad, lr, (uint32_t)nsamp,
-                       (uint32_t)stride, hist_sample, state, n, k);
     if (slots) {
-        // the sample's bound is a magnitude key, so its bits read as an fp32 are the
-        // bound itself: the slot kernels take it for their threshold
-        const float* bound = reinterpret_cast<const float*>(&state->cand_lo);
+        // the sample's bounds are magnitude keys, so their bits read as fp32 are the
+        // bounds themselves: the slot kernels take the least for their threshold
+        const float* bound = reinterpret_cast<const float*>(state->bound);
         timing_before(s);
         auto* fill = stream_past_cache(n) ? slot_fill_accumulate_kernel<false, true>
                                           : slot_fill_accumulate_kernel<false, false>;
@@ -650,10 +885,10 @@ extern "C" int okt_accumulate_topk_select(const float* d_grad, float* d_residual
         hipLaunchKernelGGL(fill, dim3((plan.ntiles + per_wg - 1) / per_wg), dim3(SLOT_FILL_BLOCK), 0,
                            s, d_grad, d_residual_inout, lr, (uint32_t)n, bound,
                            (uint16_t*)(scan_a + plan.counts_at), (SlotEntry*)(scan_a + plan.slots_at),
-                           plan.ntiles, (uint64_t*)nullptr, 0u, 0u);      // refresh_init_kernel cleared it
+                           plan.ntiles, (uint64_t*)nullptr, 0u, 0u);      // sample_bound_kernel cleared it
         timing_after(s);
-        const int rc = launch_slot_finish(d_residual_inout, n, bound, plan, scan_a, SLOT_KEEP, false,
-                                          cand_idx, cand_val, cand_cap, state->collected, s);
+        const int rc = launch_slot_finish(d_residual_inout, n, bound, plan, scan_a, SLOT_KEEP,
+                                          cand_idx, cand_val, cand_cap, state->collected, s, BOUNDS);
         if (rc != OKT_OK) return rc;
     } else {
         timing_before(s);
@@ -666,22 +901,7 @@ extern "C" int okt_accumulate_topk_select(const float* d_grad, float* d_residual
         timing_after(s);
     }
 
-    const uint64_t steps = (((n / 16) >> 2) + HIST_STEP4 - 1) / HIST_STEP4;
-    const uint64_t one_per_cu = device_cus();
-    const unsigned grid = (unsigned)(steps < one_per_cu ? (steps ? steps : 1) : one_per_cu);
-    const uint32_t* cand_keys = reinterpret_cast<const uint32_t*>(cand_val);
-    hipLaunchKernelGGL((radix_hist_kernel<20, RS_BITS1, 1>), dim3(grid), dim3(HIST_BLOCK), 0, s,
-                       d_residual_inout, cand_keys, state, hist1, n, k, cand_cap, 2, d_threshold_out,
-                       d_count_ge_out);
-    hipLaunchKernelGGL((radix_hist_kernel<9, RS_BITS2, 2>), dim3(grid), dim3(HIST_BLOCK), 0, s,
-                       d_residual_inout, cand_keys, state, hist2, n, k, cand_cap, 2, d_threshold_out,
-                       d_count_ge_out);
-    hipLaunchKernelGGL((radix_hist_kernel<0, RS_BITS3, 3>), dim3(grid), dim3(HIST_BLOCK), 0, s,
-                       d_residual_inout, cand_keys, state, hist3, n, k, cand_cap, 2, d_threshold_out,
-                       d_count_ge_out);
-    hipLaunchKernelGGL((candidate_select_kernel<SEL_BLOCK, SEL_U, SEL_STASH>), dim3(shape.nseg),
-                       dim3(SEL_BLOCK), 0, s, d_residual_inout, (uint32_t)n, state, cand_idx, cand_val,
-                       d_threshold_out, d_idx_out, d_val_out, capacity, d_nnz_out, header(scan_b),
-                       segs(scan_b), segs(scan_b) + shape.nseg, shape.nseg, shape.piece);
+    launch_resolve<true>(d_residual_inout, n, k, state, hist, cand_idx, cand_val, cand_cap, OVER_COLLECTED, d_threshold_out,
+                         d_count_ge_out, d_idx_out, d_val_out, capacity, d_nnz_out, scan_b, shape, s);
     return launch_status();
 }

@@ -1,0 +1,90 @@
+"""The exact threshold and the refresh iteration where their launches, shares and
+digits change: vector lengths around the limits of each form, candidates that fill
+one share of a workgroup or just more, answers far above the sample's bound, bounds
+above the answer, ties.  Everything against the oracle, bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2201_07598_amd as okt
+from oracle import okt_oracle as orc
+from tests.okt_harness import DEV, to_dev, u64, workspace
+from tests.test_gpu_refresh import check_refresh, lap
+
+pytestmark = pytest.mark.gpu
+
+
+def check_threshold(acc, k, ws_bytes=None):
+    th = torch.full((1,), -7.0, device=DEV)
+    cnt = torch.zeros(1, dtype=torch.int64, device=DEV)
+    ws = workspace(okt.okt_workspace_bytes(acc.size, 0) if ws_bytes is None else ws_bytes)
+    ws.fill_(0xAB)
+    okt.okt_topk_threshold_exact(to_dev(acc), k, th, cnt, ws)
+    torch.cuda.synchronize()
+    rth, rcnt = orc.topk_threshold_exact(acc, k, method="sort" if acc.size < 5000 else "partition")
+    assert th.cpu().numpy().view(np.uint32)[0] == np.float32(rth).view(np.uint32)
+    assert int(u64(cnt)[0]) == rcnt
+
+
+@pytest.mark.parametrize("n", [1, 2, 4097, 16_383, 16_384, 16_385, 40_001, 131_071, 131_072, 131_073,
+                               2_097_152, 2_097_153, 2_200_003])
+def test_threshold_lengths(n):
+    acc = lap(n, n)
+    acc[n // 2::7] = 0.0
+    for k in sorted({1, max(1, n // 1000), max(1, n // 50), max(1, n // 3), n}):
+        check_threshold(acc, k)
+    check_threshold(acc, max(1, n // 50), ws_bytes=64 * 1024)
+    same = np.full(n, -0.5, dtype=np.float32)
+    check_threshold(same, max(1, n // 50))
+    check_threshold(np.zeros(n, np.float32), max(1, n // 50))
+
+
+# k and the candidates it brings (about 1.3 k): one row, one share, just more, many shares
+@pytest.mark.parametrize("n,k", [(131_072, 40), (300_007, 3_000), (1_000_003, 17_500), (1_000_003, 18_500),
+                                 (1_000_003, 20_500), (3_000_001, 60_000), (5_000_011, 300_000),
+                                 (5_000_011, 400_000)])
+def test_refresh_shares_of_candidates(n, k):
+    g, e = lap(n + k, n), lap(n + k + 1, n, 2e-3)
+    check_refresh(g, e, 0.25, k, 2 * k)
+    check_refresh(g, e, 0.25, k, k // 2 + 1)
+
+
+@pytest.mark.parametrize("n", [200_003, 2_500_003, 4_300_003])
+def test_answers_far_from_the_bound(n):
+    rng = np.random.default_rng(n)
+    k = n // 100
+    zero = np.zeros(n, np.float32)
+    # exactly k large values over a floor of small ones: the bound lies among the small,
+    # the answer octaves above it
+    g = lap(7, n, 1e-6)
+    at = rng.choice(n, k, replace=False)
+    g[at] = rng.choice([-1.0, 1.0], k) * rng.uniform(1.0, 2.0, k)
+    for kk in (k, k - 1, k // 2):
+        check_refresh(g, zero, 1.0, kk, 2 * k)
+        check_threshold(g, kk)
+    # a handful of values, most of the vector tied at the answer or just below it
+    t = rng.choice(np.array([0.0, 1e-3, -1e-3, 3e-3], np.float32), n, p=[0.5, 0.2, 0.2, 0.1]).astype(np.float32)
+    for kk in (k, n // 10, n // 10 + 5, n // 3):
+        check_refresh(t, zero, 1.0, kk, n)
+        check_threshold(t, kk)
+    # values over the whole range of exponents, a NaN and infinities on top
+    w = (2.0 ** rng.uniform(-140, 120, n)).astype(np.float32) * rng.choice([-1, 1], n).astype(np.float32)
+    w[5], w[6], w[n - 1] = np.nan, np.inf, -np.inf
+    for kk in (1, 2, 3, 4, k):
+        check_refresh(w, zero, 1.0, kk, 2 * k)
+        check_threshold(w, kk)
+
+
+@pytest.mark.parametrize("n", [1_000_003, 4_300_003])
+def test_a_sample_that_sees_only_large_values(n):
+    """Every run of sixteen that the sample reads is large, everything else small:
+    each bound lies above the answer, too few candidates are found, and the whole
+    vector decides."""
+    g = lap(9, n, 1e-6)
+    runs = np.arange(8192, dtype=np.uint64) * np.uint64(n // 16) // np.uint64(8192)
+    for r in runs[:-1]:
+        g[int(r) * 16:int(r) * 16 + 16] = lap(int(r), 16, 1.0) + np.float32(2.0)
+    k = 150_000 if n < 2_000_000 else 300_000
+    for kk in (k, n // 13):
+        check_refresh(g, np.zeros(n, np.float32), 1.0, kk, 2 * kk)
+        check_threshold(g, kk)
