@@ -153,7 +153,7 @@ __device__ __forceinline__ float slot_threshold(const float* __restrict__ d_thre
         const uint32_t b = __float_as_uint(d_threshold[i]);
         lo = b < lo ? b : lo;
     }
-    return __uint_as_float(lo);
+    return __uint_as_float(lo != 0 ? lo : ABS_MASK);      // zero is no bound: see collect_bound
 }
 constexpr int SLOT_BOUNDS = 16;
 
