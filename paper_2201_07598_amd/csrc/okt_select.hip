@@ -69,6 +69,16 @@ int launch_slot_finish(float* d_acc, uint64_t n, const float* d_threshold, const
     uint32_t* place = (uint32_t*)(ws + plan.place_at);
     const SlotEntry* slots = (const SlotEntry*)(ws + plan.slots_at);
     uint32_t* dense_list = (uint32_t*)(ws + plan.dense_at);
+    if ((after == SLOT_RESTORE || bounds > 1) && plan.ntiles <= SLOT_FINISH_TILES) {
+        // a workgroup per compute unit, and no fewer than 64 tiles each
+        uint32_t grid = (plan.ntiles + 63) / 64;
+        if (grid > device_cus()) grid = device_cus();
+        auto* finish = bounds > 1 ? slot_finish_kernel<SLOT_KEEP, false, SLOT_BOUNDS>
+                                  : slot_finish_kernel<SLOT_RESTORE, true, 1>;
+        hipLaunchKernelGGL(finish, dim3(grid), dim3(SLOT_FINISH_BLOCK), 0, s, d_acc, (uint32_t)n, d_threshold,
+                           counts, slots, plan.ntiles, d_idx_out, d_val_out, capacity, d_nnz_out);
+        return launch_status();
+    }
     hipLaunchKernelGGL(slot_scan_kernel<SLOT_SCAN_BLOCK>, dim3(plan.nseg), dim3(SLOT_SCAN_BLOCK), 0, s, counts, place,
                        dense_list, plan.ntiles, plan.tpt, capacity, d_nnz_out, hdr, seg_desc,
                        group_desc, plan.nseg);
@@ -227,12 +237,14 @@ extern "C" int okt_accumulate_select(const float* d_grad, float* d_residual_inou
         return OKT_ERR_INVALID_ARG;
     const SelectShape shape = select_shape(n, device_cus());
     if (!d_ws || !aligned(d_ws, 256) || ws_bytes < select_ws_bytes(n)) return OKT_ERR_WORKSPACE;
+    const CacheUse use = accumulate_cache_use(n);
     if (slots_apply(n, ws_bytes, true)) {
         const SlotPlan plan = slot_plan(n, device_cus());
         char* ws = (char*)d_ws;
         timing_before(s);
-        auto* fill = stream_past_cache(n) ? slot_fill_accumulate_kernel<true, true>
-                                          : slot_fill_accumulate_kernel<true, false>;
+        auto* fill = use == ALL_PAST_CACHE        ? slot_fill_accumulate_kernel<true, ALL_PAST_CACHE>
+                     : use == GRADIENT_PAST_CACHE ? slot_fill_accumulate_kernel<true, GRADIENT_PAST_CACHE>
+                                                  : slot_fill_accumulate_kernel<true, CACHED>;
         constexpr uint32_t per_wg = SLOT_FILL_BLOCK / WAVE;
         hipLaunchKernelGGL(fill, dim3((plan.ntiles + per_wg - 1) / per_wg), dim3(SLOT_FILL_BLOCK), 0,
                            s, d_grad, d_residual_inout, lr, (uint32_t)n, d_threshold,
@@ -249,8 +261,9 @@ extern "C" int okt_accumulate_select(const float* d_grad, float* d_residual_inou
     if (launch_clear_scan_state(d_ws, scan_ws_bytes(shape.nseg) / 8, s) != hipSuccess)
         return OKT_ERR_HIP;
     timing_before(s);
-    auto* kernel = stream_past_cache(n) ? accumulate_select_kernel<SEL_BLOCK, SEL_U, SEL_STASH, true>
-                                        : accumulate_select_kernel<SEL_BLOCK, SEL_U, SEL_STASH, false>;
+    auto* kernel = use == ALL_PAST_CACHE        ? accumulate_select_kernel<SEL_BLOCK, SEL_U, SEL_STASH, ALL_PAST_CACHE>
+                   : use == GRADIENT_PAST_CACHE ? accumulate_select_kernel<SEL_BLOCK, SEL_U, SEL_STASH, GRADIENT_PAST_CACHE>
+                                                : accumulate_select_kernel<SEL_BLOCK, SEL_U, SEL_STASH, CACHED>;
     hipLaunchKernelGGL(kernel, dim3(shape.nseg), dim3(SEL_BLOCK), 0, s, d_grad, d_residual_inout, lr,
                        (uint32_t)n, d_threshold, d_idx_out, d_val_out, capacity, d_nnz_out, hdr,
                        seg_desc, group_desc, shape.nseg, shape.piece);

@@ -5,6 +5,7 @@
 #include <type_traits>
 
 #include "okt_device.h"
+#include "okt_sizes.h"
 
 namespace okt {
 
@@ -379,7 +380,7 @@ __device__ __forceinline__ void select_body(
 // unzeroed and left to the second walk of select_finish.  With ZERO false the
 // residual is written without the zeros (the parked entries are candidates only:
 // the pass that collects them for the exact threshold of a refresh iteration).
-template <int BLOCK, int U, int STASH, bool ZERO, bool NT, typename Test>
+template <int BLOCK, int U, int STASH, bool ZERO, int CACHE, typename Test>
 __device__ __forceinline__ void accumulate_select_body(
     const float* __restrict__ grad, float* __restrict__ res, float lr, uint32_t n, Test test,
     uint32_t* __restrict__ idx_out, float* __restrict__ val_out, uint64_t capacity,
@@ -387,6 +388,7 @@ __device__ __forceinline__ void accumulate_select_body(
     uint32_t nseg, uint32_t piece, uint32_t seg, StashMemory<BLOCK / WAVE, STASH>& s_stash, uint32_t* s_count,
     uint32_t* s_before) {
     constexpr int WAVES = BLOCK / WAVE;
+    constexpr bool NT = CACHE == ALL_PAST_CACHE;
     const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x >> 6;
     const uint64_t start = ((uint64_t)seg * WAVES + wave) * piece;
     const uint64_t end = start + piece < n ? start + piece : n;
@@ -434,7 +436,7 @@ __device__ __forceinline__ void accumulate_select_body(
         const float4* esrc = reinterpret_cast<const float4*>(res + at) + lane;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            g[u] = load_quad<NT>(gsrc + u * WAVE);
+            g[u] = load_quad<CACHE != CACHED>(gsrc + u * WAVE);
             e[u] = load_quad<NT>(esrc + u * WAVE);
         }
     };
@@ -456,7 +458,7 @@ __device__ __forceinline__ void accumulate_select_body(
                                                   test(a[u].y), test(a[u].z), test(a[u].w)));
     }
     for (; r + 256 <= end; r += 256) {               // whole rounds short of a batch
-        const float4 gq = load_quad<NT>(reinterpret_cast<const float4*>(grad + r) + lane);
+        const float4 gq = load_quad<CACHE != CACHED>(reinterpret_cast<const float4*>(grad + r) + lane);
         const float4 eq = load_quad<NT>(reinterpret_cast<const float4*>(res + r) + lane);
         const float4 a = make_float4(fma2(eq.x, gq.x), fma2(eq.y, gq.y), fma2(eq.z, gq.z),
                                      fma2(eq.w, gq.w));
@@ -551,7 +553,7 @@ __global__ __launch_bounds__(BLOCK) void coo_select_kernel(
     }
 }
 
-template <int BLOCK, int U, int STASH, bool NT>
+template <int BLOCK, int U, int STASH, int CACHE>
 __global__ __launch_bounds__(BLOCK) void accumulate_select_kernel(
     const float* __restrict__ grad, float* __restrict__ res, float lr, uint32_t n,
     const float* __restrict__ d_threshold, uint32_t* __restrict__ idx_out,
@@ -567,11 +569,11 @@ __global__ __launch_bounds__(BLOCK) void accumulate_select_kernel(
     const uint32_t seg = s_seg;
     const float th = *d_threshold;
     if (th == th) {
-        accumulate_select_body<BLOCK, U, STASH, true, NT>(
+        accumulate_select_body<BLOCK, U, STASH, true, CACHE>(
             grad, res, lr, n, TestFloat{__builtin_fabsf(th)}, idx_out, val_out, capacity, nnz_out,
             hdr, seg_desc, group_desc, nseg, piece, seg, s_stash, s_count, s_before);
     } else {
-        accumulate_select_body<BLOCK, U, STASH, true, NT>(
+        accumulate_select_body<BLOCK, U, STASH, true, CACHE>(
             grad, res, lr, n, TestKey{magnitude_key(th)}, idx_out, val_out, capacity, nnz_out,
             hdr, seg_desc, group_desc, nseg, piece, seg, s_stash, s_count, s_before);
     }

@@ -59,6 +59,16 @@ inline size_t select_ws_bytes(uint64_t n) {
 // that follows an accumulate, the zeros that follow a refresh iteration's pass).
 constexpr uint64_t STREAM_PAST_CACHE_N = 64u << 20;                          // 256 MiB of fp32 and up
 inline bool stream_past_cache(uint64_t n) { return n >= STREAM_PAST_CACHE_N; }
+// The passes that form the accumulator read the gradient for the last time, so from
+// 32 MiB of it on (the size of all the L2s) they read it around the cache and leave the
+// room to the residual, which the next pass or iteration reads again: accumulate and
+// select in one pass at 20 M elements 57 -> 48 us, at 27 M 76 -> 72, the plain
+// accumulate at 25 M 54 -> 46 us; at 1 M, where everything stays cached, 24 -> 26.
+enum CacheUse { CACHED = 0, GRADIENT_PAST_CACHE = 1, ALL_PAST_CACHE = 2 };
+constexpr uint64_t GRADIENT_PAST_CACHE_N = 8u << 20;
+inline CacheUse accumulate_cache_use(uint64_t n) {
+    return stream_past_cache(n) ? ALL_PAST_CACHE : n >= GRADIENT_PAST_CACHE_N ? GRADIENT_PAST_CACHE : CACHED;
+}
 
 // ---- the same through per-tile slots ----
 // With a workspace that has room for them, the streaming pass of the selects
@@ -106,14 +116,15 @@ inline SlotPlan slot_plan(uint64_t n, uint32_t cus) {
     return p;
 }
 inline size_t slot_ws_bytes(uint64_t n) { return slot_plan(n, 256).bytes; }
-// Shorter vectors take the one-kernel form: the two extra launches and the scan's
-// fixed few microseconds cost more than the leaner streaming pass saves there.
-// Measured crossover: the calls that form the accumulator on the way (12 bytes an
-// element: the saving is three times the select's) gain from about 40 M elements
-// on, the plain selects from about 100 M, where the vector no longer fits the
-// last-level cache.
+// Shorter vectors take the one-kernel form: the extra launches and their fixed few
+// microseconds cost more than the leaner streaming pass saves there.  Measured
+// crossover: the calls that form the accumulator on the way (12 bytes an element: the
+// saving is three times the select's) gain from about 24 M elements on (accumulate and
+// select, layered, 2 %: 20 M 47 against 50 us, 27 M 73 against 72, 40 M 115 against 104),
+// the plain selects from about 100 M, where the vector no longer fits the last-level
+// cache.
 constexpr uint64_t SLOT_MIN_N_SELECT = 96u << 20;
-constexpr uint64_t SLOT_MIN_N_ACCUMULATE = 1u << 25;
+constexpr uint64_t SLOT_MIN_N_ACCUMULATE = 24u << 20;
 
 // ---- index intersection and residual restore ----
 constexpr int RST_BLOCK = 256;

@@ -444,6 +444,10 @@ __global__ __launch_bounds__(RES_BLOCK) void resolve_kernel(
     // exact threshold without this, 218 so).
     auto take_quad = [&](const float4& v) {
         const uint32_t a = magnitude_key(v.x), b = magnitude_key(v.y), e = magnitude_key(v.z), f = magnitude_key(v.w);
+        if (use_cand) {                                    // (candidates are few, and spread)
+            take(a); take(b); take(e); take(f);
+            return;
+        }
         const uint32_t bin = (a - d.base) >> d.shift;
         const bool alike = bin == uniform(bin) && bin == (b - d.base) >> d.shift && bin == (e - d.base) >> d.shift &&
                            bin == (f - d.base) >> d.shift;
@@ -678,7 +682,7 @@ __global__ __launch_bounds__(RES_BLOCK) void resolve_kernel(
 // residual becomes the accumulator (no zeros), every element at or above the
 // bound goes, in index order, to the candidate list, whose length (written,
 // found) lands in state->collected.
-template <int BLOCK, int U, int STASH, bool NT>
+template <int BLOCK, int U, int STASH, int CACHE>
 __global__ __launch_bounds__(BLOCK) void accumulate_collect_kernel(
     const float* __restrict__ grad, float* __restrict__ res, float lr, uint32_t n, RadixState* state,
     uint32_t* __restrict__ cand_idx, float* __restrict__ cand_val, uint64_t cand_cap,
@@ -694,11 +698,11 @@ __global__ __launch_bounds__(BLOCK) void accumulate_collect_kernel(
     const uint32_t lo_key = collect_bound(state);
     const float lo = __uint_as_float(lo_key);               // a key below the Inf/NaN range, or NaN
     if (lo == lo) {
-        accumulate_select_body<BLOCK, U, STASH, false, NT>(
+        accumulate_select_body<BLOCK, U, STASH, false, CACHE>(
             grad, res, lr, n, TestFloat{lo}, cand_idx, cand_val, cand_cap, state->collected, hdr,
             seg_desc, group_desc, nseg, piece, seg, s_stash, s_count, s_before);
     } else {
-        accumulate_select_body<BLOCK, U, STASH, false, NT>(
+        accumulate_select_body<BLOCK, U, STASH, false, CACHE>(
             grad, res, lr, n, TestKey{lo_key}, cand_idx, cand_val, cand_cap, state->collected, hdr,
             seg_desc, group_desc, nseg, piece, seg, s_stash, s_count, s_before);
     }
@@ -893,13 +897,15 @@ extern "C" int okt_accumulate_topk_select(const float* d_grad, float* d_residual
     hipLaunchKernelGGL(sample_bound_kernel, dim3(BOUNDS), dim3(SAMPLE_BLOCK), 0, s, d_residual_inout, d_grad, lr,
                        (uint32_t)n, (uint32_t)k, state, hist, (uint64_t*)scan_a, words_a, (uint64_t*)scan_b,
                        words_b, spin_limit_setting());
+    const CacheUse use = accumulate_cache_use(n);
     if (slots) {
         // the sample's bounds are magnitude keys, so their bits read as fp32 are the
         // bounds themselves: the slot kernels take the least for their threshold
         const float* bound = reinterpret_cast<const float*>(state->bound);
         timing_before(s);
-        auto* fill = stream_past_cache(n) ? slot_fill_accumulate_kernel<false, true>
-                                          : slot_fill_accumulate_kernel<false, false>;
+        auto* fill = use == ALL_PAST_CACHE        ? slot_fill_accumulate_kernel<false, ALL_PAST_CACHE>
+                     : use == GRADIENT_PAST_CACHE ? slot_fill_accumulate_kernel<false, GRADIENT_PAST_CACHE>
+                                                  : slot_fill_accumulate_kernel<false, CACHED>;
         constexpr uint32_t per_wg = SLOT_FILL_BLOCK / WAVE;
         hipLaunchKernelGGL(fill, dim3((plan.ntiles + per_wg - 1) / per_wg), dim3(SLOT_FILL_BLOCK), 0,
                            s, d_grad, d_residual_inout, lr, (uint32_t)n, bound,
@@ -911,9 +917,10 @@ extern "C" int okt_accumulate_topk_select(const float* d_grad, float* d_residual
         if (rc != OKT_OK) return rc;
     } else {
         timing_before(s);
-        auto* collect = stream_past_cache(n)
-                            ? accumulate_collect_kernel<SEL_BLOCK, SEL_U, SEL_STASH, true>
-                            : accumulate_collect_kernel<SEL_BLOCK, SEL_U, SEL_STASH, false>;
+        auto* collect =
+            use == ALL_PAST_CACHE        ? accumulate_collect_kernel<SEL_BLOCK, SEL_U, SEL_STASH, ALL_PAST_CACHE>
+            : use == GRADIENT_PAST_CACHE ? accumulate_collect_kernel<SEL_BLOCK, SEL_U, SEL_STASH, GRADIENT_PAST_CACHE>
+                                         : accumulate_collect_kernel<SEL_BLOCK, SEL_U, SEL_STASH, CACHED>;
         hipLaunchKernelGGL(collect, dim3(shape.nseg), dim3(SEL_BLOCK), 0, s, d_grad, d_residual_inout,
                            lr, (uint32_t)n, state, cand_idx, cand_val, cand_cap, header(scan_a),
                            segs(scan_a), segs(scan_a) + shape.nseg, shape.nseg, shape.piece);

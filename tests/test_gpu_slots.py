@@ -178,3 +178,43 @@ def test_three_pass_waits_that_give_up_are_reported():
     finally:
         okt.okt_debug_spin_limit(0)
         okt.okt_debug_slot_min_n(0)
+
+
+@pytest.mark.parametrize("n", [1, 1024 * 64 + 1, 1_000_003, (3 << 20) + 1, 9_000_001])
+@pytest.mark.parametrize("fraction", [0.0, 0.003, 0.03, 0.12, 0.6, 1.0])
+def test_fused_select_parts_of_the_last_pass(n, fraction):
+    """The last pass of the fused call cuts its work by weight: vectors whose tiles
+    select nothing, a few, a slot-full or nearly everything, in stretches of a
+    hundred tiles, so that parts begin and end inside every kind of tile, with
+    room for everything and with the output cut short."""
+    rng = np.random.default_rng(n)
+    g = rng.standard_normal(n).astype(np.float32)
+    dense = (np.arange(n) // (100 * 1024)) % 3 == 1
+    # the stretches between select a thirtieth as much
+    level = np.abs(g)
+    order = np.where(dense, level, level * 0.25 if fraction < 1.0 else level).astype(np.float32) * np.sign(g)
+    g = order.astype(np.float32)
+    e = (rng.standard_normal(n) * 1e-4).astype(np.float32)
+    acc = orc.residual_accumulate(g, e, 0.5)
+    mag = np.sort(np.abs(acc))
+    th = np.float32(np.inf) if fraction == 0.0 else mag[max(0, n - max(1, int(fraction * n)))]
+    total = int((np.abs(acc) >= th).sum())
+    for capacity in sorted({total + 3, total // 2 + 1}):
+        d_g, d_e = to_dev(g), to_dev(e)
+        d_th = torch.full((1,), float(th), device=DEV)
+        idx = torch.full((capacity,), -1, dtype=torch.int32, device=DEV)
+        val = torch.zeros(capacity, device=DEV)
+        nnz = torch.zeros(2, dtype=torch.int64, device=DEV)
+        ws = workspace(okt.okt_workspace_bytes(max(n, 1 << 22), 0))
+        ws.fill_(0xAB)
+        okt.okt_debug_slot_min_n(1)
+        try:
+            okt.okt_accumulate_select(d_g, d_e, 0.5, d_th, idx, val, nnz, ws, capacity=capacity)
+            torch.cuda.synchronize()
+        finally:
+            okt.okt_debug_slot_min_n(0)
+        ridx, rval, rres, rtotal = orc.threshold_select(acc, th, capacity=capacity)
+        assert tuple(u64(nnz)) == (ridx.size, rtotal)
+        assert np.array_equal(u32(idx[:ridx.size]), ridx)
+        assert bits_equal(val[:ridx.size].cpu().numpy(), rval)
+        assert bits_equal(d_e.cpu().numpy(), rres)
