@@ -145,9 +145,16 @@ constexpr int RS_MAX_BINS = 1 << 11;
 constexpr size_t RS_STATE_BYTES = 256;
 constexpr size_t RS_HIST_BYTES = 4 * RS_MAX_BINS * sizeof(uint32_t);   // the digits'
 constexpr uint64_t RS_SAMPLE_MIN_N = 4u << 20;   // vectors whose workspace has room for slots
-constexpr uint64_t RS_SAMPLE_FROM_N = 1u << 17;  // shorter vectors are simply read three times
-constexpr uint64_t COLLECT_FROM_N = 2u << 20;    // up to here the digits run over the vector, bound or not
-constexpr uint32_t TINY_N = 16384;               // up to here one workgroup finds the threshold
+// A refresh iteration below this takes accumulate, threshold and select one after the other.
+constexpr uint64_t RS_SAMPLE_FROM_N = 1u << 17;
+// The exact threshold alone: collecting the candidates pays from the shortest length that
+// does not fit one workgroup (digits over the vector from the bound up instead: 140,000
+// elements 18.7 us against 15, 1 M 21 against 17, 2 M 25 against 22).  From k = n / 16 on,
+// up to this length, it no longer does (400,000 elements: 21.2 against 20; 255,570 with
+// most of them selected 4 us more); and with no room for candidates the two digits from
+// the bound up beat three over everything up to here.
+constexpr uint64_t BOUNDED_TO_N = 2u << 20;
+constexpr uint32_t TINY_N = 65536;               // up to here one workgroup finds the threshold
 inline size_t threshold_ws_min_bytes() { return RS_STATE_BYTES + RS_HIST_BYTES; }
 inline size_t threshold_ws_bytes(uint64_t n) {
     // state + histograms + room for the candidate keys (a few percent of the vector)

@@ -9,10 +9,10 @@
 //      atomic per workgroup for what the stashes hold at the end).
 //   3. If at least k keys were collected (always, unless the sample misled),
 //      rank k is among them, and an exact MSD radix select of two digits from the
-//      bound up runs over the candidates only.  Otherwise, or when the vector is
-//      very short or the workspace small, a radix select of 11 + 11 + 9 bits runs over
-//      the whole vector (three more passes).  A vector of up to COLLECT_FROM_N elements
-//      skips step 2: the two digits run over all of it.
+//      bound up runs over the candidates only.  Otherwise, or when the workspace has
+//      no room for the candidates, a radix select of 11 + 11 + 9 bits runs over the
+//      whole vector (three more passes).  A vector of up to BOUNDED_TO_N elements skips
+//      step 2, where there is no room or k is large, and runs the two digits over all of it.
 // Three launches at most (two without step 2, one up to TINY_N elements).
 // Either way the answer is the exact order statistic: all arithmetic is integer
 // counting, the sample only decides how much is read.  State lives in the
@@ -129,7 +129,8 @@ constexpr int SAMPLE_BLOCK = 1024;
 constexpr uint32_t SAMPLE_RUN = 16, SAMPLE_RUNS = 8192, SAMPLE_RUNS_PER_WG = SAMPLE_RUNS / BOUNDS;
 constexpr uint32_t SAMPLE_BINS = 8192;
 constexpr int SAMPLE_SHIFT = 31 - 13;
-static_assert(RS_SAMPLE_FROM_N >= SAMPLE_RUN * SAMPLE_RUNS, "the sampled blocks are distinct");
+// (A vector shorter than the sample has its blocks sampled more than once, evenly.)
+static_assert(TINY_N >= SAMPLE_RUN, "a block to sample");
 
 __global__ __launch_bounds__(SAMPLE_BLOCK) void sample_bound_kernel(
     const float* __restrict__ acc, const float* __restrict__ grad, float lr, uint32_t n, uint32_t k,
@@ -709,10 +710,11 @@ __global__ __launch_bounds__(BLOCK) void accumulate_collect_kernel(
 }
 
 // The exact threshold of a short array in one workgroup and one launch: the keys stay
-// in registers, the digits' histograms in LDS.  (TINY_N elements at most; at 11,700 this one
-// launch takes 7.3 us, the four it replaces took 19.)
+// in registers, the digits' histograms in LDS.  A call at 17,000 elements takes 8.8 us, at
+// 30,000 9.1 us, at 65,536 15 us; the launches it replaces take 17 to 19 us, and at twice
+// that length a thread's keys would no longer fit its registers.
 constexpr int TINY_BLOCK = 1024;
-constexpr uint32_t TINY_PER = TINY_N / TINY_BLOCK;
+template <uint32_t TINY_PER>                   // elements per thread
 __global__ __launch_bounds__(TINY_BLOCK) void tiny_threshold_kernel(const float* __restrict__ acc, uint32_t n,
                                                                     uint32_t k, float* threshold_out,
                                                                     uint64_t* count_ge_out) {
@@ -768,7 +770,7 @@ namespace okt {
 // 2 k where it is a thousandth.  A larger share than a workspace of
 // okt_workspace_bytes holds (9 % of n) is found as quickly by digits over the whole.
 static bool sample_pays(uint64_t n, uint64_t k, uint64_t cand_cap) {
-    return n >= RS_SAMPLE_FROM_N && cand_cap >= k + k / 4 + n / 64;
+    return cand_cap >= k + k / 4 + n / 64;
 }
 
 template <bool SELECT>
@@ -802,7 +804,10 @@ extern "C" int okt_topk_threshold_exact(const float* d_acc, uint64_t n, uint64_t
     if (!d_ws || !aligned(d_ws, 256) || ws_bytes < threshold_ws_min_bytes())
         return OKT_ERR_WORKSPACE;
     if (n <= TINY_N) {
-        hipLaunchKernelGGL(tiny_threshold_kernel, dim3(1), dim3(TINY_BLOCK), 0, s, d_acc, (uint32_t)n, (uint32_t)k,
+        auto* tiny = n <= TINY_N / 4   ? tiny_threshold_kernel<TINY_N / 4 / TINY_BLOCK>
+                     : n <= TINY_N / 2 ? tiny_threshold_kernel<TINY_N / 2 / TINY_BLOCK>
+                                       : tiny_threshold_kernel<TINY_N / TINY_BLOCK>;
+        hipLaunchKernelGGL(tiny, dim3(1), dim3(TINY_BLOCK), 0, s, d_acc, (uint32_t)n, (uint32_t)k,
                            d_threshold_out, d_count_ge_out);
         return launch_status();
     }
@@ -812,8 +817,8 @@ extern "C" int okt_topk_threshold_exact(const float* d_acc, uint64_t n, uint64_t
     const uint64_t cand_cap = ((ws_bytes - threshold_ws_min_bytes()) / 4) & ~(uint64_t)3;   // whole quads
     const SelectShape shape = select_shape(n, device_cus());
     int over = OVER_ALL;
-    if (n >= RS_SAMPLE_FROM_N && n <= COLLECT_FROM_N) over = OVER_BOUNDED;
-    else if (sample_pays(n, k, cand_cap)) over = OVER_KEYS;
+    if (sample_pays(n, k, cand_cap) && (n > BOUNDED_TO_N || k <= n / 16)) over = OVER_KEYS;
+    else if (n <= BOUNDED_TO_N) over = OVER_BOUNDED;
     if (over != OVER_ALL) {
         hipLaunchKernelGGL(sample_bound_kernel, dim3(BOUNDS), dim3(SAMPLE_BLOCK), 0, s, d_acc,
                            (const float*)nullptr, 0.0f, (uint32_t)n, (uint32_t)k, state, hist,
@@ -871,7 +876,7 @@ extern "C" int okt_accumulate_topk_select(const float* d_grad, float* d_residual
         fixed = threshold_ws_min_bytes() + 2 * scan_bytes;
         cand_cap = ws_bytes > fixed ? ((ws_bytes - fixed) / 8) & ~(uint64_t)63 : 0;
     }
-    if (!sample_pays(n, k, cand_cap)) {
+    if (n < RS_SAMPLE_FROM_N || !sample_pays(n, k, cand_cap)) {
         // short vector, large k, or a workspace without room for candidates: the three steps
         // one after the other, each with the workspace to itself
         int rc = okt_residual_accumulate(d_grad, d_residual_inout, lr, n, stream);

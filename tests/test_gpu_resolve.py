@@ -26,8 +26,8 @@ def check_threshold(acc, k, ws_bytes=None):
     assert int(u64(cnt)[0]) == rcnt
 
 
-@pytest.mark.parametrize("n", [1, 2, 4097, 16_383, 16_384, 16_385, 40_001, 131_071, 131_072, 131_073,
-                               2_097_152, 2_097_153, 2_200_003])
+@pytest.mark.parametrize("n", [1, 2, 4097, 16_383, 16_384, 16_385, 32_768, 32_769, 65_536, 65_537, 70_001,
+                               131_071, 131_072, 131_073, 300_007, 2_097_152, 2_097_153, 2_200_003])
 def test_threshold_lengths(n):
     acc = lap(n, n)
     acc[n // 2::7] = 0.0
