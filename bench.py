@@ -475,15 +475,16 @@ def headline(args, torch, np, okt, wl, ev, cfg):
 
 # the first pass of the selects of a long vector (the library's three-pass form), by
 # the names a kernel trace shows: the last template argument says whether the
-# vector is read and written with the non-temporal hint (64 Mi elements and up)
+# vector is read and written with the non-temporal hint (64 Mi elements and up; of
+# the accumulating ones 2: all of it, 1: the gradient alone)
 THREE_PASS_KERNEL = {"select": "slot_fill_kernel<{nt}>", "select_copy": "slot_fill_kernel<{nt}>",
-                     "accumulate_select": "slot_fill_accumulate_kernel<true, {nt}>",
-                     "accumulate_topk_select": "slot_fill_accumulate_kernel<false, {nt}>"}
+                     "accumulate_select": "slot_fill_accumulate_kernel<true, {use}>",
+                     "accumulate_topk_select": "slot_fill_accumulate_kernel<false, {use}>"}
 NON_TEMPORAL_FROM = 64 << 20
 
 # the kernel that moves the data in each call
 MAIN_KERNEL = {"accumulate": "accumulate_kernel", "threshold": "collect_kernel",
-               "threshold_full_vector": "radix_hist_kernel x 3 (no main kernel is bracketed)", "select": "select_kernel",
+               "threshold_full_vector": "resolve_kernel (no main kernel is bracketed)", "select": "select_kernel",
                "select_copy": "select_kernel<DenseCopySource>",
                "accumulate_select": "accumulate_select_kernel",
                "accumulate_topk_select": "accumulate_collect_kernel", "partition": "partition_kernel",
@@ -526,7 +527,8 @@ def is_three_pass(okt, call, n):
 
 def main_kernel_name(call, three_pass=False, n=0):
     if three_pass and call in THREE_PASS_KERNEL:
-        return THREE_PASS_KERNEL[call].format(nt="true" if n >= NON_TEMPORAL_FROM else "false")
+        return THREE_PASS_KERNEL[call].format(nt="true" if n >= NON_TEMPORAL_FROM else "false",
+                                              use=2 if n >= NON_TEMPORAL_FROM else 1)
     return MAIN_KERNEL.get(call, call)
 
 

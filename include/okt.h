@@ -78,7 +78,8 @@ void okt_debug_spin_limit(uint32_t polls);
 
 /*
  * Test hook: the shortest vector for which the select calls take their
- * three-pass form (per-tile slots in the workspace; see okt_threshold_select),
+ * three-pass form (two launches in the accumulating calls up to 134 M elements;
+ * per-tile slots in the workspace; see okt_threshold_select),
  * for every call made after this one, process-wide (0 = the built-in lengths).
  * Both forms give the same output; with a length of 1 small test vectors
  * exercise the three-pass form.
