@@ -9,11 +9,12 @@
 //      atomic per workgroup for what the stashes hold at the end).
 //   3. If at least k keys were collected (always, unless the sample misled),
 //      rank k is among them, and an exact MSD radix select of two digits from the
-//      bound up runs over the candidates only.  Otherwise, or when the workspace has
-//      no room for the candidates, a radix select of 11 + 11 + 9 bits runs over the
-//      whole vector (three more passes).  A vector of up to BOUNDED_TO_N elements skips
-//      step 2, where there is no room or k is large, and runs the two digits over all of it.
-// Three launches at most (two without step 2, one up to TINY_N elements).
+//      bound up runs over the candidates only.  Otherwise, if the sample misled, a radix
+//      select of 11 + 11 + 9 bits runs over the whole vector in the same launch.
+// Where step 2 is known beforehand not to pay (no room for the candidates, or a large
+// k), a longer vector takes three streaming launches, a digit each, and one of up to
+// BOUNDED_TO_N elements the sample and the two digits from its bound up over all of it.
+// Three launches at most beside those (one up to TINY_N elements).
 // Either way the answer is the exact order statistic: all arithmetic is integer
 // counting, the sample only decides how much is read.  State lives in the
 // workspace on the device; the host never waits.
@@ -44,6 +45,7 @@ struct RadixState {
     uint64_t collected[2];            // ordered collection (refresh iteration): candidates written, found
     uint32_t done[PHASES_MAX];        // shares of a phase of resolve_kernel that are finished
     uint32_t ticket;
+    uint32_t base, k_rem, above;      // of digit_kernel's launches: what the digits so far say
 };
 static_assert(sizeof(RadixState) <= RS_STATE_BYTES, "state fits its slot");
 
@@ -61,17 +63,17 @@ __device__ __forceinline__ uint32_t collect_bound(const RadixState* state) {
     return lo != 0 ? lo : ABS_MASK;
 }
 
-// Find the bin that holds rank k_rem counting from the top bin down.  1024 threads,
+// Find the bin that holds rank k_rem counting from the top bin down.  Of BLOCK threads,
 // thread t owns the `per` bins below the t * per highest ones; an inclusive scan
 // over the threads' sums names the owner, who walks its own few bins.  The
 // owner (exactly one thread, if the bins hold that many) stores (bin, keys above the
 // bin, keys in it) to s_result, whose first word is all ones otherwise.
-template <bool ELSEWHERE>             // the counts were added by other workgroups
+template <bool ELSEWHERE, int BLOCK = 1024>     // ELSEWHERE: the counts were added by other workgroups
 __device__ __forceinline__ void pick_bin(const uint32_t* hist, uint32_t bins, uint32_t k_rem,
                                          uint32_t* s_wave, uint32_t* s_result) {
     constexpr int PER_MAX = 8;
     const int t = threadIdx.x, lane = t & (WAVE - 1), wave = t >> 6;
-    const uint32_t per = bins > 1024 ? bins / 1024 : 1;               // bins is a power of two, at most 8192
+    const uint32_t per = bins > BLOCK ? bins / BLOCK : 1;             // bins is a power of two, at most 8 BLOCK
     const bool owner = (uint32_t)t * per < bins;
     uint32_t c[PER_MAX], mine = 0;
 #pragma unroll
@@ -89,7 +91,7 @@ __device__ __forceinline__ void pick_bin(const uint32_t* hist, uint32_t bins, ui
     __syncthreads();
     uint32_t before = incl - mine;
 #pragma unroll
-    for (int w = 0; w < 1024 / WAVE; ++w)
+    for (int w = 0; w < BLOCK / WAVE; ++w)
         if (w < wave) before += s_wave[w];
     if (before < k_rem && k_rem <= before + mine) {  // true for at most one thread
         uint32_t above = before, in_bin = c[0], j = 0;
@@ -280,6 +282,132 @@ __global__ void radix_init_kernel(RadixState* state, uint32_t* hist) {
     if (i < sizeof(RadixState) / 4) reinterpret_cast<uint32_t*>(state)[i] = 0;
 }
 
+// Whether CROWD lanes of the wave share a bin (see digit_kernel), and the add that serves
+// all the lanes that share the first one's; `take` does the others.
+constexpr uint32_t CROWD = 16;
+__device__ __forceinline__ bool crowded(uint32_t bin, uint32_t bins) {
+    const uint32_t lead = uniform(bin);
+    return lead < bins && (uint32_t)__popcll(__ballot(bin == lead)) >= CROWD;
+}
+template <typename Take>
+__device__ __forceinline__ void add_crowd(uint32_t* s_hist, uint32_t bin, uint32_t bins, Take&& take) {
+    const uint32_t lead = uniform(bin);
+    const uint64_t same = __ballot(bin == lead);
+    if (lead < bins && bin == lead) {
+        if (mask_rank(same) == 0) atomicAdd(&s_hist[lead], (uint32_t)__popcll(same));
+    } else {
+        take();
+    }
+}
+
+// ---------------------------------------------------------------------------
+// a digit over the whole vector, a launch each
+// ---------------------------------------------------------------------------
+// Where it is known beforehand that the digits run over all of a long vector, each is a
+// streaming launch of its own: small workgroups, four 16-byte loads of a thread in
+// flight, a histogram in LDS; the workgroup that hands in its counts last picks the bin
+// and leaves what the next launch needs.  resolve_kernel below could do it as well, with
+// one workgroup of 1024 threads per compute unit and contiguous shares by ticket, and is
+// slower at it (its shares dealt out row by row instead: 400 us at 110 M, every row on a
+// page of its own).  Two workgroups per compute unit: each adds up to 2048 bins to the
+// total, and eight of them cost more there than they save in the pass.  Exact threshold
+// with a workspace that has no room for candidates, layered values, cold:
+//              resolve_kernel   8 per unit   2 per unit
+//   25.6 M          137 us         125 us        82 us
+//   60 M            250            164          140
+//   110 M           260            240          231
+//   336 M           697            661          613
+// Keys that share a bin queue for one word of LDS, some seven cycles each.  Where one key
+// a lane, looked at before a batch, finds CROWD of the wave's lanes in one bin, the batch
+// is counted with one add for all the lanes that share the first one's bin (a vector of
+// zeros, all but a thousandth of them: 25.6 M elements 281 us without this, 112 so).
+constexpr int DIG_BLOCK = 256, DIG_QUADS = 4, DIG_PER_CU = 2;
+constexpr uint32_t DIG_STEP = DIG_BLOCK * 4 * DIG_QUADS;
+
+template <uint32_t SHIFT, int BITS, int PASS, bool NT>
+__global__ __launch_bounds__(DIG_BLOCK) void digit_kernel(const float* __restrict__ acc, uint32_t n, uint32_t k,
+                                                          RadixState* state, uint32_t* __restrict__ hist,
+                                                          float* threshold_out, uint64_t* count_ge_out) {
+    constexpr uint32_t BINS = 1u << BITS;
+    constexpr bool FIRST = PASS == 0, LAST = SHIFT == 0;
+    __shared__ uint32_t s_hist[BINS], s_wave[DIG_BLOCK / WAVE], s_result[3], s_last;
+    const uint32_t tid = threadIdx.x;
+    for (uint32_t b = tid; b < BINS; b += DIG_BLOCK) s_hist[b] = 0;
+    const uint32_t base = FIRST ? 0u : state->base, k_rem = FIRST ? k : state->k_rem, above = FIRST ? 0u : state->above;
+    __syncthreads();
+    const uint32_t prefix = base >> (SHIFT + BITS);
+    auto take = [&](float x) {
+        const uint32_t key = magnitude_key(x);
+        if (FIRST || key >> (SHIFT + BITS) == prefix) atomicAdd(&s_hist[(key >> SHIFT) & (BINS - 1)], 1u);
+    };
+    auto take_crowd = [&](float x) { add_crowd(s_hist, (magnitude_key(x) - base) >> SHIFT, BINS, [&]() { take(x); }); };
+    const uint64_t stride = (uint64_t)gridDim.x * DIG_STEP;
+    for (uint64_t r = (uint64_t)blockIdx.x * DIG_STEP; r < n; r += stride) {
+        if (r + DIG_STEP <= n) {
+            const float4* src = reinterpret_cast<const float4*>(acc + r) + tid;
+            float4 v[DIG_QUADS];
+#pragma unroll
+            for (int u = 0; u < DIG_QUADS; ++u) v[u] = load_quad<NT>(src + u * DIG_BLOCK);
+            // all four go out before the first is looked at (the compiler would otherwise wait
+            // for the first behind the second)
+            __builtin_amdgcn_sched_barrier(0);
+            const uint32_t first = (magnitude_key(v[0].x) - base) >> SHIFT;
+            if (crowded(first, BINS)) {
+#pragma unroll
+                for (int u = 0; u < DIG_QUADS; ++u) {
+                    take_crowd(v[u].x); take_crowd(v[u].y);
+                    take_crowd(v[u].z); take_crowd(v[u].w);
+                }
+            } else {
+#pragma unroll
+                for (int u = 0; u < DIG_QUADS; ++u) {
+                    take(v[u].x); take(v[u].y);
+                    take(v[u].z); take(v[u].w);
+                }
+            }
+        } else {
+            for (uint64_t i = r + tid; i < n; i += DIG_BLOCK) take(acc[i]);
+        }
+    }
+    __syncthreads();
+    uint32_t* total = hist + RS_MAX_BINS * PASS;
+    uint32_t seen = 0;
+#pragma unroll
+    for (uint32_t b = tid; b < BINS; b += DIG_BLOCK) {               // all out first, then one wait
+        const uint32_t c = s_hist[b];
+        if (c) seen |= atomicAdd(&total[b], c);
+    }
+    asm volatile("" ::"v"(seen));       // an atomic that has returned has been carried out (see resolve_kernel)
+    __syncthreads();
+    if (tid == 0) s_last = atomicAdd(&state->done[PASS], 1u) == gridDim.x - 1 ? 1u : 0u;
+    __syncthreads();
+    if (s_last == 0) return;
+    pick_bin<true, DIG_BLOCK>(total, BINS, k_rem, s_wave, s_result);
+    if (tid != 0) return;
+    const uint32_t key = base + (s_result[0] << SHIFT);
+    if (LAST) {
+        *threshold_out = __uint_as_float(key);
+        *count_ge_out = (uint64_t)above + s_result[1] + s_result[2];
+    } else {
+        state->base = key;
+        state->k_rem = k_rem - s_result[1];
+        state->above = above + s_result[1];
+    }
+}
+
+template <bool NT>
+static void launch_digits(const float* acc, uint64_t n, uint64_t k, RadixState* state, uint32_t* hist,
+                          float* d_threshold_out, uint64_t* d_count_ge_out, hipStream_t s) {
+    const uint64_t steps = (n + DIG_STEP - 1) / DIG_STEP, most = (uint64_t)DIG_PER_CU * device_cus();
+    const dim3 grid((unsigned)(steps < most ? steps : most)), block(DIG_BLOCK);
+    hipLaunchKernelGGL((digit_kernel<20, RS_BITS1, 0, NT>), grid, block, 0, s, acc, (uint32_t)n, (uint32_t)k, state,
+                       hist, d_threshold_out, d_count_ge_out);
+    hipLaunchKernelGGL((digit_kernel<9, RS_BITS2, 1, NT>), grid, block, 0, s, acc, (uint32_t)n, (uint32_t)k, state,
+                       hist, d_threshold_out, d_count_ge_out);
+    hipLaunchKernelGGL((digit_kernel<0, RS_BITS3, 2, NT>), grid, block, 0, s, acc, (uint32_t)n, (uint32_t)k, state,
+                       hist, d_threshold_out, d_count_ge_out);
+}
+
 // ---------------------------------------------------------------------------
 // the exact threshold, and the select that uses it, in one launch
 // ---------------------------------------------------------------------------
@@ -318,10 +446,10 @@ static_assert(RES_BLOCK == 1024, "pick_bin is written for 1024 threads");
 constexpr int ROWS_MAX = 6;                        // quads of a thread in a share of candidates
 constexpr uint32_t ROW = RES_BLOCK * 4;
 
-// What the digits run over: nothing known (the whole vector); the keys of candidates
-// in any order (cand_count of them); the values of candidates in index order, with
-// their indices (collected); the whole vector, with a bound.
-enum ResolveOver { OVER_ALL = 0, OVER_KEYS = 1, OVER_COLLECTED = 2, OVER_BOUNDED = 3 };
+// What the digits run over: the keys of candidates in any order (cand_count of them);
+// the values of candidates in index order, with their indices (collected); the whole
+// vector, with a bound.
+enum ResolveOver { OVER_KEYS = 1, OVER_COLLECTED = 2, OVER_BOUNDED = 3 };
 
 struct Digit {                                     // a digit, or its result
     uint32_t base, shift, bins;                    // keys base .. base + (bins << shift) - 1
@@ -403,7 +531,7 @@ __global__ __launch_bounds__(RES_BLOCK) void resolve_kernel(
     const uint32_t tid = threadIdx.x;
 
     // ---- alike in every workgroup ----
-    const uint32_t bound = over != OVER_ALL ? cand_bound(state) : 0u;
+    const uint32_t bound = cand_bound(state);
     const uint64_t found = over == OVER_COLLECTED ? state->collected[1]
                          : over == OVER_KEYS ? (uint64_t)state->cand_count : 0ull;
     const bool use_cand = k <= found && found <= cand_cap;                   // rank k is among the candidates
@@ -816,17 +944,17 @@ extern "C" int okt_topk_threshold_exact(const float* d_acc, uint64_t n, uint64_t
     uint32_t* cand = hist + HIST_WORDS;
     const uint64_t cand_cap = ((ws_bytes - threshold_ws_min_bytes()) / 4) & ~(uint64_t)3;   // whole quads
     const SelectShape shape = select_shape(n, device_cus());
-    int over = OVER_ALL;
-    if (sample_pays(n, k, cand_cap) && (n > BOUNDED_TO_N || k <= n / 16)) over = OVER_KEYS;
-    else if (n <= BOUNDED_TO_N) over = OVER_BOUNDED;
-    if (over != OVER_ALL) {
-        hipLaunchKernelGGL(sample_bound_kernel, dim3(BOUNDS), dim3(SAMPLE_BLOCK), 0, s, d_acc,
-                           (const float*)nullptr, 0.0f, (uint32_t)n, (uint32_t)k, state, hist,
-                           (uint64_t*)nullptr, 0u, (uint64_t*)nullptr, 0u, 0u);
-    } else {
+    const bool collect = sample_pays(n, k, cand_cap) && (n > BOUNDED_TO_N || k <= n / 16);
+    if (!collect && n > BOUNDED_TO_N) {
         hipLaunchKernelGGL(radix_init_kernel, dim3(HIST_WORDS / 256), dim3(256), 0, s, state, hist);
+        if (stream_past_cache(n)) launch_digits<true>(d_acc, n, k, state, hist, d_threshold_out, d_count_ge_out, s);
+        else launch_digits<false>(d_acc, n, k, state, hist, d_threshold_out, d_count_ge_out, s);
+        return launch_status();
     }
-    if (over == OVER_KEYS) {
+    hipLaunchKernelGGL(sample_bound_kernel, dim3(BOUNDS), dim3(SAMPLE_BLOCK), 0, s, d_acc,
+                       (const float*)nullptr, 0.0f, (uint32_t)n, (uint32_t)k, state, hist,
+                       (uint64_t*)nullptr, 0u, (uint64_t*)nullptr, 0u, 0u);
+    if (collect) {
         static_assert(CNT_WAVES == SEL_WAVES, "the collect pass is cut like the select");
         timing_before(s);
         hipLaunchKernelGGL(stream_past_cache(n) ? collect_kernel<true> : collect_kernel<false>,
@@ -835,8 +963,8 @@ extern "C" int okt_topk_threshold_exact(const float* d_acc, uint64_t n, uint64_t
         timing_after(s);
     }
     launch_resolve<false>(const_cast<float*>(d_acc), n, k, state, hist, nullptr, (float*)cand, cand_cap,
-                          over, d_threshold_out, d_count_ge_out, nullptr, nullptr, 0, nullptr, nullptr,
-                          shape, s);
+                          collect ? OVER_KEYS : OVER_BOUNDED, d_threshold_out, d_count_ge_out, nullptr,
+                          nullptr, 0, nullptr, nullptr, shape, s);
     return launch_status();
 }
 

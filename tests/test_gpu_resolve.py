@@ -88,3 +88,21 @@ def test_a_sample_that_sees_only_large_values(n):
     for kk in (k, n // 13):
         check_refresh(g, np.zeros(n, np.float32), 1.0, kk, 2 * kk)
         check_threshold(g, kk)
+
+
+# lengths around a step of the streaming digit passes (4096 elements), around the point
+# where their workgroups take a second step (two per compute unit), and from which they
+# read around the cache
+@pytest.mark.parametrize("n", [2_097_153, 2_097_152 + 4_096, 2_097_152 + 4_097, 2 * 2_097_152 - 1,
+                               6_291_459, 67_108_864, 67_108_867])
+def test_digit_passes_over_the_whole_vector(n):
+    acc = lap(n, n)
+    acc[n // 3:n // 3 + 200_000] = 0.0
+    acc[n - 1], acc[n - 2] = np.inf, np.nan
+    acc[5_000:5_300] = np.float32(-2.5e-3)
+    above = int((np.abs(acc) > np.float32(2.5e-3)).sum()) + 1              # and the NaN
+    for k in (above + 150, n // 2) if n > 10_000_000 else (1, 2, 3, above + 1, above + 300, n // 3, n):
+        check_threshold(acc, k, ws_bytes=64 * 1024)
+    if n < 10_000_000:
+        check_threshold(np.zeros(n, np.float32), n // 100, ws_bytes=64 * 1024)
+        check_threshold(np.full(n, -0.5, np.float32), n, ws_bytes=64 * 1024)
