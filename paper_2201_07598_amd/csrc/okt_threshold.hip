@@ -14,7 +14,7 @@
 // Where step 2 is known beforehand not to pay (no room for the candidates, or a large
 // k), a longer vector takes three streaming launches, a digit each, and one of up to
 // BOUNDED_TO_N elements the sample and the two digits from its bound up over all of it.
-// Three launches at most beside those (one up to TINY_N elements).
+// One launch up to TINY_N elements, else two to four.
 // Either way the answer is the exact order statistic: all arithmetic is integer
 // counting, the sample only decides how much is read.  State lives in the
 // workspace on the device; the host never waits.
@@ -567,25 +567,19 @@ __global__ __launch_bounds__(RES_BLOCK) void resolve_kernel(
         if (bin < d.bins) atomicAdd(&s_hist[bin], 1u);
         else if (key >= d.base) ++higher;
     };
-    // Four elements a lane.  Where a wave's all fall into one bin - a vector of zeros,
-    // mostly - one add does for all of them: added one by one they would queue for one
-    // word of LDS (25 M elements, all but a thousandth of them zero: 861 us for the
-    // exact threshold without this, 218 so).
-    auto take_quad = [&](const float4& v) {
+    // `crowd`: many of the wave's share a bin.  (Ties at the top of the candidates, 1 % of
+    // 1 M elements: 47.7 us for the exact threshold with one add an element, 33 so.)
+    auto crowd_of = [&](uint32_t key) { return crowded((key - d.base) >> d.shift, d.bins); };
+    auto take_crowd = [&](uint32_t key) {
+        add_crowd(s_hist, (key - d.base) >> d.shift, d.bins, [&]() { take(key); });
+    };
+    auto take_quad = [&](const float4& v, bool crowd) {
         const uint32_t a = magnitude_key(v.x), b = magnitude_key(v.y), e = magnitude_key(v.z), f = magnitude_key(v.w);
-        if (use_cand) {                                    // (candidates are few, and spread)
+        if (crowd) {
+            take_crowd(a); take_crowd(b); take_crowd(e); take_crowd(f);
+        } else {
             take(a); take(b); take(e); take(f);
-            return;
         }
-        const uint32_t bin = (a - d.base) >> d.shift;
-        const bool alike = bin == uniform(bin) && bin == (b - d.base) >> d.shift && bin == (e - d.base) >> d.shift &&
-                           bin == (f - d.base) >> d.shift;
-        const uint64_t active = __ballot(1);
-        if (__ballot(alike) == active && uniform(bin) < d.bins) {
-            if (mask_rank(active) == 0) atomicAdd(&s_hist[bin], 4u * (uint32_t)__popcll(active));
-            return;
-        }
-        take(a); take(b); take(e); take(f);
     };
     auto counted = [&]() {
         if (d.higher) {
@@ -669,11 +663,15 @@ __global__ __launch_bounds__(RES_BLOCK) void resolve_kernel(
         while (!d.found) {
             __syncthreads();
             clear_hist();
+            auto take_rows = [&](auto&& take_one) {
 #pragma unroll
-            for (int r = 0; r < ROWS_MAX; ++r)
+                for (int r = 0; r < ROWS_MAX; ++r)
 #pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    if (rows.have >> (4 * r + c) & 1u) take(rows.key[r][c] & ABS_MASK);
+                    for (int c = 0; c < 4; ++c)
+                        if (rows.have >> (4 * r + c) & 1u) take_one(rows.key[r][c] & ABS_MASK);
+            };
+            if (crowd_of(rows.key[0][0] & ABS_MASK)) take_rows(take_crowd);
+            else take_rows(take);
             counted();
             d = next_digit<false>(d, s_hist, s_higher, k, s_count, s_result);
         }
@@ -759,6 +757,9 @@ __global__ __launch_bounds__(RES_BLOCK) void resolve_kernel(
         // a pass over the whole of a vector longer than the last-level cache finds nothing
         // of it there
         const bool around_cache = !use_cand && len >= STREAM_PAST_CACHE_N;
+        // of candidates, which are a few rows a share, the first row says it; of a vector
+        // the first row of every four
+        bool crowd = false;
         uint64_t r = start;
         for (; r + 4 * ROW <= end; r += 4 * ROW) {
             const float4* src = reinterpret_cast<const float4*>(walked + r) + tid;
@@ -766,14 +767,17 @@ __global__ __launch_bounds__(RES_BLOCK) void resolve_kernel(
 #pragma unroll
             for (int u = 0; u < 4; ++u)
                 v[u] = around_cache ? load_quad<true>(src + u * RES_BLOCK) : load_quad<false>(src + u * RES_BLOCK);
+            __builtin_amdgcn_sched_barrier(0);             // all out before the first is looked at
+            if (!use_cand || r == start) crowd = crowd_of(magnitude_key(v[0].x));
 #pragma unroll
-            for (int u = 0; u < 4; ++u) take_quad(v[u]);
+            for (int u = 0; u < 4; ++u) take_quad(v[u], crowd);
         }
         for (; r < end; r += ROW) {
             const uint64_t i = r + 4u * tid;
             if (i + 4 <= end) {
                 const float4 v = *reinterpret_cast<const float4*>(walked + i);
-                take_quad(v);
+                if (r == start) crowd = crowd_of(magnitude_key(v.x));
+                take_quad(v, crowd);
             } else {
                 for (uint64_t j = i; j < end; ++j) take(magnitude_key(walked[j]));
             }

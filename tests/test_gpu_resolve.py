@@ -106,3 +106,23 @@ def test_digit_passes_over_the_whole_vector(n):
     if n < 10_000_000:
         check_threshold(np.zeros(n, np.float32), n // 100, ws_bytes=64 * 1024)
         check_threshold(np.full(n, -0.5, np.float32), n, ws_bytes=64 * 1024)
+
+
+@pytest.mark.parametrize("n,k", [(100_003, 4_000), (300_007, 9_000), (2_500_003, 60_000)])
+@pytest.mark.parametrize("tied", [15, 16, 17, 40, 63, 64])
+def test_candidates_that_share_a_bin(n, k, tied):
+    """Of every 64 large values `tied` are equal (CROWD of a wave's lanes, just fewer and
+    more, all of them): one add counts those, and no element is counted twice or lost.
+    Candidates that fit one share, and many."""
+    rng = np.random.default_rng(n + tied)
+    g = lap(n, n, 1e-6)
+    large = int(1.5 * k)
+    at = np.sort(rng.choice(n, large, replace=False))
+    value = rng.uniform(1.0, 1.9, large).astype(np.float32)
+    value[np.arange(large) % 64 < tied] = np.float32(1.5)
+    g[at] = value * rng.choice(np.array([-1.0, 1.0], np.float32), large)
+    above = int((value > np.float32(1.5)).sum())
+    for kk in sorted({above + 1, above + 7, k, large - 1} | ({above} if above else set())):
+        check_threshold(g, kk)
+        check_refresh(g, np.zeros(n, np.float32), 1.0, kk, large)
+    check_threshold(g, k, ws_bytes=64 * 1024)
