@@ -126,3 +126,19 @@ def test_candidates_that_share_a_bin(n, k, tied):
         check_threshold(g, kk)
         check_refresh(g, np.zeros(n, np.float32), 1.0, kk, large)
     check_threshold(g, k, ws_bytes=64 * 1024)
+
+
+@pytest.mark.parametrize("n", [70_001, 300_007, 2_500_003, 4_300_003])
+def test_a_sample_that_sees_zeros(n):
+    """Fewer than k elements that are not zero: the sample's bound is zero.  The answer is
+    zero, or, where just enough elements are not, the least of them: a subnormal, which
+    the digits from zero up find, or a value far above, which they do not."""
+    k = n // 100
+    rng = np.random.default_rng(n)
+    for nonzero, low in ((0, 1.0), (k // 10, 1.0), (k - 1, 1.0), (k, 1.0), (k, 1e-41), (k + 3, 1e-38)):
+        g = np.zeros(n, np.float32)
+        at = rng.choice(n, nonzero, replace=False)
+        g[at] = (low * rng.uniform(1.0, 1.9, nonzero)).astype(np.float32) * rng.choice(
+            np.array([-1.0, 1.0], np.float32), nonzero)
+        check_threshold(g, k)
+        check_refresh(g, np.zeros(n, np.float32), 1.0, k, n if nonzero < k else k + 10)
