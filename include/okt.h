@@ -30,14 +30,14 @@
  *   - Host threads may call the library at the same time as long as the calls
  *     share no workspace and no output buffer; the library keeps no state
  *     between calls.  okt_time_next_kernel and okt_last_hip_error act per
- *     thread, okt_debug_spin_limit and okt_debug_slot_min_n on the whole
- *     process.
+ *     thread, the test hooks (okt_debug_...) on the whole process.
  *   - The kernels that place their output through a scan across workgroups
  *     (the select family, the reduce family, the index intersection), and those
  *     that find the exact threshold digit by digit, wait for one another through
  *     device memory.  Every such wait ends by construction
  *     and is bounded all the same; should one run out, the kernel still exits
- *     normally, every count the call writes (d_nnz_out, d_count_out) is set to
+ *     normally, every count the call writes (d_nnz_out, d_count_out; d_count_ge_out
+ *     where the digits' wait ran out) is set to
  *     UINT64_MAX and the other outputs are unspecified (all stores stay inside
  *     the buffers).
  */
@@ -70,11 +70,19 @@ const char* okt_last_hip_error(void);
 /*
  * Test hook: the number of polls a wait between workgroups may take before it
  * gives up, for every call made after this one, process-wide (0 = the built-in
- * limit, about 2^24); the digits of the exact threshold keep the built-in limit.
- * With a limit of 1 a call either completes as usual or
- * reports UINT64_MAX counts as described above; it never hangs or faults.
+ * limit, about 2^24); the digits of the exact threshold have a limit of their own.
+ * With a limit of 1 a call either completes as usual or reports UINT64_MAX counts
+ * as described above; it never hangs or faults.
  */
 void okt_debug_spin_limit(uint32_t polls);
+
+/*
+ * Test hook: the same for the waits between the digits of the exact threshold
+ * (okt_topk_threshold_exact, okt_accumulate_topk_select).  While it is set, and
+ * okt_debug_spin_limit is not, the scans of okt_accumulate_topk_select take it too:
+ * a share whose digits gave up leaves those behind it waiting.
+ */
+void okt_debug_digit_spin_limit(uint32_t polls);
 
 /*
  * Test hook: the shortest vector for which the select calls take their

@@ -22,6 +22,7 @@ SIGNATURES = {
     "okt_last_hip_error": (ctypes.c_char_p, []),
     "okt_time_next_kernel": (None, [c_vp, c_vp]),
     "okt_debug_spin_limit": (None, [c_u32]),
+    "okt_debug_digit_spin_limit": (None, [c_u32]),
     "okt_debug_slot_min_n": (None, [c_u64]),
     "okt_slot_min_n": (c_u64, [c_int]),
     "okt_version": (c_int, []),
@@ -109,6 +110,11 @@ def okt_time_next_kernel(start_event, stop_event) -> None:
 def okt_debug_spin_limit(polls: int) -> None:
     """Test hook: polls a wait between workgroups may take (0 = built-in limit)."""
     load_library().okt_debug_spin_limit(int(polls))
+
+
+def okt_debug_digit_spin_limit(polls: int) -> None:
+    """Test hook: the same for the digits of the exact threshold (0 = built-in limit)."""
+    load_library().okt_debug_digit_spin_limit(int(polls))
 
 
 def okt_debug_slot_min_n(n: int) -> None:

@@ -53,6 +53,8 @@ uint32_t device_cus() {
 
 static std::atomic<uint32_t> g_spin_limit{0};
 uint32_t spin_limit_setting() { return g_spin_limit.load(std::memory_order_relaxed); }
+static std::atomic<uint32_t> g_digit_spin_limit{0};
+uint32_t digit_spin_limit_setting() { return g_digit_spin_limit.load(std::memory_order_relaxed); }
 
 __global__ void clear_scan_state_kernel(uint64_t* p, uint64_t words, uint32_t spin_limit) {
     uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -79,6 +81,10 @@ const char* okt_last_hip_error(void) { return hipGetErrorString(okt::g_last_hip_
 
 void okt_debug_spin_limit(uint32_t polls) {
     okt::g_spin_limit.store(polls, std::memory_order_relaxed);
+}
+
+void okt_debug_digit_spin_limit(uint32_t polls) {
+    okt::g_digit_spin_limit.store(polls, std::memory_order_relaxed);
 }
 
 void okt_time_next_kernel(void* start_event, void* stop_event) {

@@ -226,6 +226,8 @@ hipError_t launch_clear_scan_state(void* p, uint64_t words, hipStream_t stream);
 // Polls a bounded wait may take before it gives up, as set by
 // okt_debug_spin_limit (0 = SPIN_LIMIT).
 uint32_t spin_limit_setting();
+// The same for the digits of the exact threshold, as set by okt_debug_digit_spin_limit.
+uint32_t digit_spin_limit_setting();
 
 // Compute units of the calling thread's current device, asked of the runtime once
 // per device and kept (host side, no allocation); 256 where there is no device

@@ -33,6 +33,8 @@
 #include "okt_sizes.h"
 #include "okt_slots.h"
 
+#include <stddef.h>
+
 namespace okt {
 
 constexpr int PHASES_MAX = 4;      // digits of resolve_kernel: one from a bound and three general ones at most
@@ -46,7 +48,9 @@ struct RadixState {
     uint32_t done[PHASES_MAX];        // shares of a phase of resolve_kernel that are finished
     uint32_t ticket;
     uint32_t base, k_rem, above;      // of digit_kernel's launches: what the digits so far say
+    uint32_t spin_limit;              // polls a wait of resolve_kernel may take; 0 = SPIN_LIMIT
 };
+constexpr uint32_t STATE_SPIN_WORD = offsetof(RadixState, spin_limit) / 4;
 static_assert(sizeof(RadixState) <= RS_STATE_BYTES, "state fits its slot");
 
 __device__ __forceinline__ uint32_t cand_bound(const RadixState* state) {
@@ -137,7 +141,7 @@ static_assert(TINY_N >= SAMPLE_RUN, "a block to sample");
 __global__ __launch_bounds__(SAMPLE_BLOCK) void sample_bound_kernel(
     const float* __restrict__ acc, const float* __restrict__ grad, float lr, uint32_t n, uint32_t k,
     RadixState* state, uint32_t* __restrict__ hist, uint64_t* __restrict__ scan_a, uint32_t words_a,
-    uint64_t* __restrict__ scan_b, uint32_t words_b, uint32_t spin_limit) {
+    uint64_t* __restrict__ scan_b, uint32_t words_b, uint32_t spin_limit, uint32_t digit_spin_limit) {
     __shared__ __attribute__((aligned(16))) uint32_t s_hist[SAMPLE_BINS];
     __shared__ uint32_t s_wave[SAMPLE_BLOCK / WAVE], s_result[3];
     const uint32_t tid = threadIdx.x, wg = blockIdx.x;
@@ -155,7 +159,8 @@ __global__ __launch_bounds__(SAMPLE_BLOCK) void sample_bound_kernel(
     for (uint32_t w = i; w < HIST_WORDS; w += BOUNDS * SAMPLE_BLOCK) hist[w] = 0;
     for (uint32_t w = i; w < words_a; w += BOUNDS * SAMPLE_BLOCK) scan_a[w] = w == SCAN_SPIN_WORD ? (uint64_t)spin_limit : 0ull;
     for (uint32_t w = i; w < words_b; w += BOUNDS * SAMPLE_BLOCK) scan_b[w] = w == SCAN_SPIN_WORD ? (uint64_t)spin_limit : 0ull;
-    if (i >= BOUNDS && i < sizeof(RadixState) / 4) reinterpret_cast<uint32_t*>(state)[i] = 0;   // behind the bounds
+    if (i >= BOUNDS && i < sizeof(RadixState) / 4)                                              // behind the bounds
+        reinterpret_cast<uint32_t*>(state)[i] = i == STATE_SPIN_WORD ? digit_spin_limit : 0u;
     __syncthreads();
 #pragma unroll
     for (uint32_t u = 0; u < PER; ++u) {
@@ -419,7 +424,7 @@ static void launch_digits(const float* acc, uint64_t n, uint64_t k, RadixState* 
 // the complete histogram and works out for itself what the next phase is.  All
 // shares of earlier phases are held by running workgroups that wait only for still
 // earlier ones, so every wait ends, with however few workgroups running; the waits
-// are bounded all the same (built-in limit).
+// are bounded all the same.
 //
 // With a bound from the sample two digits do: the keys up to an octave above it in
 // 2048 bins (and one for all that lie higher), then the 4096 keys of one of those
@@ -711,8 +716,9 @@ __global__ __launch_bounds__(RES_BLOCK) void resolve_kernel(
             if (!SELECT && d.shift == 0) return;           // nothing follows the last digit
             if (tid == 0) {
                 uint32_t polls = 0;
+                const uint32_t limit = state->spin_limit ? state->spin_limit : SPIN_LIMIT;
                 while (__hip_atomic_load(&state->done[at], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != used) {
-                    if (++polls > SPIN_LIMIT) {            // give up: every count says so
+                    if (++polls > limit) {                 // give up: every count says so
                         *count_ge_out = ~0ull;
                         if (SELECT) {
                             __hip_atomic_store(&hdr->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -960,7 +966,7 @@ extern "C" int okt_topk_threshold_exact(const float* d_acc, uint64_t n, uint64_t
     }
     hipLaunchKernelGGL(sample_bound_kernel, dim3(BOUNDS), dim3(SAMPLE_BLOCK), 0, s, d_acc,
                        (const float*)nullptr, 0.0f, (uint32_t)n, (uint32_t)k, state, hist,
-                       (uint64_t*)nullptr, 0u, (uint64_t*)nullptr, 0u, 0u);
+                       (uint64_t*)nullptr, 0u, (uint64_t*)nullptr, 0u, 0u, digit_spin_limit_setting());
     if (collect) {
         static_assert(CNT_WAVES == SEL_WAVES, "the collect pass is cut like the select");
         timing_before(s);
@@ -1036,7 +1042,8 @@ extern "C" int okt_accumulate_topk_select(const float* d_grad, float* d_residual
     const uint32_t words_a = slots ? (uint32_t)(scan_ws_bytes(plan.nseg) / 8) : words_b;
     hipLaunchKernelGGL(sample_bound_kernel, dim3(BOUNDS), dim3(SAMPLE_BLOCK), 0, s, d_residual_inout, d_grad, lr,
                        (uint32_t)n, (uint32_t)k, state, hist, (uint64_t*)scan_a, words_a, (uint64_t*)scan_b,
-                       words_b, spin_limit_setting());
+                       words_b, spin_limit_setting() ? spin_limit_setting() : digit_spin_limit_setting(),
+                       digit_spin_limit_setting());
     const CacheUse use = accumulate_cache_use(n);
     if (slots) {
         // the sample's bounds are magnitude keys, so their bits read as fp32 are the

@@ -8,7 +8,7 @@ import torch
 
 import paper_2201_07598_amd as okt
 from oracle import okt_oracle as orc
-from tests.okt_harness import DEV, to_dev, u64, workspace
+from tests.okt_harness import DEV, bits_equal, to_dev, u32, u64, workspace
 from tests.test_gpu_refresh import check_refresh, lap
 
 pytestmark = pytest.mark.gpu
@@ -142,3 +142,49 @@ def test_a_sample_that_sees_zeros(n):
             np.array([-1.0, 1.0], np.float32), nonzero)
         check_threshold(g, k)
         check_refresh(g, np.zeros(n, np.float32), 1.0, k, n if nonzero < k else k + 10)
+
+
+@pytest.mark.parametrize("n,k", [(300_007, 3_000), (2_000_003, 120_000), (4_300_003, 120_000)])
+def test_digit_waits_that_give_up_are_reported(n, k):
+    """With the waits between the digits limited to one poll a call completes or reports
+    UINT64_MAX counts; it never hangs.  Candidates in one share (no wait at all), digits
+    over a vector with a bound, candidates in many shares with the select behind."""
+    g, e = lap(n + 9, n), lap(n + 10, n, 2e-3)
+    acc = orc.residual_accumulate(g, e, 0.5)
+    rth, rcnt = orc.topk_threshold_exact(acc, k, method="partition")
+    ridx, rval, rres, total = orc.threshold_select(acc, rth, capacity=2 * k)
+    bad = 0xFFFFFFFFFFFFFFFF
+    th = torch.zeros(1, device=DEV)
+    cnt = torch.zeros(1, dtype=torch.int64, device=DEV)
+    idx = torch.full((2 * k,), -1, dtype=torch.int32, device=DEV)
+    val = torch.zeros(2 * k, device=DEV)
+    nnz = torch.zeros(2, dtype=torch.int64, device=DEV)
+    ws = workspace(okt.okt_workspace_bytes(n, 0))
+    d_acc, d_g = to_dev(acc), to_dev(g)
+    outcomes = []
+    okt.okt_debug_digit_spin_limit(1)
+    try:
+        for _ in range(3):
+            cnt.fill_(-5)
+            okt.okt_topk_threshold_exact(d_acc, k, th, cnt, ws)
+            torch.cuda.synchronize()
+            c = int(u64(cnt)[0])
+            outcomes.append(c == bad)
+            if c != bad:
+                assert c == rcnt and th.cpu().numpy().view(np.uint32)[0] == np.float32(rth).view(np.uint32)
+            cnt.fill_(-5), nnz.fill_(-5)
+            d_e = to_dev(e)
+            okt.okt_accumulate_topk_select(d_g, d_e, 0.5, k, th, cnt, idx, val, nnz, ws)
+            torch.cuda.synchronize()
+            c, m = int(u64(cnt)[0]), [int(x) for x in u64(nnz)]
+            outcomes.append(m[1] == bad)
+            if bad in m:
+                assert m == [bad, bad] and c in (bad, rcnt)
+            else:
+                assert c == rcnt and m == [ridx.size, total]
+                assert np.array_equal(u32(idx[:total]), ridx) and bits_equal(d_e.cpu().numpy(), rres)
+    finally:
+        okt.okt_debug_digit_spin_limit(0)
+    print(outcomes, flush=True)
+    check_threshold(acc, k)                          # the limit restored: exact again
+    check_refresh(g, e, 0.5, k, 2 * k)
