@@ -95,6 +95,13 @@ void okt_debug_digit_spin_limit(uint32_t polls);
 void okt_debug_slot_min_n(uint64_t n);
 
 /*
+ * Test hook: nonzero makes the accumulating calls empty the slots with two launches
+ * (a scan over the tiles' counts, then a copy), as they do above 134 M elements, at
+ * every length; for every call made after this one, process-wide (0 = built in).
+ */
+void okt_debug_slot_two_launches(int on);
+
+/*
  * The length in force: vectors at least this long take the three-pass form, in
  * the plain selects (accumulating = 0) or in the calls that form the accumulator
  * on the way (okt_accumulate_select, okt_accumulate_topk_select; nonzero).

@@ -24,6 +24,7 @@ SIGNATURES = {
     "okt_debug_spin_limit": (None, [c_u32]),
     "okt_debug_digit_spin_limit": (None, [c_u32]),
     "okt_debug_slot_min_n": (None, [c_u64]),
+    "okt_debug_slot_two_launches": (None, [c_int]),
     "okt_slot_min_n": (c_u64, [c_int]),
     "okt_version": (c_int, []),
     "okt_stream_copy": (c_int, [c_vp, c_vp, c_u64, c_vp]),
@@ -120,6 +121,11 @@ def okt_debug_digit_spin_limit(polls: int) -> None:
 def okt_debug_slot_min_n(n: int) -> None:
     """Test hook: shortest vector that takes the three-pass select (0 = built-in length)."""
     load_library().okt_debug_slot_min_n(int(n))
+
+
+def okt_debug_slot_two_launches(on: bool) -> None:
+    """Test hook: the accumulating calls empty the slots with two launches at any length."""
+    load_library().okt_debug_slot_two_launches(1 if on else 0)
 
 
 def okt_slot_min_n(accumulating: bool = False) -> int:

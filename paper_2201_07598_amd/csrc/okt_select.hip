@@ -55,6 +55,8 @@ uint64_t slot_min_n(bool accumulating) {
     const uint64_t set = g_slot_min_n.load(std::memory_order_relaxed);
     return set ? set : accumulating ? SLOT_MIN_N_ACCUMULATE : SLOT_MIN_N_SELECT;
 }
+// Whether the slots are always emptied by two launches (okt_debug_slot_two_launches).
+static std::atomic<int> g_slot_two_launches{0};
 static bool slots_apply(uint64_t n, size_t ws_bytes, bool accumulating) {
     return n >= slot_min_n(accumulating) && ws_bytes >= slot_ws_bytes(n);
 }
@@ -69,7 +71,8 @@ int launch_slot_finish(float* d_acc, uint64_t n, const float* d_threshold, const
     uint32_t* place = (uint32_t*)(ws + plan.place_at);
     const SlotEntry* slots = (const SlotEntry*)(ws + plan.slots_at);
     uint32_t* dense_list = (uint32_t*)(ws + plan.dense_at);
-    if ((after == SLOT_RESTORE || bounds > 1) && plan.ntiles <= SLOT_FINISH_TILES) {
+    if ((after == SLOT_RESTORE || bounds > 1) && plan.ntiles <= SLOT_FINISH_TILES &&
+        g_slot_two_launches.load(std::memory_order_relaxed) == 0) {
         // a workgroup per compute unit, and no fewer than 64 tiles each
         uint32_t grid = (plan.ntiles + 63) / 64;
         if (grid > device_cus()) grid = device_cus();
@@ -146,6 +149,10 @@ static int launch_dense_select(float* d_acc, uint64_t n, const float* d_threshol
 
 extern "C" void okt_debug_slot_min_n(uint64_t n) {
     okt::g_slot_min_n.store(n, std::memory_order_relaxed);
+}
+
+extern "C" void okt_debug_slot_two_launches(int on) {
+    okt::g_slot_two_launches.store(on, std::memory_order_relaxed);
 }
 
 extern "C" uint64_t okt_slot_min_n(int accumulating) { return okt::slot_min_n(accumulating != 0); }

@@ -29,12 +29,16 @@ def pytest_collection_modifyitems(config, items):
             item.add_marker(skip)
 
 
-@pytest.fixture(params=["one_kernel", "three_pass"])
+@pytest.fixture(params=["one_kernel", "three_pass", "two_launches"])
 def select_form(request):
     """Runs a GPU test once with each form of the select calls: the one-kernel form
-    (chained scan inside the streaming kernel) and the three-pass form (per-tile
-    slots), which the library otherwise chooses by the vector's length."""
+    (chained scan inside the streaming kernel), the three-pass form (per-tile slots),
+    which the library otherwise chooses by the vector's length, and the latter with the
+    slots emptied by two launches in the accumulating calls as well, as on the longest
+    vectors."""
     import paper_2201_07598_amd as okt
-    okt.okt_debug_slot_min_n(1 if request.param == "three_pass" else 1 << 40)
+    okt.okt_debug_slot_min_n(1 << 40 if request.param == "one_kernel" else 1)
+    okt.okt_debug_slot_two_launches(request.param == "two_launches")
     yield request.param
     okt.okt_debug_slot_min_n(0)
+    okt.okt_debug_slot_two_launches(False)

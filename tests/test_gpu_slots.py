@@ -37,7 +37,8 @@ def tiled_vector(rng, counts, last=TILE):
 
 
 def run_select(form, call, x, th, cap, grad=None, lr=1.0):
-    okt.okt_debug_slot_min_n(1 if form == "three_pass" else 1 << 40)
+    okt.okt_debug_slot_min_n(1 << 40 if form == "one_kernel" else 1)
+    okt.okt_debug_slot_two_launches(form == "two_launches")
     try:
         n = x.size
         d = to_dev(x)
@@ -59,6 +60,7 @@ def run_select(form, call, x, th, cap, grad=None, lr=1.0):
         return u32(idx[:e]).copy(), val[:e].cpu().numpy(), d.cpu().numpy(), (e, int(c[1]))
     finally:
         okt.okt_debug_slot_min_n(0)
+        okt.okt_debug_slot_two_launches(False)
 
 
 def check_all_calls(x, th, cap, rng):
@@ -78,7 +80,7 @@ def check_all_calls(x, th, cap, rng):
     eps[carried], g[carried] = x[carried], 0.0
     acc = orc.residual_accumulate(g, eps, 0.25)
     ridx, rval, rres, total = orc.threshold_select(acc, th, capacity=cap)
-    for form in ("three_pass", "one_kernel"):
+    for form in ("three_pass", "two_launches", "one_kernel"):
         gi, gv, gd, gc = run_select(form, "fused", eps, th, cap, grad=g, lr=0.25)
         assert gc == (ridx.size, total), form
         assert np.array_equal(gi, ridx) and bits_equal(gv, rval) and bits_equal(gd, rres), form
@@ -182,7 +184,8 @@ def test_three_pass_waits_that_give_up_are_reported():
 
 @pytest.mark.parametrize("n", [1, 1024 * 64 + 1, 1_000_003, (3 << 20) + 1, 9_000_001])
 @pytest.mark.parametrize("fraction", [0.0, 0.003, 0.03, 0.12, 0.6, 1.0])
-def test_fused_select_parts_of_the_last_pass(n, fraction):
+@pytest.mark.parametrize("two_launches", [False, True])
+def test_fused_select_parts_of_the_last_pass(n, fraction, two_launches):
     """The last pass of the fused call cuts its work by weight: vectors whose tiles
     select nothing, a few, a slot-full or nearly everything, in stretches of a
     hundred tiles, so that parts begin and end inside every kind of tile, with
@@ -208,11 +211,13 @@ def test_fused_select_parts_of_the_last_pass(n, fraction):
         ws = workspace(okt.okt_workspace_bytes(max(n, 1 << 22), 0))
         ws.fill_(0xAB)
         okt.okt_debug_slot_min_n(1)
+        okt.okt_debug_slot_two_launches(two_launches)
         try:
             okt.okt_accumulate_select(d_g, d_e, 0.5, d_th, idx, val, nnz, ws, capacity=capacity)
             torch.cuda.synchronize()
         finally:
             okt.okt_debug_slot_min_n(0)
+            okt.okt_debug_slot_two_launches(False)
         ridx, rval, rres, rtotal = orc.threshold_select(acc, th, capacity=capacity)
         assert tuple(u64(nnz)) == (ridx.size, rtotal)
         assert np.array_equal(u32(idx[:ridx.size]), ridx)
