@@ -11,6 +11,7 @@ import torch
 import paper_2201_07598_amd as okt
 import workloads as wl
 from oracle import okt_oracle as orc
+from tests import sample_replay as sr
 from tests.okt_harness import (DEV, GpuPath, bits_equal, gpu_reduce, reduce_tolerance, to_dev,
                                u32, u64, workspace)
 
@@ -271,13 +272,14 @@ def test_longest_vector_the_interface_allows():
     assert bits_equal(gpu.residual[d_pos].cpu().numpy(), res_c)          # left untouched
     print("select without zeroing ok", flush=True)
 
-    # a refresh iteration in one call from a fresh residual.  Some small entries are
-    # planted where the threshold's sample looks (every 4095th block of 1024 elements
-    # at this length), so that its bound is a positive value below the others and the
-    # call's one-pass path - candidates collected, selection over them - runs at this n
+    # a refresh iteration in one call from a fresh residual.  Small entries are planted where
+    # the threshold's sample looks, twenty for each of its workgroups, so that every bound is
+    # a positive value below the others and the call's one-pass path - candidates collected,
+    # selection over them - runs at this n
     del grad
-    blocks = rng.choice(1024, 300, replace=False).astype(np.int64)
-    pos_s = blocks * ((n // 1024) // 1024) * 1024 + rng.integers(0, 1024, 300)
+    runs = np.concatenate([wg + sr.WORKGROUPS * rng.choice(sr.RUNS // sr.WORKGROUPS, 20, replace=False)
+                           for wg in range(sr.WORKGROUPS)])
+    pos_s = sr.run_starts(n)[runs].astype(np.int64) + rng.integers(0, sr.RUN, runs.size)
     pos_s = np.setdiff1d(pos_s, pos)
     pos2 = np.concatenate([pos, pos_s])
     order = np.argsort(pos2, kind="stable")
@@ -287,8 +289,14 @@ def test_longest_vector_the_interface_allows():
     gpu.residual.zero_()
     grad = torch.zeros(n, dtype=torch.float32, device=DEV)
     grad[d_pos2] = torch.from_numpy(g3_c).to(DEV)
+    keys = sr.key_of(orc.residual_accumulate(g3_c, np.zeros_like(g3_c), lr))
+    bounds = sr.bounds(n, k, pos2, keys)
+    passing = int(np.count_nonzero(keys >= bounds.min()))
+    assert bounds.min() > 0 and k <= passing
     okt.okt_accumulate_topk_select(grad, gpu.residual, lr, k, gpu.th, gpu.count_ge, gpu.idx, gpu.val,
                                    gpu.nnz, gpu.ws, capacity=gpu.capacity)
+    state = sr.State(gpu.ws)
+    assert np.array_equal(state.bounds, bounds) and state.collected == passing
     acc_c = orc.residual_accumulate(g3_c, np.zeros_like(g3_c), lr)
     th, cnt = orc.topk_threshold_exact(acc_c, k)
     assert gpu.th.cpu().numpy().view(np.uint32)[0] == np.float32(th).view(np.uint32)

@@ -12,6 +12,7 @@ import torch
 import paper_2201_07598_amd as okt
 import workloads as wl
 from oracle import okt_oracle as orc
+from tests import sample_replay as sr
 from tests.okt_harness import (DEV, GpuPath, bits_equal, gpu_reduce, reduce_tolerance, to_dev,
                                u32, u64, workspace)
 
@@ -176,14 +177,16 @@ def test_threshold_sampled_path():
     # every value equal: the candidates are the whole vector and do not fit
     same = np.full(4_500_000, 0.25, dtype=np.float32)
     assert gpu_threshold(same, 45_000) == (0.25, 4_500_000)
-    # the large values hide in blocks the sample never looks at (it reads every
-    # 4th block of 1024 elements at this length)
+    # three quarters of the elements that the sample never looks at are large: its bound lies
+    # among the small ones, and more pass it than the workspace has room for
     hidden = lap(6, n, 1e-6)
     big = np.random.default_rng(7).laplace(0, 1.0, n).astype(np.float32)
-    blocks = np.arange(n) // 1024
-    mask = (blocks % 4) == 1
+    mask = ((np.arange(n) // 1024) % 4 != 1) & ~sr.sampled(n)
     hidden[mask] = big[mask]
+    ws_bytes = okt.okt_workspace_bytes(n, 0)
     for k in (10, 40_000, 1_000_000):
+        passing = int(np.count_nonzero(sr.key_of(hidden) >= sr.bounds_dense(hidden, k).min()))
+        assert passing > ws_bytes // 4
         th, cnt = gpu_threshold(hidden, k)
         rth, rcnt = orc.topk_threshold_exact(hidden, k, method="partition")
         assert np.float32(th).view(np.uint32) == np.float32(rth).view(np.uint32) and cnt == rcnt

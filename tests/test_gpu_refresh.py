@@ -10,6 +10,7 @@ import torch
 import paper_2201_07598_amd as okt
 import workloads as wl
 from oracle import okt_oracle as orc
+from tests import sample_replay as sr
 from tests.okt_harness import DEV, bits_equal, to_dev, u32, u64, workspace
 
 pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("select_form")]
@@ -89,13 +90,15 @@ def test_workload_vector_with_carried_residual():
 def test_sample_that_misleads_and_ties():
     n = 5_000_011
     zero = np.zeros(n, dtype=np.float32)
-    # the large values hide in blocks the sample never looks at (it reads every
-    # 4th block of 1024 elements at this length): fewer candidates than k
+    # three quarters of the elements that the sample never looks at are large: its bound lies
+    # among the small ones, and more pass it than the workspace has room for
     hidden = lap(6, n, 1e-6)
     big = np.random.default_rng(7).laplace(0, 1.0, n).astype(np.float32)
-    mask = ((np.arange(n) // 1024) % 4) == 1
+    mask = ((np.arange(n) // 1024) % 4 != 1) & ~sr.sampled(n)
     hidden[mask] = big[mask]
     for k in (10, 40_000, 1_000_000):
+        passing = int(np.count_nonzero(sr.key_of(hidden) >= sr.bounds_dense(hidden, k).min()))
+        assert passing > okt.okt_workspace_bytes(n, 0) // 8
         check_refresh(hidden, zero, 1.0, k, k + 100)
     # every value equal: the candidates are the whole vector and do not fit
     same = np.full(4_500_000, 0.25, dtype=np.float32)

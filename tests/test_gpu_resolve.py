@@ -8,6 +8,7 @@ import torch
 
 import paper_2201_07598_amd as okt
 from oracle import okt_oracle as orc
+from tests import sample_replay as sr
 from tests.okt_harness import DEV, bits_equal, to_dev, u32, u64, workspace
 from tests.test_gpu_refresh import check_refresh, lap
 
@@ -81,11 +82,11 @@ def test_a_sample_that_sees_only_large_values(n):
     each bound lies above the answer, too few candidates are found, and the whole
     vector decides."""
     g = lap(9, n, 1e-6)
-    runs = np.arange(8192, dtype=np.uint64) * np.uint64(n // 16) // np.uint64(8192)
-    for r in runs[:-1]:
-        g[int(r) * 16:int(r) * 16 + 16] = lap(int(r), 16, 1.0) + np.float32(2.0)
+    seen = sr.sampled(n)
+    g[seen] = lap(n, int(seen.sum()), 1.0) + np.float32(2.0)
     k = 150_000 if n < 2_000_000 else 300_000
     for kk in (k, n // 13):
+        assert np.count_nonzero(sr.key_of(g) >= sr.bounds_dense(g, kk).min()) < kk
         check_refresh(g, np.zeros(n, np.float32), 1.0, kk, 2 * kk)
         check_threshold(g, kk)
 
@@ -188,3 +189,29 @@ def test_digit_waits_that_give_up_are_reported(n, k):
     print(outcomes, flush=True)
     check_threshold(acc, k)                          # the limit restored: exact again
     check_refresh(g, e, 0.5, k, 2 * k)
+
+
+@pytest.mark.parametrize("n", [70_001, 131_073, 300_007, 2_500_003, 5_000_011])
+def test_the_sample_is_the_one_the_host_replays(n):
+    """The bounds that the sample leaves in the workspace, and how many candidates the
+    collection finds with the least of them: what the tests that mislead the sample, or
+    count on it, take for granted."""
+    g, e = lap(n + 1, n), lap(n + 2, n, 2e-3)
+    acc = orc.residual_accumulate(g, e, 0.5)
+    th = torch.zeros(1, device=DEV)
+    cnt = torch.zeros(1, dtype=torch.int64, device=DEV)
+    ws = workspace(okt.okt_workspace_bytes(n, 0))
+    for k in (1, n // 1000, n // 50):
+        bounds = sr.bounds_dense(acc, k)
+        passing = int(np.count_nonzero(sr.key_of(acc) >= bounds.min()))
+        assert k <= passing <= n // 8              # the room that okt_workspace_bytes gives
+        okt.okt_topk_threshold_exact(to_dev(acc), k, th, cnt, ws)
+        state = sr.State(ws)
+        assert np.array_equal(state.bounds, bounds) and state.keys_found == passing
+        if n >= 131_072:
+            idx = torch.zeros(2 * k, dtype=torch.int32, device=DEV)
+            val = torch.zeros(2 * k, device=DEV)
+            nnz = torch.zeros(2, dtype=torch.int64, device=DEV)
+            okt.okt_accumulate_topk_select(to_dev(g), to_dev(e), 0.5, k, th, cnt, idx, val, nnz, ws)
+            state = sr.State(ws)
+            assert np.array_equal(state.bounds, bounds) and state.collected == passing
