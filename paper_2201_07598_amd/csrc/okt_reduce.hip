@@ -16,7 +16,7 @@
 //     of the bitmap ranks them, and the entries are summed into accumulator [rank].
 //     The tile is then written out in index order; its place in the output comes from the two-level chained scan over tile counts.
 // Traffic: every input entry is read once (tiles with more entries than registers
-// hold read them twice), every output entry is written once, plus 4 B per slot if
+// hold read indices twice), every output entry is written once, plus 4 B per slot if
 // the dense region is requested.
 #include "okt_device.h"
 #include "okt_search.h"
@@ -151,7 +151,7 @@ template <int BLOCK, uint32_t WORDS_MAX>
 __device__ __forceinline__ uint32_t bitmap_prefix(const uint32_t* s_bits, uint16_t* s_wprefix,
                                                   uint32_t words, uint32_t* s_wave, uint32_t* s_wrap) {
     static_assert(WORDS_MAX * 32 < 2 * 65536, "prefixes wrap once at most");
-    constexpr uint32_t PER = (WORDS_MAX + BLOCK - 1) / BLOCK;           // words per thread (1 to 3)
+    constexpr uint32_t PER = (WORDS_MAX + BLOCK - 1) / BLOCK;           // words per thread (1 to 6)
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid >> 6;
     uint32_t c[PER], sum = 0;
 #pragma unroll
@@ -190,8 +190,16 @@ struct __attribute__((packed, aligned(4))) Quad32 { uint32_t v[4]; };   // four 
 // threads make a chunk.  A tile that is one chunk (the host sizes tiles so that
 // this is the rule) keeps all its entries in registers: they are read from memory
 // once, both arrays at once, and the marking, the summing and the writing of the
-// indices need nothing more from memory.  A tile with more entries (many
-// contributions that hit the same slots) goes chunk by chunk, twice.
+// indices need nothing more from memory.
+//
+// A tile with more entries (slots that several contributions hit, a stretch that is
+// hit more than the rest of the region) is marked from all of them and then summed from
+// all of them, read again.  If it has more hit slots than accumulators too, it is cut
+// into windows of the bitmap with as many hit slots as there are accumulators, and only
+// the pieces of the slices that lie in a window are read for it: one pass over
+// the entries in all, where a pass over all of them for every window took 183 us
+// instead of 117 for 382 regions of 8 contributions with most hits in a quarter
+// of the region.
 //
 // What bounds it: a tile is a chain of phases - ticket, slice table, entries, marks,
 // ranks, sums, place, output - of some 14 us with two tiles of 8,000 entries to a
@@ -199,14 +207,18 @@ struct __attribute__((packed, aligned(4))) Quad32 { uint32_t v[4]; };   // four 
 // fp64 atomic add at random places an entry), and LDS (ten bytes a hit slot) is what
 // limits the tiles in flight.  490 regions of 16 contributions (1.9 GB in and out):
 // 575 us with slices read in blocks of 64 entries, twice, by 8-wave workgroups of
-// half this size, 500 us as it is here; 373 regions of 64 contributions: 734 and
-// 555 us, the longer slices of the wider tile counting for as much as the rest.
+// half this size, 519 us as it is here; 373 regions of 64 contributions: 734 and 599 us,
+// the longer slices of the wider tile counting for
+// as much as the rest.  The narrow form is held to 64 registers, for
+// four tiles to a CU: 16 contributions, a tenth of 400 K slots hit, 380 regions, 65 us
+// against 84 with slices read twice and 78 in wide tiles.
 // Tried and not kept: 16 waves with 8 entries a thread and the same tile (spills at
-// 64 registers, 526 us without them), three or four smaller tiles to a CU (540, 530
-// us), several regions' tiles in turn per workgroup with the next slice table
-// fetched ahead (500 us: what it hides, its registers and the extra barriers cost).
+// 64 registers), several regions' tiles in turn per workgroup with the next slice table
+// fetched ahead (what it hides, its registers and the extra barriers cost), tiles of
+// several regions in turn in the grid (their inputs share no lines), the tile's windows
+// each searched before its turn (a chain of searches instead of one).
 template <int BLOCK, int ROUNDS, uint32_t C, uint32_t S_MAX>
-__global__ __launch_bounds__(BLOCK, 4) void reduce_tile_kernel(
+__global__ __launch_bounds__(BLOCK, ROUNDS == 2 ? 8 : 4) void reduce_tile_kernel(
     const uint32_t* __restrict__ idx_cat, const float* __restrict__ val_cat,
     const uint64_t* __restrict__ seg_begin, const uint64_t* __restrict__ seg_end,
     uint32_t seg_stride, const uint32_t* __restrict__ lo_hi, uint32_t lo0,
@@ -217,7 +229,14 @@ __global__ __launch_bounds__(BLOCK, 4) void reduce_tile_kernel(
     constexpr int WAVES = BLOCK / WAVE;
     constexpr bool DENSE = S_MAX == C;            // accumulator = slot, always
     constexpr uint32_t WORDS_MAX = S_MAX / 32;
-    constexpr uint32_t UNITS = BLOCK / 4 * ROUNDS;
+    constexpr uint32_t UNITS = BLOCK / 4 * ROUNDS, WINDOWS_MAX = 15;
+    // A tile of at most EXCESS chunks is marked and summed chunk by chunk, the units spread
+    // over all threads; a longer one goes slice by slice, without a barrier between chunks.
+    // The narrow form keeps the first chunk in registers also then: beside a second chunk
+    // the wide form has none for it.
+    constexpr uint32_t EXCESS = 2;
+    constexpr bool KEEP = ROUNDS == 2;
+    static_assert(S_MAX <= WINDOWS_MAX * (C - 32), "windows of a tile");
     // Lanes without an entry work on a slot, a rank and an accumulator of their own
     // past the end (one of SPARE), so that the loops over the entries have no branch.
     constexpr uint32_t SPARE = 32, SLOT_BITS = 17, SLOT_MASK = (1u << SLOT_BITS) - 1u;
@@ -227,8 +246,8 @@ __global__ __launch_bounds__(BLOCK, 4) void reduce_tile_kernel(
     __shared__ __attribute__((aligned(16))) uint32_t s_bits[WORDS_MAX + SPARE];
     __shared__ uint16_t s_wprefix[WORDS_MAX + SPARE];
     __shared__ uint64_t s_unit[UNITS];            // first entry << 6 | whole unit readable << 5 | entries
-    __shared__ uint32_t s_wave[3][WAVES];
-    __shared__ uint32_t s_tile, s_before[2], s_wrap;
+    __shared__ uint32_t s_wave[2][WAVES];
+    __shared__ uint32_t s_tile, s_before[2], s_wrap, s_cut[WINDOWS_MAX + 1], s_cut_rank[WINDOWS_MAX + 1];
 
     const int tid = threadIdx.x, lane = tid & (WAVE - 1);
     const int wave = (int)uniform((uint32_t)tid >> 6);
@@ -291,18 +310,13 @@ __global__ __launch_bounds__(BLOCK, 4) void reduce_tile_kernel(
             sl_readable = readable < 0xffffffffull ? (uint32_t)readable : 0xffffffffu;
         }
     };
-    uint32_t units = 0, entries = 0;    // of the contributions fetched last
+    uint32_t units = 0;                 // of the contributions fetched last
     auto number_slices = [&]() {                                  // one barrier
         const uint32_t mine = (sl_len + RED_UNIT - 1) / RED_UNIT;
         const uint32_t incl = wave_inclusive_scan_u32(member == 0 ? mine : 0u);
-        const uint32_t incl_entries = wave_inclusive_scan_u32(member == 0 ? sl_len : 0u);
-        if (lane == WAVE - 1) {
-            s_wave[0][wave] = incl_entries;
-            s_wave[1][wave] = incl;
-        }
+        if (lane == WAVE - 1) s_wave[0][wave] = incl;
         __syncthreads();
-        entries = sum_of_waves<WAVES>(s_wave[0]).total;
-        const WaveSums sums = sum_of_waves<WAVES>(s_wave[1]);
+        const WaveSums sums = sum_of_waves<WAVES>(s_wave[0]);
         sl_unit0 = sums.before + incl - mine;                     // the members of a slice agree
         units = sums.total;
     };
@@ -321,43 +335,38 @@ __global__ __launch_bounds__(BLOCK, 4) void reduce_tile_kernel(
     struct Chunk {
         uint32_t slot[ROUNDS][4];    // slot in the tile, later rank << SLOT_BITS | slot; from S_MAX on: no entry
         float value[ROUNDS][4];
+        bool last;                   // the wave has units in the last round (uniform): a chunk is seldom full
     };
-    auto load_chunk = [&](Chunk& c, uint32_t in_chunk, auto with_values) {
+    const uint32_t nowhere = S_MAX + 32u * ((uint32_t)lane % SPARE);
+    // Quad u of a chunk: the first `left` of the four entries at `from`, read with 16-byte
+    // loads if all four lie inside the contribution (past the slice's end though they may be).
+    auto load_entries = [&](Chunk& c, int u, uint64_t from, uint32_t left, bool whole, auto with_values) {
         constexpr bool VALUES = decltype(with_values)::value;
-        uint32_t left[ROUNDS];
-        const uint32_t nowhere = S_MAX + 32u * ((uint32_t)lane % SPARE);
 #pragma unroll
-        for (int u = 0; u < ROUNDS; ++u) {
-            const uint32_t unit = ((uint32_t)tid >> 2) + u * (BLOCK / 4);
-            const uint64_t d = unit < in_chunk ? s_unit[unit] : 0ull;
-            const uint32_t len = (uint32_t)d & 31u, first = 4u * ((uint32_t)tid & 3u);
-            left[u] = len > first ? len - first : 0u;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                c.slot[u][j] = 0;
-                c.value[u][j] = 0.0f;
-            }
-            if (left[u] != 0) {
-                const uint64_t from = (d >> 6) + first;
-                if ((uint32_t)d & 32u) {                      // past the slice's end, not the contribution's
-                    const Quad32 i4 = *reinterpret_cast<const Quad32*>(idx_cat + from);
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) c.slot[u][j] = i4.v[j];
-                    if (VALUES) {
-                        const Quad32 v4 = *reinterpret_cast<const Quad32*>(val_cat + from);
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) c.value[u][j] = __uint_as_float(v4.v[j]);
-                    }
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        if ((uint32_t)j < left[u]) {
-                            c.slot[u][j] = idx_cat[from + j];
-                            if (VALUES) c.value[u][j] = val_cat[from + j];
-                        }
-                }
-            }
+        for (int j = 0; j < 4; ++j) {
+            c.slot[u][j] = 0;
+            c.value[u][j] = 0.0f;
         }
+        if (left == 0) return;
+        if (whole) {
+            const Quad32 i4 = *reinterpret_cast<const Quad32*>(idx_cat + from);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) c.slot[u][j] = i4.v[j];
+            if (VALUES) {
+                const Quad32 v4 = *reinterpret_cast<const Quad32*>(val_cat + from);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) c.value[u][j] = __uint_as_float(v4.v[j]);
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if ((uint32_t)j < left) {
+                    c.slot[u][j] = idx_cat[from + j];
+                    if (VALUES) c.value[u][j] = val_cat[from + j];
+                }
+        }
+    };
+    auto settle = [&](Chunk& c, const uint32_t (&left)[ROUNDS]) {          // indices -> slots of the tile
 #pragma unroll
         for (int u = 0; u < ROUNDS; ++u)
 #pragma unroll
@@ -366,9 +375,40 @@ __global__ __launch_bounds__(BLOCK, 4) void reduce_tile_kernel(
                 c.slot[u][j] = (uint32_t)j < left[u] && s < tslots ? s : nowhere;   // beyond tslots: unsorted input only
             }
     };
+    auto load_chunk = [&](Chunk& c, uint32_t in_chunk, auto with_values) {
+        uint32_t left[ROUNDS];
+        c.last = in_chunk > (uint32_t)(ROUNDS - 1) * (BLOCK / 4) + (uint32_t)wave * (WAVE / 4);
+#pragma unroll
+        for (int u = 0; u < ROUNDS; ++u) {
+            const uint32_t unit = ((uint32_t)tid >> 2) + u * (BLOCK / 4);
+            const uint64_t d = unit < in_chunk ? s_unit[unit] : 0ull;
+            const uint32_t len = (uint32_t)d & 31u, first = 4u * ((uint32_t)tid & 3u);
+            left[u] = len > first ? len - first : 0u;
+            load_entries(c, u, (d >> 6) + first, left[u], ((uint32_t)d & 32u) != 0, with_values);
+        }
+        settle(c, left);
+    };
+    // The slices at hand, each read by the threads that hold it: no table of units and no
+    // barrier, so a wave goes on to its next entries by itself.
+    auto stream_slices = [&](auto with_values, auto&& body) {
+        const uint32_t step = 4u << share;
+        for (uint32_t i0 = 4u * member; i0 < sl_len; i0 += ROUNDS * step) {
+            Chunk c;
+            uint32_t left[ROUNDS];
+            c.last = true;
+#pragma unroll
+            for (int u = 0; u < ROUNDS; ++u) {
+                const uint32_t i = i0 + u * step;
+                left[u] = i < sl_len ? sl_len - i : 0u;
+                load_entries(c, u, sl_start + i, left[u], i + 4 <= sl_readable, with_values);
+            }
+            settle(c, left);
+            body(c);
+        }
+    };
     using Yes = std::true_type;
     using No = std::false_type;
-    auto for_each_chunk = [&](auto with_values, auto&& body) {
+    auto for_each_chunk = [&](auto&& body) {
         for (uint32_t p0 = 0; p0 < P; p0 += BLOCK) {
             fetch_slices(p0);
             number_slices();
@@ -376,7 +416,7 @@ __global__ __launch_bounds__(BLOCK, 4) void reduce_tile_kernel(
                 write_units(u0);
                 __syncthreads();
                 Chunk c;
-                load_chunk(c, units - u0 < UNITS ? units - u0 : UNITS, with_values);
+                load_chunk(c, units - u0 < UNITS ? units - u0 : UNITS, Yes{});
                 body(c);
                 __syncthreads();                              // s_unit and s_wave are free again
             }
@@ -388,8 +428,9 @@ __global__ __launch_bounds__(BLOCK, 4) void reduce_tile_kernel(
         for (int u = 0; u < ROUNDS; ++u)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                __hip_atomic_fetch_or(&s_bits[c.slot[u][j] >> 5], 1u << (c.slot[u][j] & 31), __ATOMIC_RELAXED,
-                                      __HIP_MEMORY_SCOPE_WORKGROUP);
+                if (u < ROUNDS - 1 || c.last)
+                    __hip_atomic_fetch_or(&s_bits[c.slot[u][j] >> 5], 1u << (c.slot[u][j] & 31), __ATOMIC_RELAXED,
+                                          __HIP_MEMORY_SCOPE_WORKGROUP);
     };
     // Hit slots of the tile below bitmap word w.  MAY_WRAP: there may be more than
     // 65,535 of them (a chunk's entries alone never make as many).
@@ -404,6 +445,7 @@ __global__ __launch_bounds__(BLOCK, 4) void reduce_tile_kernel(
         for (int u = 0; u < ROUNDS; ++u)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
+                if (u == ROUNDS - 1 && !c.last) break;
                 const uint32_t s = c.slot[u][j];
                 const uint32_t below = s_bits[s >> 5] & ((1u << (s & 31)) - 1u);
                 uint32_t rank = hits_below(s >> 5, general) + (uint32_t)__popc(below);
@@ -443,9 +485,17 @@ __global__ __launch_bounds__(BLOCK, 4) void reduce_tile_kernel(
     };
     uint32_t distinct = 0, exclusive = 0;
 
+    auto finish = [&]() {
+        if (tile != r.ntiles - 1 || tid != 0) return;
+        const uint64_t total = (uint64_t)exclusive + distinct;
+        const bool failed =
+            __hip_atomic_load(&hdr->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+        nnz[0] = failed ? ~0ull : (total < capacity ? total : capacity);
+        nnz[1] = failed ? ~0ull : total;
+    };
     if constexpr (DENSE) {
         // ---- densely hit region: accumulator = slot, one sweep ----
-        for_each_chunk(Yes{}, [&](Chunk& c) {
+        for_each_chunk([&](Chunk& c) {
 #pragma unroll
             for (int u = 0; u < ROUNDS; ++u)
 #pragma unroll
@@ -455,7 +505,7 @@ __global__ __launch_bounds__(BLOCK, 4) void reduce_tile_kernel(
                                                __HIP_MEMORY_SCOPE_WORKGROUP);
             mark(c);
         });
-        distinct = bitmap_prefix<BLOCK, WORDS_MAX>(s_bits, s_wprefix, words, s_wave[2], &s_wrap);
+        distinct = bitmap_prefix<BLOCK, WORDS_MAX>(s_bits, s_wprefix, words, s_wave[1], &s_wrap);
         exclusive = place_tile(distinct);
         // a thread writes out the hit slots of one EMIT_BITS-wide piece of a bitmap
         // word: a tile has fewer words than the workgroup has threads, a word up
@@ -483,7 +533,7 @@ __global__ __launch_bounds__(BLOCK, 4) void reduce_tile_kernel(
         // ---- sparsely hit region: mark, rank, then sum into accumulator [rank] ----
         uint32_t* s_idx = reinterpret_cast<uint32_t*>(s_sum);   // takes over once the sums are read
         auto rank_tile = [&]() {
-            distinct = bitmap_prefix<BLOCK, WORDS_MAX>(s_bits, s_wprefix, words, s_wave[2], &s_wrap);
+            distinct = bitmap_prefix<BLOCK, WORDS_MAX>(s_bits, s_wprefix, words, s_wave[1], &s_wrap);
             // the count is known before the sums: publish it now, wait for the others later
             if (tid == 0) scan_publish_early(tile_desc, tile, distinct);
         };
@@ -520,56 +570,143 @@ __global__ __launch_bounds__(BLOCK, 4) void reduce_tile_kernel(
         };
         fetch_slices(0);
         number_slices();
-        if (P <= (uint32_t)BLOCK && units <= UNITS && entries <= C) {
-            // all entries in registers, and no more hit slots than accumulators
+        // the units from u0 on, a chunk at a time
+        auto chunks = [&](uint32_t u0, auto with_values, auto&& body) {
+            for (; u0 < units; u0 += UNITS) {
+                __syncthreads();                              // s_unit has been read
+                write_units(u0);
+                __syncthreads();
+                Chunk c;
+                load_chunk(c, units - u0 < UNITS ? units - u0 : UNITS, with_values);
+                body(c);
+            }
+        };
+        const bool by_chunk = P <= (uint32_t)BLOCK && (units <= EXCESS * UNITS || share < 3);
+        if (by_chunk && (KEEP || units <= UNITS)) {
+            // The first chunk, which is all there is as a rule, stays in registers from the
+            // marking to the writing of the indices; what lies beyond it is read for each.
             write_units(0);
             __syncthreads();
             Chunk mine;
-            load_chunk(mine, units, Yes{});
+            load_chunk(mine, units < UNITS ? units : UNITS, Yes{});
             mark(mine);
+            if (KEEP) chunks(UNITS, No{}, mark);
             __syncthreads();
             rank_tile();
-            add(mine, 0, No{});
-            __syncthreads();
-            look_back();
-            write_out(0, distinct, [&]() {
+            if (distinct <= C) {
+                add(mine, 0, No{});
+                if (KEEP) chunks(UNITS, Yes{}, [&](Chunk& c) { add(c, 0, No{}); });
+                __syncthreads();
+                look_back();
+                write_out(0, distinct, [&]() {
+                    if (KEEP && units > UNITS) {
+                        for (uint32_t w = tid; w < words; w += BLOCK) {
+                            uint32_t bits = s_bits[w], rank = hits_below(w, No{});
+                            for (; bits; bits &= bits - 1, ++rank) s_idx[rank] = a + w * 32u + (uint32_t)(__ffs(bits) - 1);
+                        }
+                        return;
+                    }
 #pragma unroll
-                for (int u = 0; u < ROUNDS; ++u)
+                    for (int u = 0; u < ROUNDS; ++u)
 #pragma unroll
-                    for (int j = 0; j < 4; ++j)               // every hit of a slot writes the same
-                        s_idx[mine.slot[u][j] >> SLOT_BITS] = a + (mine.slot[u][j] & SLOT_MASK);
-            });
+                        for (int j = 0; j < 4; ++j)           // every hit of a slot writes the same
+                            if (u < ROUNDS - 1 || mine.last)
+                                s_idx[mine.slot[u][j] >> SLOT_BITS] = a + (mine.slot[u][j] & SLOT_MASK);
+                });
+                finish();
+                return;
+            }
         } else {
-            __syncthreads();                                      // s_wave read by all
-            for_each_chunk(No{}, mark);
-            rank_tile();
-            uint32_t r0 = 0;
-            do {                                              // one round, unless the estimate was off
-                if (r0) {                                     // the first round starts cleared
-                    __syncthreads();                          // previous round fully read
-                    for (uint32_t s = tid; s < C; s += BLOCK) s_sum[s] = 0.0;
-                    __syncthreads();
+            if (!KEEP && by_chunk) {
+                chunks(0, No{}, mark);
+            } else {
+                for (uint32_t p0 = 0; p0 < P; p0 += BLOCK) {
+                    if (p0) fetch_slices(p0);
+                    stream_slices(No{}, mark);
                 }
-                for_each_chunk(Yes{}, [&](Chunk& c) { add(c, r0, Yes{}); });
-                if (r0 == 0) look_back();
-                write_out(r0, distinct - r0 < C ? distinct - r0 : C, [&]() {
-                    for (uint32_t w = tid; w < words; w += BLOCK) {
+            }
+            __syncthreads();
+            rank_tile();
+        }
+        {
+            // More entries than registers hold, or more hit slots than accumulators: the tile
+            // is cut, at words of the bitmap, into windows of at most C hit slots, and every
+            // window's entries are read, summed and written in turn.  Window k ends in the word
+            // that holds hit slot (k + 1) distinct / windows, up to 31 hit slots early.
+            const uint32_t windows = distinct > C ? (distinct + C - 33) / (C - 32) : 1u;
+            for (uint32_t w = tid; w < words; w += BLOCK) {
+                const uint32_t here = hits_below(w, Yes{}), next = w + 1 < words ? hits_below(w + 1, Yes{}) : distinct;
+                for (uint32_t k = 1; k < windows; ++k) {
+                    const uint32_t target = k * distinct / windows;
+                    if (here <= target && target < next) {        // one word for every k
+                        s_cut[k] = w;
+                        s_cut_rank[k] = here;
+                    }
+                }
+            }
+            if (tid == 0) {
+                s_cut[0] = s_cut_rank[0] = 0;
+                s_cut[windows] = words;
+                s_cut_rank[windows] = distinct;
+            }
+            __syncthreads();
+            // A slice is sorted, so a window's entries are a piece of it, whose end is searched
+            // from where it would lie if the slice were spread as the tile's hits are: by the
+            // threads that hold the slice, one window each, where LDS has room for the ends,
+            // else when the window's turn comes.  (With more contributions than threads every
+            // window reads all entries; those of other windows fall out by their rank.)
+            const uint32_t slice = (uint32_t)tid >> share;
+            const uint64_t whole_start = sl_start;
+            const uint32_t whole_len = sl_len, whole_readable = sl_readable;
+            auto window_end = [&](uint32_t k, uint32_t from) -> uint32_t {
+                if (k == windows || whole_len == 0) return whole_len;
+                const uint64_t guess = whole_start + (uint64_t)whole_len * s_cut_rank[k] / distinct;
+                return (uint32_t)(lower_bound_near(idx_cat, whole_start + from, whole_start + whole_len,
+                                                   a + s_cut[k] * 32u, guess) - whole_start);
+            };
+            uint32_t* const s_end = reinterpret_cast<uint32_t*>(s_unit);
+            const bool ends_kept = P <= (uint32_t)BLOCK && P * windows <= 2 * UNITS;
+            if (ends_kept) {
+                if (slice < P)
+                    for (uint32_t k = member + 1; k <= windows; k += 1u << share) s_end[slice * windows + k - 1] = window_end(k, 0);
+                __syncthreads();
+            }
+            uint32_t begin = 0;
+            for (uint32_t k = 0; k < windows; ++k) {
+                const uint32_t w0 = uniform(s_cut[k]), w1 = uniform(s_cut[k + 1]);
+                const uint32_t r0 = uniform(s_cut_rank[k]), r1 = uniform(s_cut_rank[k + 1]);
+                auto sum = [&](Chunk& c) { add(c, r0, Yes{}); };
+                if (P <= (uint32_t)BLOCK) {
+                    const uint32_t end = !ends_kept ? window_end(k + 1, begin) : slice < P ? s_end[slice * windows + k] : 0u;
+                    sl_start = whole_start + begin;
+                    sl_len = end > begin ? end - begin : 0u;
+                    sl_readable = whole_readable > begin ? whole_readable - begin : 0u;
+                    begin = end > begin ? end : begin;
+                    if (!KEEP && by_chunk && windows == 1) chunks(0, Yes{}, sum);
+                    else stream_slices(Yes{}, sum);
+                } else {
+                    for (uint32_t p0 = 0; p0 < P; p0 += BLOCK) {
+                        fetch_slices(p0);
+                        stream_slices(Yes{}, sum);
+                    }
+                }
+                __syncthreads();
+                if (k == 0) look_back();
+                write_out(r0, r1 - r0, [&]() {
+                    for (uint32_t w = w0 + tid; w < w1; w += BLOCK) {
                         uint32_t bits = s_bits[w], rank = hits_below(w, Yes{}) - r0;
                         for (; bits; bits &= bits - 1, ++rank)
                             if (rank < C) s_idx[rank] = a + w * 32u + (uint32_t)(__ffs(bits) - 1);
                     }
                 });
-                r0 += C;
-            } while (r0 < distinct);
+                if (k + 1 == windows) break;
+                __syncthreads();                              // sums and indices fully read
+                for (uint32_t i = tid; i < C; i += BLOCK) s_sum[i] = 0.0;
+                __syncthreads();
+            }
         }
     }
-    if (tile == r.ntiles - 1 && tid == 0) {
-        const uint64_t total = (uint64_t)exclusive + distinct;
-        const bool failed =
-            __hip_atomic_load(&hdr->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-        nnz[0] = failed ? ~0ull : (total < capacity ? total : capacity);
-        nnz[1] = failed ? ~0ull : total;
-    }
+    finish();
 }
 
 // traffic_only: the measurement entry point okt_stream_gather - the same tiles and
@@ -591,15 +728,7 @@ int reduce_launch(const uint32_t* d_idx_cat, const float* d_val_cat,
         !aligned(d_dense, 4) || !aligned(d_lo_hi, 4))
         return OKT_ERR_INVALID_ARG;
     // the caller's bound on the size of the union doubles as the density estimate
-    const ReduceShape wide = reduce_tile_shape(max_width, capacity, P, true);
-    ReduceShape shape = wide;
-    // The wide tiles are for throughput.  A launch that cannot fill the chip with them
-    // is nothing but the latency of its tiles: it takes tiles of half the size.
-    if ((uint64_t)B * reduce_tiles(max_width, wide.slots) < RED_WIDE_TILES_PER_CU * (uint64_t)device_cus()) {
-        shape = reduce_tile_shape(max_width, capacity, P, false);
-        // twice the tiles need twice the table: not with a workspace sized for less
-        if (ws_bytes < reduce_ws_bytes_region(max_width, P, shape.slots) * B) shape = wide;
-    }
+    const ReduceShape shape = reduce_shape(B, max_width, capacity, P, (uint64_t)device_cus(), ws_bytes);
     const uint32_t slots = shape.slots;
     const size_t region_bytes = reduce_ws_bytes_region(max_width, P, slots);
     if (region_bytes > 0xffffffffull) return OKT_ERR_INVALID_ARG;
@@ -638,17 +767,15 @@ int reduce_launch(const uint32_t* d_idx_cat, const float* d_val_cat,
                            d_idx_out, d_val_out, capacity, d_nnz_out, d_dense, (char*)d_ws,
                            (uint32_t)region_bytes, table_offset);
     };
-    using W = ReduceWide;
-    using N = ReduceNarrow;
-    if (shape.wide) {
-        if (shape.kind == RED_DENSE) launch(reduce_tile_kernel<W::BLOCK, W::ROUNDS, W::C_DENSE, W::C_DENSE>, W::BLOCK);
-        else if (shape.kind == RED_RANKED) launch(reduce_tile_kernel<W::BLOCK, W::ROUNDS, W::C_RANKED, W::S_RANKED>, W::BLOCK);
-        else launch(reduce_tile_kernel<W::BLOCK, W::ROUNDS, W::C_SPARSE, W::S_SPARSE>, W::BLOCK);
-    } else {
-        if (shape.kind == RED_DENSE) launch(reduce_tile_kernel<N::BLOCK, N::ROUNDS, N::C_DENSE, N::C_DENSE>, N::BLOCK);
-        else if (shape.kind == RED_RANKED) launch(reduce_tile_kernel<N::BLOCK, N::ROUNDS, N::C_RANKED, N::S_RANKED>, N::BLOCK);
-        else launch(reduce_tile_kernel<N::BLOCK, N::ROUNDS, N::C_SPARSE, N::S_SPARSE>, N::BLOCK);
-    }
+    auto launch_form = [&](auto form) {
+        using F = decltype(form);
+        if (shape.kind == RED_DENSE) launch(reduce_tile_kernel<F::BLOCK, F::ROUNDS, F::C_DENSE, F::C_DENSE>, F::BLOCK);
+        else if (shape.kind == RED_RANKED) launch(reduce_tile_kernel<F::BLOCK, F::ROUNDS, F::C_RANKED, F::S_RANKED>, F::BLOCK);
+        else launch(reduce_tile_kernel<F::BLOCK, F::ROUNDS, F::C_SPARSE, F::S_SPARSE>, F::BLOCK);
+    };
+    if (shape.form == RED_WIDE5) launch_form(ReduceWide5{});
+    else if (shape.form == RED_WIDE4) launch_form(ReduceWide4{});
+    else launch_form(ReduceNarrow{});
     timing_after(s);
     return launch_status();
 }

@@ -2,6 +2,7 @@
 #ifndef OKT_SIZES_H
 #define OKT_SIZES_H
 
+#include <math.h>
 #include <stddef.h>
 #include <stdint.h>
 
@@ -179,65 +180,94 @@ inline size_t refresh_ws_bytes(uint64_t n) {
 // them, and the accumulators are indexed by rank, so the LDS holds hit slots only.
 // Very sparsely hit regions trade accumulators for bitmap.
 constexpr uint32_t RED_UNIT = 16;               // entries read by four lanes with one 16-byte load each
-// Two wide tiles to a CU (80 KB of LDS each), or four narrow ones.
-struct ReduceWide {
-    static constexpr int BLOCK = 512, ROUNDS = 4;   // ROUNDS: units per four threads that stay in registers
+// Three forms of tile: two wide tiles to a CU (80 KB of LDS each), whose threads hold
+// five units per four threads in registers (ROUNDS) or four, or four narrow ones.
+enum ReduceForm { RED_WIDE5, RED_WIDE4, RED_NARROW };
+struct ReduceWide5 {
+    static constexpr int BLOCK = 512, ROUNDS = 5;
+    static constexpr uint32_t C_DENSE = 9216, C_RANKED = 7968, S_RANKED = 65536, C_SPARSE = 7168, S_SPARSE = 98304;
+    static constexpr double FILL = 0.93;
+};
+struct ReduceWide4 {
+    static constexpr int BLOCK = 512, ROUNDS = 4;
     static constexpr uint32_t C_DENSE = 9216, C_RANKED = 8064, S_RANKED = 65536, C_SPARSE = 7168, S_SPARSE = 98304;
+    static constexpr double FILL = 0.93;
 };
 struct ReduceNarrow {
     static constexpr int BLOCK = 512, ROUNDS = 2;
     static constexpr uint32_t C_DENSE = 4096, C_RANKED = 3968, S_RANKED = 32768, C_SPARSE = 3584, S_SPARSE = 49152;
+    static constexpr double FILL = 0.9;
 };
 constexpr uint32_t RED_SLOTS_MIN = 4096;        // no tile is narrower
-// Launches with fewer tiles than this take the narrow form: more, shorter tiles.
+// Launches with fewer wide tiles than this take the narrow form: more, shorter tiles.
 constexpr uint64_t RED_WIDE_TILES_PER_CU = 2;
-// From this share of its slots hit on, a region is taken as densely hit: of a tile of
-// C_DENSE slots only that share of the accumulators is used, but one sweep does.
-// Measured over 8 to 256 contributions in batches: at 0.3 ranked tiles are ahead
-// (135 against 179 us), at 0.4 dense ones (168 against 147 us), and where
-// contributions collide (more entries per hit slot) dense ones from less on.
+// So do regions of at most RED_NARROW_TILES narrow tiles with at most RED_FEW
+// contributions: with four tiles to a CU one waits while three work, a tile that is hit
+// more than the rest holds up less, and long slices fill half as many units as well.
+// Over 800 batches of 2 to 32 contributions in 200 K to 800 K slots the narrow form is
+// 1.2 to 1.3 times as fast where they are hit evenly (8 contributions, a tenth of 400 K
+// slots hit: 62 against 78 us) and up to 1.6 times where most hits lie in a few layers.
+// In longer regions the entries' cost decides: 490 regions of 16 contributions, 67 narrow
+// tiles each, take 601 us narrow and 532 us wide; so do more contributions, whose slices
+// are shorter: 373 regions of 64, 831 and 690 us.
+constexpr uint32_t RED_FEW = 32, RED_NARROW_TILES = 48;
+// Wide tiles have a fifth round for entries that share slots and for stretches that are
+// hit somewhat more than the rest: batches of 8 contributions in 4 M slots, 30 % of their
+// entries among the same tenth, are 1.06 times as fast as with tiles that read every slice
+// twice, where four rounds are 0.77 times; 40 contributions that hit every other 12,500 of
+// 400 K slots 1.18 and 0.78 times.  From RED_MANY contributions on four rounds lose
+// nothing there, and their registers count: 373 regions of 64, 690 against 702 us.
+// A region is taken as densely hit where the ranked tile would be no wider than the
+// dense one.  With RED_MANY contributions it is from a lower share on, as more
+// entries than assumed share slots then: 48 regions of 256 contributions that hit 0.37
+// of the slots take 152 us dense and 177 us ranked.  With fewer the ranked tile is ahead
+// there: 93 regions of 40 contributions that hit 0.35 of 400 K slots, 70 against 100 us.
+constexpr uint32_t RED_MANY = 64;
 constexpr double RED_DENSE_FROM = 0.35;
 
 // Tile shape for a region `width` wide whose union is expected to hold at most
 // `expected` entries, from P contributions.  A tile is as wide - any multiple of
-// 32 slots - as keeps the expected number of hit slots at RED_FILL of the
-// accumulators, and the units the entries make (about one entry per hit slot, and
-// half a unit lost at the end of every slice) within what a chunk holds, unless
-// that would leave more than half the accumulators idle.
-constexpr double RED_FILL = 0.9, RED_FILL_UNITS = 0.95;
+// 32 slots - as keeps the expected number of hit slots at FILL of the
+// accumulators, and the units the entries make within what a chunk holds.  Its entries
+// are more than its hit slots: P contributions of one length that hit `share` of the
+// slots together, at random, hold 1 - (1 - share)^(1/P) of them each (1.8 entries a hit
+// slot for 8 at 0.7), and half a unit is lost at the end of every slice, which
+// is not minded where it is more than half of what the accumulators could hold.
+// The hits of even tiles vary by 1 to 2 %.  Narrow tiles cover less of the region, so
+// what differs between its parts averages out less: they have more room.
+constexpr double RED_FILL_UNITS = 0.98;
 enum ReduceKind { RED_DENSE = 0, RED_RANKED = 1, RED_SPARSE = 2 };
 struct ReduceShape {
     uint32_t slots;
     ReduceKind kind;
-    bool wide;
+    ReduceForm form;
 };
 template <typename Form>
-inline ReduceShape reduce_tile_shape_of(uint64_t width, uint64_t expected, uint32_t P, bool wide) {
+inline ReduceShape reduce_tile_shape_of(uint64_t width, uint64_t expected, uint32_t P, ReduceForm form) {
     if (width == 0 || expected == 0)
-        return expected == 0 && width > Form::C_DENSE ? ReduceShape{Form::S_SPARSE, RED_SPARSE, wide}
-                                                      : ReduceShape{Form::C_DENSE, RED_DENSE, wide};
-    const double units = RED_FILL_UNITS * (Form::BLOCK / 4 * Form::ROUNDS) - 0.5 * P;
+        return expected == 0 && width > Form::C_DENSE ? ReduceShape{Form::S_SPARSE, RED_SPARSE, form}
+                                                      : ReduceShape{Form::C_DENSE, RED_DENSE, form};
+    const double share = (double)expected < 0.999 * (double)width ? (double)expected / (double)width : 0.999;
+    const double per_slot = P * (1.0 - pow(1.0 - share, 1.0 / P)) / share;       // entries per hit slot
+    const double entries = (RED_FILL_UNITS * (Form::BLOCK / 4 * Form::ROUNDS) - 0.5 * P) * RED_UNIT;
     auto hits = [&](uint32_t c) {
-        const double most = RED_FILL * c;
-        return units * RED_UNIT < most && units * RED_UNIT > 0.5 * c ? units * RED_UNIT : most;
+        const double most = Form::FILL * c;
+        return entries > 0.5 * c && entries < most * per_slot ? entries / per_slot : most;
     };
     const double per_hit = (double)width / (double)expected;          // slots per hit
     const double want = per_hit * hits(Form::C_RANKED);
-    if ((double)expected >= RED_DENSE_FROM * (double)width) return ReduceShape{Form::C_DENSE, RED_DENSE, wide};
+    if (want <= Form::C_DENSE || (P >= RED_MANY && share >= RED_DENSE_FROM))
+        return ReduceShape{Form::C_DENSE, RED_DENSE, form};
     if (want > Form::S_RANKED) {
         const double sparse = per_hit * hits(Form::C_SPARSE);
-        if (sparse >= Form::S_SPARSE) return ReduceShape{Form::S_SPARSE, RED_SPARSE, wide};
+        if (sparse >= Form::S_SPARSE) return ReduceShape{Form::S_SPARSE, RED_SPARSE, form};
         const uint32_t slots = (uint32_t)sparse / 32 * 32;
         // narrower than the other shape's widest tile: that one holds more per tile
-        return slots > Form::S_RANKED ? ReduceShape{slots, RED_SPARSE, wide}
-                                      : ReduceShape{Form::S_RANKED, RED_RANKED, wide};
+        return slots > Form::S_RANKED ? ReduceShape{slots, RED_SPARSE, form}
+                                      : ReduceShape{Form::S_RANKED, RED_RANKED, form};
     }
     const uint32_t slots = (uint32_t)want / 32 * 32;
-    return ReduceShape{slots < RED_SLOTS_MIN ? RED_SLOTS_MIN : slots, RED_RANKED, wide};
-}
-inline ReduceShape reduce_tile_shape(uint64_t width, uint64_t expected, uint32_t P, bool wide) {
-    return wide ? reduce_tile_shape_of<ReduceWide>(width, expected, P, true)
-                : reduce_tile_shape_of<ReduceNarrow>(width, expected, P, false);
+    return ReduceShape{slots < RED_SLOTS_MIN ? RED_SLOTS_MIN : slots, RED_RANKED, form};
 }
 inline uint64_t reduce_tiles(uint64_t width, uint32_t slots) { return (width + slots - 1) / slots; }
 // per region: a 64-byte header, one descriptor per tile and one per 64 tiles,
@@ -247,6 +277,19 @@ inline size_t reduce_ws_bytes_region(uint64_t max_width, uint32_t P, uint32_t sl
     if (t == 0) t = 1;
     size_t bytes = 64 + 8 * (size_t)(t + (t + 63) / 64) + 4 * (size_t)(t + 1) * P;
     return (bytes + 63) & ~(size_t)63;
+}
+// The form a call takes, with a workspace of ws_bytes.
+inline ReduceShape reduce_shape(uint64_t B, uint64_t max_width, uint64_t expected, uint32_t P, uint64_t cus,
+                                size_t ws_bytes) {
+    const ReduceShape wide = P < RED_MANY
+        ? reduce_tile_shape_of<ReduceWide5>(max_width, expected, P, RED_WIDE5)
+        : reduce_tile_shape_of<ReduceWide4>(max_width, expected, P, RED_WIDE4);
+    const ReduceShape narrow = reduce_tile_shape_of<ReduceNarrow>(max_width, expected, P, RED_NARROW);
+    const bool fills = B * reduce_tiles(max_width, wide.slots) >= RED_WIDE_TILES_PER_CU * cus;
+    const bool small = P <= RED_FEW && reduce_tiles(max_width, narrow.slots) <= RED_NARROW_TILES;
+    // twice the tiles need twice the table: not with a workspace sized for less
+    if ((fills && !small) || ws_bytes < reduce_ws_bytes_region(max_width, P, narrow.slots) * B) return wide;
+    return narrow;
 }
 inline size_t reduce_ws_bytes(uint64_t B, uint64_t max_width, uint32_t P) {
     return (size_t)B * reduce_ws_bytes_region(max_width, P, RED_SLOTS_MIN);     // largest

@@ -3,7 +3,8 @@
 // three-pass select (scan state, counts, places, list, slots) is in order, does
 // not overlap, covers every tile, stays inside what okt_workspace_bytes-style
 // bounds promise for any device, and the second pass's shape (tiles per thread,
-// workgroups) covers all tiles within the limits its kernel assumes.  Prints the
+// workgroups) covers all tiles within the limits its kernel assumes; and for random
+// regions, that the reduce's tiles are ones its kernels hold and its workspace covers.  Prints the
 // number of cases and exits 0, or the first violations and exits 1.
 #include <cstdint>
 #include <cstdio>
@@ -57,6 +58,27 @@ int main() {
         if (one > select_ws_bytes(n)) fail("one-kernel scan state exceeds select_ws_bytes", n, cus);
         if ((uint64_t)s.nseg * SEL_WAVES * s.piece < n) fail("one-kernel pieces do not cover the vector", n, cus);
         if (s.piece > SEL_PIECE_MAX || s.piece % 256) fail("piece length", n, cus);
+    }
+    // the reduce: every tile shape is one its kernels hold, and fits the workspace it was chosen for
+    for (int rep = 0; rep < 200000; ++rep) {
+        const uint64_t width = rng() % 3 ? 1 + rng() % (1ull << (1 + rng() % 27)) : rng() % 0xffffffffull;
+        const uint64_t expected = rng() % 4 ? (uint64_t)((double)width * (rng() % 2000) / 1000.0) : rng() % (width + 2);
+        const uint32_t P = 1 + rng() % (1u << (1 + rng() % 16)), Pc = P > 65535 ? 65535 : P;
+        const uint64_t B = 1 + rng() % (1u << (rng() % 12));
+        const uint32_t cus = cu_counts[rng() % (sizeof(cu_counts) / sizeof(cu_counts[0]))];
+        ++cases;
+        for (const size_t ws : {reduce_ws_bytes(B, width, Pc), (size_t)0}) {
+            const ReduceShape s = reduce_shape(B, width, expected, Pc, cus, ws);
+            if (ws && ws < reduce_ws_bytes_region(width, Pc, s.slots) * B) fail("reduce workspace too small for its tiles", width, Pc);
+            if (!ws && s.form == RED_NARROW) fail("narrow tiles without the room", width, Pc);
+            const bool narrow = s.form == RED_NARROW;
+            const uint32_t dense = narrow ? ReduceNarrow::C_DENSE : ReduceWide5::C_DENSE;
+            const uint32_t ranked = narrow ? ReduceNarrow::S_RANKED : ReduceWide5::S_RANKED;
+            const uint32_t sparse = narrow ? ReduceNarrow::S_SPARSE : ReduceWide5::S_SPARSE;
+            if (s.kind == RED_DENSE && s.slots != dense) fail("dense tile", width, Pc);
+            if (s.kind == RED_RANKED && (s.slots > ranked || s.slots < RED_SLOTS_MIN || s.slots % 32)) fail("ranked tile", width, Pc);
+            if (s.kind == RED_SPARSE && (s.slots > sparse || s.slots <= ranked || s.slots % 32)) fail("sparse tile", width, Pc);
+        }
     }
     std::printf("%ld cases, %ld violations\n", cases, bad);
     return bad ? 1 : 0;

@@ -96,3 +96,83 @@ def test_wide_tiles_with_more_hits_than_they_have_room_for():
     regions[B - 1] = (5, 5 + width, [none, none, full[5:]])
     run_batch(regions, P, width, 4_000)
     run_batch(regions, P, width, width // 20)
+
+
+def clustered(rng, lo, width, blocks, per_block, length):
+    """`per_block` indices in each of some stretches of `length` indices: hit far more than the rest."""
+    parts = [some(rng, lo + int(at), length, per_block) for at in blocks]
+    return np.unique(np.concatenate(parts)).astype(np.uint32)
+
+
+@pytest.mark.parametrize("B,P,dense_part,share", [
+    # one stretch that is hit throughout: 1 window and just over, 2, many (narrow, then wide tiles)
+    (2, 1, 3_968, 0.05), (2, 1, 3_969, 0.05), (2, 3, 8_000, 0.05), (2, 8, 32_768, 0.05), (3, 40, 30_000, 0.02),
+    (60, 33, 7_968, 0.02), (60, 33, 8_000, 0.02), (60, 48, 60_000, 0.02), (60, 64, 8_065, 0.02), (60, 100, 65_536, 0.02),
+    # the ends of all windows of all slices do not fit in LDS: searched in turn
+    (2, 300, 32_768, 0.02), (40, 512, 65_536, 0.02),
+    # more contributions than threads: every window reads all entries
+    (2, 513, 32_768, 0.02)])
+def test_windows_of_a_tile(B, P, dense_part, share):
+    """Tiles planned for a region hit evenly, with a stretch that is hit throughout: by
+    one contribution, by several that share it, by pieces of all."""
+    rng = np.random.default_rng(P + dense_part)
+    width = 700_001
+    regions = []
+    for b in range(B):
+        lo = b * 3_001
+        whole = np.arange(dense_part, dtype=np.uint32) + np.uint32(lo + 100_000 + 17 * b)
+        ps = [np.unique(np.concatenate([whole[p::max(1, P // 3)] if P > 1 else whole,
+                                        some(rng, lo, width, 40)])).astype(np.uint32) for p in range(P)]
+        regions.append((lo, lo + width, ps if b in (0, 1, B - 1) else [p[:2] for p in ps]))
+    run_batch(regions, P, width, int(share * width) + B, lead=B % 4)
+    run_batch(regions[:2], P, width, 5_000)                 # output cut short, inside a window
+    run_batch(regions[:1], P, width, width)                 # planned for a densely hit region
+
+
+@pytest.mark.parametrize("P,units", [(1, 256), (1, 257), (2, 300), (8, 512), (8, 513), (8, 700), (16, 256), (31, 400),
+                                     (32, 1_100), (33, 640), (40, 641), (64, 512), (65, 513), (128, 1_400)])
+@pytest.mark.parametrize("B", [1, 36])
+def test_entries_beyond_a_chunk(B, P, units):
+    """Contributions that hit the same slots: about `units` pieces of 16 entries to a tile,
+    around one and two chunks of each form, and fewer hit slots than accumulators."""
+    rng = np.random.default_rng(P * 31 + units)
+    width = 900_001
+    per = max(1, units // P) * 16
+    regions = []
+    for b in range(B):
+        lo = 11 * b
+        common = some(rng, lo, 30_000, min(3_900, per + 100))
+        ps = [np.sort(rng.choice(common, min(per - (p % 3) * (per > 16), common.size), replace=False)).astype(np.uint32)
+              for p in range(P)]
+        regions.append((lo, lo + width, ps if b in (0, B - 1) else [p[:1] for p in ps]))
+    run_batch(regions, P, width, 60_000 if B == 1 else 120_000, lead=P % 4)
+
+
+@pytest.mark.parametrize("P", [1, 8, 32, 33, 64, 600])
+def test_windows_with_the_dense_copy(P):
+    """The dense region of a tile that is written in windows: every hit slot's sum, zeros elsewhere."""
+    rng = np.random.default_rng(P)
+    lo, width = 1_000, 300_007
+    ps = [clustered(rng, lo, width, (0, 120_000, width - 9_000), max(1, 9_000 // P) if P > 1 else 9_000, 9_000)
+          for _ in range(P)]
+    ps[0] = np.unique(np.concatenate([ps[0], np.arange(lo + 120_000, lo + 129_000)])).astype(np.uint32)
+    idx = np.concatenate(ps)
+    val = (rng.integers(-2048, 2048, idx.size) * 2.0 ** -12).astype(np.float32)
+    off = np.concatenate([[0], np.cumsum([p.size for p in ps])]).astype(np.uint64)
+    ref = orc.sparse_reduce(idx, val, off, lo, lo + width)
+    U = ref["idx"].size
+    cap = U + 3
+    o_idx = torch.zeros(cap, dtype=torch.int32, device=DEV)
+    o_val, dense = torch.zeros(cap, device=DEV), torch.full((width,), 7.0, device=DEV)
+    nnz = torch.zeros(2, dtype=torch.int64, device=DEV)
+    ws = torch.empty(okt.okt_sparse_reduce_batch_workspace_bytes(1, P, width), dtype=torch.uint8, device=DEV)
+    okt.okt_sparse_reduce(dev(idx), dev(val), dev(off), lo, lo + width, o_idx, o_val, nnz, ws,
+                          dense_out=dense, capacity=cap)
+    torch.cuda.synchronize()
+    assert nnz.tolist() == [U, U]
+    assert np.array_equal(o_idx.cpu().numpy().view(np.uint32)[:U], ref["idx"])
+    want = ref["val"].astype(np.float32)
+    assert np.array_equal(o_val.cpu().numpy()[:U], want)
+    full = np.zeros(width, np.float32)
+    full[ref["idx"].astype(np.int64) - lo] = want
+    assert np.array_equal(dense.cpu().numpy(), full)
