@@ -25,16 +25,18 @@ periods instead (there the step starts from a residual brought to its steady sta
 beforehand, see steady_state()).  All inputs are seeded, synthetic and resident
 in HBM before the timed region starts.
 
-Prints ONE JSON line (see the driver's contract) with
+Prints ONE JSON line, short enough for a reader that keeps only the end of the output,
+and writes everything measured to bench_detail.json beside this file.  In the line:
   roofline      the dominant kernel of the step, timed with HIP events inside the
                 timed region
   cpu_baseline  the numpy oracle on the same workload, on the host cores
   per_config    for cfg1 .. cfg5: every call of the path timed on its own at that
                 configuration's size (select + compact, the fused calls, the exact
-                threshold, the lone reduce) with algorithmic bytes and fraction of
-                the HBM peak, and the batched reduce (> 1 GB of regions of that
-                configuration's shape in one launch)
-  reduce_batch  the batched-reduce rows of per_config side by side
+                threshold, the lone reduce): the median of the call and of its main
+                kernel and the fraction of the HBM peak; and the batched reduce (> 1 GB
+                of regions of that configuration's shape in one launch)
+and in the file also the spread, the algorithmic bytes, the plain copy, sum and gather of
+the same data, and the calls of the global stage.
 """
 from __future__ import annotations
 
@@ -484,7 +486,7 @@ NON_TEMPORAL_FROM = 64 << 20
 
 # the kernel that moves the data in each call
 MAIN_KERNEL = {"accumulate": "accumulate_kernel", "threshold": "collect_kernel",
-               "threshold_full_vector": "resolve_kernel (no main kernel is bracketed)", "select": "select_kernel",
+               "threshold_full_vector": "digit_kernel (three launches, none bracketed)", "select": "select_kernel",
                "select_copy": "select_kernel<DenseCopySource>",
                "accumulate_select": "accumulate_select_kernel",
                "accumulate_topk_select": "accumulate_collect_kernel", "partition": "partition_kernel",
@@ -548,6 +550,44 @@ def read_traffic(workload, call):
     return None
 
 
+LINE_MAX = 8000                # characters: a reader that keeps the end of the output gets all of it
+
+
+def result_line(out):
+    """The result as one line of at most LINE_MAX characters: the headline whole, of the
+    rest each call's medians and fraction of the HBM peak.  A block that would not
+    fit is left out and named in `left_out`."""
+    def us(stat):
+        return stat.get("us_median") if isinstance(stat, dict) else None
+
+    def short(block):
+        res = {}
+        for name, row in block.get("kernels", {}).items():
+            res[name] = {"us": us(row["us_per_call"])}
+            if "frac_of_hbm_peak" in row["us_per_call"]:
+                res[name]["frac"] = row["us_per_call"]["frac_of_hbm_peak"]
+            if us(row.get("us_main_kernel")) is not None:
+                res[name]["main_us"] = us(row["us_main_kernel"])
+        if "reduce_batch" in block:
+            res["reduce_batch"] = {"us": block["reduce_batch"]["us_per_launch"],
+                                   "frac": block["reduce_batch"]["frac_of_hbm_peak"]}
+        if us(block.get("reduce", {}).get("us_per_call")) is not None:
+            res["reduce"] = {"us": us(block["reduce"]["us_per_call"])}
+        return res
+
+    line = {key: v for key, v in out.items() if key not in ("per_config", "reduce_batch")}
+    line["per_config"] = {name: short(b) for name, b in out.get("per_config", {}).items()}
+    left_out = []
+    for key in ("kernels", "overlapped_path", "separate_calls_path", "sanity", "per_config", "cpu_baseline",
+                "roofline", None):
+        text = json.dumps({**line, "left_out": left_out} if left_out else line)
+        if len(text) <= LINE_MAX or key is None:
+            return text
+        if key in line:
+            del line[key]
+            left_out.append(key)
+
+
 # ----------------------------------------------------------------------------
 # every call on its own, at one configuration's size
 # ----------------------------------------------------------------------------
@@ -563,6 +603,10 @@ def measure_calls(args, torch, np, okt, wl, ev, cfg):
     reps = 12
     slots = [torch.empty(n, dtype=torch.float32, device=DEV) for _ in range(nslots)]
     G = len(cfg.grads)
+    # a slot has a gradient of its own too: one that the round before has read is partly
+    # in the last-level cache, which a training step's new gradient is not
+    refresh_grads = [cfg.grads[0].clone() for _ in range(nslots)]
+    reuse_grads = [cfg.grads[1].clone() for _ in range(nslots)] if G > 1 else []
 
     # states: start (before a refresh iteration), acc0 (accumulated, not yet selected),
     # res1 (after the refresh iteration: what the first reuse iteration starts from)
@@ -591,7 +635,7 @@ def measure_calls(args, torch, np, okt, wl, ev, cfg):
         return lambda s: slots[s].copy_(src)
 
     calls = {
-        "accumulate": (lambda s: okt.okt_residual_accumulate(cfg.grads[s % G], slots[s], w.lr),
+        "accumulate": (lambda s: okt.okt_residual_accumulate(refresh_grads[s], slots[s], w.lr),
                        from_(cfg.start), 12.0 * n),
         "threshold": (lambda s: okt.okt_topk_threshold_exact(slots[s], k, cfg.th, cfg.count_ge, cfg.ws),
                       from_(acc0), 4.0 * n),
@@ -602,7 +646,7 @@ def measure_calls(args, torch, np, okt, wl, ev, cfg):
                                                                 cfg.ws, capacity=cfg.cap),
                         from_(acc0), 4.0 * n + 8.0 * nnz0),
         "accumulate_topk_select": (lambda s: okt.okt_accumulate_topk_select(
-            cfg.grads[0], slots[s], w.lr, k, cfg.th, cfg.count_ge, cfg.idx, cfg.val, cfg.nnz, cfg.ws,
+            refresh_grads[s], slots[s], w.lr, k, cfg.th, cfg.count_ge, cfg.idx, cfg.val, cfg.nnz, cfg.ws,
             capacity=cfg.cap), from_(cfg.start), 12.0 * n + 12.0 * nnz0),
     }
     # the exact threshold without its sample: with a workspace that has no room for
@@ -613,7 +657,7 @@ def measure_calls(args, torch, np, okt, wl, ev, cfg):
                                       from_(acc0), 12.0 * n)
     if G > 1:
         calls["accumulate_select"] = (lambda s: okt.okt_accumulate_select(
-            cfg.grads[1], slots[s], w.lr, th0, cfg.idx, cfg.val, cfg.nnz, cfg.ws, capacity=cfg.cap),
+            reuse_grads[s], slots[s], w.lr, th0, cfg.idx, cfg.val, cfg.nnz, cfg.ws, capacity=cfg.cap),
             from_(res1), 12.0 * n + 8.0 * nnz1)
     out = {"n": n, "k": k, "selected_refresh_iteration": nnz0, "selected_reuse_iteration": nnz1,
            "slots": nslots,
@@ -641,7 +685,7 @@ def measure_calls(args, torch, np, okt, wl, ev, cfg):
         out["max_abs_drift"] = round(max(abs(v - k) / k for v in drift), 4)
     # restore the selection of the refresh iteration for what follows
     cfg.th.copy_(th0)
-    del slots, acc0
+    del slots, acc0, refresh_grads, reuse_grads
     out["_res1"] = res1
     return out
 
@@ -745,11 +789,12 @@ def time_reduce_batch(args, torch, np, okt, wl, w, width):
         gtimes.append(a.elapsed_time(b) * 1e3)
     gus = float(np.median(gtimes[2:]))
     gbytes = 8.0 * B * E1 + 8.0 * B * gcap
-    gather = {"what": "okt_stream_gather: same tiles, same slice table, every entry read once and as "
-                      "many written as the union holds, no arithmetic", "us_per_launch": round(gus, 1), "bytes": gbytes,
+    gather = {"what": "okt_stream_gather: same tiles, same slice table, every slice read once by the wave it "
+                      "falls to and as many entries written as the union holds, no arithmetic; a plain "
+                      "gather, not a bound: the reduce reads in other units and may be faster", "us_per_launch": round(gus, 1), "bytes": gbytes,
               "GBs": round(gbytes / gus * 1e-3, 1), "frac_of_hbm_peak": round(gbytes / gus * 1e-3 / HBM_PEAK_GBS, 4)}
     log(f"[bench] {w.name} reduce batch: {us:9.1f} us = {nbytes / us * 1e-3 / HBM_PEAK_GBS * 100:5.1f} % of peak; "
-        f"gather ceiling {gus:9.1f} us = {gbytes / gus * 1e-3 / HBM_PEAK_GBS * 100:5.1f} % of peak")
+        f"plain gather {gus:9.1f} us = {gbytes / gus * 1e-3 / HBM_PEAK_GBS * 100:5.1f} % of peak")
     return {"gather_ceiling": gather, "frac_of_gather_ceiling": round((nbytes / us) / (gbytes / gus), 4),
             "shape": f"P={P}, {m} entries per contribution, region width {width}", "regions": B,
             "entries_in": B * E1, "union_out": U, "us_per_launch": round(us, 1),
@@ -972,7 +1017,14 @@ def main():
         log(f"[bench] per_config {name} done ({time.time() - t0:.1f}s)")
     out["per_config"] = blocks
     out["reduce_batch"] = {name: b["reduce_batch"] for name, b in blocks.items() if "reduce_batch" in b}
-    print(json.dumps(out), flush=True)
+    detail = os.path.join(ROOT, "bench_detail.json")
+    try:
+        with open(detail, "w") as fh:
+            json.dump(out, fh, indent=1)
+        log(f"[bench] everything measured: {detail}")
+    except OSError as e:
+        log(f"[bench] {detail} not written: {e}")
+    print(result_line(out), flush=True)
 
 
 if __name__ == "__main__":

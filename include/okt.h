@@ -117,9 +117,9 @@ uint64_t okt_slot_min_n(int accumulating);
  * family, okt_accumulate_select, the pass of okt_accumulate_topk_select that
  * forms the accumulator, okt_region_partition, the tile kernel of the reduce
  * family, the collect pass of okt_topk_threshold_exact (not recorded when that
- * call makes none: up to two million elements, a large k, a small workspace), the
- * intersect kernel.  The pair is used once and forgotten; a call that launches no such kernel (an argument error, an
- * empty input) leaves it armed for the next one.  For benchmarks: so that an
+ * call makes none: up to 65,536 elements, a large k, a small workspace), the
+ * intersect kernel.  The pair is used once and forgotten; a call that launches no
+ * such kernel (an argument error, an empty input) leaves it armed for the next one.  For benchmarks: so that an
  * event time can be compared with a profiler's kernel duration.
  */
 void okt_time_next_kernel(void* start_event, void* stop_event);

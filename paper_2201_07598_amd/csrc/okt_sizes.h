@@ -121,8 +121,9 @@ inline size_t slot_ws_bytes(uint64_t n) { return slot_plan(n, 256).bytes; }
 // microseconds cost more than the leaner streaming pass saves there.  Measured
 // crossover: the calls that form the accumulator on the way (12 bytes an element: the
 // saving is three times the select's) gain from about 24 M elements on (accumulate and
-// select, layered, 2 %: 20 M 47 against 50 us, 27 M 73 against 72, 40 M 115 against 104),
-// the plain selects from about 100 M, where the vector no longer fits the last-level
+// select, layered, 2 %, a gradient that is handed in again and lies partly in the
+// last-level cache: 20 M 47 against 50 us, 27 M 73 against 72, 40 M 115 against 104; one
+// that comes from memory: 25.6 M 65.2 against 61.7), the plain selects from about 100 M, where the vector no longer fits the last-level
 // cache.
 constexpr uint64_t SLOT_MIN_N_SELECT = 96u << 20;
 constexpr uint64_t SLOT_MIN_N_ACCUMULATE = 24u << 20;

@@ -574,7 +574,7 @@ __device__ __forceinline__ void slot_finish_body(float* __restrict__ acc, uint32
     };
 
     // ---- where this workgroup's part begins and ends ----
-    const uint32_t chunk = ((ntiles + BLOCK - 1) / BLOCK + 7) / 8 * 8;       // tiles of a thread, at most 512
+    const uint32_t chunk = ((ntiles + BLOCK - 1) / BLOCK + 7) / 8 * 8;       // tiles of a thread, at most 128
     const uint32_t first = tid * chunk;
     uint32_t mine = 0;
     constexpr uint32_t FLIGHT = 8;                         // loads in flight

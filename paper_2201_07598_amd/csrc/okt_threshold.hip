@@ -39,6 +39,7 @@ namespace okt {
 
 constexpr int PHASES_MAX = 4;      // digits of resolve_kernel: one from a bound and three general ones at most
 constexpr int BOUNDS = 16;         // workgroups of the sample
+static_assert(SLOT_BOUNDS == BOUNDS, "the slots' first pass reads every bound");
 constexpr uint32_t HIST_WORDS = 4 * RS_MAX_BINS;
 
 struct RadixState {
