@@ -47,8 +47,8 @@ __device__ __forceinline__ RegionView region_view(const uint32_t* lo_hi, uint32_
 // Every search starts from a guess, which makes it two or three waits and lines of
 // memory instead of a bisection's fifteen: 35 boundaries x 16 contributions x 490
 // regions in 33 us against 49 with a gallop of single probes from the same guess, 102
-// against 129 us for 55 x 64 x 373; a lone region (317 x 32), reduced in 26.1 us
-// instead of 26.9 with plain bisections.
+// against 129 us for 55 x 64 x 373; a lone region (317 x 32) takes as long as with
+// plain bisections.
 __global__ __launch_bounds__(256) void reduce_slices_kernel(
     const uint32_t* __restrict__ idx_cat, const uint64_t* __restrict__ seg_begin,
     const uint64_t* __restrict__ seg_end, uint32_t seg_stride,
@@ -728,11 +728,12 @@ int reduce_launch(const uint32_t* d_idx_cat, const float* d_val_cat,
         !aligned(d_dense, 4) || !aligned(d_lo_hi, 4))
         return OKT_ERR_INVALID_ARG;
     // the caller's bound on the size of the union doubles as the density estimate
+    const size_t least = reduce_ws_bytes_region(max_width, P, reduce_least_shape(max_width, capacity, P).slots);
+    if (least > 0xffffffffull) return OKT_ERR_INVALID_ARG;
+    if (!d_ws || !aligned(d_ws, 256) || ws_bytes < least * B) return OKT_ERR_WORKSPACE;
     const ReduceShape shape = reduce_shape(B, max_width, capacity, P, (uint64_t)device_cus(), ws_bytes);
     const uint32_t slots = shape.slots;
     const size_t region_bytes = reduce_ws_bytes_region(max_width, P, slots);
-    if (region_bytes > 0xffffffffull) return OKT_ERR_INVALID_ARG;
-    if (!d_ws || !aligned(d_ws, 256) || ws_bytes < region_bytes * B) return OKT_ERR_WORKSPACE;
     uint64_t tiles = reduce_tiles(max_width, slots);
     if (tiles == 0) tiles = 1;
     const uint32_t table_offset = (uint32_t)(64 + 8 * (tiles + (tiles + 63) / 64));

@@ -279,18 +279,39 @@ inline size_t reduce_ws_bytes_region(uint64_t max_width, uint32_t P, uint32_t sl
     size_t bytes = 64 + 8 * (size_t)(t + (t + 63) / 64) + 4 * (size_t)(t + 1) * P;
     return (bytes + 63) & ~(size_t)63;
 }
-// The form a call takes, with a workspace of ws_bytes.
+// The least a call asks of its workspace: the table of wide tiles as a region would have
+// them that is hit evenly by entries that share no slots.  Such tiles are correct for any
+// input, and are taken where the workspace has no room for more.
+inline ReduceShape reduce_least_shape(uint64_t width, uint64_t expected, uint32_t P) {
+    using Form = ReduceWide4;
+    if (width == 0 || expected == 0) return reduce_tile_shape_of<Form>(width, expected, P, RED_WIDE4);
+    const double per_hit = (double)width / (double)expected;
+    const double entries = (0.95 * (Form::BLOCK / 4 * Form::ROUNDS) - 0.5 * P) * RED_UNIT;
+    auto slots = [&](uint32_t c) { return per_hit * (entries < 0.9 * c && entries > 0.5 * c ? entries : 0.9 * c); };
+    if ((double)expected >= RED_DENSE_FROM * (double)width) return ReduceShape{Form::C_DENSE, RED_DENSE, RED_WIDE4};
+    double want = slots(Form::C_RANKED);
+    if (want <= Form::S_RANKED)
+        return ReduceShape{want < RED_SLOTS_MIN ? RED_SLOTS_MIN : (uint32_t)want / 32 * 32, RED_RANKED, RED_WIDE4};
+    want = slots(Form::C_SPARSE);
+    if (want >= Form::S_SPARSE) return ReduceShape{Form::S_SPARSE, RED_SPARSE, RED_WIDE4};
+    return want >= Form::S_RANKED + 32 ? ReduceShape{(uint32_t)want / 32 * 32, RED_SPARSE, RED_WIDE4}
+                                       : ReduceShape{Form::S_RANKED, RED_RANKED, RED_WIDE4};
+}
+// The shape a call takes with a workspace of ws_bytes, at least what the least shape needs.
 inline ReduceShape reduce_shape(uint64_t B, uint64_t max_width, uint64_t expected, uint32_t P, uint64_t cus,
                                 size_t ws_bytes) {
+    auto fits = [&](const ReduceShape& s) {
+        const size_t region = reduce_ws_bytes_region(max_width, P, s.slots);
+        return region <= 0xffffffffull && ws_bytes >= region * B;
+    };
     const ReduceShape wide = P < RED_MANY
         ? reduce_tile_shape_of<ReduceWide5>(max_width, expected, P, RED_WIDE5)
         : reduce_tile_shape_of<ReduceWide4>(max_width, expected, P, RED_WIDE4);
     const ReduceShape narrow = reduce_tile_shape_of<ReduceNarrow>(max_width, expected, P, RED_NARROW);
     const bool fills = B * reduce_tiles(max_width, wide.slots) >= RED_WIDE_TILES_PER_CU * cus;
     const bool small = P <= RED_FEW && reduce_tiles(max_width, narrow.slots) <= RED_NARROW_TILES;
-    // twice the tiles need twice the table: not with a workspace sized for less
-    if ((fills && !small) || ws_bytes < reduce_ws_bytes_region(max_width, P, narrow.slots) * B) return wide;
-    return narrow;
+    if ((!fills || small) && fits(narrow)) return narrow;
+    return fits(wide) ? wide : reduce_least_shape(max_width, expected, P);
 }
 inline size_t reduce_ws_bytes(uint64_t B, uint64_t max_width, uint32_t P) {
     return (size_t)B * reduce_ws_bytes_region(max_width, P, RED_SLOTS_MIN);     // largest

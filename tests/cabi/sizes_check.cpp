@@ -67,10 +67,14 @@ int main() {
         const uint64_t B = 1 + rng() % (1u << (rng() % 12));
         const uint32_t cus = cu_counts[rng() % (sizeof(cu_counts) / sizeof(cu_counts[0]))];
         ++cases;
-        for (const size_t ws : {reduce_ws_bytes(B, width, Pc), (size_t)0}) {
+        const size_t told = reduce_ws_bytes(B, width, Pc);
+        const size_t least = reduce_ws_bytes_region(width, Pc, reduce_least_shape(width, expected, Pc).slots);
+        if (least > 0xffffffffull) continue;                       // refused
+        if (least * B > told) fail("a call asks for more than its callers are told", width, Pc);
+        for (const size_t ws : {told, (least * B + told) / 2, least * B}) {
             const ReduceShape s = reduce_shape(B, width, expected, Pc, cus, ws);
-            if (ws && ws < reduce_ws_bytes_region(width, Pc, s.slots) * B) fail("reduce workspace too small for its tiles", width, Pc);
-            if (!ws && s.form == RED_NARROW) fail("narrow tiles without the room", width, Pc);
+            const size_t region = reduce_ws_bytes_region(width, Pc, s.slots);
+            if (ws < region * B || region > 0xffffffffull) fail("reduce workspace too small for its tiles", width, Pc);
             const bool narrow = s.form == RED_NARROW;
             const uint32_t dense = narrow ? ReduceNarrow::C_DENSE : ReduceWide5::C_DENSE;
             const uint32_t ranked = narrow ? ReduceNarrow::S_RANKED : ReduceWide5::S_RANKED;

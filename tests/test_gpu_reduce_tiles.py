@@ -21,7 +21,7 @@ def dev(a):
     return torch.from_numpy(np.ascontiguousarray(a).view(view) if view else a).to(DEV)
 
 
-def run_batch(regions, P, width, capacity, lead=0):
+def run_batch(regions, P, width, capacity, lead=0, ws_share=1.0):
     """regions: list of (lo, hi, [P index arrays]); checks every region against the oracle."""
     B = len(regions)
     parts = [p for _, _, ps in regions for p in ps]
@@ -41,7 +41,8 @@ def run_batch(regions, P, width, capacity, lead=0):
     o_idx = torch.full((B * max(capacity, 1),), -1, dtype=torch.int32, device=DEV)
     o_val = torch.zeros(B * max(capacity, 1), device=DEV)
     nnz = torch.zeros(2 * B, dtype=torch.int64, device=DEV)
-    ws = torch.empty(okt.okt_sparse_reduce_batch_workspace_bytes(B, P, width), dtype=torch.uint8, device=DEV)
+    told = okt.okt_sparse_reduce_batch_workspace_bytes(B, P, width)
+    ws = torch.empty(int(ws_share * told), dtype=torch.uint8, device=DEV)
     okt.okt_sparse_reduce_batch(d_idx, d_val, dev(off.reshape(-1)), lo_hi, B, P, width, o_idx, o_val,
                                 capacity, nnz, ws)
     torch.cuda.synchronize()
@@ -176,3 +177,18 @@ def test_windows_with_the_dense_copy(P):
     full = np.zeros(width, np.float32)
     full[ref["idx"].astype(np.int64) - lo] = want
     assert np.array_equal(dense.cpu().numpy(), full)
+
+
+@pytest.mark.parametrize("P,share,least", [(2, 0.05, 0.09), (8, 0.1, 0.0835), (8, 0.7, 0.46), (33, 0.2, 0.125), (64, 0.05, 0.056)])
+@pytest.mark.parametrize("B", [1, 40])
+def test_less_workspace_than_told(B, P, share, least):
+    """From the table of the tiles of a region hit evenly on, any workspace does: the
+    same results, whatever tiles it has room for.  Below it the call is refused."""
+    rng = np.random.default_rng(P)
+    width = 700_001
+    regions = [(b * 13, b * 13 + width, [some(rng, b * 13, width, 2_000 if b in (0, B - 1) else 3) for _ in range(P)])
+               for b in range(B)]
+    for ws_share in (1.0, 0.5, least):
+        run_batch(regions, P, width, int(share * width), ws_share=ws_share)
+    with pytest.raises(okt.OktError):
+        run_batch(regions, P, width, int(share * width), ws_share=0.5 * least)
