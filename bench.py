@@ -795,7 +795,7 @@ def time_reduce_batch(args, torch, np, okt, wl, w, width):
               "GBs": round(gbytes / gus * 1e-3, 1), "frac_of_hbm_peak": round(gbytes / gus * 1e-3 / HBM_PEAK_GBS, 4)}
     log(f"[bench] {w.name} reduce batch: {us:9.1f} us = {nbytes / us * 1e-3 / HBM_PEAK_GBS * 100:5.1f} % of peak; "
         f"plain gather {gus:9.1f} us = {gbytes / gus * 1e-3 / HBM_PEAK_GBS * 100:5.1f} % of peak")
-    return {"gather_ceiling": gather, "frac_of_gather_ceiling": round((nbytes / us) / (gbytes / gus), 4),
+    return {"plain_gather": gather, "plain_gather_over_reduce": round((nbytes / us) / (gbytes / gus), 4),
             "shape": f"P={P}, {m} entries per contribution, region width {width}", "regions": B,
             "entries_in": B * E1, "union_out": U, "us_per_launch": round(us, 1),
             "us_min": round(float(np.min(times[2:])), 1),

@@ -297,9 +297,10 @@ int okt_accumulate_select(const float* d_grad, float* d_residual_inout, float lr
  * element above a bound read off a sample; the exact selection and the final
  * select then run over those candidates (a few percent of the vector), and only
  * the emitted entries are zeroed in the residual with scattered stores: 12 B per
- * element instead of 20, three launches (five for a long vector).  A shorter vector, a smaller workspace (the minimum is
- * what the three calls need), or a sample that misled take the three steps over
- * the whole vector: the results are the same.
+ * element instead of 20, three launches (four for a long vector, five above 134 million
+ * elements).  A shorter vector, a smaller workspace (the minimum is what the three calls
+ * need), or a sample that misled take the three steps over the whole vector: the
+ * results are the same.
  */
 int okt_accumulate_topk_select(const float* d_grad, float* d_residual_inout, float lr, uint64_t n,
                                uint64_t k, float* d_threshold_out, uint64_t* d_count_ge_out,
