@@ -208,10 +208,9 @@ struct __attribute__((packed, aligned(4))) Quad32 { uint32_t v[4]; };   // four 
 // limits the tiles in flight.  490 regions of 16 contributions (1.9 GB in and out):
 // 575 us with slices read in blocks of 64 entries, twice, by 8-wave workgroups of
 // half this size, 519 us as it is here; 373 regions of 64 contributions: 734 and 599 us,
-// the longer slices of the wider tile counting for
-// as much as the rest.  The narrow form is held to 64 registers, for
-// four tiles to a CU: 16 contributions, a tenth of 400 K slots hit, 380 regions, 65 us
-// against 84 with slices read twice and 78 in wide tiles.
+// the longer slices of the wider tile counting for as much as the rest.  The narrow form
+// is held to 64 registers, for four tiles to a CU: 16 contributions, a tenth of 400 K slots
+// hit, 380 regions, 65 us against 84 with slices read twice and 78 in wide tiles.
 // Tried and not kept: 16 waves with 8 entries a thread and the same tile (spills at
 // 64 registers), several regions' tiles in turn per workgroup with the next slice table
 // fetched ahead (what it hides, its registers and the extra barriers cost), tiles of

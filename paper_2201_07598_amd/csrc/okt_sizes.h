@@ -205,9 +205,9 @@ constexpr uint64_t RED_WIDE_TILES_PER_CU = 2;
 // So do regions of at most RED_NARROW_TILES narrow tiles with at most RED_FEW
 // contributions: with four tiles to a CU one waits while three work, a tile that is hit
 // more than the rest holds up less, and long slices fill half as many units as well.
-// Over 800 batches of 2 to 32 contributions in 200 K to 800 K slots the narrow form is
-// 1.2 to 1.3 times as fast where they are hit evenly (8 contributions, a tenth of 400 K
-// slots hit: 62 against 78 us) and up to 1.6 times where most hits lie in a few layers.
+// In batches of 16 M entries, 2 to 32 contributions in 200 K to 800 K slots, the narrow form
+// is 1.2 to 1.3 times as fast where they are hit evenly (8 contributions, a tenth of 400 K
+// slots hit: 61 against 76 us) and up to 1.5 times where most hits lie in a few layers.
 // In longer regions the entries' cost decides: 490 regions of 16 contributions, 67 narrow
 // tiles each, take 601 us narrow and 532 us wide; so do more contributions, whose slices
 // are shorter: 373 regions of 64, 831 and 690 us.
