@@ -26,6 +26,9 @@ __device__ __forceinline__ uint32_t uniform(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
 }
 
+// Four words at any word address, read together.
+struct __attribute__((packed, aligned(4))) QuadAt4 { uint32_t v[4]; };
+
 // Sum over the 64 lanes of a wave; every lane gets the result.
 __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
 #pragma unroll

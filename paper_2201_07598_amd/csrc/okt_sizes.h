@@ -129,17 +129,27 @@ constexpr uint64_t SLOT_MIN_N_SELECT = 96u << 20;
 constexpr uint64_t SLOT_MIN_N_ACCUMULATE = 24u << 20;
 
 // ---- index intersection and residual restore ----
-constexpr int RST_BLOCK = 256;
-constexpr int RST_ROWS = 4;                              // entries per thread
+constexpr int RST_BLOCK = 1024, RST_WAVES = RST_BLOCK / 64;
+constexpr int RST_ROWS = 1;                              // entries per thread
 constexpr uint32_t RST_TILE = RST_BLOCK * RST_ROWS;      // local entries per workgroup
-constexpr uint32_t RST_WINDOW = 4096;                    // global entries a workgroup stages in LDS
+constexpr uint32_t RST_SAMPLES = 1024;                   // places of the global list that say where a tile's part of it lies
+constexpr uint32_t RST_WINDOW = 4096;                    // elements of that part that a workgroup holds at a time
+constexpr uint32_t RST_BETWEEN = 16;                     // elements between two of a longer part's that are read and compared
+constexpr uint32_t RST_TABLE_BITS = 13, RST_TABLE = 1u << RST_TABLE_BITS;   // hash table of a tile's entries
+constexpr uint32_t RST_DIRECT_TILES = 4096;              // up to here every workgroup adds up the counts before its tile
+constexpr int RST_SCAN_BLOCK = 1024;
+constexpr uint32_t RST_PER_CU = 2;                        // workgroups of a launch
 inline uint64_t restore_tiles(uint64_t max_local) {
     return max_local == 0 ? 1 : (max_local + RST_TILE - 1) / RST_TILE;
 }
+// What a call asks for, more than a count per tile and one for all of them.
 inline size_t restore_ws_bytes(uint64_t max_local) {
     const uint64_t t = restore_tiles(max_local);
     return 64 + 8 * (size_t)(t + (t + 63) / 64);
 }
+// Where a bit per entry goes behind the counts, in a workspace that has room for them
+// (okt_workspace_bytes always does: about two bytes an entry).
+inline size_t restore_masks_at(uint64_t max_local) { return (4 * (size_t)(restore_tiles(max_local) + 1) + 63) / 64 * 64; }
 
 // ---- exact threshold (radix select over the 31-bit magnitude key) ----
 constexpr int RS_BITS1 = 11, RS_BITS2 = 11, RS_BITS3 = 9;   // 11 + 11 + 9 = 31

@@ -1,0 +1,91 @@
+"""The global stage's calls on short lists, at the lengths where their kernels change
+form: the intersection with a global list that is searched in one, two or more steps, with and
+without room for the first launch's bits.  Everything is bit-exact.
+"""
+import numpy as np
+import pytest
+import torch
+
+import paper_2201_07598_amd as okt
+from oracle import okt_oracle as orc
+from tests.okt_harness import DEV, bits_equal, to_dev, u32, u64, workspace
+
+pytestmark = pytest.mark.gpu
+
+
+def ascending(rng, space, count):
+    return np.sort(rng.choice(space, count, replace=False)).astype(np.uint32)
+
+
+def intersect(acc, local, glob, zero, ws_bytes, slack=3):
+    residual = acc.copy()
+    if not zero:
+        residual[local] = 0.0
+    d_res = to_dev(residual)
+    d_local = to_dev(np.concatenate([local, np.zeros(slack, np.uint32)]))
+    d_val = to_dev(np.concatenate([acc[local], np.full(slack, 9.0, np.float32)]))
+    d_glob = to_dev(np.concatenate([glob, np.full(1, 7, np.uint32)]))
+    d_nl, d_ng = (to_dev(np.array([a.size], np.uint64)) for a in (local, glob))
+    out = torch.full((local.size + slack,), -1, dtype=torch.int32, device=DEV)
+    cnt = torch.full((1,), -5, dtype=torch.int64, device=DEV)
+    ws = workspace(ws_bytes)[:ws_bytes]
+    kw = dict(indexes_out=out, max_local=local.size + slack, max_global=glob.size)
+    if zero:
+        okt.okt_index_intersect_zero(d_res, d_local, d_nl, d_glob, d_ng, cnt, ws, **kw)
+    else:
+        okt.okt_index_intersect_restore(d_res, d_local, d_val, d_nl, d_glob, d_ng, cnt, ws, **kw)
+    c = int(u64(cnt)[0])
+    return d_res.cpu().numpy(), u32(out[:c])
+
+
+def least_bytes(max_local):
+    tiles = max(1, -(-max_local // 1024))
+    return 64 + 8 * (tiles + (tiles + 63) // 64)
+
+
+# 1024 places of the global list are searched first; up to 16 elements between two of
+# them are read at once (17 x 1024 = 17,408), of longer lists the part that a tile lies
+# in, which fits in LDS up to 4096, else is sampled, and bisected from 17 x 4096 on
+@pytest.mark.parametrize("ng", [1, 1023, 1024, 1025, 2048, 17_407, 17_408, 17_409, 60_000, 400_000])
+@pytest.mark.parametrize("small_ws", [False, True])
+@pytest.mark.parametrize("zero", [False, True])
+def test_intersection_at_the_steps_of_the_search(ng, small_ws, zero):
+    rng = np.random.default_rng(ng)
+    n = 1_200_000
+    acc = rng.normal(size=n).astype(np.float32)
+    glob = ascending(rng, n, ng)
+    # a crowded stretch, a sparse one whose tile spans most of the global list, the very ends
+    crowd = np.arange(n // 2, n // 2 + 3000, dtype=np.uint32)
+    local = np.unique(np.concatenate([crowd, glob[::5], ascending(rng, n, 700),
+                                      np.array([0, n - 1], np.uint32)])).astype(np.uint32)
+    nbytes = least_bytes(local.size + 3) if small_ws else okt.okt_workspace_bytes(local.size + 3, 0)
+    got, indexes = intersect(acc, local, glob, zero, nbytes)
+    want = orc.index_intersection(local, glob)
+    assert np.array_equal(indexes, want)
+    assert bits_equal(got, orc.residual_update(acc, want))
+
+
+def test_intersection_of_a_sparse_tile_with_a_long_list():
+    """One tile of local entries over a list of 3 M: sampled in LDS, then bisected."""
+    rng = np.random.default_rng(5)
+    n = 9_000_000
+    acc = rng.normal(size=n).astype(np.float32)
+    glob = ascending(rng, n, 3_000_000)
+    local = np.unique(np.concatenate([rng.choice(glob, 500), ascending(rng, n, 400)])).astype(np.uint32)
+    got, indexes = intersect(acc, local, glob, True, okt.okt_workspace_bytes(local.size + 3, 0))
+    want = orc.index_intersection(local, glob)
+    assert np.array_equal(indexes, want)
+    assert bits_equal(got, orc.residual_update(acc, want))
+
+
+def test_intersection_of_more_tiles_than_are_added_up():
+    """More than 4096 tiles of room: the counts are made prefixes by a launch of their own."""
+    rng = np.random.default_rng(6)
+    n = 6_000_000
+    acc = rng.normal(size=n).astype(np.float32)
+    local = ascending(rng, n, 4_300_000)
+    glob = ascending(rng, n, 900_000)
+    got, indexes = intersect(acc, local, glob, False, okt.okt_workspace_bytes(local.size + 3, 0))
+    want = orc.index_intersection(local, glob)
+    assert np.array_equal(indexes, want)
+    assert bits_equal(got, orc.residual_update(acc, want))
