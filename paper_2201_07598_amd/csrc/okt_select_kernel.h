@@ -518,41 +518,6 @@ __global__ __launch_bounds__(BLOCK) void select_kernel(
     }
 }
 
-// The same selection over the values of a sorted COO list whose length is on the
-// device (at most max_nnz): entries at or above the threshold are copied, in
-// order, with their indices; the input is not modified.
-template <int BLOCK, int U, int STASH>
-__global__ __launch_bounds__(BLOCK) void coo_select_kernel(
-    const uint32_t* __restrict__ idx_in, const float* __restrict__ val_in,
-    const uint64_t* __restrict__ d_nnz_in, uint32_t max_nnz,
-    const float* __restrict__ d_threshold, uint32_t* __restrict__ idx_out,
-    float* __restrict__ val_out, uint64_t capacity, uint64_t* __restrict__ nnz_out,
-    ScanHeader* hdr, uint64_t* seg_desc, uint64_t* group_desc, uint32_t nseg, uint32_t piece) {
-    constexpr int WAVES = BLOCK / WAVE;
-    __shared__ StashMemory<WAVES, STASH> s_stash;
-    __shared__ uint32_t s_count[WAVES];
-    __shared__ uint32_t s_seg;
-    __shared__ uint32_t s_before[2];
-    if (threadIdx.x == 0) s_seg = atomicAdd(&hdr->ticket, 1u);
-    __syncthreads();
-    const uint32_t seg = s_seg;
-    const uint64_t have = *d_nnz_in;
-    const uint32_t n = have < max_nnz ? (uint32_t)have : max_nnz;
-    float* vals = const_cast<float*>(val_in);         // CooSource never writes
-    const float th = *d_threshold;
-    if (th == th) {
-        select_body<BLOCK, U, STASH, false>(vals, n, TestFloat{__builtin_fabsf(th)},
-                                             CooSource{idx_in}, idx_out, val_out, capacity,
-                                             nnz_out, hdr, seg_desc, group_desc, nseg, piece, seg,
-                                             s_stash, s_count, s_before);
-    } else {
-        select_body<BLOCK, U, STASH, false>(vals, n, TestKey{magnitude_key(th)},
-                                             CooSource{idx_in}, idx_out, val_out, capacity,
-                                             nnz_out, hdr, seg_desc, group_desc, nseg, piece, seg,
-                                             s_stash, s_count, s_before);
-    }
-}
-
 template <int BLOCK, int U, int STASH, int CACHE>
 __global__ __launch_bounds__(BLOCK) void accumulate_select_kernel(
     const float* __restrict__ grad, float* __restrict__ res, float lr, uint32_t n,

@@ -53,6 +53,12 @@ inline size_t select_ws_bytes(uint64_t n) {
     return 64 + 8 * (size_t)(t + (t + 63) / 64);
 }
 
+// ---- the same over a COO list ----
+// Short lists need no scan across workgroups (okt_select_kernel.h): one workgroup up to
+// COO_SMALL_N entries, a count a tile of 1024 up to COO_TILED_N, as many as the
+// least workspace of a call has room for (two bytes each).
+constexpr uint32_t COO_SMALL_N = 32768, COO_TILED_N = 4u << 20;
+
 // Vectors longer than the 256 MB last-level cache are read, and where a kernel
 // rewrites them densely written, with the non-temporal hint: nothing of them is
 // found cached again, and what goes around the cache pushes nothing out.  Shorter

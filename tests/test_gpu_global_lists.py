@@ -1,5 +1,6 @@
 """The global stage's calls on short lists, at the lengths where their kernels change
-form: the intersection with a global list that is searched in one, two or more steps, with and
+form: the COO select in one workgroup, by tiles, and through the chained scan; the
+intersection with a global list that is searched in one, two or more steps, with and
 without room for the first launch's bits.  Everything is bit-exact.
 """
 import numpy as np
@@ -89,3 +90,30 @@ def test_intersection_of_more_tiles_than_are_added_up():
     want = orc.index_intersection(local, glob)
     assert np.array_equal(indexes, want)
     assert bits_equal(got, orc.residual_update(acc, want))
+
+
+@pytest.mark.parametrize("nnz", [4, 1023, 16_384, 16_385, 32_768, 32_769, 33_793, 4 << 20, (4 << 20) + 1])
+@pytest.mark.parametrize("slack", [0, 5])
+def test_coo_select_at_the_lengths_of_its_forms(nnz, slack):
+    rng = np.random.default_rng(nnz)
+    idx = np.cumsum(rng.integers(1, 9, nnz), dtype=np.uint64).astype(np.uint32)
+    val = rng.normal(size=nnz).astype(np.float32)
+    val[::211] = np.float32(np.nan)
+    th = np.float32(1.1)
+    # the indices at an odd word address, garbage behind the entries there are
+    store = to_dev(np.concatenate([np.zeros(1, np.uint32), idx, np.full(slack, 3, np.uint32)]))[1:]
+    d_val = to_dev(np.concatenate([val, np.full(slack, 1e30, np.float32)]))
+    ws_bytes = 64 + 8 * (nnz // 262_144 + 1025 + (nnz // 262_144 + 1025 + 63) // 64) + 16
+    want_idx, want_val, total = orc.coo_threshold_select(idx, val, th)
+    for cap in (nnz + slack, total // 2):
+        out_idx = torch.full((nnz + slack,), -1, dtype=torch.int32, device=DEV)
+        out_val = torch.zeros(nnz + slack, device=DEV)
+        out_nnz = torch.zeros(2, dtype=torch.int64, device=DEV)
+        okt.okt_coo_threshold_select(store, d_val, to_dev(np.array([nnz], np.uint64)), to_dev(np.array([th])),
+                                     out_idx, out_val, out_nnz, workspace(ws_bytes)[:ws_bytes],
+                                     max_nnz=nnz + slack, capacity=cap)
+        emitted, found = (int(x) for x in u64(out_nnz))
+        assert found == total and emitted == min(cap, total)
+        assert np.array_equal(u32(out_idx[:emitted]), want_idx[:emitted])
+        assert bits_equal(out_val[:emitted].cpu().numpy(), want_val[:emitted])
+        assert bool((out_idx[emitted:] == -1).all())
