@@ -450,6 +450,7 @@ constexpr int RES_BLOCK = SEL_BLOCK;
 constexpr int RES_WAVES = RES_BLOCK / WAVE;
 static_assert(RES_BLOCK == 1024, "pick_bin is written for 1024 threads");
 constexpr int ROWS_MAX = 6;                        // quads of a thread in a share of candidates
+constexpr uint32_t HELPERS = 16;                   // workgroups that write out what fits one share
 constexpr uint32_t ROW = RES_BLOCK * 4;
 
 // What the digits run over: the keys of candidates in any order (cand_count of them);
@@ -496,8 +497,9 @@ struct CandRows {
     uint32_t key[ROWS_MAX][4];                     // the value's bits
     uint32_t idx[INDICES ? ROWS_MAX : 1][4];
     uint32_t have;                                 // bit 4 row + c: there is one
+    template <typename Wanted>                     // the rows whose indices are
     __device__ __forceinline__ void load(const uint32_t* __restrict__ vals, const uint32_t* __restrict__ indices,
-                                         uint32_t start, uint32_t end) {
+                                         uint32_t start, uint32_t end, Wanted&& wanted) {
         // No branch between the loads: rows past the end read the last quad again (the
         // arrays have room for whole quads).
         const uint32_t last = (end - 1) / 4 * 4;
@@ -507,7 +509,7 @@ struct CandRows {
             const uint32_t i = start + r * ROW + 4u * threadIdx.x, q = i < last ? i : last;
             const uint4 v = *reinterpret_cast<const uint4*>(vals + q);
             key[r][0] = v.x; key[r][1] = v.y; key[r][2] = v.z; key[r][3] = v.w;
-            if (INDICES) {
+            if (INDICES && wanted(r)) {
                 const uint4 j = *reinterpret_cast<const uint4*>(indices + q);
                 idx[r][0] = j.x; idx[r][1] = j.y; idx[r][2] = j.z; idx[r][3] = j.w;
             }
@@ -556,8 +558,13 @@ __global__ __launch_bounds__(RES_BLOCK) void resolve_kernel(
         per_share = rows * ROW;
     }
     const uint32_t used = (uint32_t)(((uint64_t)len + per_share - 1) / per_share);
-    // there is work for as many workgroups as there are shares
-    if (blockIdx.x >= used) return;
+    // There is work for as many workgroups as there are shares.  Of a single share of
+    // candidates all find the answer for themselves, and each writes out a part: the stores of
+    // one compute unit, most of them to lines of their own, take longer than all the rest
+    // (10,500 of 13,600 candidates: the launch 18.1 us with one workgroup, 11.5 with sixteen).
+    const bool single = use_cand && used == 1;
+    const uint32_t helpers = !SELECT || !single ? 1u : gridDim.x < HELPERS ? gridDim.x : HELPERS;
+    if (blockIdx.x >= (single ? helpers : used)) return;
     // A bound of zero over the whole vector: fewer than k elements, as far as the sample
     // saw, that are not, so the answer is zero most likely, which the digits from there
     // find in two (1 M elements, all but a thousandth of them zero: 36 us, general ones 42).
@@ -597,6 +604,8 @@ __global__ __launch_bounds__(RES_BLOCK) void resolve_kernel(
         }
         __syncthreads();
     };
+    // Of the rows of a single share, those whose 256 candidates a wave of this workgroup writes out.
+    auto mine_to_write = [&](int r) { return !single || (uniform(tid >> 6) + (uint32_t)r) % helpers == blockIdx.x; };
     // The candidates of a share at or above the threshold: their places from a scan over
     // rows and waves, and over the shares before; stores straight from registers.
     auto compact = [&](const auto& rows, uint32_t share) {
@@ -643,6 +652,7 @@ __global__ __launch_bounds__(RES_BLOCK) void resolve_kernel(
             scan_close_group(group_desc, share / SCAN_GROUP, exclusive + aggregate);
 #pragma unroll
         for (int r = 0; r < ROWS_MAX; ++r) {
+            if (!mine_to_write(r)) continue;
             uint64_t pos = (uint64_t)exclusive + s_rows[r][wave] +
                            ((incl[r / 3] - packed[r / 3]) >> (10 * (r % 3)) & 1023u);
 #pragma unroll
@@ -656,7 +666,7 @@ __global__ __launch_bounds__(RES_BLOCK) void resolve_kernel(
                     ++pos;
                 }
         }
-        if (share == used - 1 && tid == 0) {
+        if (share == used - 1 && tid == 0 && (!single || blockIdx.x == 0)) {
             const uint64_t total = (uint64_t)exclusive + aggregate;
             const bool failed =
                 __hip_atomic_load(&hdr->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
@@ -665,10 +675,10 @@ __global__ __launch_bounds__(RES_BLOCK) void resolve_kernel(
         }
     };
 
-    if (use_cand && used == 1) {
+    if (single) {
         // ---- one share: no exchange with other workgroups ----
         CandRows<SELECT> rows;
-        rows.load(reinterpret_cast<const uint32_t*>(cand), cand_idx, 0, len);
+        rows.load(reinterpret_cast<const uint32_t*>(cand), cand_idx, 0, len, mine_to_write);
         while (!d.found) {
             __syncthreads();
             clear_hist();
@@ -684,7 +694,7 @@ __global__ __launch_bounds__(RES_BLOCK) void resolve_kernel(
             counted();
             d = next_digit<false>(d, s_hist, s_higher, k, s_count, s_result);
         }
-        if (tid == 0) {
+        if (tid == 0 && blockIdx.x == 0) {
             *threshold_out = __uint_as_float(d.base);
             *count_ge_out = (uint64_t)d.above + d.equal;
         }
@@ -747,7 +757,7 @@ __global__ __launch_bounds__(RES_BLOCK) void resolve_kernel(
                     CandRows<true> rows;
                     const uint32_t start = share * per_share;
                     rows.load(reinterpret_cast<const uint32_t*>(cand), cand_idx, start,
-                              len - start < per_share ? len : start + per_share);
+                              len - start < per_share ? len : start + per_share, mine_to_write);
                     compact(rows, share);
                 } else {
                     StashMemory<RES_WAVES, STASH>& s_stash = *reinterpret_cast<StashMemory<RES_WAVES, STASH>*>(s_memory);
