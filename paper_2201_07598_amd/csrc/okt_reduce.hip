@@ -132,6 +132,141 @@ __global__ __launch_bounds__(256) void reduce_slices_wave_kernel(
     }
 }
 
+// ---- launches whose tiles are all in flight together ----
+// A lone region takes as long as one tile, and every step of that is latency.  Tickets
+// on one counter are served one at a time, 30 ns each - 361 tiles, 11 us - and each tile waits for
+// the counts of those before it.  So the table, and a count of every tile's hit slots, are made
+// by workgroups with a tile each, which read the indices once more than the scan does, and
+// reduce_tile_kernel<PLACED> adds up the counts before its tile: no ticket, no
+// descriptors to clear, no wait.  One region of 3.4 M slots, 32 contributions, 1.1 M entries:
+// 8.0 us for the table and 16.5 for the tiles with tickets, 10.0 and 11.2 so.
+constexpr int COUNT_BLOCK = 512;
+constexpr uint32_t PLACED_P = COUNT_BLOCK / 2;       // a thread at least for each end of a slice
+
+// lower_bound_near by `lanes` consecutive lanes (a power of two, at most 16) that all
+// have the same arguments: each reads sixteen entries of one window around the guess.
+__device__ __forceinline__ uint64_t lower_bound_lanes(const uint32_t* __restrict__ a, uint64_t lo, uint64_t hi,
+                                                      uint32_t x, uint64_t guess, uint32_t lanes) {
+    const uint32_t sub = (uint32_t)lane_id() & (lanes - 1), window = 16 * lanes;
+    for (int miss = 0; miss < SEARCH_GUESSES; ++miss) {
+        if (hi <= lo) return lo;
+        uint64_t w = guess < lo + window / 2 ? lo : guess - window / 2;
+        if (w + window > hi) w = hi < lo + window ? lo : hi - window;
+        const uint64_t at = w + 16 * sub;
+        uint32_t v[16], below = 0;
+        if (at + 16 <= hi) {
+            const SearchWindow win = *reinterpret_cast<const SearchWindow*>(a + at);
+#pragma unroll
+            for (int j = 0; j < 16; ++j) v[j] = win.v[j];
+        } else {
+#pragma unroll
+            for (int j = 0; j < 16; ++j) v[j] = at + j < hi ? a[at + j] : ~0u;   // past the end counts as not below
+        }
+#pragma unroll
+        for (int j = 0; j < 16; ++j) below += v[j] < x ? 1u : 0u;
+        uint32_t first = v[0], last = v[15];
+        for (uint32_t s = 1; s < lanes; s <<= 1) below += __shfl_xor(below, (int)s, WAVE);
+        first = __shfl(first, (int)((uint32_t)lane_id() & ~(lanes - 1)), WAVE);
+        last = __shfl(last, (int)((uint32_t)lane_id() | (lanes - 1)), WAVE);
+        const bool whole = w + window <= hi;
+        const bool up = whole && below == window && w + window < hi, down = below == 0 && w > lo;
+        if (!up && !down) return w + below;
+        const float per = (float)(window - 1) / (float)(whole && last > first ? last - first : 1u);   // entries per index
+        if (down) {
+            hi = w;
+            const uint64_t back = (uint64_t)((float)(first - x) * per);
+            guess = back < w ? w - back : 0;
+        } else {
+            lo = w + window;
+            guess = lo + (uint64_t)((float)(x - last) * per);
+        }
+    }
+    return lower_bound_idx(a, lo, hi, x);
+}
+
+template <uint32_t S_MAX>
+__global__ __launch_bounds__(COUNT_BLOCK) void reduce_count_kernel(
+    const uint32_t* __restrict__ idx_cat, const uint64_t* __restrict__ seg_begin,
+    const uint64_t* __restrict__ seg_end, uint32_t seg_stride, const uint32_t* __restrict__ lo_hi, uint32_t lo0,
+    uint32_t hi0, uint32_t P, uint32_t max_width, uint32_t slots, char* ws, uint32_t ws_region_bytes,
+    uint32_t table_offset) {
+    constexpr uint32_t WORDS_MAX = S_MAX / 32;
+    __shared__ __attribute__((aligned(16))) uint32_t s_bits[WORDS_MAX];
+    __shared__ uint64_t s_from[PLACED_P], s_upto[PLACED_P];
+    __shared__ uint32_t s_wave[COUNT_BLOCK / WAVE];
+    const uint32_t tid = threadIdx.x, region = blockIdx.y, tile = blockIdx.x;
+    const RegionView r = region_view(lo_hi, lo0, hi0, region, max_width, slots);
+    if (tile >= r.ntiles) return;
+    char* const region_ws = ws + (size_t)region * ws_region_bytes;
+    uint32_t* const table = (uint32_t*)(region_ws + table_offset);
+    const uint64_t* begin = seg_begin + (size_t)region * seg_stride;
+    const uint64_t* end = seg_end + (size_t)region * seg_stride;
+    const uint32_t a = r.lo + tile * slots, tslots = (r.hi - a) < slots ? (r.hi - a) : slots;
+    for (uint32_t w = tid; w < WORDS_MAX / 4; w += COUNT_BLOCK) reinterpret_cast<uint4*>(s_bits)[w] = uint4{0, 0, 0, 0};
+    // ---- where the tile begins and ends in every contribution ----
+    uint32_t lanes = 1;
+    while (lanes < 16 && 4 * P * lanes <= (uint32_t)COUNT_BLOCK) lanes <<= 1;
+    {
+        const uint32_t team = tid / lanes, p = team >> 1, which = team & 1u;
+        if (p < P) {                                 // a team is in or out together
+            const uint64_t cb = begin[p], ce = end[p] > cb ? end[p] : cb;
+            const uint64_t bound = (uint64_t)a + (which ? tslots : 0u);
+            const uint64_t guess = cb + (ce - cb) * (bound - r.lo) / r.width;    // both factors are below 2^32
+            const uint64_t at = bound > 0xffffffffull ? ce : lower_bound_lanes(idx_cat, cb, ce, (uint32_t)bound, guess, lanes);
+            if (tid % lanes == 0) {
+                (which ? s_upto : s_from)[p] = at;
+                if (!which) table[(size_t)tile * P + p] = (uint32_t)(at - cb);
+                else if (tile == r.ntiles - 1) table[(size_t)(tile + 1) * P + p] = (uint32_t)(at - cb);
+            }
+        }
+    }
+    __syncthreads();
+    // ---- the hit slots ----
+    uint32_t share = 0;                              // 2^share threads read a slice
+    while (share < 8 && (P << (share + 1)) <= (uint32_t)COUNT_BLOCK) ++share;
+    const uint32_t member = tid & ((1u << share) - 1u), q = tid >> share;
+    if (q < P) {
+        constexpr int FLIGHT = 4;
+        const uint64_t from = s_from[q], upto = s_upto[q], step = 4ull << share;
+        for (uint64_t i0 = from + 4 * member; i0 < upto; i0 += FLIGHT * step) {
+            uint32_t v[FLIGHT][4];
+#pragma unroll
+            for (int u = 0; u < FLIGHT; ++u) {
+                const uint64_t i = i0 + u * step;
+                if (i + 4 <= upto) {
+                    const QuadAt4 x = *reinterpret_cast<const QuadAt4*>(idx_cat + i);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) v[u][j] = x.v[j];
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) v[u][j] = i + j < upto ? idx_cat[i + j] : a + tslots;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < FLIGHT; ++u)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const uint32_t s = v[u][j] - a;
+                    if (s < tslots)
+                        __hip_atomic_fetch_or(&s_bits[s >> 5], 1u << (s & 31), __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
+        }
+    }
+    __syncthreads();
+    uint32_t hits = 0;
+    for (uint32_t w = tid; w < WORDS_MAX; w += COUNT_BLOCK) hits += (uint32_t)__popc(s_bits[w]);
+    hits = wave_sum(hits);
+    if (tid % WAVE == 0) s_wave[tid / WAVE] = hits;
+    __syncthreads();
+    if (tid == 0) {
+        uint32_t total = 0;
+#pragma unroll
+        for (int w = 0; w < COUNT_BLOCK / WAVE; ++w) total += s_wave[w];
+        ((uint32_t*)(region_ws + SCAN_HEADER_BYTES))[tile] = total;
+    }
+}
+
 // From one count per wave of the workgroup in LDS: the counts of the waves before
 // the calling one, and of all.
 struct WaveSums { uint32_t before, total; };
@@ -176,8 +311,6 @@ __device__ __forceinline__ uint32_t bitmap_prefix(const uint32_t* s_bits, uint16
     return sums.total;
 }
 
-struct __attribute__((packed, aligned(4))) Quad32 { uint32_t v[4]; };   // four words at any word address
-
 // grid = (tiles of the widest region, B).  Region j: chunk offsets at seg_begin /
 // seg_end + j * seg_stride; bounds from lo_hi[2j..] if lo_hi != NULL else (lo0, hi0).
 //
@@ -216,7 +349,7 @@ struct __attribute__((packed, aligned(4))) Quad32 { uint32_t v[4]; };   // four 
 // fetched ahead (what it hides, its registers and the extra barriers cost), tiles of
 // several regions in turn in the grid (their inputs share no lines), the tile's windows
 // each searched before its turn (a chain of searches instead of one).
-template <int BLOCK, int ROUNDS, uint32_t C, uint32_t S_MAX>
+template <int BLOCK, int ROUNDS, uint32_t C, uint32_t S_MAX, bool PLACED = false>
 __global__ __launch_bounds__(BLOCK, ROUNDS == 2 ? 8 : 4) void reduce_tile_kernel(
     const uint32_t* __restrict__ idx_cat, const float* __restrict__ val_cat,
     const uint64_t* __restrict__ seg_begin, const uint64_t* __restrict__ seg_end,
@@ -245,7 +378,7 @@ __global__ __launch_bounds__(BLOCK, ROUNDS == 2 ? 8 : 4) void reduce_tile_kernel
     __shared__ __attribute__((aligned(16))) uint32_t s_bits[WORDS_MAX + SPARE];
     __shared__ uint16_t s_wprefix[WORDS_MAX + SPARE];
     __shared__ uint64_t s_unit[UNITS];            // first entry << 6 | whole unit readable << 5 | entries
-    __shared__ uint32_t s_wave[2][WAVES];
+    __shared__ uint32_t s_wave[2][WAVES], s_placed[WAVES];
     __shared__ uint32_t s_tile, s_before[2], s_wrap, s_cut[WINDOWS_MAX + 1], s_cut_rank[WINDOWS_MAX + 1];
 
     const int tid = threadIdx.x, lane = tid & (WAVE - 1);
@@ -256,7 +389,7 @@ __global__ __launch_bounds__(BLOCK, ROUNDS == 2 ? 8 : 4) void reduce_tile_kernel
     uint64_t* tile_desc = (uint64_t*)(region_ws + SCAN_HEADER_BYTES);
     uint64_t* group_desc = tile_desc + gridDim.x;
     if (tid == 0) {
-        s_tile = atomicAdd(&hdr->ticket, 1u);
+        if (!PLACED) s_tile = atomicAdd(&hdr->ticket, 1u);
         s_wrap = ~0u;
     }
     if (tid < (int)SPARE) s_wprefix[WORDS_MAX + tid] = (uint16_t)(C + tid);
@@ -266,7 +399,7 @@ __global__ __launch_bounds__(BLOCK, ROUNDS == 2 ? 8 : 4) void reduce_tile_kernel
     for (uint32_t w = tid; w < WORDS_MAX / 4; w += BLOCK) reinterpret_cast<uint4*>(s_bits)[w] = uint4{0, 0, 0, 0};
     for (uint32_t s = tid; s < C / 2; s += BLOCK) reinterpret_cast<double2*>(s_sum)[s] = double2{0.0, 0.0};
     __syncthreads();
-    const uint32_t tile = uniform(s_tile);
+    const uint32_t tile = PLACED ? blockIdx.x : uniform(s_tile);
     if (r.ntiles == 0) {
         if (tile == 0 && tid == 0) {
             nnz[0] = r.bad ? ~0ull : 0ull;
@@ -348,11 +481,11 @@ __global__ __launch_bounds__(BLOCK, ROUNDS == 2 ? 8 : 4) void reduce_tile_kernel
         }
         if (left == 0) return;
         if (whole) {
-            const Quad32 i4 = *reinterpret_cast<const Quad32*>(idx_cat + from);
+            const QuadAt4 i4 = *reinterpret_cast<const QuadAt4*>(idx_cat + from);
 #pragma unroll
             for (int j = 0; j < 4; ++j) c.slot[u][j] = i4.v[j];
             if (VALUES) {
-                const Quad32 v4 = *reinterpret_cast<const Quad32*>(val_cat + from);
+                const QuadAt4 v4 = *reinterpret_cast<const QuadAt4*>(val_cat + from);
 #pragma unroll
                 for (int j = 0; j < 4; ++j) c.value[u][j] = __uint_as_float(v4.v[j]);
             }
@@ -462,13 +595,26 @@ __global__ __launch_bounds__(BLOCK, ROUNDS == 2 ? 8 : 4) void reduce_tile_kernel
     // before this one.  What the two waves look at first is asked for early
     // (look_back) and, as a rule, there by the time it is needed.
     const uint32_t group = tile / SCAN_GROUP;
+    if constexpr (PLACED) {
+        // the count before this tile, as reduce_count_kernel found it
+        const uint32_t* counts = (const uint32_t*)(region_ws + SCAN_HEADER_BYTES);
+        uint32_t sum = 0;
+        for (uint32_t t = tid; t < tile; t += BLOCK) sum += counts[t];
+        sum = wave_sum(sum);
+        if (lane == 0) s_placed[wave] = sum;
+    }
     uint64_t seen = 0;
     auto look_back = [&]() {
+        if (PLACED) return;
         seen = 0;
         if (wave == 0 && (uint32_t)lane < tile % SCAN_GROUP) seen = desc_load(tile_desc + group * SCAN_GROUP + lane);
         if (wave == 1 && (uint32_t)lane < group) seen = desc_load(group_desc + (group - 1 - lane));
     };
     auto place_tile = [&](uint32_t count) -> uint32_t {
+        if constexpr (PLACED) {
+            __syncthreads();
+            return sum_of_waves<WAVES>(s_placed).total;
+        }
         if (wave == 0) {
             const uint32_t before = scan_within_group(hdr, tile_desc, group_desc, tile, count, seen);
             if (lane == 0) s_before[0] = before;
@@ -488,7 +634,7 @@ __global__ __launch_bounds__(BLOCK, ROUNDS == 2 ? 8 : 4) void reduce_tile_kernel
         if (tile != r.ntiles - 1 || tid != 0) return;
         const uint64_t total = (uint64_t)exclusive + distinct;
         const bool failed =
-            __hip_atomic_load(&hdr->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+            !PLACED && __hip_atomic_load(&hdr->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
         nnz[0] = failed ? ~0ull : (total < capacity ? total : capacity);
         nnz[1] = failed ? ~0ull : total;
     };
@@ -534,7 +680,7 @@ __global__ __launch_bounds__(BLOCK, ROUNDS == 2 ? 8 : 4) void reduce_tile_kernel
         auto rank_tile = [&]() {
             distinct = bitmap_prefix<BLOCK, WORDS_MAX>(s_bits, s_wprefix, words, s_wave[1], &s_wrap);
             // the count is known before the sums: publish it now, wait for the others later
-            if (tid == 0) scan_publish_early(tile_desc, tile, distinct);
+            if (!PLACED && tid == 0) scan_publish_early(tile_desc, tile, distinct);
         };
         // The sums of ranks r0 .. r0 + in_round - 1 leave LDS, the indices take their
         // place, and both go out in output order; the wait for the tiles before this
@@ -731,6 +877,8 @@ int reduce_launch(const uint32_t* d_idx_cat, const float* d_val_cat,
     if (least > 0xffffffffull) return OKT_ERR_INVALID_ARG;
     if (!d_ws || !aligned(d_ws, 256) || ws_bytes < least * B) return OKT_ERR_WORKSPACE;
     const ReduceShape shape = reduce_shape(B, max_width, capacity, P, (uint64_t)device_cus(), ws_bytes);
+    // (and contributions whose ends a workgroup finds side by side)
+    const bool placed = !traffic_only && P <= PLACED_P && reduce_counts_first(shape, B, max_width, device_cus());
     const uint32_t slots = shape.slots;
     const size_t region_bytes = reduce_ws_bytes_region(max_width, P, slots);
     uint64_t tiles = reduce_tiles(max_width, slots);
@@ -739,7 +887,14 @@ int reduce_launch(const uint32_t* d_idx_cat, const float* d_val_cat,
     const uint64_t cells = (tiles + 1) * P;
     uint64_t sblocks = (cells + 255) / 256;
     if (sblocks > 4096) sblocks = 4096;
-    if (cells * B <= 4096) {
+    if (placed) {
+        auto* count = shape.kind == RED_DENSE    ? reduce_count_kernel<ReduceNarrow::C_DENSE>
+                      : shape.kind == RED_RANKED ? reduce_count_kernel<ReduceNarrow::S_RANKED>
+                                                 : reduce_count_kernel<ReduceNarrow::S_SPARSE>;
+        hipLaunchKernelGGL(count, dim3((unsigned)tiles, B), dim3(COUNT_BLOCK), 0, s, d_idx_cat, d_seg_begin,
+                           d_seg_end, seg_stride, d_lo_hi, lo, hi, P, max_width, slots, (char*)d_ws,
+                           (uint32_t)region_bytes, table_offset);
+    } else if (cells * B <= 4096) {
         // few cells: a wave each
         hipLaunchKernelGGL(reduce_slices_wave_kernel, dim3((unsigned)((cells + 3) / 4), B),
                            dim3(256), 0, s, d_idx_cat, d_seg_begin, d_seg_end, seg_stride, d_lo_hi,
@@ -767,6 +922,14 @@ int reduce_launch(const uint32_t* d_idx_cat, const float* d_val_cat,
                            d_idx_out, d_val_out, capacity, d_nnz_out, d_dense, (char*)d_ws,
                            (uint32_t)region_bytes, table_offset);
     };
+    if (placed) {
+        using F = ReduceNarrow;
+        if (shape.kind == RED_DENSE) launch(reduce_tile_kernel<F::BLOCK, F::ROUNDS, F::C_DENSE, F::C_DENSE, true>, F::BLOCK);
+        else if (shape.kind == RED_RANKED) launch(reduce_tile_kernel<F::BLOCK, F::ROUNDS, F::C_RANKED, F::S_RANKED, true>, F::BLOCK);
+        else launch(reduce_tile_kernel<F::BLOCK, F::ROUNDS, F::C_SPARSE, F::S_SPARSE, true>, F::BLOCK);
+        timing_after(s);
+        return launch_status();
+    }
     auto launch_form = [&](auto form) {
         using F = decltype(form);
         if (shape.kind == RED_DENSE) launch(reduce_tile_kernel<F::BLOCK, F::ROUNDS, F::C_DENSE, F::C_DENSE>, F::BLOCK);
