@@ -450,7 +450,10 @@ constexpr int RES_BLOCK = SEL_BLOCK;
 constexpr int RES_WAVES = RES_BLOCK / WAVE;
 static_assert(RES_BLOCK == 1024, "pick_bin is written for 1024 threads");
 constexpr int ROWS_MAX = 6;                        // quads of a thread in a share of candidates
-constexpr uint32_t HELPERS = 16;                   // workgroups that write out what fits one share
+// Up to SINGLE_ROWS rows of candidates are a single share: every workgroup of HELPERS holds all
+// of them in registers, finds the answer for itself and writes out a part.
+constexpr int SINGLE_ROWS = 10;
+constexpr uint32_t HELPERS = 32;
 constexpr uint32_t ROW = RES_BLOCK * 4;
 
 // What the digits run over: the keys of candidates in any order (cand_count of them);
@@ -497,9 +500,8 @@ struct CandRows {
     uint32_t key[ROWS_MAX][4];                     // the value's bits
     uint32_t idx[INDICES ? ROWS_MAX : 1][4];
     uint32_t have;                                 // bit 4 row + c: there is one
-    template <typename Wanted>                     // the rows whose indices are
     __device__ __forceinline__ void load(const uint32_t* __restrict__ vals, const uint32_t* __restrict__ indices,
-                                         uint32_t start, uint32_t end, Wanted&& wanted) {
+                                         uint32_t start, uint32_t end) {
         // No branch between the loads: rows past the end read the last quad again (the
         // arrays have room for whole quads).
         const uint32_t last = (end - 1) / 4 * 4;
@@ -509,7 +511,7 @@ struct CandRows {
             const uint32_t i = start + r * ROW + 4u * threadIdx.x, q = i < last ? i : last;
             const uint4 v = *reinterpret_cast<const uint4*>(vals + q);
             key[r][0] = v.x; key[r][1] = v.y; key[r][2] = v.z; key[r][3] = v.w;
-            if (INDICES && wanted(r)) {
+            if (INDICES) {
                 const uint4 j = *reinterpret_cast<const uint4*>(indices + q);
                 idx[r][0] = j.x; idx[r][1] = j.y; idx[r][2] = j.z; idx[r][3] = j.w;
             }
@@ -534,7 +536,7 @@ __global__ __launch_bounds__(RES_BLOCK) void resolve_kernel(
     static_assert(LDS >= BINS_MAX * 4, "room for a histogram");
     __shared__ __attribute__((aligned(16))) unsigned char s_memory[LDS];
     __shared__ uint32_t s_count[RES_WAVES], s_result[3], s_before[2], s_rows[ROWS_MAX][RES_WAVES];
-    __shared__ uint32_t s_ticket, s_last, s_higher, s_give_up;
+    __shared__ uint32_t s_ticket, s_last, s_higher, s_give_up, s_few;
     uint32_t* s_hist = reinterpret_cast<uint32_t*>(s_memory);
     const uint32_t tid = threadIdx.x;
 
@@ -558,11 +560,16 @@ __global__ __launch_bounds__(RES_BLOCK) void resolve_kernel(
         per_share = rows * ROW;
     }
     const uint32_t used = (uint32_t)(((uint64_t)len + per_share - 1) / per_share);
-    // There is work for as many workgroups as there are shares.  Of a single share of
-    // candidates all find the answer for themselves, and each writes out a part: the stores of
-    // one compute unit, most of them to lines of their own, take longer than all the rest
-    // (10,500 of 13,600 candidates: the launch 18.1 us with one workgroup, 11.5 with sixteen).
-    const bool single = use_cand && used == 1;
+    // There is work for as many workgroups as there are shares.  Of a single share all find
+    // the answer for themselves, from registers and LDS, and each writes out a part: no
+    // exchange, which costs some eight microseconds a digit, and not all of the stores, most of
+    // them to lines of their own, from one compute unit.  Refresh iterations, us:
+    //                               digits across workgroups   one workgroup   32, the last digit gathered
+    //   1 M, 1 % (13,600 candidates)                              33.4         25.6
+    //   1 M, 2 % (26,400)                     35.2                             30.9
+    //   2 M, 1 % (26,600)                     37.3                             34.9
+    //   4 M, 1 % (52,000)                     41.0                             42.2 (with room for 81,920)
+    const bool single = use_cand && len <= SINGLE_ROWS * ROW;
     const uint32_t helpers = !SELECT || !single ? 1u : gridDim.x < HELPERS ? gridDim.x : HELPERS;
     if (blockIdx.x >= (single ? helpers : used)) return;
     // A bound of zero over the whole vector: fewer than k elements, as far as the sample
@@ -604,8 +611,6 @@ __global__ __launch_bounds__(RES_BLOCK) void resolve_kernel(
         }
         __syncthreads();
     };
-    // Of the rows of a single share, those whose 256 candidates a wave of this workgroup writes out.
-    auto mine_to_write = [&](int r) { return !single || (uniform(tid >> 6) + (uint32_t)r) % helpers == blockIdx.x; };
     // The candidates of a share at or above the threshold: their places from a scan over
     // rows and waves, and over the shares before; stores straight from registers.
     auto compact = [&](const auto& rows, uint32_t share) {
@@ -633,7 +638,7 @@ __global__ __launch_bounds__(RES_BLOCK) void resolve_kernel(
             const uint32_t c0 = in ? cells[2 * lane] : 0u, c1 = in ? cells[2 * lane + 1] : 0u;
             const uint32_t upto = wave_inclusive_scan_u32(c0 + c1);
             const uint32_t aggregate = (uint32_t)__builtin_amdgcn_readlane((int)upto, WAVE - 1);
-            const uint32_t before = used == 1 ? 0u : scan_within_group(hdr, seg_desc, group_desc, share, aggregate);
+            const uint32_t before = scan_within_group(hdr, seg_desc, group_desc, share, aggregate);
             if (lane == 0) {
                 s_before[0] = before;
                 s_count[0] = aggregate;
@@ -643,16 +648,15 @@ __global__ __launch_bounds__(RES_BLOCK) void resolve_kernel(
                 cells[2 * lane + 1] = upto - c1;
             }
         } else if (wave == 1) {
-            const uint32_t before = used == 1 ? 0u : scan_across_groups(hdr, group_desc, share / SCAN_GROUP);
+            const uint32_t before = scan_across_groups(hdr, group_desc, share / SCAN_GROUP);
             if (lane == 0) s_before[1] = before;
         }
         __syncthreads();
         const uint32_t exclusive = uniform(s_before[0] + s_before[1]), aggregate = uniform(s_count[0]);
-        if (used != 1 && tid == 0 && share / SCAN_GROUP != 0 && share % SCAN_GROUP == SCAN_GROUP - 1)
+        if (tid == 0 && share / SCAN_GROUP != 0 && share % SCAN_GROUP == SCAN_GROUP - 1)
             scan_close_group(group_desc, share / SCAN_GROUP, exclusive + aggregate);
 #pragma unroll
         for (int r = 0; r < ROWS_MAX; ++r) {
-            if (!mine_to_write(r)) continue;
             uint64_t pos = (uint64_t)exclusive + s_rows[r][wave] +
                            ((incl[r / 3] - packed[r / 3]) >> (10 * (r % 3)) & 1023u);
 #pragma unroll
@@ -666,7 +670,7 @@ __global__ __launch_bounds__(RES_BLOCK) void resolve_kernel(
                     ++pos;
                 }
         }
-        if (share == used - 1 && tid == 0 && (!single || blockIdx.x == 0)) {
+        if (share == used - 1 && tid == 0) {
             const uint64_t total = (uint64_t)exclusive + aggregate;
             const bool failed =
                 __hip_atomic_load(&hdr->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
@@ -677,19 +681,72 @@ __global__ __launch_bounds__(RES_BLOCK) void resolve_kernel(
 
     if (single) {
         // ---- one share: no exchange with other workgroups ----
-        CandRows<SELECT> rows;
-        rows.load(reinterpret_cast<const uint32_t*>(cand), cand_idx, 0, len, mine_to_write);
+        const uint32_t* vals = reinterpret_cast<const uint32_t*>(cand);
+        const uint32_t rows = (len + ROW - 1) / ROW, last = (len - 1) / 4 * 4;
+        const int wave = (int)uniform(tid >> 6), lane = tid & (WAVE - 1);
+        uint32_t key[SINGLE_ROWS][4];                                // 0: none (a candidate's is not)
+#pragma unroll
+        for (int r = 0; r < SINGLE_ROWS; ++r)
+            if ((uint32_t)r < rows) {
+                const uint32_t i = r * ROW + 4u * tid;
+                const uint4 v = *reinterpret_cast<const uint4*>(vals + (i < last ? i : last));
+                key[r][0] = v.x; key[r][1] = v.y; key[r][2] = v.z; key[r][3] = v.w;
+            }
+        // the first row whose 256 candidates this wave writes out
+        uint32_t own = ((uint32_t)blockIdx.x + HELPERS * helpers - (uint32_t)wave) % helpers;
+        uint4 own_val = uint4{0, 0, 0, 0}, own_idx = uint4{0, 0, 0, 0};
+        auto load_own = [&]() {
+            const uint32_t i = own * ROW + 4u * tid, q = i < last ? i : last;
+            own_val = *reinterpret_cast<const uint4*>(vals + q);
+            own_idx = *reinterpret_cast<const uint4*>(cand_idx + q);
+        };
+        if (SELECT && own < rows) load_own();
+#pragma unroll
+        for (int r = 0; r < SINGLE_ROWS; ++r)
+            if ((uint32_t)r < rows) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    key[r][c] = r * ROW + 4u * tid + c < len ? key[r][c] & ABS_MASK : 0u;
+            }
+        if (tid == 0) s_few = 0;
         while (!d.found) {
             __syncthreads();
+            if (d.shift == 0 && d.equal <= (uint32_t)WAVE) {
+                // The last digit of so few keys needs no histogram: they are gathered, and
+                // every wave counts for each how many are larger.
+#pragma unroll
+                for (int r = 0; r < SINGLE_ROWS; ++r)
+                    if ((uint32_t)r < rows) {
+#pragma unroll
+                        for (int c = 0; c < 4; ++c)
+                            if (key[r][c] - d.base < d.bins) s_hist[atomicAdd(&s_few, 1u)] = key[r][c];
+                    }
+                __syncthreads();
+                const uint32_t n_few = uniform(s_few), mine = (uint32_t)lane < n_few ? s_hist[lane] : 0u;
+                uint32_t larger = 0, same = 0;
+                for (uint32_t j = 0; j < n_few; ++j) {
+                    const uint32_t v = (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)j);
+                    larger += v > mine ? 1u : 0u;
+                    same += v == mine ? 1u : 0u;
+                }
+                const uint64_t is = __ballot((uint32_t)lane < n_few && larger < d.k_rem && d.k_rem <= larger + same);
+                const int at = __ffsll((unsigned long long)is) - 1;             // the keys that are equal, all the same
+                d.base = (uint32_t)__builtin_amdgcn_readlane((int)mine, at);
+                d.above += (uint32_t)__builtin_amdgcn_readlane((int)larger, at);
+                d.equal = (uint32_t)__builtin_amdgcn_readlane((int)same, at);
+                d.found = true;
+                break;
+            }
             clear_hist();
             auto take_rows = [&](auto&& take_one) {
 #pragma unroll
-                for (int r = 0; r < ROWS_MAX; ++r)
+                for (int r = 0; r < SINGLE_ROWS; ++r)
+                    if ((uint32_t)r < rows) {
 #pragma unroll
-                    for (int c = 0; c < 4; ++c)
-                        if (rows.have >> (4 * r + c) & 1u) take_one(rows.key[r][c] & ABS_MASK);
+                        for (int c = 0; c < 4; ++c) take_one(key[r][c]);
+                    }
             };
-            if (crowd_of(rows.key[0][0] & ABS_MASK)) take_rows(take_crowd);
+            if (crowd_of(key[0][0])) take_rows(take_crowd);
             else take_rows(take);
             counted();
             d = next_digit<false>(d, s_hist, s_higher, k, s_count, s_result);
@@ -699,8 +756,63 @@ __global__ __launch_bounds__(RES_BLOCK) void resolve_kernel(
             *count_ge_out = (uint64_t)d.above + d.equal;
         }
         if constexpr (SELECT) {
+            // how many of every row's and wave's 256 go out, and how many before them
+            __shared__ uint32_t s_cell[SINGLE_ROWS * RES_WAVES];
+#pragma unroll
+            for (int r = 0; r < SINGLE_ROWS; ++r)
+                if ((uint32_t)r < rows) {
+                    uint32_t chosen = 0;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) chosen += (uint32_t)__popcll(__ballot(key[r][c] >= d.base));
+                    if (lane == 0) s_cell[r * RES_WAVES + wave] = chosen;
+                }
             __syncthreads();
-            compact(rows, 0);
+            const uint32_t cells = rows * RES_WAVES;
+            if (wave == 0) {
+                constexpr int PER = (SINGLE_ROWS * RES_WAVES + WAVE - 1) / WAVE;
+                uint32_t c[PER], sum = 0;
+#pragma unroll
+                for (int j = 0; j < PER; ++j) {
+                    const uint32_t i = (uint32_t)lane * PER + j;
+                    c[j] = i < cells ? s_cell[i] : 0u;
+                    sum += c[j];
+                }
+                uint32_t before = wave_inclusive_scan_u32(sum) - sum;
+#pragma unroll
+                for (int j = 0; j < PER; ++j) {
+                    const uint32_t i = (uint32_t)lane * PER + j;
+                    if (i < cells) s_cell[i] = before;
+                    before += c[j];
+                }
+                if (lane == WAVE - 1 && blockIdx.x == 0) {
+                    nnz_out[0] = before < capacity ? before : capacity;
+                    nnz_out[1] = before;
+                }
+            }
+            __syncthreads();
+            while (own < rows) {
+                const uint32_t i = own * ROW + 4u * tid;
+                const uint32_t val[4] = {own_val.x, own_val.y, own_val.z, own_val.w};
+                const uint32_t idx[4] = {own_idx.x, own_idx.y, own_idx.z, own_idx.w};
+                uint32_t chosen = 0;
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if (i + c < len && (val[c] & ABS_MASK) >= d.base) chosen |= 1u << c;
+                const uint32_t mine = (uint32_t)__popc(chosen);
+                uint64_t pos = s_cell[own * RES_WAVES + wave] + wave_inclusive_scan_u32(mine) - mine;
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if (chosen >> c & 1u) {
+                        if (pos < capacity) {
+                            idx_out[pos] = idx[c];
+                            val_out[pos] = __uint_as_float(val[c]);
+                            vec[idx[c]] = 0.0f;
+                        }
+                        ++pos;
+                    }
+                own += helpers;
+                if (own < rows) load_own();
+            }
         }
         return;
     }
@@ -757,7 +869,7 @@ __global__ __launch_bounds__(RES_BLOCK) void resolve_kernel(
                     CandRows<true> rows;
                     const uint32_t start = share * per_share;
                     rows.load(reinterpret_cast<const uint32_t*>(cand), cand_idx, start,
-                              len - start < per_share ? len : start + per_share, mine_to_write);
+                              len - start < per_share ? len : start + per_share);
                     compact(rows, share);
                 } else {
                     StashMemory<RES_WAVES, STASH>& s_stash = *reinterpret_cast<StashMemory<RES_WAVES, STASH>*>(s_memory);
