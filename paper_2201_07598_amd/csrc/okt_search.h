@@ -73,8 +73,11 @@ OKT_SEARCH_FN PartitionCut partition_cut(const uint32_t* idx, uint64_t nnz, uint
     if (r == 0) return PartitionCut{0u, 0ull};
     if (r == R) return PartitionCut{(uint32_t)n, nnz};
     if (nnz == 0) return PartitionCut{(uint32_t)((r * n) / R), 0ull};     // r, n < 2^32: no overflow
-    const uint32_t b = idx[(r * nnz) / R];                                 // r, nnz < 2^32
-    return PartitionCut{b, lower_bound_idx(idx, 0, nnz, b)};
+    const uint64_t at = (r * nnz) / R;                                     // r, nnz < 2^32
+    const uint32_t b = idx[at];
+    // in a list that ascends strictly, as a select's does, that is where b is first
+    if (at == 0 || idx[at - 1] < b) return PartitionCut{b, at};
+    return PartitionCut{b, lower_bound_idx(idx, 0, at, b)};
 }
 
 }  // namespace okt
