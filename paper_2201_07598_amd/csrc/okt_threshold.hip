@@ -114,6 +114,24 @@ __device__ __forceinline__ void pick_bin(const uint32_t* hist, uint32_t bins, ui
     __syncthreads();
 }
 
+// The key of rank k_rem among n <= 64 keys in LDS, how many of them are larger and how
+// many equal: every wave works it out for itself.
+struct KeyRank { uint32_t key, above, equal; };
+__device__ __forceinline__ KeyRank rank_of_few(const uint32_t* s_keys, uint32_t n, uint32_t k_rem) {
+    const uint32_t lane = (uint32_t)lane_id(), mine = lane < n ? s_keys[lane] : 0u;
+    uint32_t larger = 0, same = 0;
+    for (uint32_t j = 0; j < n; ++j) {
+        const uint32_t v = (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)j);
+        larger += v > mine ? 1u : 0u;
+        same += v == mine ? 1u : 0u;
+    }
+    // the lanes whose key it is hold the same
+    const uint64_t is = __ballot(lane < n && larger < k_rem && k_rem <= larger + same);
+    const int at = __ffsll((unsigned long long)is) - 1;
+    return KeyRank{(uint32_t)__builtin_amdgcn_readlane((int)mine, at), (uint32_t)__builtin_amdgcn_readlane((int)larger, at),
+                   (uint32_t)__builtin_amdgcn_readlane((int)same, at)};
+}
+
 // ---------------------------------------------------------------------------
 // the sample
 // ---------------------------------------------------------------------------
@@ -722,18 +740,10 @@ __global__ __launch_bounds__(RES_BLOCK) void resolve_kernel(
                             if (key[r][c] - d.base < d.bins) s_hist[atomicAdd(&s_few, 1u)] = key[r][c];
                     }
                 __syncthreads();
-                const uint32_t n_few = uniform(s_few), mine = (uint32_t)lane < n_few ? s_hist[lane] : 0u;
-                uint32_t larger = 0, same = 0;
-                for (uint32_t j = 0; j < n_few; ++j) {
-                    const uint32_t v = (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)j);
-                    larger += v > mine ? 1u : 0u;
-                    same += v == mine ? 1u : 0u;
-                }
-                const uint64_t is = __ballot((uint32_t)lane < n_few && larger < d.k_rem && d.k_rem <= larger + same);
-                const int at = __ffsll((unsigned long long)is) - 1;             // the keys that are equal, all the same
-                d.base = (uint32_t)__builtin_amdgcn_readlane((int)mine, at);
-                d.above += (uint32_t)__builtin_amdgcn_readlane((int)larger, at);
-                d.equal = (uint32_t)__builtin_amdgcn_readlane((int)same, at);
+                const KeyRank few = rank_of_few(s_hist, uniform(s_few), d.k_rem);
+                d.base = few.key;
+                d.above += few.above;
+                d.equal = few.equal;
                 d.found = true;
                 break;
             }
@@ -983,8 +993,9 @@ __global__ __launch_bounds__(TINY_BLOCK) void tiny_threshold_kernel(const float*
                                                                     uint32_t k, float* threshold_out,
                                                                     uint64_t* count_ge_out) {
     __shared__ uint32_t s_hist[RS_MAX_BINS];
-    __shared__ uint32_t s_wave[TINY_BLOCK / WAVE], s_result[3];
+    __shared__ uint32_t s_wave[TINY_BLOCK / WAVE], s_result[3], s_few;
     const uint32_t tid = threadIdx.x;
+    if (tid == 0) s_few = 0;
     uint32_t key[TINY_PER];                        // all ones: no element
 #pragma unroll
     for (uint32_t u = 0; u < TINY_PER / 4; ++u) {
@@ -1000,11 +1011,23 @@ __global__ __launch_bounds__(TINY_BLOCK) void tiny_threshold_kernel(const float*
             for (uint32_t j = 0; j < 4; ++j) key[4 * u + j] = i + j < n ? magnitude_key(acc[i + j]) : ~0u;
         }
     }
-    uint32_t base = 0, above = 0, k_rem = k;
+    uint32_t base = 0, above = 0, k_rem = k, in_bin = n;
 #pragma unroll
     for (int digit = 0; digit < 3; ++digit) {
         const uint32_t shift = digit == 0 ? 20u : digit == 1 ? 9u : 0u;
         const uint32_t bins = digit == 2 ? 1u << RS_BITS3 : 1u << RS_BITS1;
+        if (digit == 2 && in_bin <= (uint32_t)WAVE) {              // no histogram for so few: see resolve_kernel
+#pragma unroll
+            for (uint32_t j = 0; j < TINY_PER; ++j)
+                if (key[j] - base < bins) s_hist[atomicAdd(&s_few, 1u)] = key[j];
+            __syncthreads();
+            const KeyRank few = rank_of_few(s_hist, uniform(s_few), k_rem);
+            if (tid == 0) {
+                *threshold_out = __uint_as_float(few.key);
+                *count_ge_out = (uint64_t)above + few.above + few.equal;
+            }
+            return;
+        }
         for (uint32_t b = tid; b < bins; b += TINY_BLOCK) s_hist[b] = 0;
         __syncthreads();
 #pragma unroll
@@ -1014,9 +1037,10 @@ __global__ __launch_bounds__(TINY_BLOCK) void tiny_threshold_kernel(const float*
         }
         __syncthreads();
         pick_bin<false>(s_hist, bins, k_rem, s_wave, s_result);
-        base += s_result[0] << shift;
-        above += s_result[1];
-        k_rem -= s_result[1];
+        base += uniform(s_result[0]) << shift;
+        above += uniform(s_result[1]);
+        k_rem -= uniform(s_result[1]);
+        in_bin = uniform(s_result[2]);
         if (digit == 2 && tid == 0) {
             *threshold_out = __uint_as_float(base);
             *count_ge_out = (uint64_t)above + s_result[2];
