@@ -46,9 +46,12 @@ __device__ __forceinline__ RegionView region_view(const uint32_t* lo_hi, uint32_
 // lo + t * slots (clipped to hi), for t = 0 .. ntiles.
 // Every search starts from a guess, which makes it two or three waits and lines of
 // memory instead of a bisection's fifteen: 35 boundaries x 16 contributions x 490
-// regions in 33 us against 49 with a gallop of single probes from the same guess, 102
-// against 129 us for 55 x 64 x 373; a lone region (317 x 32) takes as long as with
-// plain bisections.
+// regions in 33 us against 49 with a gallop of single probes from the same guess; a
+// lone region (317 x 32) takes as long as with plain bisections.
+// Neighbouring threads search the same contribution for neighbouring boundaries: their
+// probes share lines where its slices are short.  A contribution lies inside its region as
+// a rule, and one entry says so: 868 regions of one tile, 88 contributions of 77 entries,
+// 55.9 -> 53.5 us a call.
 __global__ __launch_bounds__(256) void reduce_slices_kernel(
     const uint32_t* __restrict__ idx_cat, const uint64_t* __restrict__ seg_begin,
     const uint64_t* __restrict__ seg_end, uint32_t seg_stride,
@@ -66,20 +69,133 @@ __global__ __launch_bounds__(256) void reduce_slices_kernel(
         scan_state[i] = i == SCAN_SPIN_WORD ? (uint64_t)spin_limit : 0ull;
     const uint64_t* begin = seg_begin + (size_t)region * seg_stride;
     const uint64_t* end = seg_end + (size_t)region * seg_stride;
-    const uint64_t cells = (uint64_t)(r.ntiles + 1) * P;
-    for (uint64_t c = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; c < cells;
-         c += (uint64_t)gridDim.x * blockDim.x) {
-        // neighbouring threads search the same contribution for neighbouring
-        // boundaries: their probes share all but the last few levels
-        const uint32_t p = (uint32_t)(c / (r.ntiles + 1)), t = (uint32_t)(c % (r.ntiles + 1));
-        uint64_t bound = (uint64_t)r.lo + (uint64_t)t * slots;
-        if (bound > r.hi) bound = r.hi;
+    const uint32_t cells = (r.ntiles + 1) * P;                // below 2^32
+    const float per_index = r.width ? 1.0f / (float)r.width : 0.0f;
+    for (uint32_t c = blockIdx.x * blockDim.x + threadIdx.x; c < cells; c += gridDim.x * blockDim.x) {
+        const uint32_t p = c / (r.ntiles + 1), t = c - p * (r.ntiles + 1);
+        const uint32_t x = r.width < (uint64_t)t * slots ? r.hi : r.lo + t * slots;
         const uint64_t cb = begin[p], ce = end[p] > cb ? end[p] : cb;
-        // where the boundary would fall if the contribution's indices were spread evenly
-        // over the region (both factors are below 2^32)
-        const uint64_t guess = cb + (r.width ? (ce - cb) * (bound - r.lo) / r.width : 0);
-        table[(size_t)t * P + p] =
-            (uint32_t)(lower_bound_near(idx_cat, cb, ce, (uint32_t)bound, guess) - cb);
+        // from where the boundary would fall if the indices were spread evenly over the region
+        uint64_t at;
+        if (t == 0 && cb < ce && idx_cat[cb] >= x) at = cb;
+        else if (t == r.ntiles && cb < ce && idx_cat[ce - 1] < x) at = ce;
+        else at = lower_bound_near(idx_cat, cb, ce, x, cb + (uint64_t)((float)(ce - cb) * ((float)(x - r.lo) * per_index)));
+        table[(size_t)t * P + p] = (uint32_t)(at - cb);
+    }
+}
+
+// The same by teams of lanes, for regions of many tiles and longer slices: a cell costs
+// lines of the index lists at random places, so lines are what is saved.  A team reads a
+// whole line a guess and finds `chain` boundaries of a contribution in turn, each guessed
+// from the one before (the end of a slice of 117 entries to about ten, where a guess from
+// the contribution's ends is up to 36 off); neighbouring teams hold neighbouring
+// contributions, whose cells share lines of the table.  A thread a cell -> teams:
+//   373 regions, 64 contributions, 54 tiles, slices of 97 entries    98 -> 64 us
+//   490 regions, 16 contributions, 33 tiles, 484 entries             31 -> 23
+//    48 regions, 256 contributions, 47 tiles, 92 entries             28 -> 21
+// (Whole calls of the first and last: 696 -> 663 and 140 -> 133 us, with teams of four
+// lanes 661 and 135, of eight 680 and 146.)
+constexpr uint32_t TEAM = 2;
+// Sum over the lanes of a team; every lane gets it.
+__device__ __forceinline__ uint32_t team_sum(uint32_t v) {
+    static_assert(TEAM == 2, "one exchange");
+    return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xb1, 0xf, 0xf, false);     // quad_perm: the neighbour
+}
+
+__global__ __launch_bounds__(256) void reduce_slices_team_kernel(
+    const uint32_t* __restrict__ idx_cat, const uint64_t* __restrict__ seg_begin,
+    const uint64_t* __restrict__ seg_end, uint32_t seg_stride,
+    const uint32_t* __restrict__ lo_hi, uint32_t lo0, uint32_t hi0, uint32_t P,
+    uint32_t max_width, uint32_t slots, char* ws, uint32_t ws_region_bytes,
+    uint32_t table_offset, uint32_t spin_limit, uint32_t chain) {
+    const uint32_t region = blockIdx.y;
+    const RegionView r = region_view(lo_hi, lo0, hi0, region, max_width, slots);
+    uint32_t* table = (uint32_t*)(ws + (size_t)region * ws_region_bytes + table_offset);
+    uint64_t* scan_state = (uint64_t*)(ws + (size_t)region * ws_region_bytes);
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < table_offset / 8;
+         i += gridDim.x * blockDim.x)
+        scan_state[i] = i == SCAN_SPIN_WORD ? (uint64_t)spin_limit : 0ull;
+    const uint64_t* begin = seg_begin + (size_t)region * seg_stride;
+    const uint64_t* end = seg_end + (size_t)region * seg_stride;
+    constexpr uint32_t QUADS = SEARCH_LINE / 4 / TEAM;        // loads of a lane, its team's side by side
+    const uint32_t lane = (uint32_t)lane_id(), sub = lane & (TEAM - 1);
+    const uint32_t units = P * (r.ntiles / chain + 1);        // fewer than cells, which are below 2^32
+    for (uint32_t u = (blockIdx.x * blockDim.x + threadIdx.x) / TEAM; u < units;
+         u += gridDim.x * (blockDim.x / TEAM)) {              // a team is in or out together
+        const uint32_t c = u / P, p = u - c * P, t_end = min((c + 1) * chain, r.ntiles + 1);
+        uint32_t t = c * chain;
+        const uint64_t cb = begin[p], ce = end[p];
+        const uint32_t* const list = idx_cat + cb;
+        const uint32_t skew = (uint32_t)((uintptr_t)list / sizeof(uint32_t)) & (SEARCH_LINE - 1);
+        auto bound_of = [&](uint32_t tile) {
+            return r.hi - r.lo < (uint64_t)tile * slots ? r.hi : r.lo + tile * slots;
+        };
+        if (ce > cb && ce - cb > 0xffffffffull - SEARCH_LINE) {       // positions would not fit 32 bits
+            for (; t < t_end; ++t)
+                table[(size_t)t * P + p] = (uint32_t)(lower_bound_idx(idx_cat, cb, ce, bound_of(t)) - cb);
+            continue;
+        }
+        const uint32_t len = ce > cb ? (uint32_t)(ce - cb) : 0u;
+        const uint32_t* const a = list - skew;                // positions count from here
+        const uint32_t upto = len + skew;
+        uint32_t x = bound_of(t);
+        // as if the contribution's indices were spread evenly over the region
+        LineSearch s{skew, upto, skew + (r.width ? (uint32_t)((float)len * ((float)(x - r.lo) / (float)r.width)) : 0u)};
+        for (int guesses = 0;;) {
+            bool known = s.hi <= s.lo;
+            if (!known && guesses == 0) {
+                if (t == 0 && list[0] >= x) {
+                    known = true;
+                } else if (t == r.ntiles && list[len - 1] < x) {
+                    s.lo = upto;
+                    known = true;
+                }
+            }
+            if (!known && guesses == SEARCH_GUESSES) {        // any input ends
+                s.lo = (uint32_t)lower_bound_idx(a, s.lo, s.hi, x);
+                known = true;
+            } else if (!known) {
+                const uint32_t line = line_of_guess(s, skew, upto);
+                uint32_t v[QUADS][4], below = 0;
+                if (len >= SEARCH_LINE) {                     // alike in a team
+#pragma unroll
+                    for (uint32_t q = 0; q < QUADS; ++q) {
+                        const QuadAt4 quad = *reinterpret_cast<const QuadAt4*>(a + line + 4 * (q * TEAM + sub));
+#pragma unroll
+                        for (uint32_t j = 0; j < 4; ++j) v[q][j] = quad.v[j];
+                    }
+                } else {
+#pragma unroll
+                    for (uint32_t q = 0; q < QUADS; ++q)
+#pragma unroll
+                        for (uint32_t j = 0; j < 4; ++j) {
+                            const uint32_t at = line + 4 * (q * TEAM + sub) + j;
+                            v[q][j] = at < upto ? a[at] : ~0u;
+                        }
+                }
+#pragma unroll
+                for (uint32_t q = 0; q < QUADS; ++q)
+#pragma unroll
+                    for (uint32_t j = 0; j < 4; ++j) below += v[q][j] < x ? 1u : 0u;
+                below = team_sum(below);
+                uint32_t first = 0, last = 0;
+                if (below == 0 || below == SEARCH_LINE) {     // alike in a team
+                    first = __shfl(v[0][0], (int)(lane & ~(TEAM - 1)), WAVE);
+                    last = __shfl(v[QUADS - 1][3], (int)(lane | (TEAM - 1)), WAVE);
+                }
+                known = line_says(s, line, below, first, last, x);
+                ++guesses;
+            }
+            if (!known) continue;
+            if (sub == 0) table[(size_t)t * P + p] = s.lo - skew;
+            if (++t == t_end) break;
+            // the next boundary lies at or behind this one, as far on as if the rest were spread evenly
+            const uint32_t rest = r.hi - x, step = rest < slots ? rest : slots;
+            x += step;
+            s.hi = upto;
+            s.guess = s.lo + (uint32_t)((float)(upto - s.lo) * ((float)step / (float)rest));
+            guesses = 0;
+        }
     }
 }
 
@@ -885,8 +1001,6 @@ int reduce_launch(const uint32_t* d_idx_cat, const float* d_val_cat,
     if (tiles == 0) tiles = 1;
     const uint32_t table_offset = (uint32_t)(64 + 8 * (tiles + (tiles + 63) / 64));
     const uint64_t cells = (tiles + 1) * P;
-    uint64_t sblocks = (cells + 255) / 256;
-    if (sblocks > 4096) sblocks = 4096;
     if (placed) {
         auto* count = shape.kind == RED_DENSE    ? reduce_count_kernel<ReduceNarrow::C_DENSE>
                       : shape.kind == RED_RANKED ? reduce_count_kernel<ReduceNarrow::S_RANKED>
@@ -901,10 +1015,18 @@ int reduce_launch(const uint32_t* d_idx_cat, const float* d_val_cat,
                            lo, hi, P, max_width, slots, (char*)d_ws, (uint32_t)region_bytes,
                            table_offset, spin_limit_setting());
     } else {
-        hipLaunchKernelGGL(reduce_slices_kernel, dim3((unsigned)sblocks, B), dim3(256), 0, s,
-                           d_idx_cat, d_seg_begin, d_seg_end, seg_stride, d_lo_hi, lo, hi, P,
-                           max_width, slots, (char*)d_ws, (uint32_t)region_bytes, table_offset,
-                           spin_limit_setting());
+        const uint32_t chain = reduce_chain(cells * B);
+        const bool teams = reduce_by_teams(shape, max_width, capacity, P);
+        const uint64_t threads = teams ? P * (tiles / chain + 1) * TEAM : cells;
+        const dim3 grid((unsigned)(threads < 4096 * 256 ? (threads + 255) / 256 : 4096), B);
+        if (teams)
+            hipLaunchKernelGGL(reduce_slices_team_kernel, grid, dim3(256), 0, s, d_idx_cat, d_seg_begin, d_seg_end,
+                               seg_stride, d_lo_hi, lo, hi, P, max_width, slots, (char*)d_ws, (uint32_t)region_bytes,
+                               table_offset, spin_limit_setting(), chain);
+        else
+            hipLaunchKernelGGL(reduce_slices_kernel, grid, dim3(256), 0, s, d_idx_cat, d_seg_begin, d_seg_end,
+                               seg_stride, d_lo_hi, lo, hi, P, max_width, slots, (char*)d_ws, (uint32_t)region_bytes,
+                               table_offset, spin_limit_setting());
     }
     if (traffic_only) {
         timing_before(s);

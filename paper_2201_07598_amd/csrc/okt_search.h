@@ -59,6 +59,45 @@ OKT_SEARCH_FN uint64_t lower_bound_near(const uint32_t* a, uint64_t lo, uint64_t
     return lower_bound_idx(a, lo, hi, x);
 }
 
+// The same again by whole lines of memory: the SEARCH_LINE entries of the aligned line
+// that holds the guess are read at once (at the ends of a list the first or last as many),
+// so that a guess costs one line and one wait and hits if it is some sixteen entries off.
+// Positions count from the beginning of the line that holds the list's first entry, which
+// is at `from`; the last one is before `upto`.
+constexpr uint32_t SEARCH_LINE = 32;
+struct LineSearch { uint32_t lo, hi, guess; };               // the answer lies in [lo, hi]
+
+// Where the line of the guess begins (there is one: lo < hi), inside the list unless that
+// is shorter than a line.
+OKT_SEARCH_FN uint32_t line_of_guess(const LineSearch& s, uint32_t from, uint32_t upto) {
+    const uint32_t g = s.guess < s.lo ? s.lo : s.guess >= s.hi ? s.hi - 1 : s.guess;
+    const uint32_t line = g & ~(SEARCH_LINE - 1);
+    return line < from || upto - from < SEARCH_LINE ? from : line + SEARCH_LINE > upto ? upto - SEARCH_LINE : line;
+}
+
+// What the line says: `below` of its entries are below x (an entry past the end of the
+// list is not), `first` and `last` are its ends.  True if that is the answer, which is in
+// lo then.  Every line takes the guess off [lo, hi], sorted or not.
+OKT_SEARCH_FN bool line_says(LineSearch& s, uint32_t line, uint32_t below, uint32_t first, uint32_t last, uint32_t x) {
+    const uint32_t at = line + below, lo = s.lo, hi = s.hi;
+    const uint32_t in = at < lo ? lo : at > hi ? hi : at;
+    if (below != 0 && below != SEARCH_LINE) {
+        s.lo = in;
+        return true;
+    }
+    const float per = (float)(SEARCH_LINE - 1) / (float)(last > first ? last - first : 1u);   // entries per index
+    if (below == 0) {
+        s.hi = in;
+        const float back = (float)(first - x) * per;
+        s.guess = back < (float)in ? in - (uint32_t)back : 0u;
+    } else {
+        s.lo = in;
+        const float on = (float)(x - last) * per;
+        s.guess = on < (float)(hi - in) ? in + (uint32_t)on : hi;
+    }
+    return s.hi <= s.lo;
+}
+
 // Boundary r (0 <= r <= R) of the balanced split of [0, n) by a sorted index list
 // of nnz entries (Sec. 3.1.1), and the list position where region r begins:
 // b[r] = idx[floor(r * nnz / R)], b[0] = 0, b[R] = n; without entries the equal
