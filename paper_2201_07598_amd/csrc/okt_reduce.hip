@@ -606,11 +606,17 @@ __global__ __launch_bounds__(BLOCK, ROUNDS == 2 ? 8 : 4) void reduce_tile_kernel
                 for (int j = 0; j < 4; ++j) c.value[u][j] = __uint_as_float(v4.v[j]);
             }
         } else {
+            // The compiler must not see that the first index here is the first one there: it
+            // would read that one in front of the branch and the other three behind it, two
+            // loads a quad (373 regions of 64 contributions 663 us a call, 637 with one; 490 of
+            // 16, 525 and 507).
+            uint64_t at = from;
+            asm volatile("" : "+v"(at));
 #pragma unroll
             for (int j = 0; j < 4; ++j)
                 if ((uint32_t)j < left) {
-                    c.slot[u][j] = idx_cat[from + j];
-                    if (VALUES) c.value[u][j] = val_cat[from + j];
+                    c.slot[u][j] = idx_cat[at + j];
+                    if (VALUES) c.value[u][j] = val_cat[at + j];
                 }
         }
     };
