@@ -606,17 +606,15 @@ __global__ __launch_bounds__(BLOCK, ROUNDS == 2 ? 8 : 4) void reduce_tile_kernel
                 for (int j = 0; j < 4; ++j) c.value[u][j] = __uint_as_float(v4.v[j]);
             }
         } else {
-            // The compiler must not see that the first index here is the first one there: it
-            // would read that one in front of the branch and the other three behind it, two
-            // loads a quad (373 regions of 64 contributions 663 us a call, 637 with one; 490 of
-            // 16, 525 and 507).
-            uint64_t at = from;
-            asm volatile("" : "+v"(at));
+            // Other loads than those, relaxed atomic ones, or the compiler makes one of what the
+            // two branches begin or end with and reads a quad in two parts (373 regions of 64
+            // contributions 663 us a call, 637 so; 490 of 16, 525 and 507).
+            auto apart = [](const auto* at) { return __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT); };
 #pragma unroll
             for (int j = 0; j < 4; ++j)
                 if ((uint32_t)j < left) {
-                    c.slot[u][j] = idx_cat[at + j];
-                    if (VALUES) c.value[u][j] = val_cat[at + j];
+                    c.slot[u][j] = apart(idx_cat + from + j);
+                    if (VALUES) c.value[u][j] = apart(val_cat + from + j);
                 }
         }
     };
