@@ -13,6 +13,7 @@
 // of a tile's entries matched (a bit each) and how many, and every workgroup adds up
 // the counts of the tiles before its own.
 #include "okt_device.h"
+#include "okt_search.h"
 #include "okt_select_kernel.h"
 #include "okt_sizes.h"
 
@@ -167,7 +168,8 @@ __device__ __forceinline__ Membership tile_members(const uint32_t* __restrict__ 
     }
     // ---- a long part ----
     __syncthreads();                                 // the table has been cleared: its place is taken
-    const uint32_t step = (part + RST_WINDOW - 1) / RST_WINDOW, staged = (part + step - 1) / step;
+    const SpreadSample sample_of_part = spread_sample(part, RST_WINDOW);
+    const uint32_t step = sample_of_part.step, staged = sample_of_part.count;
     {
         constexpr int FLIGHT = RST_WINDOW / RST_BLOCK;
         uint32_t v[FLIGHT];

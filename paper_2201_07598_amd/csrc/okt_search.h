@@ -98,6 +98,14 @@ OKT_SEARCH_FN bool line_says(LineSearch& s, uint32_t line, uint32_t below, uint3
     return s.hi <= s.lo;
 }
 
+// Every step-th of `part` > 0 elements, from the first on, at most `room` of them: count
+// elements, (count - 1) * step < part <= count * step.  For every part below 2^32.
+struct SpreadSample { uint32_t step, count; };
+OKT_SEARCH_FN SpreadSample spread_sample(uint32_t part, uint32_t room) {
+    const uint32_t step = (part - 1) / room + 1;             // (part + room - 1 may not fit)
+    return SpreadSample{step, (part - 1) / step + 1};
+}
+
 // Boundary r (0 <= r <= R) of the balanced split of [0, n) by a sorted index list
 // of nnz entries (Sec. 3.1.1), and the list position where region r begins:
 // b[r] = idx[floor(r * nnz / R)], b[0] = 0, b[R] = n; without entries the equal
