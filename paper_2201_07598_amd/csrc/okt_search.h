@@ -72,7 +72,7 @@ struct LineSearch { uint32_t lo, hi, guess; };               // the answer lies 
 OKT_SEARCH_FN uint32_t line_of_guess(const LineSearch& s, uint32_t from, uint32_t upto) {
     const uint32_t g = s.guess < s.lo ? s.lo : s.guess >= s.hi ? s.hi - 1 : s.guess;
     const uint32_t line = g & ~(SEARCH_LINE - 1);
-    return line < from || upto - from < SEARCH_LINE ? from : line + SEARCH_LINE > upto ? upto - SEARCH_LINE : line;
+    return line < from || upto - from < SEARCH_LINE ? from : line > upto - SEARCH_LINE ? upto - SEARCH_LINE : line;
 }
 
 // What the line says: `below` of its entries are below x (an entry past the end of the

@@ -21,6 +21,15 @@ static void check_spread(uint32_t part, uint32_t room) {
     expect((uint64_t)(s.count - 1) * s.step < part && (uint64_t)s.count * s.step >= part, "does not cover", part, room);
 }
 
+// The line of a guess lies inside a list that is a line long or more, whatever the guess,
+// and takes in the guess where that is in [lo, hi).
+static void check_line(uint32_t from, uint32_t upto, uint32_t lo, uint32_t hi, uint32_t guess) {
+    const uint32_t line = okt::line_of_guess(okt::LineSearch{lo, hi, guess}, from, upto);
+    expect(line >= from && (uint64_t)line + okt::SEARCH_LINE <= upto, "line outside the list", line, upto);
+    const uint32_t g = guess < lo ? lo : guess >= hi ? hi - 1 : guess;
+    expect(line <= g && g - line < okt::SEARCH_LINE, "line without its guess", line, g);
+}
+
 int main() {
     std::mt19937_64 rng(32);
     for (const uint32_t room : {1u, 2u, 1000u, 1024u, 4096u})
@@ -29,6 +38,13 @@ int main() {
             check_spread(1 + d, room);
             check_spread(1 + (uint32_t)(rng() % 0xffffffffull), room);
         }
+    for (int rep = 0; rep < 400000; ++rep) {
+        const uint32_t from = (uint32_t)(rng() % okt::SEARCH_LINE);
+        const uint32_t upto = rng() % 2 ? 0xffffffffu - (uint32_t)(rng() % 100) : from + okt::SEARCH_LINE + (uint32_t)(rng() % 100);
+        const uint32_t lo = rng() % 2 ? upto - 1 - (uint32_t)(rng() % okt::SEARCH_LINE) : from + (uint32_t)(rng() % (upto - from));
+        const uint32_t hi = rng() % 2 ? upto : lo + 1 + (uint32_t)(rng() % (upto - lo));
+        check_line(from, upto, lo, hi, rng() % 2 ? upto - (uint32_t)(rng() % 80) : (uint32_t)rng());
+    }
     std::printf("%ld cases, %ld violations\n", cases, bad);
     return bad ? 1 : 0;
 }
