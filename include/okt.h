@@ -32,7 +32,8 @@
  *     between calls.  okt_time_next_kernel and okt_last_hip_error act per
  *     thread, the test hooks (okt_debug_...) on the whole process.
  *   - The kernels that place their output through a scan across workgroups
- *     (the select family, the reduce family), and those
+ *     (the select family, the reduce family, the index intersection in the least
+ *     workspace it accepts), and those
  *     that find the exact threshold digit by digit, wait for one another through
  *     device memory.  Every such wait ends by construction
  *     and is bounded all the same; should one run out, the kernel still exits

@@ -11,7 +11,8 @@
 // consecutive local entries and looks them up in the global list (tile_members).
 // A second launch writes the matched indices in ascending order: the first left which
 // of a tile's entries matched (a bit each) and how many, and every workgroup adds up
-// the counts of the tiles before its own.
+// the counts of the tiles before its own.  A call whose workspace has no room for the bits
+// finds a tile's place with a scan across workgroups instead.
 #include "okt_device.h"
 #include "okt_search.h"
 #include "okt_select_kernel.h"
@@ -26,16 +27,19 @@ struct RestoreMemory {
     };
     uint32_t below[2][RST_WAVES];
 };
+template <int ROWS>                                  // entries of a thread
 struct Membership {
-    uint32_t idx[RST_ROWS];
-    bool active[RST_ROWS], member[RST_ROWS];
+    uint32_t idx[ROWS];
+    bool active[ROWS], member[ROWS];
 };
 __device__ __forceinline__ uint32_t entries_of(const uint64_t* d_nnz, uint32_t most) {
     const uint64_t have = *d_nnz;
     return have < most ? (uint32_t)have : most;
 }
+template <int ROWS>
 __device__ __forceinline__ uint32_t tiles_of(uint32_t entries) {
-    return (uint32_t)(((uint64_t)entries + RST_TILE - 1) / RST_TILE);
+    constexpr uint32_t TILE = ROWS * RST_BLOCK;
+    return entries / TILE + (entries % TILE ? 1u : 0u);
 }
 
 // at[c] + the number of s[at[c] .. top[c]) that are below x[c], for the entries of a thread.
@@ -70,18 +74,20 @@ __device__ __forceinline__ void lower_bounds(const uint32_t* s, uint32_t (&at)[R
 // every LDS access (ten steps of a binary search 2.5 us), so sixteen waves share the
 // work of a tile (four waves, four entries a thread: 13.6 and 8.4 us for the first launch,
 // 11.9 and 6.2 so), and the table is eight times the entries (four times: 6.8).
-__device__ __forceinline__ Membership tile_members(const uint32_t* __restrict__ local_idx, uint32_t base,
-                                                   uint32_t end, const uint32_t* __restrict__ global_idx,
-                                                   uint32_t ng, RestoreMemory& lds) {
+template <int ROWS>
+__device__ __forceinline__ Membership<ROWS> tile_members(const uint32_t* __restrict__ local_idx, uint32_t base,
+                                                         uint32_t end, const uint32_t* __restrict__ global_idx,
+                                                         uint32_t ng, RestoreMemory& lds) {
     constexpr uint32_t EMPTY = ~0u;                  // no index: vectors are shorter than 2^32
+    static_assert(4 * ROWS * RST_BLOCK <= RST_TABLE, "a quarter of the table");
     const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid >> 6;
-    Membership m;
+    Membership<ROWS> m;
     constexpr int PER = RST_SAMPLES / RST_BLOCK;
     const uint32_t apart = ng / RST_SAMPLES + 1;
     uint32_t sample[PER];
     uint64_t place[PER];
 #pragma unroll
-    for (int c = 0; c < RST_ROWS; ++c) {
+    for (int c = 0; c < ROWS; ++c) {
         const uint32_t j = base + c * RST_BLOCK + tid;
         m.active[c] = j < end;
         m.idx[c] = m.active[c] ? local_idx[j] : EMPTY;
@@ -125,9 +131,9 @@ __device__ __forceinline__ Membership tile_members(const uint32_t* __restrict__ 
             v[u] = i < part ? global_idx[w0 + i] : EMPTY;
         }
         auto slot_of = [](uint32_t key) { return key * 2654435769u >> (32 - RST_TABLE_BITS); };
-        uint32_t slot[RST_ROWS];
+        uint32_t slot[ROWS];
 #pragma unroll
-        for (int c = 0; c < RST_ROWS; ++c) {
+        for (int c = 0; c < ROWS; ++c) {
             slot[c] = slot_of(m.idx[c]);
             if (m.active[c])
                 while (true) {                       // a quarter of the table is filled at most, so it ends
@@ -163,7 +169,7 @@ __device__ __forceinline__ Membership tile_members(const uint32_t* __restrict__ 
             }
         __syncthreads();
 #pragma unroll
-        for (int c = 0; c < RST_ROWS; ++c) m.member[c] = m.active[c] && lds.table.hit[slot[c]] != 0;
+        for (int c = 0; c < ROWS; ++c) m.member[c] = m.active[c] && lds.table.hit[slot[c]] != 0;
         return m;
     }
     // ---- a long part ----
@@ -182,15 +188,15 @@ __device__ __forceinline__ Membership tile_members(const uint32_t* __restrict__ 
         for (int u = 0; u < FLIGHT; ++u) lds.window[u * RST_BLOCK + tid] = v[u];
     }
     __syncthreads();
-    uint32_t at[RST_ROWS], top[RST_ROWS], lo[RST_ROWS], hi[RST_ROWS];
+    uint32_t at[ROWS], top[ROWS], lo[ROWS], hi[ROWS];
 #pragma unroll
-    for (int c = 0; c < RST_ROWS; ++c) {
+    for (int c = 0; c < ROWS; ++c) {
         at[c] = 0;
         top[c] = m.active[c] ? staged : 0u;
     }
-    lower_bounds<RST_ROWS>(lds.window, at, top, m.idx, staged);
+    lower_bounds<ROWS>(lds.window, at, top, m.idx, staged);
 #pragma unroll
-    for (int c = 0; c < RST_ROWS; ++c) {
+    for (int c = 0; c < ROWS; ++c) {
         m.member[c] = m.active[c] && at[c] < staged && lds.window[at[c]] == m.idx[c];
         lo[c] = at[c] ? w0 + (at[c] - 1) * step + 1 : w0;                        // elements lo .. hi - 1 are left
         const uint64_t next = (uint64_t)w0 + (uint64_t)at[c] * step;
@@ -199,7 +205,7 @@ __device__ __forceinline__ Membership tile_members(const uint32_t* __restrict__ 
     }
     if (step > RST_BETWEEN + 1) {                    // a part of more than 70,000
 #pragma unroll
-        for (int c = 0; c < RST_ROWS; ++c)
+        for (int c = 0; c < ROWS; ++c)
             while (hi[c] - lo[c] > RST_BETWEEN) {
                 const uint32_t mid = lo[c] + ((hi[c] - lo[c]) >> 1), x = global_idx[mid];
                 if (x < m.idx[c]) {
@@ -212,26 +218,47 @@ __device__ __forceinline__ Membership tile_members(const uint32_t* __restrict__ 
     }
     // Equal is a member, wherever it stands, so a read may reach past both ends of what is left.
     constexpr uint32_t QUADS = RST_BETWEEN / 4;
-    QuadAt4 v[QUADS][RST_ROWS];
+    QuadAt4 v[QUADS][ROWS];
 #pragma unroll
     for (uint32_t q = 0; q < QUADS; ++q)
 #pragma unroll
-        for (int c = 0; c < RST_ROWS; ++c)
+        for (int c = 0; c < ROWS; ++c)
             v[q][c] = *reinterpret_cast<const QuadAt4*>(global_idx + (lo[c] < ng - 4 * (q + 1) ? lo[c] + 4 * q : ng - 4));
 #pragma unroll
     for (uint32_t q = 0; q < QUADS; ++q)
 #pragma unroll
-        for (int c = 0; c < RST_ROWS; ++c)
+        for (int c = 0; c < ROWS; ++c)
 #pragma unroll
             for (int j = 0; j < 4; ++j) m.member[c] |= m.active[c] && v[q][c].v[j] == m.idx[c];
     return m;
 }
 
-// ZERO_MEMBERS false: the vector has every local entry zeroed already, the entries
-// outside the intersection get their value back.  true: the vector is the
-// untouched accumulator, the entries of the intersection are zeroed (local_val
-// is not read).  `masks`, if there is room for them: a bit per entry, the tile's ballots
-// row by row and wave by wave.
+// The tile's entries looked up and the vector put right.  ZERO_MEMBERS false: the vector has
+// every local entry zeroed already, the entries outside the intersection get their value
+// back.  true: the vector is the untouched accumulator, the entries of the intersection
+// are zeroed (local_val is not read).
+template <int ROWS, bool ZERO_MEMBERS>
+__device__ __forceinline__ Membership<ROWS> restore_tile(float* residual, uint32_t n, const uint32_t* local_idx,
+                                                         const float* local_val, uint32_t base, uint32_t end,
+                                                         const uint32_t* global_idx, uint32_t ng, RestoreMemory& lds) {
+    float value[ROWS];
+    if (!ZERO_MEMBERS) {
+#pragma unroll
+        for (int c = 0; c < ROWS; ++c) {
+            const uint32_t j = base + c * RST_BLOCK + threadIdx.x;
+            value[c] = j < end ? local_val[j] : 0.0f;
+        }
+    }
+    const Membership<ROWS> m = tile_members<ROWS>(local_idx, base, end, global_idx, ng, lds);
+#pragma unroll
+    for (int c = 0; c < ROWS; ++c)
+        if (m.active[c] && m.member[c] == ZERO_MEMBERS && m.idx[c] < n)
+            residual[m.idx[c]] = ZERO_MEMBERS ? 0.0f : value[c];
+    return m;
+}
+
+// `masks`, if the matched indices are wanted: a bit per entry, the tile's ballots row by row
+// and wave by wave.
 template <bool ZERO_MEMBERS>
 __global__ __launch_bounds__(RST_BLOCK) void intersect_kernel(
     float* __restrict__ residual, uint32_t n, const uint32_t* __restrict__ local_idx,
@@ -243,26 +270,17 @@ __global__ __launch_bounds__(RST_BLOCK) void intersect_kernel(
     __shared__ uint32_t s_count[RST_WAVES];
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid >> 6;
     const uint32_t nl = entries_of(d_local_nnz, max_local), ng = entries_of(d_global_nnz, max_global);
-    const uint32_t used = tiles_of(nl);
+    const uint32_t used = tiles_of<RST_ROWS>(nl);
     // The room a caller has, which sizes the launch, is often several times the entries there
     // are, and a workgroup of sixteen waves costs something also where it finds nothing to
     // do: no more are launched than run at a time.
     for (uint32_t tile = blockIdx.x; tile < used; tile += gridDim.x) {
         const uint32_t base = tile * RST_TILE, end = nl - base > RST_TILE ? base + RST_TILE : nl;
-        float value[RST_ROWS];
-        if (!ZERO_MEMBERS) {
-#pragma unroll
-            for (int c = 0; c < RST_ROWS; ++c) {
-                const uint32_t j = base + c * RST_BLOCK + tid;
-                value[c] = j < end ? local_val[j] : 0.0f;
-            }
-        }
-        const Membership m = tile_members(local_idx, base, end, global_idx, ng, s_memory);
+        const Membership<RST_ROWS> m = restore_tile<RST_ROWS, ZERO_MEMBERS>(residual, n, local_idx, local_val, base, end,
+                                                                            global_idx, ng, s_memory);
         uint32_t found = 0;
 #pragma unroll
         for (int c = 0; c < RST_ROWS; ++c) {
-            if (m.active[c] && m.member[c] == ZERO_MEMBERS && m.idx[c] < n)
-                residual[m.idx[c]] = ZERO_MEMBERS ? 0.0f : value[c];
             const uint64_t ballot = __ballot(m.member[c]);
             if (masks && lane == 0) masks[(size_t)tile * (RST_TILE / WAVE) + c * RST_WAVES + wave] = ballot;
             found += (uint32_t)__popcll(ballot);
@@ -279,6 +297,84 @@ __global__ __launch_bounds__(RST_BLOCK) void intersect_kernel(
     }
 }
 
+// The matched indices of a tile from the waves' ballots (s_row has a word per row and wave):
+// tile_count says how many there are (one barrier), emit_tile writes them from `at` on.
+template <int ROWS>
+__device__ __forceinline__ uint32_t tile_count(const uint64_t (&ballot)[ROWS], uint32_t (&s_row)[ROWS][RST_WAVES]) {
+    const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int c = 0; c < ROWS; ++c)
+        if (lane == 0) s_row[c][wave] = (uint32_t)__popcll(ballot[c]);
+    __syncthreads();
+    uint32_t total = 0;
+#pragma unroll
+    for (int c = 0; c < ROWS; ++c)
+#pragma unroll
+        for (int w = 0; w < RST_WAVES; ++w) total += s_row[c][w];
+    return total;
+}
+template <int ROWS>
+__device__ __forceinline__ void emit_tile(const uint32_t (&idx)[ROWS], const uint64_t (&ballot)[ROWS],
+                                          const uint32_t (&s_row)[ROWS][RST_WAVES], uint32_t at, uint32_t* indexes_out) {
+    const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int c = 0; c < ROWS; ++c) {
+#pragma unroll
+        for (int w = 0; w < RST_WAVES; ++w) {
+            if (w == wave && (ballot[c] >> lane & 1u)) indexes_out[at + mask_rank(ballot[c])] = idx[c];
+            at += s_row[c][w];
+        }
+    }
+}
+
+// The same in one launch, a tile's place from a scan across the workgroups: for a workspace
+// without room for a bit per entry.  A ticket is 30 ns and they are served one at a time, so
+// a tile has twice the entries here, and workgroups without entries leave before they take
+// one.  1.1 M entries in a list of 1.6 M 33.8 us a call, 4.3 M in 5.0 M 114; looking everything
+// up again in the second launch instead 52.2 and 189, workgroups that take several tiles of
+// 1024 in turn 54.2 and 179.
+template <bool ZERO_MEMBERS>
+__global__ __launch_bounds__(RST_BLOCK) void intersect_chained_kernel(
+    float* residual, uint32_t n, const uint32_t* local_idx, const float* local_val, const uint64_t* d_local_nnz,
+    uint32_t max_local, const uint32_t* global_idx, const uint64_t* d_global_nnz, uint32_t max_global,
+    uint32_t* indexes_out, uint64_t* count_out, ScanHeader* hdr, uint64_t* tile_desc, uint64_t* group_desc) {
+    constexpr int ROWS = RST_CHAINED_ROWS;
+    constexpr uint32_t TILE = ROWS * RST_BLOCK;
+    __shared__ RestoreMemory s_memory;
+    __shared__ uint32_t s_row[ROWS][RST_WAVES];
+    __shared__ uint32_t s_tile, s_before[2];
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid >> 6;
+    const uint32_t nl = entries_of(d_local_nnz, max_local), ng = entries_of(d_global_nnz, max_global);
+    const uint32_t used = tiles_of<ROWS>(nl);
+    if (used == 0 && blockIdx.x == 0 && tid == 0) *count_out = 0;
+    if (blockIdx.x >= used) return;
+    if (tid == 0) s_tile = atomicAdd(&hdr->ticket, 1u);
+    __syncthreads();
+    const uint32_t tile = uniform(s_tile), base = tile * TILE, end = nl - base > TILE ? base + TILE : nl;
+    const Membership<ROWS> m = restore_tile<ROWS, ZERO_MEMBERS>(residual, n, local_idx, local_val, base, end, global_idx,
+                                                                ng, s_memory);
+    uint64_t ballot[ROWS];
+#pragma unroll
+    for (int c = 0; c < ROWS; ++c) ballot[c] = __ballot(m.member[c]);
+    const uint32_t aggregate = tile_count(ballot, s_row), group = tile / SCAN_GROUP;
+    if (wave == 0) {
+        const uint32_t before = scan_within_group(hdr, tile_desc, group_desc, tile, aggregate);
+        if (lane == 0) s_before[0] = before;
+    } else if (wave == 1) {
+        const uint32_t before = scan_across_groups(hdr, group_desc, group);
+        if (lane == 0) s_before[1] = before;
+    }
+    __syncthreads();
+    const uint32_t exclusive = s_before[0] + s_before[1];
+    if (tid == 0 && group != 0 && tile % SCAN_GROUP == SCAN_GROUP - 1)
+        scan_close_group(group_desc, group, exclusive + aggregate);
+    if (tile == used - 1 && tid == 0) {
+        const bool failed = __hip_atomic_load(&hdr->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+        *count_out = failed ? ~0ull : (uint64_t)exclusive + aggregate;
+    }
+    emit_tile(m.idx, ballot, s_row, exclusive, indexes_out);
+}
+
 // Sum over the workgroup (one barrier; s_wave has a word per wave).
 __device__ __forceinline__ uint32_t block_sum(uint32_t v, uint32_t* s_wave) {
     v = wave_sum(v);
@@ -292,24 +388,22 @@ __device__ __forceinline__ uint32_t block_sum(uint32_t v, uint32_t* s_wave) {
 
 // The matched indices, in order: a tile's place is the sum of the counts before it
 // (adding up RST_DIRECT_TILES counts takes a workgroup two microseconds; of more tiles
-// than that intersect_scan_kernel has made prefixes of the counts).  MASKS false: the
-// first launch had no room for its bits, and the tile is searched again.
-template <bool MASKS, bool PREFIXES>
+// than that intersect_scan_kernel has made prefixes of the counts).
+template <bool PREFIXES>
 __global__ __launch_bounds__(RST_BLOCK) void intersect_emit_kernel(
     const uint32_t* __restrict__ local_idx, const uint64_t* __restrict__ d_local_nnz, uint32_t max_local,
-    const uint32_t* __restrict__ global_idx, const uint64_t* __restrict__ d_global_nnz, uint32_t max_global,
     const uint32_t* __restrict__ counts, const uint64_t* __restrict__ masks,
     uint32_t* __restrict__ indexes_out, uint64_t* __restrict__ count_out) {
-    __shared__ uint32_t s_sum[RST_WAVES], s_row[RST_ROWS][RST_WAVES];
-    __shared__ typename std::conditional<MASKS, uint32_t, RestoreMemory>::type s_memory;   // to search again
-    const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid >> 6;
-    const uint32_t nl = entries_of(d_local_nnz, max_local), used = tiles_of(nl);
+    __shared__ uint32_t s_sum[RST_WAVES];
+    __shared__ uint32_t s_row[RST_ROWS][RST_WAVES];
+    const int tid = threadIdx.x, wave = tid >> 6;
+    const uint32_t nl = entries_of(d_local_nnz, max_local), used = tiles_of<RST_ROWS>(nl);
     if (used == 0 && blockIdx.x == 0 && tid == 0) *count_out = 0;
     for (uint32_t tile = blockIdx.x; tile < used; tile += gridDim.x) {
         const uint32_t base = tile * RST_TILE, end = nl - base > RST_TILE ? base + RST_TILE : nl;
         uint32_t idx[RST_ROWS];
         uint64_t ballot[RST_ROWS];
-        if (MASKS && indexes_out) {
+        if (indexes_out) {
 #pragma unroll
             for (int c = 0; c < RST_ROWS; ++c) {
                 const uint32_t j = base + c * RST_BLOCK + tid;
@@ -330,29 +424,9 @@ __global__ __launch_bounds__(RST_BLOCK) void intersect_emit_kernel(
             __syncthreads();                             // s_sum has been read
             continue;
         }
-        if constexpr (!MASKS) {
-            const Membership m = tile_members(local_idx, base, end, global_idx,
-                                              entries_of(d_global_nnz, max_global), s_memory);
-#pragma unroll
-            for (int c = 0; c < RST_ROWS; ++c) {
-                idx[c] = m.idx[c];
-                ballot[c] = __ballot(m.member[c]);
-            }
-        }
-#pragma unroll
-        for (int c = 0; c < RST_ROWS; ++c)
-            if (lane == 0) s_row[c][wave] = (uint32_t)__popcll(ballot[c]);
-        __syncthreads();
-        uint32_t at = before;
-#pragma unroll
-        for (int c = 0; c < RST_ROWS; ++c) {
-#pragma unroll
-            for (int w = 0; w < RST_WAVES; ++w) {
-                if (w == wave && (ballot[c] >> lane & 1u)) indexes_out[at + mask_rank(ballot[c])] = idx[c];
-                at += s_row[c][w];
-            }
-        }
-        __syncthreads();                             // LDS is free again
+        tile_count(ballot, s_row);
+        emit_tile(idx, ballot, s_row, before, indexes_out);
+        __syncthreads();                                 // LDS is free again
     }
 }
 
@@ -360,7 +434,7 @@ __global__ __launch_bounds__(RST_BLOCK) void intersect_emit_kernel(
 __global__ __launch_bounds__(RST_SCAN_BLOCK) void intersect_scan_kernel(
     const uint64_t* __restrict__ d_local_nnz, uint32_t max_local, uint32_t* __restrict__ counts) {
     __shared__ uint32_t s_wave[RST_SCAN_BLOCK / WAVE];
-    const uint32_t tid = threadIdx.x, wave = tid >> 6, used = tiles_of(entries_of(d_local_nnz, max_local));
+    const uint32_t tid = threadIdx.x, wave = tid >> 6, used = tiles_of<RST_ROWS>(entries_of(d_local_nnz, max_local));
     uint32_t before = 0;
     for (uint32_t t0 = 0; t0 < used; t0 += RST_SCAN_BLOCK) {
         const uint32_t c = t0 + tid < used ? counts[t0 + tid] : 0u;
@@ -400,10 +474,23 @@ static int launch_intersect(float* d_vec, uint64_t n, const uint32_t* d_local_id
     const uint32_t ntiles = (uint32_t)restore_tiles(max_local);
     if (!d_ws || !aligned(d_ws, 256) || ws_bytes < restore_ws_bytes(max_local))
         return OKT_ERR_WORKSPACE;
-    uint32_t* counts = (uint32_t*)d_ws;                              // one more than there are tiles
     const bool room = ws_bytes >= restore_masks_at(max_local) + (size_t)ntiles * (RST_TILE / 8);
+    if (d_indexes_out_or_null && !room) {
+        constexpr uint64_t TILE = RST_CHAINED_ROWS * RST_BLOCK;
+        const uint32_t tiles = max_local ? (uint32_t)((max_local + TILE - 1) / TILE) : 1u;
+        uint64_t* tile_desc = (uint64_t*)((char*)d_ws + SCAN_HEADER_BYTES);
+        if (launch_clear_scan_state(d_ws, scan_ws_bytes(tiles) / 8, s) != hipSuccess) return OKT_ERR_HIP;
+        timing_before(s);
+        hipLaunchKernelGGL(intersect_chained_kernel<ZERO_MEMBERS>, dim3(tiles), dim3(RST_BLOCK), 0, s, d_vec,
+                           (uint32_t)n, d_local_idx, d_local_val, d_local_nnz, (uint32_t)max_local, d_global_idx,
+                           d_global_nnz, (uint32_t)max_global, d_indexes_out_or_null, d_count_out,
+                           (ScanHeader*)d_ws, tile_desc, tile_desc + tiles);
+        timing_after(s);
+        return launch_status();
+    }
     const uint32_t grid = ntiles < RST_PER_CU * device_cus() ? ntiles : RST_PER_CU * device_cus();
-    uint64_t* masks = room && d_indexes_out_or_null ? (uint64_t*)((char*)d_ws + restore_masks_at(max_local)) : nullptr;
+    uint32_t* counts = (uint32_t*)d_ws;                              // one more than there are tiles
+    uint64_t* masks = d_indexes_out_or_null ? (uint64_t*)((char*)d_ws + restore_masks_at(max_local)) : nullptr;
     timing_before(s);
     hipLaunchKernelGGL(intersect_kernel<ZERO_MEMBERS>, dim3(grid), dim3(RST_BLOCK), 0, s, d_vec,
                        (uint32_t)n, d_local_idx, d_local_val, d_local_nnz, (uint32_t)max_local,
@@ -413,10 +500,8 @@ static int launch_intersect(float* d_vec, uint64_t n, const uint32_t* d_local_id
     if (prefixes)
         hipLaunchKernelGGL(intersect_scan_kernel, dim3(1), dim3(RST_SCAN_BLOCK), 0, s, d_local_nnz,
                            (uint32_t)max_local, counts);
-    auto* emit = room ? (prefixes ? intersect_emit_kernel<true, true> : intersect_emit_kernel<true, false>)
-                      : (prefixes ? intersect_emit_kernel<false, true> : intersect_emit_kernel<false, false>);
-    hipLaunchKernelGGL(emit, dim3(grid), dim3(RST_BLOCK), 0, s, d_local_idx, d_local_nnz,
-                       (uint32_t)max_local, d_global_idx, d_global_nnz, (uint32_t)max_global, counts, masks,
+    hipLaunchKernelGGL(prefixes ? intersect_emit_kernel<true> : intersect_emit_kernel<false>, dim3(grid),
+                       dim3(RST_BLOCK), 0, s, d_local_idx, d_local_nnz, (uint32_t)max_local, counts, masks,
                        d_indexes_out_or_null, d_count_out);
     return launch_status();
 }

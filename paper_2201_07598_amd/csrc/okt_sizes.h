@@ -138,6 +138,7 @@ constexpr uint64_t SLOT_MIN_N_ACCUMULATE = 24u << 20;
 constexpr int RST_BLOCK = 1024, RST_WAVES = RST_BLOCK / 64;
 constexpr int RST_ROWS = 1;                              // entries per thread
 constexpr uint32_t RST_TILE = RST_BLOCK * RST_ROWS;      // local entries per workgroup
+constexpr int RST_CHAINED_ROWS = 2;                      // the same in the form with a scan across workgroups
 constexpr uint32_t RST_SAMPLES = 1024;                   // places of the global list that say where a tile's part of it lies
 constexpr uint32_t RST_WINDOW = 4096;                    // elements of that part that a workgroup holds at a time
 constexpr uint32_t RST_BETWEEN = 16;                     // elements between two of a longer part's that are read and compared

@@ -79,6 +79,34 @@ def test_intersection_of_a_sparse_tile_with_a_long_list():
     assert bits_equal(got, orc.residual_update(acc, want))
 
 
+def test_intersection_waits_that_give_up_are_reported():
+    """The least workspace has no room for a bit per entry: places come from a scan across
+    workgroups, whose waits are limited to one poll here.  A call completes or reports
+    UINT64_MAX; it never hangs.  More tiles than workgroups are launched."""
+    rng = np.random.default_rng(7)
+    n = 2_000_000
+    acc = rng.normal(size=n).astype(np.float32)
+    local, glob = ascending(rng, n, 700_000), ascending(rng, n, 900_000)
+    want = orc.index_intersection(local, glob)
+    d_res, d_local, d_glob = to_dev(acc), to_dev(local), to_dev(glob)
+    d_nl, d_ng = (to_dev(np.array([a.size], np.uint64)) for a in (local, glob))
+    out = torch.full((local.size,), -1, dtype=torch.int32, device=DEV)
+    ws = workspace(least_bytes(local.size))[:least_bytes(local.size)]
+    for limit in (1, 0):
+        okt.okt_debug_spin_limit(limit)
+        try:
+            for _ in range(3):
+                cnt = torch.full((1,), -5, dtype=torch.int64, device=DEV)
+                okt.okt_index_intersect_zero(d_res, d_local, d_nl, d_glob, d_ng, cnt, ws, indexes_out=out)
+                torch.cuda.synchronize()
+                c = int(u64(cnt)[0])
+                if limit == 0 or c != 0xFFFFFFFFFFFFFFFF:
+                    assert c == want.size and np.array_equal(u32(out[:c]), want)
+        finally:
+            okt.okt_debug_spin_limit(0)
+    assert bits_equal(d_res.cpu().numpy(), orc.residual_update(acc, want))
+
+
 def test_intersection_of_more_tiles_than_are_added_up():
     """More than 4096 tiles of room: the counts are made prefixes by a launch of their own."""
     rng = np.random.default_rng(6)
