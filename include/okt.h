@@ -33,7 +33,7 @@
  *     thread, the test hooks (okt_debug_...) on the whole process.
  *   - The kernels that place their output through a scan across workgroups
  *     (the select family, the reduce family, the index intersection in the least
- *     workspace it accepts), and those
+ *     workspace it accepts or in place), and those
  *     that find the exact threshold digit by digit, wait for one another through
  *     device memory.  Every such wait ends by construction
  *     and is bounded all the same; should one run out, the kernel still exits
@@ -455,6 +455,8 @@ int okt_coo_threshold_select(const uint32_t* d_idx_in, const float* d_val_in,
  *   d_count_out       out uint64[1] the size of the intersection
  * Local indices must be strictly ascending and below n, global indices ascending
  * (anything else is undefined, except that an index >= n is never written to).
+ * d_indexes_out_or_null may be d_local_idx or d_global_idx itself, and d_count_out one of
+ * the two counts; the call then takes a form with a scan across workgroups.
  * Workspace: okt_workspace_bytes(max_local, 0).
  */
 int okt_index_intersect_restore(float* d_residual_inout, uint64_t n,

@@ -258,6 +258,10 @@ __global__ void gather_ceiling_kernel(const uint32_t* idx_cat, const float* val_
                                       uint32_t table_offset);
 
 inline bool aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
+// Whether two buffers of so many bytes share any.
+inline bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
+    return (uintptr_t)a < (uintptr_t)b + b_bytes && (uintptr_t)b < (uintptr_t)a + a_bytes;
+}
 
 }  // namespace okt
 #endif

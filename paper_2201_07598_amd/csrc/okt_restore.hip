@@ -11,8 +11,8 @@
 // consecutive local entries and looks them up in the global list (tile_members).
 // A second launch writes the matched indices in ascending order: the first left which
 // of a tile's entries matched (a bit each) and how many, and every workgroup adds up
-// the counts of the tiles before its own.  A call whose workspace has no room for the bits
-// finds a tile's place with a scan across workgroups instead.
+// the counts of the tiles before its own.  A call whose workspace has no room for the bits,
+// or that writes over its inputs, finds a tile's place with a scan across workgroups instead.
 #include "okt_device.h"
 #include "okt_search.h"
 #include "okt_select_kernel.h"
@@ -328,7 +328,10 @@ __device__ __forceinline__ void emit_tile(const uint32_t (&idx)[ROWS], const uin
 }
 
 // The same in one launch, a tile's place from a scan across the workgroups: for a workspace
-// without room for a bit per entry.  A ticket is 30 ns and they are served one at a time, so
+// without room for a bit per entry, and for outputs that take the place of an input: what a
+// tile writes, the indices and the count, goes out when it and all tiles before it have
+// read theirs, where the second launch of the other form reads the local list and its
+// length again.  A ticket is 30 ns and they are served one at a time, so
 // a tile has twice the entries here, and workgroups without entries leave before they take
 // one.  1.1 M entries in a list of 1.6 M 33.8 us a call, 4.3 M in 5.0 M 114; looking everything
 // up again in the second launch instead 52.2 and 189, workgroups that take several tiles of
@@ -372,7 +375,7 @@ __global__ __launch_bounds__(RST_BLOCK) void intersect_chained_kernel(
         const bool failed = __hip_atomic_load(&hdr->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
         *count_out = failed ? ~0ull : (uint64_t)exclusive + aggregate;
     }
-    emit_tile(m.idx, ballot, s_row, exclusive, indexes_out);
+    if (indexes_out) emit_tile(m.idx, ballot, s_row, exclusive, indexes_out);
 }
 
 // Sum over the workgroup (one barrier; s_wave has a word per wave).
@@ -475,7 +478,11 @@ static int launch_intersect(float* d_vec, uint64_t n, const uint32_t* d_local_id
     if (!d_ws || !aligned(d_ws, 256) || ws_bytes < restore_ws_bytes(max_local))
         return OKT_ERR_WORKSPACE;
     const bool room = ws_bytes >= restore_masks_at(max_local) + (size_t)ntiles * (RST_TILE / 8);
-    if (d_indexes_out_or_null && !room) {
+    const size_t out_bytes = d_indexes_out_or_null ? 4 * (size_t)max_local : 0;
+    const bool over_input = overlap(d_count_out, 8, d_local_nnz, 8) || overlap(d_count_out, 8, d_global_nnz, 8) ||
+                            overlap(d_indexes_out_or_null, out_bytes, d_local_idx, 4 * (size_t)max_local) ||
+                            overlap(d_indexes_out_or_null, out_bytes, d_global_idx, 4 * (size_t)max_global);
+    if (over_input || (d_indexes_out_or_null && !room)) {
         constexpr uint64_t TILE = RST_CHAINED_ROWS * RST_BLOCK;
         const uint32_t tiles = max_local ? (uint32_t)((max_local + TILE - 1) / TILE) : 1u;
         uint64_t* tile_desc = (uint64_t*)((char*)d_ws + SCAN_HEADER_BYTES);

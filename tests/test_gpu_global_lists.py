@@ -79,6 +79,38 @@ def test_intersection_of_a_sparse_tile_with_a_long_list():
     assert bits_equal(got, orc.residual_update(acc, want))
 
 
+# a few tiles, and more than run at a time
+@pytest.mark.parametrize("nl,ng", [(900, 1_300), (5_000, 7_000), (700_000, 900_000)])
+@pytest.mark.parametrize("over", ["local", "global", "counts"])
+@pytest.mark.parametrize("zero", [False, True])
+def test_intersection_written_over_its_input(nl, ng, over, zero):
+    """The matched indices take the place of the local or the global list, the count that of
+    an input's count."""
+    rng = np.random.default_rng(nl)
+    n = 2_000_000
+    acc = rng.normal(size=n).astype(np.float32)
+    local, glob = ascending(rng, n, nl), ascending(rng, n, ng)
+    want = orc.index_intersection(local, glob)
+    residual = acc.copy()
+    if not zero:
+        residual[local] = 0.0
+    d_res, d_val = to_dev(residual), to_dev(acc[local])
+    d_local, d_glob = to_dev(local), to_dev(glob)
+    d_nl, d_ng = (to_dev(np.array([a.size], np.uint64)) for a in (local, glob))
+    out = {"local": d_local, "global": d_glob}.get(over)
+    if out is None:
+        out = torch.full((nl,), -1, dtype=torch.int32, device=DEV)
+    cnt = d_nl if over != "global" else d_ng
+    ws = workspace(okt.okt_workspace_bytes(nl, 0))
+    if zero:
+        okt.okt_index_intersect_zero(d_res, d_local, d_nl, d_glob, d_ng, cnt, ws, indexes_out=out)
+    else:
+        okt.okt_index_intersect_restore(d_res, d_local, d_val, d_nl, d_glob, d_ng, cnt, ws, indexes_out=out)
+    assert int(u64(cnt)[0]) == want.size
+    assert np.array_equal(u32(out[:want.size]), want)
+    assert bits_equal(d_res.cpu().numpy(), orc.residual_update(acc, want))
+
+
 def test_intersection_waits_that_give_up_are_reported():
     """The least workspace has no room for a bit per entry: places come from a scan across
     workgroups, whose waits are limited to one poll here.  A call completes or reports
