@@ -423,7 +423,8 @@ int okt_sparse_reduce_batch(const uint32_t* d_idx_cat, const float* d_val_cat,
  *   d_threshold         in  fp32[1] the global threshold (its sign is ignored)
  *   d_idx_out, d_val_out out uint32/fp32[capacity]  the entries j, in order, with
  *                       key(val[j]) >= key(*d_threshold); bit copies
- *   d_nnz_out           out uint64[2] {emitted = min(selected, capacity), selected}
+ *   d_nnz_out           out uint64[2] {emitted = min(selected, capacity), selected};
+ *                       may begin at d_nnz_in
  * Workspace: okt_workspace_bytes(max_nnz, 0).  max_nnz = 0 gives {0, 0}.
  * The global threshold itself (Algorithm 1, lines 9-12) is
  * okt_topk_threshold_exact applied to the value array of the gathered reduced

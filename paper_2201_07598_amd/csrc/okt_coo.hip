@@ -61,15 +61,15 @@ __device__ __forceinline__ uint32_t coo_length(const uint64_t* d_nnz_in, uint32_
 constexpr int COO_SMALL_BLOCK = 1024;
 template <int ROWS>                              // quads per thread
 __global__ __launch_bounds__(COO_SMALL_BLOCK) void coo_small_kernel(
-    const uint32_t* __restrict__ idx_in, const float* __restrict__ val_in, const uint64_t* __restrict__ d_nnz_in,
-    uint32_t max_nnz, const float* __restrict__ d_threshold, uint32_t* __restrict__ idx_out,
-    float* __restrict__ val_out, uint64_t capacity, uint64_t* __restrict__ nnz_out) {
+    const uint32_t* idx_in, const float* val_in, const uint64_t* d_nnz_in, uint32_t max_nnz, const float* d_threshold,
+    uint32_t* idx_out, float* val_out, uint64_t capacity, uint64_t* nnz_out) {
     constexpr int WAVES = COO_SMALL_BLOCK / WAVE, CELLS = ROWS * WAVES;
     static_assert(CELLS <= 2 * WAVE && CELLS % 2 == 0, "two cells a lane");
     __shared__ uint32_t s_cell[CELLS + 1];
     const uint32_t tid = threadIdx.x;
     const int lane = tid & (WAVE - 1), wave = (int)uniform(tid >> 6);
-    // everything is asked for at once, up to the host's bound
+    // Everything is asked for at once, up to the host's bound, and read before anything is
+    // written: outputs may take the place of inputs.
     CooQuad q[ROWS];
     uint32_t idx[ROWS][4], incl[ROWS];
 #pragma unroll
@@ -248,7 +248,11 @@ extern "C" int okt_coo_threshold_select(const uint32_t* d_idx_in, const float* d
         timing_after(s);
         return launch_status();
     }
-    if (max_nnz <= COO_TILED_N) {
+    // The second launch by tiles reads the length and the values again while other workgroups
+    // already write: outputs that take their place are for the kernel for long lists.
+    const uint64_t most_out = capacity < max_nnz ? capacity : max_nnz;
+    const bool over_input = overlap(d_nnz_out, 16, d_nnz_in, 8) || overlap(d_val_out, 4 * most_out, d_val_in, 4 * max_nnz);
+    if (max_nnz <= COO_TILED_N && !over_input) {
         uint16_t* counts = (uint16_t*)d_ws;
         const dim3 grid((unsigned)((max_nnz + COO_TILE - 1) / COO_TILE));
         hipLaunchKernelGGL(coo_count_kernel, grid, dim3(COO_BLOCK), 0, s, d_val_in, d_nnz_in, (uint32_t)max_nnz,

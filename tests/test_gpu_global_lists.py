@@ -177,3 +177,24 @@ def test_coo_select_at_the_lengths_of_its_forms(nnz, slack):
         assert np.array_equal(u32(out_idx[:emitted]), want_idx[:emitted])
         assert bits_equal(out_val[:emitted].cpu().numpy(), want_val[:emitted])
         assert bool((out_idx[emitted:] == -1).all())
+
+
+@pytest.mark.parametrize("nnz,over", [(3_000, "all"), (32_768, "all"), (40_000, "counts"), (40_000, "values"),
+                                      (600_000, "counts"), (600_000, "values")])
+def test_coo_select_written_over_its_input(nnz, over):
+    """The counts, the values or, in a list that one workgroup selects, all outputs take the
+    place of their inputs."""
+    rng = np.random.default_rng(nnz)
+    idx = np.cumsum(rng.integers(1, 9, nnz), dtype=np.uint64).astype(np.uint32)
+    val = rng.normal(size=nnz).astype(np.float32)
+    th = np.float32(1.1)
+    want_idx, want_val, total = orc.coo_threshold_select(idx, val, th)
+    d_th, ws = to_dev(np.array([th])), workspace(okt.okt_workspace_bytes(nnz, 0))
+    for _ in range(5):
+        d_idx, d_val, d_nnz = to_dev(idx), to_dev(val), to_dev(np.array([nnz, nnz], np.uint64))
+        out_idx = d_idx if over == "all" else torch.full((nnz,), -1, dtype=torch.int32, device=DEV)
+        out_val = d_val if over != "counts" else torch.zeros(nnz, device=DEV)
+        out_nnz = d_nnz if over != "values" else torch.zeros(2, dtype=torch.int64, device=DEV)
+        okt.okt_coo_threshold_select(d_idx, d_val, d_nnz, d_th, out_idx, out_val, out_nnz, ws)
+        assert [int(x) for x in u64(out_nnz)] == [total, total]
+        assert np.array_equal(u32(out_idx[:total]), want_idx) and bits_equal(out_val[:total].cpu().numpy(), want_val)
