@@ -606,7 +606,7 @@ __global__ __launch_bounds__(RES_BLOCK) void resolve_kernel(
     auto take = [&](uint32_t key) {
         const uint32_t bin = (key - d.base) >> d.shift;              // below the base: wraps to the far end
         if (bin < d.bins) atomicAdd(&s_hist[bin], 1u);
-        else if (key >= d.base) ++higher;
+        else if ((int32_t)key >= (int32_t)d.base) ++higher;          // (all ones: no candidate)
     };
     // `crowd`: many of the wave's share a bin.  (Ties at the top of the candidates, 1 % of
     // 1 M elements: 47.7 us for the exact threshold with one add an element, 33 so.)
@@ -702,7 +702,7 @@ __global__ __launch_bounds__(RES_BLOCK) void resolve_kernel(
         const uint32_t* vals = reinterpret_cast<const uint32_t*>(cand);
         const uint32_t rows = (len + ROW - 1) / ROW, last = (len - 1) / 4 * 4;
         const int wave = (int)uniform(tid >> 6), lane = tid & (WAVE - 1);
-        uint32_t key[SINGLE_ROWS][4];                                // 0: none (a candidate's is not)
+        uint32_t key[SINGLE_ROWS][4];                                // all ones: none, and in no digit's bins
 #pragma unroll
         for (int r = 0; r < SINGLE_ROWS; ++r)
             if ((uint32_t)r < rows) {
@@ -724,7 +724,7 @@ __global__ __launch_bounds__(RES_BLOCK) void resolve_kernel(
             if ((uint32_t)r < rows) {
 #pragma unroll
                 for (int c = 0; c < 4; ++c)
-                    key[r][c] = r * ROW + 4u * tid + c < len ? key[r][c] & ABS_MASK : 0u;
+                    key[r][c] = r * ROW + 4u * tid + c < len ? key[r][c] & ABS_MASK : ~0u;
             }
         if (tid == 0) s_few = 0;
         while (!d.found) {
@@ -773,7 +773,7 @@ __global__ __launch_bounds__(RES_BLOCK) void resolve_kernel(
                 if ((uint32_t)r < rows) {
                     uint32_t chosen = 0;
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) chosen += (uint32_t)__popcll(__ballot(key[r][c] >= d.base));
+                    for (int c = 0; c < 4; ++c) chosen += (uint32_t)__popcll(__ballot((int32_t)key[r][c] >= (int32_t)d.base));
                     if (lane == 0) s_cell[r * RES_WAVES + wave] = chosen;
                 }
             __syncthreads();
