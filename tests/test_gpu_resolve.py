@@ -129,6 +129,29 @@ def test_candidates_that_share_a_bin(n, k, tied):
     check_threshold(g, k, ws_bytes=64 * 1024)
 
 
+# candidates in one share and in many, vectors that one workgroup takes; up to 16 keys are
+# ranked instead of counted
+@pytest.mark.parametrize("n,k", [(4_003, 40), (60_001, 600), (300_007, 3_000), (2_500_003, 60_000)])
+@pytest.mark.parametrize("close", [1, 2, 15, 16, 17, 63, 64, 65])
+def test_the_last_digit_of_a_few_keys(n, k, close):
+    """`close` keys that differ in the lowest bits alone, some of them equal, and the answer
+    among them: the first, one in the middle, the last, and its neighbours on both sides."""
+    rng = np.random.default_rng(n + close)
+    g = lap(n, n, 1e-6)
+    large = max(int(1.3 * k), 4 * close)
+    bits = np.float32(1.25).view(np.uint32) + rng.choice(400, close, replace=False).astype(np.uint32)
+    bits[close // 2:close // 2 + 2] = bits[close // 2]
+    value = rng.uniform(1.0, 1.9, large).astype(np.float32)
+    value[(value > 1.24) & (value < 1.26)] = np.float32(1.3)
+    value[rng.choice(large, close, replace=False)] = bits.view(np.float32)
+    at = rng.choice(n, large, replace=False)
+    g[at] = value * rng.choice(np.array([-1.0, 1.0], np.float32), large)
+    above = int((value > 1.28).sum())
+    for kk in (above, above + 1, above + (close + 1) // 2, above + close, above + close + 1):
+        check_threshold(g, kk)
+        check_refresh(g, np.zeros(n, np.float32), 1.0, kk, large)
+
+
 @pytest.mark.parametrize("n", [70_001, 300_007, 2_500_003, 4_300_003])
 def test_a_sample_that_sees_zeros(n):
     """Fewer than k elements that are not zero: the sample's bound is zero.  The answer is
