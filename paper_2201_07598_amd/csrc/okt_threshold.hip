@@ -471,10 +471,11 @@ constexpr int RES_BLOCK = SEL_BLOCK;
 constexpr int RES_WAVES = RES_BLOCK / WAVE;
 static_assert(RES_BLOCK == 1024, "pick_bin is written for 1024 threads");
 constexpr int ROWS_MAX = 6;                        // quads of a thread in a share of candidates
-// Up to SINGLE_ROWS rows of candidates are a single share: every workgroup of HELPERS holds all
-// of them in registers, finds the answer for itself and writes out a part.
+// Up to SINGLE_ROWS rows of candidates (ROWS_MAX of the threshold alone) are a single share,
+// if they are spread: every workgroup of HELPERS holds all of them in registers, finds the
+// answer for itself and writes out a part.
 constexpr int SINGLE_ROWS = 10;
-constexpr uint32_t HELPERS = 32;
+constexpr uint32_t HELPERS = 32, ALIKE = 10;
 constexpr uint32_t ROW = RES_BLOCK * 4;
 
 // What the digits run over: the keys of candidates in any order (cand_count of them);
@@ -590,7 +591,25 @@ __global__ __launch_bounds__(RES_BLOCK) void resolve_kernel(
     //   1 M, 2 % (26,400)                     35.2                             30.9
     //   2 M, 1 % (26,600)                     37.3                             34.9
     //   4 M, 1 % (52,000)                     41.0                             42.2 (with room for 81,920)
-    const bool single = use_cand && len <= SINGLE_ROWS * ROW;
+    bool single = use_cand && len <= (SELECT ? SINGLE_ROWS : ROWS_MAX) * ROW;
+    if (single && len > ROWS_MAX * ROW) {
+        // More than ROWS_MAX rows are a single share only if their keys are spread.  Keys that share
+        // a bin queue for one word of LDS, some seven cycles each, and ten rows of them in one
+        // workgroup take longer than a row in each of ten; so does the threshold alone (!SELECT),
+        // as it has no stores to share out.  The first row, which all workgroups see alike,
+        // says it: one of four lanes of some wave is among more than ALIKE in a bin.  Refresh
+        // iterations of 1 M elements (27,000 and 40,000 candidates), us, shares / single / as the
+        // first row says: spread 37.3 / 28.2 / 30.2 and 37.8 / 31.3 / 32.8, of four values
+        // 38.3 / 41.0 / 39.1 and 38.7 / 49.8 / 39.4, half of them equal 40.2 / 47.4 / 40.9.
+        const uint32_t bin = (magnitude_key(cand[4u * tid]) - bound) >> BOUND_SHIFT;
+        uint32_t alike = 0;
+#pragma unroll
+        for (int l = 0; l < WAVE; l += WAVE / 4) {
+            const uint32_t here = (uint32_t)__popcll(__ballot(bin == (uint32_t)__builtin_amdgcn_readlane((int)bin, l)));
+            alike = here > alike ? here : alike;
+        }
+        single = !__syncthreads_or(alike > ALIKE);
+    }
     const uint32_t helpers = !SELECT || !single ? 1u : gridDim.x < HELPERS ? gridDim.x : HELPERS;
     if (blockIdx.x >= (single ? helpers : used)) return;
     // A bound of zero over the whole vector: fewer than k elements, as far as the sample

@@ -40,7 +40,7 @@ def test_threshold_lengths(n):
     check_threshold(np.zeros(n, np.float32), max(1, n // 50))
 
 
-# k and the candidates it brings (about 1.3 k): one row, one share, just more, many shares
+# k and the candidates it brings (about 1.3 k): one row, several, around 24,576, many shares
 @pytest.mark.parametrize("n,k", [(131_072, 40), (300_007, 3_000), (1_000_003, 17_500), (1_000_003, 18_500),
                                  (1_000_003, 20_500), (3_000_001, 60_000), (5_000_011, 300_000),
                                  (5_000_011, 400_000)])
@@ -48,6 +48,40 @@ def test_refresh_shares_of_candidates(n, k):
     g, e = lap(n + k, n), lap(n + k + 1, n, 2e-3)
     check_refresh(g, e, 0.25, k, 2 * k)
     check_refresh(g, e, 0.25, k, k // 2 + 1)
+
+
+def with_candidates(acc, k, count):
+    """`acc` changed where the sample does not look, so that exactly `count` elements pass
+    its bound for k."""
+    bound = sr.bounds_dense(acc, k).min()
+    passing, free = sr.key_of(acc) >= bound, ~sr.sampled(acc.size)
+    there = int(passing.sum())
+    if there > count:
+        acc[np.flatnonzero(passing & free)[:there - count]] = 0.0
+    else:
+        low = np.flatnonzero(~passing & free)[:count - there]
+        acc[low] = np.array([bound], np.uint32).view(np.float32)[0] * np.linspace(1.0, 1.5, low.size, dtype=np.float32)
+    assert sr.bounds_dense(acc, k).min() == bound
+    assert np.count_nonzero(sr.key_of(acc) >= bound) == count
+    return acc
+
+
+# The candidates' limits: a single share of the threshold alone and one of the refresh that
+# takes no vote on it (24,576), the rows after that, the largest single share (40,960).
+# Spread keys are a single share there, keys that are alike are several.
+@pytest.mark.parametrize("count", [24_575, 24_576, 24_577, 28_673, 32_769, 36_864, 36_865, 40_959, 40_960, 40_961])
+@pytest.mark.parametrize("values", [0, 1, 3])
+def test_candidates_at_the_limits_of_a_single_share(count, values):
+    n, k = 1_000_003, int(count / 1.28)
+    g = lap(count + values, n)
+    if values:
+        top = np.argpartition(-np.abs(g), 2 * k)[:2 * k]
+        g[top] = np.random.default_rng(count).choice(np.array([0.25, -0.375, 0.5][:values], np.float32), 2 * k)
+        k = 2 * k * 9 // 16 if values == 3 else k                  # among the two larger of the three; a tie
+    g = with_candidates(g, k, count)
+    check_threshold(g, k)
+    for cap in (count, k, k // 3):
+        check_refresh(g, np.zeros(n, np.float32), 1.0, k, cap)
 
 
 @pytest.mark.parametrize("n", [200_003, 2_500_003, 4_300_003])
