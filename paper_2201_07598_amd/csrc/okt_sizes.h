@@ -340,7 +340,8 @@ inline bool reduce_counts_first(const ReduceShape& shape, uint64_t B, uint64_t m
     return shape.form == RED_NARROW && tiles >= RED_PLACED_FROM && B * tiles <= RED_PLACED_TILES_PER_CU * cus;
 }
 // Whether teams of lanes search for the ends of the slices: in regions of RED_TEAM_TILES tiles
-// or more with slices of RED_TEAM_SLICE entries or more, as a region hit evenly has them.
+// or more with slices of RED_TEAM_SLICE entries or more, as a region hit evenly has them (a
+// capacity of the whole width or more cannot be a count of hit slots: it is one of entries).
 // Whole calls, a thread a cell and teams: slices of 100 entries, 54 tiles, 696 and 663 us; of
 // 450, two tiles, 57 and 58; of 19, 25 tiles, 117 and 122; of 16 to 21 in dense tiles, 256
 // contributions, 17 to 218 tiles, 2 to 7 % more with teams, of 30 to 50 even.
@@ -348,8 +349,9 @@ constexpr uint64_t RED_TEAM_TILES = 16;
 constexpr double RED_TEAM_SLICE = 64;
 inline bool reduce_by_teams(const ReduceShape& shape, uint64_t width, uint64_t expected, uint32_t P) {
     if (reduce_tiles(width, shape.slots) < RED_TEAM_TILES) return false;
-    const double share = (double)expected < 0.999 * (double)width ? (double)expected / (double)width : 0.999;
-    return shape.slots * (1.0 - pow(1.0 - share, 1.0 / P)) >= RED_TEAM_SLICE;
+    const double share = (double)expected / (double)width;
+    const double hit_by_one = share < 1.0 ? 1.0 - pow(1.0 - share, 1.0 / P) : share / P;
+    return shape.slots * hit_by_one >= RED_TEAM_SLICE;
 }
 // Boundaries that a team of the slice table's kernel finds in turn: as many as leave enough
 // teams to fill the chip (1 and 4: 1.3 M cells 670 and 660 us a call, 72,000 cells 72 and 78).
