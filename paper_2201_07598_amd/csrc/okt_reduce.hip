@@ -256,8 +256,16 @@ __global__ __launch_bounds__(256) void reduce_slices_wave_kernel(
 // reduce_tile_kernel<PLACED> adds up the counts before its tile: no ticket, no
 // descriptors to clear, no wait.  One region of 3.4 M slots, 32 contributions, 1.1 M entries:
 // 8.0 us for the table and 16.5 for the tiles with tickets, 10.0 and 11.2 so.
+// It pays up to PLACED_P contributions: with more, two searches for each of them in every
+// tile and short slices cost more than the tickets (whole calls with tickets and so, 3.4 M
+// slots, 0.4 to 0.78 hit: 96 contributions 31 to 42 and 25 to 39 us, 128 31 to 42 and 28 to 43,
+// 160 32 to 43 and 30 to 46, 256 34 to 47 and 38 to 56).  It does not pay where a few tiles
+// hold most of the entries, as the first launch then lasts as long as the busiest: with
+// log-normal stretches (sigma 1.5), 0.4 hit, 32 contributions 77 and 92 us; layers of which a
+// quarter is hit eight times as often as the rest come out even (73 to 80, 55 and 56).
 constexpr int COUNT_BLOCK = 512;
-constexpr uint32_t PLACED_P = COUNT_BLOCK / 2;       // a thread at least for each end of a slice
+constexpr uint32_t PLACED_P = 96;
+static_assert(4 * PLACED_P <= COUNT_BLOCK, "two lanes at least for each end of a slice");
 
 // lower_bound_near by `lanes` consecutive lanes (a power of two, at most 16) that all
 // have the same arguments: each reads sixteen entries of one window around the guess.

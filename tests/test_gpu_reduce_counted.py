@@ -44,9 +44,9 @@ def picks(rng, lo, width, m):
     return (np.sort(rng.choice(width, min(m, width), replace=False)) + lo).astype(np.uint32)
 
 
-# narrow dense tiles are 4096 slots: 127 of them take tickets, 128 do not
+# narrow dense tiles are 4096 slots: 127 of them take tickets, 128 do not (up to 96 contributions)
 @pytest.mark.parametrize("width", [127 * 4096, 127 * 4096 + 1, 128 * 4096 + 5, 700_001])
-@pytest.mark.parametrize("P", [1, 2, 16, 17, 100, 256, 257])
+@pytest.mark.parametrize("P", [1, 2, 16, 17, 33, 96, 97, 100, 256, 257])
 def test_dense_tiles(width, P):
     rng = np.random.default_rng(width + P)
     lo = 3_000_001
@@ -55,7 +55,7 @@ def test_dense_tiles(width, P):
 
 
 @pytest.mark.parametrize("P,m,width", [(1, 300_000, 3_000_000), (3, 200_000, 3_400_000), (32, 34_375, 3_437_500),
-                                       (33, 4_000, 4_000_000), (200, 700, 6_400_000), (256, 2_000, 3_500_000)])
+                                       (33, 4_000, 4_000_000), (96, 1_500, 6_400_000), (200, 700, 6_400_000), (256, 2_000, 3_500_000)])
 def test_ranked_and_sparse_tiles(P, m, width):
     rng = np.random.default_rng(P)
     lo = 17
