@@ -144,8 +144,9 @@ int okt_stream_sum(const float* d_src, uint64_t n, float* d_partials_out, void* 
 /*
  * Measurement only: the memory traffic of okt_sparse_reduce_batch without its
  * arithmetic.  Arguments as okt_sparse_reduce_batch (no counts, no dense copy):
- * the region is cut into the same tiles, the same kernel builds the same table of
- * slice boundaries, and then one workgroup per tile reads every entry of the
+ * the region is cut into the same tiles, the kernel that the reduce of a batch takes builds
+ * the same table of slice boundaries (a large lone region's is built by another one there,
+ * which counts hit slots too), and then one workgroup per tile reads every entry of the
  * tile's slices once - short sorted runs of (index, value) pairs scattered over
  * d_idx_cat / d_val_cat - and writes it to d_idx_out / d_val_out[j * capacity + p],
  * p being the entry's position among region j's input entries (entries beyond
@@ -194,7 +195,7 @@ int okt_residual_accumulate(const float* d_grad, float* d_residual_inout, float 
  *                                   only when values tie with the k-th)
  * Integer work only: the result is exact and run-to-run identical.
  * Workspace: okt_workspace_bytes(n, 0); a smaller one (>= 64 KiB) still gives
- * the same result, with more passes over d_acc.  One to three launches.
+ * the same result, with more passes over d_acc.  One to four launches.
  */
 int okt_topk_threshold_exact(const float* d_acc, uint64_t n, uint64_t k,
                              float* d_threshold_out, uint64_t* d_count_ge_out,

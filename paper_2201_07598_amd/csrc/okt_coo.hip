@@ -8,11 +8,6 @@
 
 namespace okt {
 
-__global__ void coo_empty_kernel(uint64_t* nnz_out) {
-    nnz_out[0] = 0;
-    nnz_out[1] = 0;
-}
-
 // ---- short COO lists ----
 // A list of up to COO_SMALL_N entries is selected by one workgroup in one launch, one of
 // up to COO_TILED_N by many in two: the first counts what every tile selects, the
@@ -227,7 +222,7 @@ extern "C" int okt_coo_threshold_select(const uint32_t* d_idx_in, const float* d
     if (!d_nnz_out || !aligned(d_nnz_out, 8)) return OKT_ERR_INVALID_ARG;
     if (max_nnz > 0xffffffffull) return OKT_ERR_INVALID_ARG;
     if (max_nnz == 0) {
-        hipLaunchKernelGGL(coo_empty_kernel, dim3(1), dim3(1), 0, s, d_nnz_out);
+        hipLaunchKernelGGL(select_empty_kernel, dim3(1), dim3(1), 0, s, d_nnz_out);
         return launch_status();
     }
     if (!d_idx_in || !d_val_in || !d_nnz_in || !d_threshold || !aligned(d_idx_in, 4) ||

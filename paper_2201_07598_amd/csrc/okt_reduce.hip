@@ -3,10 +3,13 @@
 // Sec. 3.1.1).  Plain sum over the union of the supports.
 //
 // Two kernels per call.
-//  1. reduce_slices_kernel: the region is cut into tiles of `slots` consecutive
-//     index slots; one thread per (tile boundary, contribution) finds, by binary
-//     search in the sorted contribution, where the boundary falls.  All searches
-//     of a call run side by side, so their latency is paid once.
+//  1. The region is cut into tiles of `slots` consecutive index slots; for every (tile
+//     boundary, contribution) the first launch finds, in the sorted contribution, where the
+//     boundary falls, all searches side by side, so that their latency is paid once.  Four
+//     kernels do it: a wave a boundary where there are few (reduce_slices_wave_kernel), a
+//     thread a boundary (reduce_slices_kernel), teams of lanes that find several in turn
+//     where slices are longer (reduce_slices_team_kernel), and a workgroup a tile, which
+//     also counts the tile's hit slots, where all tiles run at a time (reduce_count_kernel).
 //  2. reduce_tile_kernel: a workgroup owns one tile.  Its slice of every
 //     contribution is known from the table, so all its entries are addressed up
 //     front, read with 16-byte loads all in flight and kept in registers.  Entries are
@@ -14,7 +17,8 @@
 //     accumulator of a slot is the slot itself.  Where it is sparsely hit the tile is
 //     wider than the accumulator array: the hit slots are marked in a bitmap, the popcount prefix
 //     of the bitmap ranks them, and the entries are summed into accumulator [rank].
-//     The tile is then written out in index order; its place in the output comes from the two-level chained scan over tile counts.
+//     The tile is then written out in index order; its place in the output comes from the
+//     two-level chained scan over tile counts, or is the sum of the counts before it.
 // Traffic: every input entry is read once (tiles with more entries than registers
 // hold read indices twice), every output entry is written once, plus 4 B per slot if
 // the dense region is requested.
@@ -92,9 +96,7 @@ __global__ __launch_bounds__(256) void reduce_slices_kernel(
 // contributions, whose cells share lines of the table.  A thread a cell -> teams:
 //   373 regions, 64 contributions, 54 tiles, slices of 97 entries    98 -> 64 us
 //   490 regions, 16 contributions, 33 tiles, 484 entries             31 -> 23
-//    48 regions, 256 contributions, 47 tiles, 92 entries             28 -> 21
-// (Whole calls of the first and last: 696 -> 663 and 140 -> 133 us, with teams of four
-// lanes 661 and 135, of eight 680 and 146.)
+// (Whole calls of the first: 696 -> 663 us, with teams of four lanes 661, of eight 680.)
 constexpr uint32_t TEAM = 2;
 // Sum over the lanes of a team; every lane gets it.
 __device__ __forceinline__ uint32_t team_sum(uint32_t v) {

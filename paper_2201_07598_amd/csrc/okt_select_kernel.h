@@ -9,6 +9,9 @@
 
 namespace okt {
 
+// Counts of a select over nothing: {0, 0}.
+__global__ void select_empty_kernel(uint64_t* nnz_out);
+
 // Lanes below this one that have their bit set in a 64-bit wave mask.
 __device__ __forceinline__ uint32_t mask_rank(uint64_t m) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));

@@ -54,7 +54,7 @@ inline size_t select_ws_bytes(uint64_t n) {
 }
 
 // ---- the same over a COO list ----
-// Short lists need no scan across workgroups (okt_select_kernel.h): one workgroup up to
+// Short lists need no scan across workgroups (okt_coo.hip): one workgroup up to
 // COO_SMALL_N entries, a count a tile of 1024 up to COO_TILED_N, as many as the
 // least workspace of a call has room for (two bytes each).
 constexpr uint32_t COO_SMALL_N = 32768, COO_TILED_N = 4u << 20;

@@ -463,8 +463,9 @@ static void launch_digits(const float* acc, uint64_t n, uint64_t k, RadixState* 
 // elements went from 45 to 27 us, of 14.7 M from 84 to 74).  A phase boundary costs about four microseconds (counts out, last share
 // noticed, histogram read), a launch five.  Tickets on one counter are served one at
 // a time, some 30 ns each, so candidates are cut into SHARES_AIM shares or so (510
-// shares: 33 us for two digits over 1.7 M candidates, 21 us with 69), and one
-// workgroup does alone, from registers, what fits into a single share.
+// shares: 33 us for two digits over 1.7 M candidates, 21 us with 69).  What fits into a
+// single share is resolved from registers, without an exchange: by one workgroup, or, where
+// a select follows, by each of several that share out the stores.
 constexpr uint32_t BOUND_SHIFT = 12, BOUND_LOG_BINS = 11;   // first digit from a bound: 2^12 keys a bin
 constexpr uint32_t SHARES_AIM = 64;
 constexpr int RES_BLOCK = SEL_BLOCK;
@@ -572,10 +573,10 @@ __global__ __launch_bounds__(RES_BLOCK) void resolve_kernel(
     float* walked = use_cand ? cand : vec;
     uint32_t per_share = piece * (uint32_t)RES_WAVES;                        // the launch's, for the whole vector
     if (bounded) {
-        // whole rows: as many as make SHARES_AIM shares; of candidates ROWS_MAX, which
-        // registers hold, and all of them in one share if that holds them
+        // whole rows: as many as make SHARES_AIM shares; of candidates at most ROWS_MAX, which
+        // registers hold
         uint32_t rows = (uint32_t)(((uint64_t)len + SHARES_AIM * ROW - 1) / (SHARES_AIM * ROW));
-        if (use_cand && (rows > (uint32_t)ROWS_MAX || len <= ROWS_MAX * ROW)) rows = ROWS_MAX;
+        if (use_cand && rows > (uint32_t)ROWS_MAX) rows = ROWS_MAX;
         // no more shares than the launch has descriptors for
         const uint32_t least = (uint32_t)(((uint64_t)len + (uint64_t)nseg * ROW - 1) / ((uint64_t)nseg * ROW));
         if (rows < least) rows = least;
