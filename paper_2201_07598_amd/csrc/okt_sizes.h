@@ -341,7 +341,8 @@ inline bool reduce_counts_first(const ReduceShape& shape, uint64_t B, uint64_t m
 }
 // Whether teams of lanes search for the ends of the slices: in regions of RED_TEAM_TILES tiles
 // or more with slices of RED_TEAM_SLICE entries or more, as a region hit evenly has them (a
-// capacity of the whole width or more cannot be a count of hit slots: it is one of entries).
+// capacity of the whole width or more cannot be a count of hit slots: it is one of entries;
+// 3.4 M slots, 256 contributions of 15,900 entries, taken as 0.999 hit 43.2 us, so 41.4).
 // Whole calls, a thread a cell and teams: slices of 100 entries, 54 tiles, 696 and 663 us; of
 // 450, two tiles, 57 and 58; of 19, 25 tiles, 117 and 122; of 16 to 21 in dense tiles, 256
 // contributions, 17 to 218 tiles, 2 to 7 % more with teams, of 30 to 50 even.
