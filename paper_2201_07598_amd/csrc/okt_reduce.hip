@@ -16,7 +16,8 @@
 //     summed with LDS fp64 atomic adds.  Where the region is densely hit the
 //     accumulator of a slot is the slot itself.  Where it is sparsely hit the tile is
 //     wider than the accumulator array: the hit slots are marked in a bitmap, the popcount prefix
-//     of the bitmap ranks them, and the entries are summed into accumulator [rank].
+//     of the bitmap ranks them, and the entries are summed into accumulator [rank]; in the
+//     slim form only those of slots that several entries hit.
 //     The tile is then written out in index order; its place in the output comes from the
 //     two-level chained scan over tile counts, or is the sum of the counts before it.
 // Traffic: every input entry is read once (tiles with more entries than registers
@@ -470,40 +471,82 @@ __device__ __forceinline__ uint32_t bitmap_prefix(const uint32_t* s_bits, uint16
 // the longer slices of the wider tile counting for as much as the rest.  The narrow form
 // is held to 64 registers, for four tiles to a CU: 16 contributions, a tenth of 400 K slots
 // hit, 380 regions, 65 us against 84 with slices read twice and 78 in wide tiles.
+//
+// SLIM: a sparsely hit region's slots are hit by one entry as a rule, which is the sum then.  So
+// the marking notes which entries find their slot marked already; the first of every slot puts
+// its value, a float, at the slot's rank, and the others go to a list, where each slot that has
+// any gets an fp64 accumulator - in the list entry of the one that gets there first - with all of
+// the slot's values added.  The list takes the place of the units, the bitmap and the prefixes,
+// which nobody needs once the ranks are known.  So a hit slot takes four bytes of LDS instead of
+// eight, and three tiles of 6,566 planned hits run on a CU where two of 7,410 did; no entry but the
+// listed ones needs an LDS atomic on a double.  Held to 80 registers.  490 regions of 16
+// contributions 507 -> 423 us a call, 373 of 64 629 -> 514, 200 of 40 in 400 K slots 74 -> 62; the
+// tile kernel moves 4.9 TB/s of HBM traffic then, where the plain copy reaches 5.9, and neither
+// a look at the descriptors before the list, nor four narrower tiles to a CU (452 us), nor the
+// slice table made in the same launch by workgroups between the tiles (433 to 482 us: they wait
+// for memory in places that tiles could have) makes it any faster.  Stores of outputs beyond
+// the last-level cache go past it: 423 -> 414 us with outputs of 1 GB; with outputs of 120 MB the call
+// gains 2 us and a kernel that reads them loses 9.  A tile with more hits, entries or listed
+// entries than there is room for goes by windows, as others do, with fp64 accumulators in all
+// that the bitmap leaves free; those are fewer than in a wide tile, so regions that are
+// hit unevenly gain less or nothing (16 to 256 contributions, 1.6 M slots, log-normal stretches
+// 0.9 to 1.07 times as fast, layers 0.94 to 1.06, halves 0.96 to 1.3, 30 % in common 0.9 to 1.15).
+//
 // Tried and not kept: 16 waves with 8 entries a thread and the same tile (spills at
 // 64 registers), several regions' tiles in turn per workgroup with the next slice table
 // fetched ahead (what it hides, its registers and the extra barriers cost), tiles of
 // several regions in turn in the grid (their inputs share no lines), the tile's windows
 // each searched before its turn (a chain of searches instead of one).
-template <int BLOCK, int ROUNDS, uint32_t C, uint32_t S_MAX, bool PLACED = false>
-__global__ __launch_bounds__(BLOCK, ROUNDS == 2 ? 8 : 4) void reduce_tile_kernel(
+// A thread's entries of a chunk: QUADS of four.
+template <int QUADS>
+struct TileEntries {
+    static constexpr int ROUNDS = QUADS;
+    uint32_t slot[ROUNDS][4];    // slot in the tile, later rank << SLOT_BITS | slot; from S_MAX on: no entry
+    float value[ROUNDS][4];
+    uint32_t have;               // bit 4u + j: there is such an entry
+    bool last;                   // the wave has units in the last round (uniform): a chunk is seldom full
+};
+
+template <int BLOCK, int ROUNDS, uint32_t C, uint32_t S_MAX, bool PLACED = false, bool SLIM = false>
+__global__ __launch_bounds__(BLOCK, SLIM ? 6 : ROUNDS == 2 ? 8 : 4) void reduce_tile_kernel(
     const uint32_t* __restrict__ idx_cat, const float* __restrict__ val_cat,
     const uint64_t* __restrict__ seg_begin, const uint64_t* __restrict__ seg_end,
     uint32_t seg_stride, const uint32_t* __restrict__ lo_hi, uint32_t lo0,
     uint32_t hi0, uint32_t P, uint32_t max_width, uint32_t slots,
     uint32_t* __restrict__ idx_out, float* __restrict__ val_out, uint64_t capacity,
     uint64_t* __restrict__ nnz_out, float* __restrict__ dense_out, char* ws,
-    uint32_t ws_region_bytes, uint32_t table_offset) {
+    uint32_t ws_region_bytes, uint32_t table_offset, uint32_t past_cache) {
     constexpr int WAVES = BLOCK / WAVE;
     constexpr bool DENSE = S_MAX == C;            // accumulator = slot, always
     constexpr uint32_t WORDS_MAX = S_MAX / 32;
-    constexpr uint32_t UNITS = BLOCK / 4 * ROUNDS, WINDOWS_MAX = 15;
+    constexpr uint32_t UNITS = BLOCK / 4 * ROUNDS, WINDOWS_MAX = SLIM ? 29 : 15;
     // A tile of at most EXCESS chunks is marked and summed chunk by chunk, the units spread
     // over all threads; a longer one goes slice by slice, without a barrier between chunks.
     // The narrow form keeps the first chunk in registers also then: beside a second chunk
     // the wide form has none for it.
     constexpr uint32_t EXCESS = 2;
     constexpr bool KEEP = ROUNDS == 2;
-    static_assert(S_MAX <= WINDOWS_MAX * (C - 32), "windows of a tile");
     // Lanes without an entry work on a slot, a rank and an accumulator of their own
     // past the end (one of SPARE), so that the loops over the entries have no branch.
     constexpr uint32_t SPARE = 32, SLOT_BITS = 17, SLOT_MASK = (1u << SLOT_BITS) - 1u;
     static_assert(S_MAX + 32 * SPARE <= SLOT_MASK && C + SPARE <= 1u << (32 - SLOT_BITS), "a slot and a rank share a word");
-    static_assert(C % 2 == 0 && WORDS_MAX % 4 == 0, "cleared 16 bytes at a time");
-    __shared__ __attribute__((aligned(16))) double s_sum[C + SPARE];
-    __shared__ __attribute__((aligned(16))) uint32_t s_bits[WORDS_MAX + SPARE];
-    __shared__ uint16_t s_wprefix[WORDS_MAX + SPARE];
-    __shared__ uint64_t s_unit[UNITS];            // first entry << 6 | whole unit readable << 5 | entries
+    // LDS: accumulators | units | bitmap | prefixes.  SLIM: the list lies behind the C values, over
+    // the rest; the fp64 accumulators of a tile that goes by windows have what the rest leaves free.
+    constexpr uint32_t FIXED = 8 * UNITS + 6 * (WORDS_MAX + SPARE), VALUES = 4 * (C + SPARE);
+    constexpr uint32_t LIST = SLIM ? RED_SLIM_LIST : 1;
+    static_assert(!SLIM || (FIXED <= 8 * LIST && (VALUES + 8 * LIST - FIXED + 8 * UNITS) % 16 == 0), "the list holds the rest");
+    constexpr uint32_t ACC = SLIM ? ((VALUES + 8 * LIST - FIXED) / 8 - SPARE) & ~1u : C;    // fp64 accumulators
+    static_assert(S_MAX <= WINDOWS_MAX * (ACC - 32), "windows of a tile");
+    static_assert(ACC % 2 == 0 && WORDS_MAX % 4 == 0, "cleared 16 bytes at a time");
+    constexpr uint32_t UNITS_AT = SLIM ? VALUES + 8 * LIST - FIXED : 8 * (C + SPARE);
+    __shared__ __attribute__((aligned(16))) char s_mem[UNITS_AT + FIXED];
+    double* const s_sum = (double*)s_mem;
+    uint64_t* const s_unit = (uint64_t*)(s_mem + UNITS_AT);   // first entry << 6 | whole unit readable << 5 | entries
+    uint32_t* const s_bits = (uint32_t*)(s_mem + UNITS_AT + 8 * UNITS);
+    uint16_t* const s_wprefix = (uint16_t*)(s_mem + UNITS_AT + 8 * UNITS + 4 * (WORDS_MAX + SPARE));
+    uint64_t* const s_list = (uint64_t*)(s_mem + VALUES);
+    constexpr uint32_t MORE = SLIM ? (C + SPARE + 31) / 32 : 1;
+    __shared__ uint32_t s_more[MORE], s_again;    // SLIM: ranks that have an fp64 sum, listed entries
     __shared__ uint32_t s_wave[2][WAVES], s_placed[WAVES];
     __shared__ uint32_t s_tile, s_before[2], s_wrap, s_cut[WINDOWS_MAX + 1], s_cut_rank[WINDOWS_MAX + 1];
 
@@ -517,13 +560,16 @@ __global__ __launch_bounds__(BLOCK, ROUNDS == 2 ? 8 : 4) void reduce_tile_kernel
     if (tid == 0) {
         if (!PLACED) s_tile = atomicAdd(&hdr->ticket, 1u);
         s_wrap = ~0u;
+        if (SLIM) s_again = 0;
     }
+    if (SLIM && tid < (int)MORE) s_more[tid] = 0;
     if (tid < (int)SPARE) s_wprefix[WORDS_MAX + tid] = (uint16_t)(C + tid);
     const RegionView r = region_view(lo_hi, lo0, hi0, region, max_width, slots);
     uint64_t* nnz = nnz_out + 2 * (size_t)region;
     // the bitmap and the accumulators are cleared while the ticket is under way
     for (uint32_t w = tid; w < WORDS_MAX / 4; w += BLOCK) reinterpret_cast<uint4*>(s_bits)[w] = uint4{0, 0, 0, 0};
-    for (uint32_t s = tid; s < C / 2; s += BLOCK) reinterpret_cast<double2*>(s_sum)[s] = double2{0.0, 0.0};
+    if (!SLIM)
+        for (uint32_t s = tid; s < ACC / 2; s += BLOCK) reinterpret_cast<double2*>(s_sum)[s] = double2{0.0, 0.0};
     __syncthreads();
     const uint32_t tile = PLACED ? blockIdx.x : uniform(s_tile);
     if (r.ntiles == 0) {
@@ -590,15 +636,12 @@ __global__ __launch_bounds__(BLOCK, ROUNDS == 2 ? 8 : 4) void reduce_tile_kernel
         }
     };
     // ---- this thread's entries of a chunk ----
-    struct Chunk {
-        uint32_t slot[ROUNDS][4];    // slot in the tile, later rank << SLOT_BITS | slot; from S_MAX on: no entry
-        float value[ROUNDS][4];
-        bool last;                   // the wave has units in the last round (uniform): a chunk is seldom full
-    };
+    using Chunk = TileEntries<ROUNDS>;
+    using Streamed = TileEntries<SLIM ? 2 : ROUNDS>;
     const uint32_t nowhere = S_MAX + 32u * ((uint32_t)lane % SPARE);
     // Quad u of a chunk: the first `left` of the four entries at `from`, read with 16-byte
     // loads if all four lie inside the contribution (past the slice's end though they may be).
-    auto load_entries = [&](Chunk& c, int u, uint64_t from, uint32_t left, bool whole, auto with_values) {
+    auto load_entries = [&](auto& c, int u, uint64_t from, uint32_t left, bool whole, auto with_values) {
         constexpr bool VALUES = decltype(with_values)::value;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -628,9 +671,13 @@ __global__ __launch_bounds__(BLOCK, ROUNDS == 2 ? 8 : 4) void reduce_tile_kernel
                 }
         }
     };
-    auto settle = [&](Chunk& c, const uint32_t (&left)[ROUNDS]) {          // indices -> slots of the tile
+    auto settle = [&](auto& c, const auto& left) {            // indices -> slots of the tile
+        constexpr int QUADS = std::remove_reference_t<decltype(c)>::ROUNDS;
+        c.have = 0;
 #pragma unroll
-        for (int u = 0; u < ROUNDS; ++u)
+        for (int u = 0; u < QUADS; ++u) c.have |= (left[u] < 4 ? (1u << left[u]) - 1u : 15u) << (4 * u);
+#pragma unroll
+        for (int u = 0; u < QUADS; ++u)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const uint32_t s = c.slot[u][j] - a;
@@ -653,13 +700,14 @@ __global__ __launch_bounds__(BLOCK, ROUNDS == 2 ? 8 : 4) void reduce_tile_kernel
     // The slices at hand, each read by the threads that hold it: no table of units and no
     // barrier, so a wave goes on to its next entries by itself.
     auto stream_slices = [&](auto with_values, auto&& body) {
+        constexpr int QUADS = Streamed::ROUNDS;
         const uint32_t step = 4u << share;
-        for (uint32_t i0 = 4u * member; i0 < sl_len; i0 += ROUNDS * step) {
-            Chunk c;
-            uint32_t left[ROUNDS];
+        for (uint32_t i0 = 4u * member; i0 < sl_len; i0 += QUADS * step) {
+            Streamed c;
+            uint32_t left[QUADS];
             c.last = true;
 #pragma unroll
-            for (int u = 0; u < ROUNDS; ++u) {
+            for (int u = 0; u < QUADS; ++u) {
                 const uint32_t i = i0 + u * step;
                 left[u] = i < sl_len ? sl_len - i : 0u;
                 load_entries(c, u, sl_start + i, left[u], i + 4 <= sl_readable, with_values);
@@ -685,12 +733,13 @@ __global__ __launch_bounds__(BLOCK, ROUNDS == 2 ? 8 : 4) void reduce_tile_kernel
             if (units == 0) __syncthreads();
         }
     };
-    auto mark = [&](const Chunk& c) {
+    auto mark = [&](const auto& c) {
+        constexpr int QUADS = std::remove_reference_t<decltype(c)>::ROUNDS;
 #pragma unroll
-        for (int u = 0; u < ROUNDS; ++u)
+        for (int u = 0; u < QUADS; ++u)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                if (u < ROUNDS - 1 || c.last)
+                if (u < QUADS - 1 || c.last)
                     __hip_atomic_fetch_or(&s_bits[c.slot[u][j] >> 5], 1u << (c.slot[u][j] & 31), __ATOMIC_RELAXED,
                                           __HIP_MEMORY_SCOPE_WORKGROUP);
     };
@@ -701,24 +750,100 @@ __global__ __launch_bounds__(BLOCK, ROUNDS == 2 ? 8 : 4) void reduce_tile_kernel
     };
     // Sums the entries and notes every entry's rank.  GENERAL: only those whose rank
     // lies in [r0, r0 + C).
-    auto add = [&](Chunk& c, uint32_t r0, auto general) {
+    auto add = [&](auto& c, uint32_t r0, auto general) {
+        constexpr int QUADS = std::remove_reference_t<decltype(c)>::ROUNDS;
         constexpr bool GENERAL = decltype(general)::value;
+#pragma unroll
+        for (int u = 0; u < QUADS; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (u == QUADS - 1 && !c.last) break;
+                const uint32_t s = c.slot[u][j];
+                const uint32_t below = s_bits[s >> 5] & ((1u << (s & 31)) - 1u);
+                uint32_t rank = hits_below(s >> 5, general) + (uint32_t)__popc(below);
+                if (GENERAL) rank = s < S_MAX ? rank - r0 : ACC;
+                else c.slot[u][j] = rank << SLOT_BITS | s;
+                float x = c.value[u][j];
+                asm volatile("" : "+v"(x));      // widened here, not where it was loaded: registers
+                if (!GENERAL || rank < ACC)
+                    __hip_atomic_fetch_add(&s_sum[rank], (double)x, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+    };
+
+    // SLIM: marks the entries and notes those whose slot was marked before them.
+    auto mark_again = [&](const Chunk& c, uint32_t& again) {
+#pragma unroll
+        for (int u = 0; u < ROUNDS; ++u) {
+            if (u == ROUNDS - 1 && !c.last) break;
+            uint32_t was[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                was[j] = __hip_atomic_fetch_or(&s_bits[c.slot[u][j] >> 5], 1u << (c.slot[u][j] & 31), __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_WORKGROUP);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) again |= (was[j] >> (c.slot[u][j] & 31) & 1u) << (4 * u + j);
+        }
+        again &= c.have;
+    };
+    // SLIM: ranks the entries and leaves the slots' sums, as floats, where the accumulators are.
+    auto sum_slim = [&](Chunk& c, uint32_t again, uint32_t at, uint32_t listed) {
+        uint32_t* const s_val = reinterpret_cast<uint32_t*>(s_sum);
+        const uint32_t spare = C + (uint32_t)lane % SPARE;
 #pragma unroll
         for (int u = 0; u < ROUNDS; ++u)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 if (u == ROUNDS - 1 && !c.last) break;
-                const uint32_t s = c.slot[u][j];
+                uint32_t s = c.slot[u][j];
+                asm volatile("" : "+v"(s));      // addresses are formed here, not kept from the marking: registers
                 const uint32_t below = s_bits[s >> 5] & ((1u << (s & 31)) - 1u);
-                uint32_t rank = hits_below(s >> 5, general) + (uint32_t)__popc(below);
-                if (GENERAL) rank = s < S_MAX ? rank - r0 : C;
-                else c.slot[u][j] = rank << SLOT_BITS | s;
-                float x = c.value[u][j];
-                asm volatile("" : "+v"(x));      // widened here, not where it was loaded: registers
-                if (!GENERAL || rank < C)
-                    __hip_atomic_fetch_add(&s_sum[rank], (double)x, __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+                const uint32_t rank = (uint32_t)s_wprefix[s >> 5] + (uint32_t)__popc(below);
+                c.slot[u][j] = rank << SLOT_BITS | s;
+                s_val[again >> (4 * u + j) & 1u ? spare : rank] = __float_as_uint(c.value[u][j]);
             }
+        if (listed == 0) return;
+        __syncthreads();                              // ranks are known: the list takes the place of what told them
+#pragma unroll
+        for (int u = 0; u < ROUNDS; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (again >> (4 * u + j) & 1u)
+                    s_list[at++] = (uint64_t)__float_as_uint(c.value[u][j]) << 32 | c.slot[u][j] >> SLOT_BITS;
+        __syncthreads();
+        // The first of a slot's entries to get here starts the sum in its own place and says in
+        // the slot's value where that is; the others add to it; the first rounds it.
+        constexpr int TURNS = (int)((LIST + BLOCK - 1) / BLOCK);
+        uint32_t rank[TURNS], first = 0;
+#pragma unroll
+        for (int t = 0; t < TURNS; ++t) {
+            rank[t] = 0;
+            const uint32_t i = (uint32_t)tid + t * BLOCK;
+            if (i < listed) {
+                const uint64_t e = s_list[i];
+                const uint32_t r = rank[t] = (uint32_t)e, bit = 1u << (r & 31);
+                if (!(__hip_atomic_fetch_or(&s_more[r >> 5], bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) & bit)) {
+                    first |= 1u << t;
+                    const double sum = (double)__uint_as_float(s_val[r]) + (double)__uint_as_float((uint32_t)(e >> 32));
+                    s_list[i] = (uint64_t)__double_as_longlong(sum);
+                    s_val[r] = i;
+                }
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < TURNS; ++t) {
+            const uint32_t i = (uint32_t)tid + t * BLOCK;
+            if (i < listed && !(first >> t & 1u))
+                __hip_atomic_fetch_add(reinterpret_cast<double*>(s_list) + s_val[rank[t]],
+                                       (double)__uint_as_float((uint32_t)(s_list[i] >> 32)), __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < TURNS; ++t)
+            if (first >> t & 1u)
+                s_val[rank[t]] = __float_as_uint((float)__longlong_as_double((long long)s_list[(uint32_t)tid + t * BLOCK]));
     };
 
     // Both waves of the chained scan; every thread gets the count of all tiles
@@ -815,15 +940,15 @@ __global__ __launch_bounds__(BLOCK, ROUNDS == 2 ? 8 : 4) void reduce_tile_kernel
         // The sums of ranks r0 .. r0 + in_round - 1 leave LDS, the indices take their
         // place, and both go out in output order; the wait for the tiles before this
         // one lies in between.
-        auto write_out = [&](uint32_t r0, uint32_t in_round, auto&& put_indices) {
-            constexpr int PER = (int)((C + BLOCK - 1) / BLOCK);
+        auto write_out = [&](uint32_t r0, uint32_t in_round, const auto* sums, auto&& put_indices) {
+            constexpr int PER = (int)(((sizeof(*sums) == sizeof(float) ? C : ACC) + BLOCK - 1) / BLOCK);
             float x[PER];
             uint32_t k0 = (uint32_t)tid;
             asm volatile("" : "+v"(k0));             // addresses are formed here, not kept from before
 #pragma unroll
             for (int i = 0; i < PER; ++i) {
                 const uint32_t k = k0 + i * BLOCK;
-                x[i] = k < in_round ? (float)s_sum[k] : 0.0f;
+                x[i] = k < in_round ? (float)sums[k] + 0.0f : 0.0f;     // a lone -0 becomes +0, as 0 + -0 does
             }
             __syncthreads();
             put_indices();
@@ -837,8 +962,13 @@ __global__ __launch_bounds__(BLOCK, ROUNDS == 2 ? 8 : 4) void reduce_tile_kernel
             for (int i = 0; i < PER; ++i) {
                 const uint32_t k = k0 + i * BLOCK;
                 if (k < out) {
-                    to_idx[k] = s_idx[k];
-                    to_val[k] = x[i];
+                    if (SLIM && past_cache) {
+                        __builtin_nontemporal_store(s_idx[k], to_idx + k);
+                        __builtin_nontemporal_store(x[i], to_val + k);
+                    } else {
+                        to_idx[k] = s_idx[k];
+                        to_val[k] = x[i];
+                    }
                 }
                 if (dense && k < in_round) dense[s_idx[k] - a] = x[i];
             }
@@ -864,16 +994,48 @@ __global__ __launch_bounds__(BLOCK, ROUNDS == 2 ? 8 : 4) void reduce_tile_kernel
             __syncthreads();
             Chunk mine;
             load_chunk(mine, units < UNITS ? units : UNITS, Yes{});
-            mark(mine);
-            if (KEEP) chunks(UNITS, No{}, mark);
-            __syncthreads();
-            rank_tile();
-            if (distinct <= C) {
+            if constexpr (SLIM) {
+                uint32_t again = 0, at = 0;                  // listed entries, the first one's place in the list
+                mark_again(mine, again);
+                {
+                    const uint32_t n = (uint32_t)__popc(again), incl = wave_inclusive_scan_u32(n);
+                    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, WAVE - 1);
+                    if (total) {
+                        uint32_t base = 0;
+                        if (lane == 0) base = __hip_atomic_fetch_add(&s_again, total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        at = uniform(base) + incl - n;
+                    }
+                }
+                __syncthreads();
+                rank_tile();
+                const uint32_t listed = uniform(s_again);
+                if (distinct <= C && listed <= LIST) {
+                    sum_slim(mine, again, at, listed);
+                    __syncthreads();
+                    look_back();
+                    write_out(0, distinct, reinterpret_cast<const float*>(s_sum), [&]() {
+#pragma unroll
+                        for (int u = 0; u < ROUNDS; ++u)
+#pragma unroll
+                            for (int j = 0; j < 4; ++j)       // every hit of a slot writes the same
+                                if (u < ROUNDS - 1 || mine.last)
+                                    s_idx[mine.slot[u][j] >> SLOT_BITS] = a + (mine.slot[u][j] & SLOT_MASK);
+                    });
+                    finish();
+                    return;
+                }
+            } else {
+                mark(mine);
+                if (KEEP) chunks(UNITS, No{}, mark);
+                __syncthreads();
+                rank_tile();
+            }
+            if (!SLIM && distinct <= C) {
                 add(mine, 0, No{});
                 if (KEEP) chunks(UNITS, Yes{}, [&](Chunk& c) { add(c, 0, No{}); });
                 __syncthreads();
                 look_back();
-                write_out(0, distinct, [&]() {
+                write_out(0, distinct, s_sum, [&]() {
                     if (KEEP && units > UNITS) {
                         for (uint32_t w = tid; w < words; w += BLOCK) {
                             uint32_t bits = s_bits[w], rank = hits_below(w, No{});
@@ -908,7 +1070,9 @@ __global__ __launch_bounds__(BLOCK, ROUNDS == 2 ? 8 : 4) void reduce_tile_kernel
             // is cut, at words of the bitmap, into windows of at most C hit slots, and every
             // window's entries are read, summed and written in turn.  Window k ends in the word
             // that holds hit slot (k + 1) distinct / windows, up to 31 hit slots early.
-            const uint32_t windows = distinct > C ? (distinct + C - 33) / (C - 32) : 1u;
+            const uint32_t windows = distinct > ACC ? (distinct + ACC - 33) / (ACC - 32) : 1u;
+            if (SLIM)
+                for (uint32_t i = tid; i < ACC; i += BLOCK) s_sum[i] = 0.0;
             for (uint32_t w = tid; w < words; w += BLOCK) {
                 const uint32_t here = hits_below(w, Yes{}), next = w + 1 < words ? hits_below(w + 1, Yes{}) : distinct;
                 for (uint32_t k = 1; k < windows; ++k) {
@@ -925,6 +1089,7 @@ __global__ __launch_bounds__(BLOCK, ROUNDS == 2 ? 8 : 4) void reduce_tile_kernel
                 s_cut_rank[windows] = distinct;
             }
             __syncthreads();
+            if (SLIM) fetch_slices(0);                       // read again, not kept in registers until here
             // A slice is sorted, so a window's entries are a piece of it, whose end is searched
             // from where it would lie if the slice were spread as the tile's hits are: by the
             // threads that hold the slice, one window each, where LDS has room for the ends,
@@ -940,7 +1105,8 @@ __global__ __launch_bounds__(BLOCK, ROUNDS == 2 ? 8 : 4) void reduce_tile_kernel
                                                    a + s_cut[k] * 32u, guess) - whole_start);
             };
             uint32_t* const s_end = reinterpret_cast<uint32_t*>(s_unit);
-            const bool ends_kept = P <= (uint32_t)BLOCK && P * windows <= 2 * UNITS;
+            const bool whole = !KEEP && by_chunk && windows <= 1;
+            const bool ends_kept = P <= (uint32_t)BLOCK && P * windows <= 2 * UNITS && !whole;
             if (ends_kept) {
                 if (slice < P)
                     for (uint32_t k = member + 1; k <= windows; k += 1u << share) s_end[slice * windows + k - 1] = window_end(k, 0);
@@ -950,15 +1116,16 @@ __global__ __launch_bounds__(BLOCK, ROUNDS == 2 ? 8 : 4) void reduce_tile_kernel
             for (uint32_t k = 0; k < windows; ++k) {
                 const uint32_t w0 = uniform(s_cut[k]), w1 = uniform(s_cut[k + 1]);
                 const uint32_t r0 = uniform(s_cut_rank[k]), r1 = uniform(s_cut_rank[k + 1]);
-                auto sum = [&](Chunk& c) { add(c, r0, Yes{}); };
-                if (P <= (uint32_t)BLOCK) {
+                auto sum = [&](auto& c) { add(c, r0, Yes{}); };
+                if (whole) {
+                    chunks(0, Yes{}, sum);
+                } else if (P <= (uint32_t)BLOCK) {
                     const uint32_t end = !ends_kept ? window_end(k + 1, begin) : slice < P ? s_end[slice * windows + k] : 0u;
                     sl_start = whole_start + begin;
                     sl_len = end > begin ? end - begin : 0u;
                     sl_readable = whole_readable > begin ? whole_readable - begin : 0u;
                     begin = end > begin ? end : begin;
-                    if (!KEEP && by_chunk && windows == 1) chunks(0, Yes{}, sum);
-                    else stream_slices(Yes{}, sum);
+                    stream_slices(Yes{}, sum);
                 } else {
                     for (uint32_t p0 = 0; p0 < P; p0 += BLOCK) {
                         fetch_slices(p0);
@@ -967,16 +1134,16 @@ __global__ __launch_bounds__(BLOCK, ROUNDS == 2 ? 8 : 4) void reduce_tile_kernel
                 }
                 __syncthreads();
                 if (k == 0) look_back();
-                write_out(r0, r1 - r0, [&]() {
+                write_out(r0, r1 - r0, s_sum, [&]() {
                     for (uint32_t w = w0 + tid; w < w1; w += BLOCK) {
                         uint32_t bits = s_bits[w], rank = hits_below(w, Yes{}) - r0;
                         for (; bits; bits &= bits - 1, ++rank)
-                            if (rank < C) s_idx[rank] = a + w * 32u + (uint32_t)(__ffs(bits) - 1);
+                            if (rank < ACC) s_idx[rank] = a + w * 32u + (uint32_t)(__ffs(bits) - 1);
                     }
                 });
                 if (k + 1 == windows) break;
                 __syncthreads();                              // sums and indices fully read
-                for (uint32_t i = tid; i < C; i += BLOCK) s_sum[i] = 0.0;
+                for (uint32_t i = tid; i < ACC; i += BLOCK) s_sum[i] = 0.0;
                 __syncthreads();
             }
         }
@@ -1052,17 +1219,25 @@ int reduce_launch(const uint32_t* d_idx_cat, const float* d_val_cat,
         return launch_status();
     }
     timing_before(s);
+    const uint32_t past_cache = stream_past_cache(2 * (uint64_t)B * capacity);
     auto launch = [&](auto* tile_kernel, uint32_t block) {
         hipLaunchKernelGGL(tile_kernel, dim3((unsigned)tiles, B), dim3(block), 0, s, d_idx_cat, d_val_cat,
                            d_seg_begin, d_seg_end, seg_stride, d_lo_hi, lo, hi, P, max_width, slots,
                            d_idx_out, d_val_out, capacity, d_nnz_out, d_dense, (char*)d_ws,
-                           (uint32_t)region_bytes, table_offset);
+                           (uint32_t)region_bytes, table_offset, past_cache);
     };
     if (placed) {
         using F = ReduceNarrow;
         if (shape.kind == RED_DENSE) launch(reduce_tile_kernel<F::BLOCK, F::ROUNDS, F::C_DENSE, F::C_DENSE, true>, F::BLOCK);
         else if (shape.kind == RED_RANKED) launch(reduce_tile_kernel<F::BLOCK, F::ROUNDS, F::C_RANKED, F::S_RANKED, true>, F::BLOCK);
         else launch(reduce_tile_kernel<F::BLOCK, F::ROUNDS, F::C_SPARSE, F::S_SPARSE, true>, F::BLOCK);
+        timing_after(s);
+        return launch_status();
+    }
+    if (shape.form == RED_SLIM) {
+        using F = ReduceSlim;
+        if (shape.kind == RED_RANKED) launch(reduce_tile_kernel<F::BLOCK, F::ROUNDS, F::C_RANKED, F::S_RANKED, false, true>, F::BLOCK);
+        else launch(reduce_tile_kernel<F::BLOCK, F::ROUNDS, F::C_SPARSE, F::S_SPARSE, false, true>, F::BLOCK);
         timing_after(s);
         return launch_status();
     }

@@ -198,9 +198,9 @@ inline size_t refresh_ws_bytes(uint64_t n) {
 // them, and the accumulators are indexed by rank, so the LDS holds hit slots only.
 // Very sparsely hit regions trade accumulators for bitmap.
 constexpr uint32_t RED_UNIT = 16;               // entries read by four lanes with one 16-byte load each
-// Three forms of tile: two wide tiles to a CU (80 KB of LDS each), whose threads hold
-// five units per four threads in registers (ROUNDS) or four, or four narrow ones.
-enum ReduceForm { RED_WIDE5, RED_WIDE4, RED_NARROW };
+// Four forms of tile: two wide tiles to a CU (80 KB of LDS each), whose threads hold
+// five units per four threads in registers (ROUNDS) or four, three slim ones, or four narrow ones.
+enum ReduceForm { RED_WIDE5, RED_WIDE4, RED_NARROW, RED_SLIM };
 struct ReduceWide5 {
     static constexpr int BLOCK = 512, ROUNDS = 5;
     static constexpr uint32_t C_DENSE = 9216, C_RANKED = 7968, S_RANKED = 65536, C_SPARSE = 7168, S_SPARSE = 98304;
@@ -211,6 +211,14 @@ struct ReduceWide4 {
     static constexpr uint32_t C_DENSE = 9216, C_RANKED = 8064, S_RANKED = 65536, C_SPARSE = 7168, S_SPARSE = 98304;
     static constexpr double FILL = 0.93;
 };
+// Three tiles to a CU (53 KB of LDS each), whose accumulators are floats and hold what a slot's
+// first entry brings; the others go to a list of RED_SLIM_LIST (reduce_tile_kernel).
+struct ReduceSlim {
+    static constexpr int BLOCK = 512, ROUNDS = 4;
+    static constexpr uint32_t C_DENSE = 0, C_RANKED = 6912, S_RANKED = 65536, C_SPARSE = 6912, S_SPARSE = 98304;
+    static constexpr double FILL = 0.95;
+};
+constexpr uint32_t RED_SLIM_LIST = 2968;
 struct ReduceNarrow {
     static constexpr int BLOCK = 512, ROUNDS = 2;
     static constexpr uint32_t C_DENSE = 4096, C_RANKED = 3968, S_RANKED = 32768, C_SPARSE = 3584, S_SPARSE = 49152;
@@ -259,6 +267,11 @@ constexpr double RED_DENSE_FROM = 0.35;
 // The hits of even tiles vary by 1 to 2 %.  Narrow tiles cover less of the region, so
 // what differs between its parts averages out less: they have more room.
 constexpr double RED_FILL_UNITS = 0.98;
+// Slim tiles of fewer than RED_SLIM_EVEN contributions have room for the entries of regions that
+// have 30 % of them in common, which wide tiles of so few hold in registers too (with more, neither
+// does, and narrower tiles would cost even regions more): 4 contributions, 1.6 M slots, 0.2 hit,
+// 30 % in common, 52 us wide, 68 us slim without and 51 with it; hit evenly 55, 48 and 50.
+constexpr uint32_t RED_SLIM_EVEN = 8;
 enum ReduceKind { RED_DENSE = 0, RED_RANKED = 1, RED_SPARSE = 2 };
 struct ReduceShape {
     uint32_t slots;
@@ -271,7 +284,8 @@ inline ReduceShape reduce_tile_shape_of(uint64_t width, uint64_t expected, uint3
         return expected == 0 && width > Form::C_DENSE ? ReduceShape{Form::S_SPARSE, RED_SPARSE, form}
                                                       : ReduceShape{Form::C_DENSE, RED_DENSE, form};
     const double share = (double)expected < 0.999 * (double)width ? (double)expected / (double)width : 0.999;
-    const double per_slot = P * (1.0 - pow(1.0 - share, 1.0 / P)) / share;       // entries per hit slot
+    double per_slot = P * (1.0 - pow(1.0 - share, 1.0 / P)) / share;       // entries per hit slot
+    if (form == RED_SLIM && P < RED_SLIM_EVEN) per_slot *= P / (0.3 + 0.7 * P);
     const double entries = (RED_FILL_UNITS * (Form::BLOCK / 4 * Form::ROUNDS) - 0.5 * P) * RED_UNIT;
     auto hits = [&](uint32_t c) {
         const double most = Form::FILL * c;
@@ -319,6 +333,17 @@ inline ReduceShape reduce_least_shape(uint64_t width, uint64_t expected, uint32_
     return want >= Form::S_RANKED + 32 ? ReduceShape{(uint32_t)want / 32 * 32, RED_SPARSE, RED_WIDE4}
                                        : ReduceShape{Form::S_RANKED, RED_RANKED, RED_WIDE4};
 }
+// Slim tiles for a region, RED_DENSE where they are not to be had: with more contributions than
+// threads (every window of a tile with too many hits would read them all), and from RED_SLIM_TO of
+// the slots hit on, where the entries that share slots are too many for the list to be quick: 7
+// contributions, 1.6 M slots, 0.32 / 0.4 / 0.5 / 0.6 hit, 1.02 / 0.99 / 0.97 / 0.90 times as fast as
+// wide tiles, 16 contributions 1.08 / 1.08 / 1.05 / 1.00.
+constexpr double RED_SLIM_TO = 0.4;
+inline ReduceShape reduce_slim_shape(uint64_t width, uint64_t expected, uint32_t P) {
+    if (P > (uint32_t)ReduceSlim::BLOCK || (double)expected > RED_SLIM_TO * (double)width)
+        return ReduceShape{ReduceWide5::C_DENSE, RED_DENSE, RED_WIDE5};
+    return reduce_tile_shape_of<ReduceSlim>(width, expected, P, RED_SLIM);
+}
 // The shape a call takes with a workspace of ws_bytes, at least what the least shape needs.
 inline ReduceShape reduce_shape(uint64_t B, uint64_t max_width, uint64_t expected, uint32_t P, uint64_t cus,
                                 size_t ws_bytes) {
@@ -333,6 +358,8 @@ inline ReduceShape reduce_shape(uint64_t B, uint64_t max_width, uint64_t expecte
     const bool fills = B * reduce_tiles(max_width, wide.slots) >= RED_WIDE_TILES_PER_CU * cus;
     const bool small = P <= RED_FEW && reduce_tiles(max_width, narrow.slots) <= RED_NARROW_TILES;
     if ((!fills || small) && fits(narrow)) return narrow;
+    const ReduceShape slim = reduce_slim_shape(max_width, expected, P);
+    if (wide.kind != RED_DENSE && slim.kind != RED_DENSE && fits(slim)) return slim;
     return fits(wide) ? wide : reduce_least_shape(max_width, expected, P);
 }
 inline bool reduce_counts_first(const ReduceShape& shape, uint64_t B, uint64_t max_width, uint64_t cus) {

@@ -1,0 +1,97 @@
+"""The slim tiles of the reduce (floats for a slot's first entry, a list for the others) at
+the edges of what they hold: hit slots, listed entries and units up to and one past the limit,
+slots that many contributions share, both kinds of bitmap, outputs written past the cache.
+
+Sums are of dyadic values small enough that fp64 adds them exactly in any order, so the oracle's
+result is the only correct one, bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2201_07598_amd as okt
+from test_gpu_reduce_tiles import DEV, dev, run_batch
+
+pytestmark = pytest.mark.gpu
+HITS, LIST = 6912, 2968
+
+
+def tile(rng, lo, span, P, distinct, again, most=1 << 30):
+    """P contributions that hit `distinct` of the first `span` slots from lo, with `again` entries more
+    than that: each slot hit by at most `most`."""
+    slots = np.sort(rng.choice(span, distinct, replace=False))
+    owner = rng.permutation(np.arange(distinct) % P)             # all as long as each other
+    have = [set(slots[owner == p].tolist()) for p in range(P)]
+    hot = slots[: max(1, -(-again // max(1, min(most, P) - 1)))]      # slots that take the rest
+    left = again
+    for s in hot.tolist():
+        for p in range(P):
+            if left and s not in have[p]:
+                have[p].add(s)
+                left -= 1
+    assert left == 0
+    return [(np.array(sorted(h), dtype=np.int64) + lo).astype(np.uint32) for h in have]
+
+
+def regions_of(make, B, P, width):
+    """B regions with one entry a contribution, and `make`'s at both ends of the launch."""
+    los = [b * 1_013 for b in range(B)]
+    return [(lo, lo + width, make(lo) if lo in (0, los[-1]) else [np.array([lo + 3 * p], np.uint32) for p in range(P)])
+            for lo in los]
+
+
+@pytest.mark.parametrize("P,distinct,again,most", [
+    (40, HITS, 0, 2), (40, HITS + 1, 0, 2), (40, HITS, 1, 2), (40, 1, 39, 40),
+    (40, 4000, LIST, 2), (40, 4000, LIST + 1, 2), (40, 4000, LIST, 40), (40, 5000, 1536, 3), (40, 5000, 1537, 40),
+    (64, 8192 - 64, 0, 2), (64, 6000, 2192, 64), (64, 6000, 2193, 64), (512, 512, 2900, 512), (511, 511, 511, 2),
+    (33, 6000, 500, 33)])
+def test_what_a_tile_holds(P, distinct, again, most):
+    """Regions of 60,001 slots, enough of them for wide tiles; the hits lie in the first of two tiles."""
+    rng = np.random.default_rng(P * 7 + distinct + again)
+    width, span = 60_001, 50_000
+    regions = regions_of(lambda lo: tile(rng, lo, span, P, distinct, again, most), 530, P, width)
+    run_batch(regions, P, width, 7_000, lead=P % 4)
+    run_batch(regions, P, width, 5_003)                           # planned wider, outputs cut short
+
+
+@pytest.mark.parametrize("P,width,span,distinct,again,capacity", [
+    (40, 98_304, 98_304, 5_000, 700, 5_900), (40, 65_536 * 9, 65_536, 6_000, 1_000, 6_000 * 9),
+    (3, 2_000_001, 40_000, 3_000, 2_500, 200_000), (7, 2_000_001, 40_000, 3_000, 2_500, 200_000),
+    (8, 2_000_001, 40_000, 5_000, 1_000, 200_000),
+    # 530 x 64,000 entries of eight bytes: more than the last-level cache
+    (40, 1_600_001, 150_000, 9_000, 900, 64_000)])
+def test_kinds_of_slim_tiles(P, width, span, distinct, again, capacity):
+    """Wide bitmaps and the widest, few contributions in long regions, outputs past the cache."""
+    rng = np.random.default_rng(width + distinct)
+    regions = regions_of(lambda lo: tile(rng, lo, span, P, distinct, again), 40 if width > 1_999_999 else 530,
+                         P, width)
+    run_batch(regions, P, width, capacity, lead=1)
+
+
+def test_values_that_are_no_ordinary_numbers():
+    """A lone -0 leaves as +0, as an fp64 sum that starts at +0 makes of it; NaN, infinities and
+    subnormals stay what they are, alone and in sums."""
+    P, width, B = 40, 40_003, 520
+    special = np.array([-0.0, np.nan, np.inf, -np.inf, 1e-45, -1e-45, 0.0, 3.0e38], np.float32)
+    first = np.arange(0, 16, dtype=np.uint32)                    # contribution 0: each value twice
+    second = np.arange(8, 16, dtype=np.uint32)                   # contribution 1: the second eight once more
+    idx = np.concatenate([np.concatenate([first, second]) + np.uint32(7 * b) for b in range(B)])
+    val = np.tile(np.concatenate([special, special, special]), B)
+    off = np.zeros((B, P + 1), np.uint64)
+    off[:, 0] = 24 * np.arange(B)
+    off[:, 1] = off[:, 0] + 16
+    off[:, 2:] = (off[:, 0] + 24)[:, None]
+    lo_hi = np.stack([7 * np.arange(B), 7 * np.arange(B) + width], 1).astype(np.uint32)
+    cap = 6_000
+    o_idx = torch.zeros(B * cap, dtype=torch.int32, device=DEV)
+    o_val = torch.zeros(B * cap, device=DEV)
+    nnz = torch.zeros(2 * B, dtype=torch.int64, device=DEV)
+    ws = torch.empty(okt.okt_sparse_reduce_batch_workspace_bytes(B, P, width), dtype=torch.uint8, device=DEV)
+    okt.okt_sparse_reduce_batch(dev(idx), dev(val), dev(off.reshape(-1)), dev(lo_hi.reshape(-1)), B, P, width, o_idx,
+                                o_val, cap, nnz, ws)
+    torch.cuda.synchronize()
+    assert (nnz == 16).all()
+    with np.errstate(over="ignore", invalid="ignore"):
+        want = np.concatenate([0.0 + special.astype(np.float64), special.astype(np.float64) * 2]).astype(np.float32)
+    got = o_val.cpu().numpy().reshape(B, cap)[:, :16]
+    assert np.array_equal(got, np.broadcast_to(want, got.shape), equal_nan=True)
+    assert np.array_equal(np.signbit(got[:, [0, 6, 8, 14]]), np.zeros((B, 4), bool))
