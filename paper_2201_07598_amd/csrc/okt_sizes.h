@@ -247,7 +247,9 @@ constexpr uint32_t RED_FEW = 32, RED_NARROW_TILES = 48;
 // entries among the same tenth, are 1.06 times as fast as with tiles that read every slice
 // twice, where four rounds are 0.77 times; 40 contributions that hit every other 12,500 of
 // 400 K slots 1.18 and 0.78 times.  From RED_MANY contributions on four rounds lose
-// nothing there, and their registers count: 373 regions of 64, 690 against 702 us.
+// nothing there, and their registers count: 373 regions of 64, 690 against 702 us.  Dense tiles
+// have five rounds all the same: 150 regions of 200, 100 K slots, 72 us with four, 66 with
+// five, 48 of 256 131.5 and 129.4, 80 of 100 80.3 and 81.2.
 // A region is taken as densely hit where the ranked tile would be no wider than the
 // dense one.  With RED_MANY contributions it is from a lower share on, as more
 // entries than assumed share slots then: 48 regions of 256 contributions that hit 0.37
