@@ -489,8 +489,9 @@ __device__ __forceinline__ uint32_t bitmap_prefix(const uint32_t* s_bits, uint16
 // gains 2 us and a kernel that reads them loses 9.  A tile with more hits, entries or listed
 // entries than there is room for goes by windows, as others do, with fp64 accumulators in all
 // that the bitmap leaves free; those are fewer than in a wide tile, so regions that are
-// hit unevenly gain less or nothing (16 to 256 contributions, 1.6 M slots, log-normal stretches
-// 0.9 to 1.07 times as fast, layers 0.94 to 1.06, halves 0.96 to 1.3, 30 % in common 0.9 to 1.15).
+// hit unevenly gain less or nothing (4 to 128 contributions, 400 K to 5 M slots, log-normal stretches
+// 0.93 to 1.13 times as fast, layers 0.88 to 1.16, halves 0.98 to 1.33, 30 % in common 0.92 to 1.4,
+// zipf 0.91 to 1.3); what is known to lose takes other tiles (reduce_slim_pays).
 //
 // Tried and not kept: 16 waves with 8 entries a thread and the same tile (spills at
 // 64 registers), several regions' tiles in turn per workgroup with the next slice table
@@ -537,6 +538,7 @@ __global__ __launch_bounds__(BLOCK, SLIM ? 6 : ROUNDS == 2 ? 8 : 4) void reduce_
     static_assert(!SLIM || (FIXED <= 8 * LIST && (VALUES + 8 * LIST - FIXED + 8 * UNITS) % 16 == 0), "the list holds the rest");
     constexpr uint32_t ACC = SLIM ? ((VALUES + 8 * LIST - FIXED) / 8 - SPARE) & ~1u : C;    // fp64 accumulators
     static_assert(S_MAX <= WINDOWS_MAX * (ACC - 32), "windows of a tile");
+    static_assert(!SLIM || ACC >= RED_SLIM_ACC, "as the rule for slim tiles has it");
     static_assert(ACC % 2 == 0 && WORDS_MAX % 4 == 0, "cleared 16 bytes at a time");
     constexpr uint32_t UNITS_AT = SLIM ? VALUES + 8 * LIST - FIXED : 8 * (C + SPARE);
     __shared__ __attribute__((aligned(16))) char s_mem[UNITS_AT + FIXED];

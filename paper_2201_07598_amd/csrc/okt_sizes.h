@@ -218,7 +218,7 @@ struct ReduceSlim {
     static constexpr uint32_t C_DENSE = 0, C_RANKED = 6912, S_RANKED = 65536, C_SPARSE = 6912, S_SPARSE = 98304;
     static constexpr double FILL = 0.95;
 };
-constexpr uint32_t RED_SLIM_LIST = 2968;
+constexpr uint32_t RED_SLIM_LIST = 2968, RED_SLIM_ACC = 3568;      // fp64 accumulators of a tile in windows, at least
 struct ReduceNarrow {
     static constexpr int BLOCK = 512, ROUNDS = 2;
     static constexpr uint32_t C_DENSE = 4096, C_RANKED = 3968, S_RANKED = 32768, C_SPARSE = 3584, S_SPARSE = 49152;
@@ -335,16 +335,35 @@ inline ReduceShape reduce_least_shape(uint64_t width, uint64_t expected, uint32_
     return want >= Form::S_RANKED + 32 ? ReduceShape{(uint32_t)want / 32 * 32, RED_SPARSE, RED_WIDE4}
                                        : ReduceShape{Form::S_RANKED, RED_RANKED, RED_WIDE4};
 }
-// Slim tiles for a region, RED_DENSE where they are not to be had: with more contributions than
-// threads (every window of a tile with too many hits would read them all), and from RED_SLIM_TO of
-// the slots hit on, where the entries that share slots are too many for the list to be quick: 7
-// contributions, 1.6 M slots, 0.32 / 0.4 / 0.5 / 0.6 hit, 1.02 / 0.99 / 0.97 / 0.90 times as fast as
-// wide tiles, 16 contributions 1.08 / 1.08 / 1.05 / 1.00.
-constexpr double RED_SLIM_TO = 0.4;
+// Whether slim tiles take the place of wide ones in a region.  They do not
+// - from RED_SLIM_TO of the slots hit on, where the entries that share slots are too many for the
+//   list to be quick: 7 contributions, 1.6 M slots, 0.32 / 0.4 / 0.5 / 0.6 hit, 1.02 / 0.99 / 0.97 /
+//   0.90 times as fast as wide tiles, 16 contributions 1.08 / 1.08 / 1.05 / 1.00;
+// - from RED_SLIM_P contributions on: their slices are short, and where they collide the windows of
+//   a slim tile read little pieces of each (256 contributions, zipf, 60 K to 500 K slots, 0.81 to
+//   0.98 times; 30 % in common 0.91 to 0.98; evenly hit 1.13 to 1.2; 128 contributions 0.94 to 1.22,
+//   0.98 to 1.0 and 1.14 to 1.17);
+// - where the bitmap limits wide tiles so that the entries of a region with 30 % in common (1.41
+//   entries a hit slot) still fit their registers, and slim ones have no room for as many: 36
+//   contributions, a tenth of 150 K to 1.6 M slots hit, 30 % in common 0.89 to 0.93 times, evenly hit
+//   1.17.  With more than RED_FEW contributions also where entries that collide (zipf, two a hit
+//   slot) make windows of a slim tile and none of a wide one: 36 contributions, 0.06 of 200 K and
+//   500 K slots 0.73 to 0.75.
+constexpr double RED_SLIM_TO = 0.4, RED_COMMON = 1.41;
+constexpr uint32_t RED_SLIM_P = 192;
+inline bool reduce_slim_pays(const ReduceShape& slim, const ReduceShape& wide, uint64_t width, uint64_t expected, uint32_t P) {
+    if (wide.kind == RED_DENSE || slim.kind == RED_DENSE) return false;
+    if (P >= RED_SLIM_P || (double)expected > RED_SLIM_TO * (double)width) return false;
+    auto in_common = [&](const ReduceShape& s) { return RED_COMMON * s.slots * (double)expected / (double)width; };
+    auto entries = [&](int rounds) { return (RED_FILL_UNITS * (ReduceSlim::BLOCK / 4 * rounds) - 0.5 * P) * RED_UNIT; };
+    static_assert(ReduceSlim::BLOCK == ReduceWide5::BLOCK, "units of both");
+    if (wide.form != RED_WIDE5 || in_common(wide) > entries(ReduceWide5::ROUNDS)) return true;
+    return P > RED_FEW ? in_common(slim) <= RED_COMMON * 0.93 * RED_SLIM_ACC : in_common(slim) <= entries(ReduceSlim::ROUNDS);
+}
+// A region that a narrower bitmap covers takes the tiles that have it: more is left for sums.
 inline ReduceShape reduce_slim_shape(uint64_t width, uint64_t expected, uint32_t P) {
-    if (P > (uint32_t)ReduceSlim::BLOCK || (double)expected > RED_SLIM_TO * (double)width)
-        return ReduceShape{ReduceWide5::C_DENSE, RED_DENSE, RED_WIDE5};
-    return reduce_tile_shape_of<ReduceSlim>(width, expected, P, RED_SLIM);
+    const ReduceShape s = reduce_tile_shape_of<ReduceSlim>(width, expected, P, RED_SLIM);
+    return s.kind == RED_SPARSE && width <= ReduceSlim::S_RANKED ? ReduceShape{ReduceSlim::S_RANKED, RED_RANKED, RED_SLIM} : s;
 }
 // The shape a call takes with a workspace of ws_bytes, at least what the least shape needs.
 inline ReduceShape reduce_shape(uint64_t B, uint64_t max_width, uint64_t expected, uint32_t P, uint64_t cus,
@@ -361,7 +380,7 @@ inline ReduceShape reduce_shape(uint64_t B, uint64_t max_width, uint64_t expecte
     const bool small = P <= RED_FEW && reduce_tiles(max_width, narrow.slots) <= RED_NARROW_TILES;
     if ((!fills || small) && fits(narrow)) return narrow;
     const ReduceShape slim = reduce_slim_shape(max_width, expected, P);
-    if (wide.kind != RED_DENSE && slim.kind != RED_DENSE && fits(slim)) return slim;
+    if (reduce_slim_pays(slim, wide, max_width, expected, P) && fits(slim)) return slim;
     return fits(wide) ? wide : reduce_least_shape(max_width, expected, P);
 }
 inline bool reduce_counts_first(const ReduceShape& shape, uint64_t B, uint64_t max_width, uint64_t cus) {

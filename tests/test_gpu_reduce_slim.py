@@ -42,23 +42,23 @@ def regions_of(make, B, P, width):
 @pytest.mark.parametrize("P,distinct,again,most", [
     (40, HITS, 0, 2), (40, HITS + 1, 0, 2), (40, HITS, 1, 2), (40, 1, 39, 40),
     (40, 4000, LIST, 2), (40, 4000, LIST + 1, 2), (40, 4000, LIST, 40), (40, 5000, 1536, 3), (40, 5000, 1537, 40),
-    (64, 8192 - 64, 0, 2), (64, 6000, 2192, 64), (64, 6000, 2193, 64), (512, 512, 2900, 512), (511, 511, 511, 2),
+    (64, 8192 - 64, 0, 2), (64, 6000, 2192, 64), (64, 6000, 2193, 64), (190, 512, 2900, 190), (191, 511, 511, 2),
     (33, 6000, 500, 33)])
 def test_what_a_tile_holds(P, distinct, again, most):
     """Regions of 60,001 slots, enough of them for wide tiles; the hits lie in the first of two tiles."""
     rng = np.random.default_rng(P * 7 + distinct + again)
-    width, span = 60_001, 50_000
+    width, span = 60_001, 39_000
     regions = regions_of(lambda lo: tile(rng, lo, span, P, distinct, again, most), 530, P, width)
-    run_batch(regions, P, width, 7_000, lead=P % 4)
-    run_batch(regions, P, width, 5_003)                           # planned wider, outputs cut short
+    run_batch(regions, P, width, 9_000, lead=P % 4)
+    run_batch(regions, P, width, 6_800)                           # planned wider, outputs cut short
 
 
 @pytest.mark.parametrize("P,width,span,distinct,again,capacity", [
-    (40, 98_304, 98_304, 5_000, 700, 5_900), (40, 65_536 * 9, 65_536, 6_000, 1_000, 6_000 * 9),
-    (3, 2_000_001, 40_000, 3_000, 2_500, 200_000), (7, 2_000_001, 40_000, 3_000, 2_500, 200_000),
-    (8, 2_000_001, 40_000, 5_000, 1_000, 200_000),
+    (70, 98_304, 98_304, 5_000, 700, 5_900), (70, 65_536 * 9, 65_536, 6_000, 1_000, 6_000 * 9),
+    (3, 2_000_001, 40_000, 3_000, 2_500, 240_000), (7, 2_000_001, 40_000, 3_000, 2_500, 240_000),
+    (8, 2_000_001, 40_000, 5_000, 1_000, 240_000),
     # 530 x 64,000 entries of eight bytes: more than the last-level cache
-    (40, 1_600_001, 150_000, 9_000, 900, 64_000)])
+    (70, 1_600_001, 150_000, 9_000, 900, 64_000)])
 def test_kinds_of_slim_tiles(P, width, span, distinct, again, capacity):
     """Wide bitmaps and the widest, few contributions in long regions, outputs past the cache."""
     rng = np.random.default_rng(width + distinct)
