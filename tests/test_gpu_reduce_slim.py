@@ -95,3 +95,55 @@ def test_values_that_are_no_ordinary_numbers():
     got = o_val.cpu().numpy().reshape(B, cap)[:, :16]
     assert np.array_equal(got, np.broadcast_to(want, got.shape), equal_nan=True)
     assert np.array_equal(np.signbit(got[:, [0, 6, 8, 14]]), np.zeros((B, 4), bool))
+
+
+def test_dense_copy_and_replays():
+    """The dense regions beside the sparse outputs, eager and from a captured graph replayed on other
+    values, with another launch in the workspace in between."""
+    rng = np.random.default_rng(5)
+    P, width, B, cap = 40, 60_001, 520, 9_000
+    ps = tile(rng, 0, 39_000, P, 5_000, 1_200)
+    one = np.concatenate(ps)
+    idx = np.concatenate([one, np.concatenate([np.array([3 * p], np.uint32) for p in range(P)])])
+    off = np.zeros((B, P + 1), np.uint64)
+    off[0] = np.concatenate([[0], np.cumsum([p.size for p in ps])])
+    off[1:] = one.size + np.arange(P + 1)                        # all others share one short input
+    lo_hi = np.tile(np.array([0, width], np.uint32), B)
+    d_idx, d_off, d_lo_hi = dev(idx), dev(off.reshape(-1)), dev(lo_hi)
+    vals = [(rng.integers(-2048, 2048, idx.size) * 2.0 ** -12).astype(np.float32) for _ in range(2)]
+    d_val = dev(vals[0]).clone()
+    o_idx = torch.zeros(B * cap, dtype=torch.int32, device=DEV)
+    o_val = torch.zeros(B * cap, device=DEV)
+    dense = torch.full((B * width,), 7.0, device=DEV)
+    nnz = torch.zeros(2 * B, dtype=torch.int64, device=DEV)
+    ws = torch.empty(okt.okt_sparse_reduce_batch_workspace_bytes(B, P, width), dtype=torch.uint8, device=DEV)
+
+    def call():
+        okt.okt_sparse_reduce_batch(d_idx, d_val, d_off, d_lo_hi, B, P, width, o_idx, o_val, cap, nnz, ws, dense_out=dense)
+
+    def check(val):
+        torch.cuda.synchronize()
+        for b, part in ((0, slice(0, one.size)), (1, slice(one.size, None)), (B - 1, slice(one.size, None))):
+            full = np.zeros(width)
+            np.add.at(full, idx[part], val[part].astype(np.float64))
+            hit = np.unique(idx[part])
+            assert nnz[2 * b:2 * b + 2].tolist() == [hit.size, hit.size]
+            assert np.array_equal(o_idx[b * cap:b * cap + hit.size].cpu().numpy().view(np.uint32), hit)
+            assert np.array_equal(o_val[b * cap:b * cap + hit.size].cpu().numpy(), full[hit].astype(np.float32))
+            assert np.array_equal(dense[b * width:(b + 1) * width].cpu().numpy(), full.astype(np.float32))
+
+    call()
+    check(vals[0])
+    graph = torch.cuda.CUDAGraph()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        call()
+        side.synchronize()
+        with torch.cuda.graph(graph, stream=side):
+            call()
+    for i in range(4):
+        d_val.copy_(dev(vals[i % 2]))
+        dense.fill_(7.0), o_val.zero_(), nnz.zero_()
+        graph.replay()
+        check(vals[i % 2])
+        ws.random_(0, 255)                                       # garbage between the replays
