@@ -341,7 +341,8 @@ inline ReduceShape reduce_least_shape(uint64_t width, uint64_t expected, uint32_
 //   0.90 times as fast as wide tiles, 16 contributions 1.08 / 1.08 / 1.05 / 1.00;
 // - from RED_SLIM_P contributions on: their slices are short, and where they collide the windows of
 //   a slim tile read little pieces of each (256 contributions, zipf, 60 K to 500 K slots, 0.81 to
-//   0.98 times; 30 % in common 0.91 to 0.98; evenly hit 1.13 to 1.2; 128 contributions 0.94 to 1.22,
+//   0.98 times; 30 % in common 0.91 to 0.98; evenly hit 1.13 to 1.2; 150, zipf, and 191, 30 % in common,
+//   0.84 and 0.83; 128, zipf, in common and evenly, 0.94 to 1.22,
 //   0.98 to 1.0 and 1.14 to 1.17);
 // - where the bitmap limits wide tiles so that the entries of a region with 30 % in common (1.41
 //   entries a hit slot) still fit their registers, and slim ones have no room for as many: 36
@@ -350,7 +351,7 @@ inline ReduceShape reduce_least_shape(uint64_t width, uint64_t expected, uint32_
 //   slot) make windows of a slim tile and none of a wide one: 36 contributions, 0.06 of 200 K and
 //   500 K slots 0.73 to 0.75.
 constexpr double RED_SLIM_TO = 0.4, RED_COMMON = 1.41;
-constexpr uint32_t RED_SLIM_P = 192;
+constexpr uint32_t RED_SLIM_P = 129;
 inline bool reduce_slim_pays(const ReduceShape& slim, const ReduceShape& wide, uint64_t width, uint64_t expected, uint32_t P) {
     if (wide.kind == RED_DENSE || slim.kind == RED_DENSE) return false;
     if (P >= RED_SLIM_P || (double)expected > RED_SLIM_TO * (double)width) return false;

@@ -42,7 +42,7 @@ def regions_of(make, B, P, width):
 @pytest.mark.parametrize("P,distinct,again,most", [
     (40, HITS, 0, 2), (40, HITS + 1, 0, 2), (40, HITS, 1, 2), (40, 1, 39, 40),
     (40, 4000, LIST, 2), (40, 4000, LIST + 1, 2), (40, 4000, LIST, 40), (40, 5000, 1536, 3), (40, 5000, 1537, 40),
-    (64, 8192 - 64, 0, 2), (64, 6000, 2192, 64), (64, 6000, 2193, 64), (190, 512, 2900, 190), (191, 511, 511, 2),
+    (64, 8192 - 64, 0, 2), (64, 6000, 2192, 64), (64, 6000, 2193, 64), (128, 512, 2900, 128), (127, 511, 511, 2),
     (33, 6000, 500, 33)])
 def test_what_a_tile_holds(P, distinct, again, most):
     """Regions of 60,001 slots, enough of them for wide tiles; the hits lie in the first of two tiles."""
