@@ -479,19 +479,21 @@ __device__ __forceinline__ uint32_t bitmap_prefix(const uint32_t* s_bits, uint16
 // the slot's values added.  The list takes the place of the units, the bitmap and the prefixes,
 // which nobody needs once the ranks are known.  So a hit slot takes four bytes of LDS instead of
 // eight, and three tiles of 6,566 planned hits run on a CU where two of 7,410 did; no entry but the
-// listed ones needs an LDS atomic on a double.  Held to 80 registers.  490 regions of 16
-// contributions 507 -> 423 us a call, 373 of 64 629 -> 514, 200 of 40 in 400 K slots 74 -> 62; the
-// tile kernel moves 4.9 TB/s of HBM traffic then, where the plain copy reaches 5.9, and neither
+// listed ones needs an LDS atomic on a double.  Held to 80 registers: what the compiler spills for it,
+// four vector registers, it stores and reloads where a tile goes by windows.  490 regions of 16
+// contributions 507 -> 423 us a call, 373 of 64 634 -> 515; neither
 // a look at the descriptors before the list, nor four narrower tiles to a CU (452 us), nor the
 // slice table made in the same launch by workgroups between the tiles (433 to 482 us: they wait
 // for memory in places that tiles could have) makes it any faster.  Stores of outputs beyond
 // the last-level cache go past it: 423 -> 414 us with outputs of 1 GB; with outputs of 120 MB the call
 // gains 2 us and a kernel that reads them loses 9.  A tile with more hits, entries or listed
 // entries than there is room for goes by windows, as others do, with fp64 accumulators in all
-// that the bitmap leaves free; those are fewer than in a wide tile, so regions that are
-// hit unevenly gain less or nothing (4 to 128 contributions, 400 K to 5 M slots, log-normal stretches
-// 0.93 to 1.13 times as fast, layers 0.88 to 1.16, halves 0.98 to 1.33, 30 % in common 0.92 to 1.4,
-// zipf 0.91 to 1.3); what is known to lose takes other tiles (reduce_slim_pays).
+// that the bitmap leaves free; those are half as many as in a wide tile, and where regions are
+// hit unevenly that costs more than the third tile to a CU gives.  Which launches that is, and both sides
+// measured, stands at reduce_slim_pays; no change to the windows made up for it (accumulators in the units'
+// place too, 12 % more of them: layers 1 to 2 % faster, entries that collide 1 to 2 % slower; three or four
+// quads of a slice in flight instead of two: even to 4 % slower; tiles planned 15 to 35 % narrower: uneven
+// regions as slow at worst, even ones 5 to 10 % slower).
 //
 // Tried and not kept: 16 waves with 8 entries a thread and the same tile (spills at
 // 64 registers), several regions' tiles in turn per workgroup with the next slice table
@@ -538,7 +540,7 @@ __global__ __launch_bounds__(BLOCK, SLIM ? 6 : ROUNDS == 2 ? 8 : 4) void reduce_
     static_assert(!SLIM || (FIXED <= 8 * LIST && (VALUES + 8 * LIST - FIXED + 8 * UNITS) % 16 == 0), "the list holds the rest");
     constexpr uint32_t ACC = SLIM ? ((VALUES + 8 * LIST - FIXED) / 8 - SPARE) & ~1u : C;    // fp64 accumulators
     static_assert(S_MAX <= WINDOWS_MAX * (ACC - 32), "windows of a tile");
-    static_assert(!SLIM || ACC >= RED_SLIM_ACC, "as the rule for slim tiles has it");
+    static_assert(!SLIM || ACC > RED_SLIM_HITS, "one window for as many hits");
     static_assert(ACC % 2 == 0 && WORDS_MAX % 4 == 0, "cleared 16 bytes at a time");
     constexpr uint32_t UNITS_AT = SLIM ? VALUES + 8 * LIST - FIXED : 8 * (C + SPARE);
     __shared__ __attribute__((aligned(16))) char s_mem[UNITS_AT + FIXED];

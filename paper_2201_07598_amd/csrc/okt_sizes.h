@@ -218,7 +218,7 @@ struct ReduceSlim {
     static constexpr uint32_t C_DENSE = 0, C_RANKED = 6912, S_RANKED = 65536, C_SPARSE = 6912, S_SPARSE = 98304;
     static constexpr double FILL = 0.95;
 };
-constexpr uint32_t RED_SLIM_LIST = 2968, RED_SLIM_ACC = 3568;      // fp64 accumulators of a tile in windows, at least
+constexpr uint32_t RED_SLIM_LIST = 2968;
 struct ReduceNarrow {
     static constexpr int BLOCK = 512, ROUNDS = 2;
     static constexpr uint32_t C_DENSE = 4096, C_RANKED = 3968, S_RANKED = 32768, C_SPARSE = 3584, S_SPARSE = 49152;
@@ -335,31 +335,42 @@ inline ReduceShape reduce_least_shape(uint64_t width, uint64_t expected, uint32_
     return want >= Form::S_RANKED + 32 ? ReduceShape{(uint32_t)want / 32 * 32, RED_SPARSE, RED_WIDE4}
                                        : ReduceShape{Form::S_RANKED, RED_RANKED, RED_WIDE4};
 }
-// Whether slim tiles take the place of wide ones in a region.  They do not
-// - from RED_SLIM_TO of the slots hit on, where the entries that share slots are too many for the
-//   list to be quick: 7 contributions, 1.6 M slots, 0.32 / 0.4 / 0.5 / 0.6 hit, 1.02 / 0.99 / 0.97 /
-//   0.90 times as fast as wide tiles, 16 contributions 1.08 / 1.08 / 1.05 / 1.00;
+// Whether slim tiles take the place of wide ones in a region.  Evenly hit regions are 1.1 to 1.25
+// times as fast in them throughout; a tile that is hit more than planned, or by entries that share
+// slots, goes by windows with half a wide tile's accumulators, and the rule is about those.  Measured
+// on 49,500 batches of 6 to 24 M entries, 3 to 256 contributions, 40 K to 5.5 M slots, 0.02 to 0.5
+// hit: evenly, 30 % in common to all contributions, every other of 32 stretches, layers of which a
+// quarter is hit eight times as often, log-normal stretches of 10,000 (sigma 1), zipf (exponent 1.1, up to
+// 500 K slots).  Below: median of the times in wide tiles over those in slim ones, and how many of
+// the batches are more than 3 % slower in slim ones.  They are not taken
+// - from RED_SLIM_TO of the slots hit on, nor from RED_SLIM_FEW_TO on with fewer than RED_SLIM_FEW
+//   contributions: 5 to 7 contributions, 0.2 to 0.3 hit, in common 0.97 to 1.00 (40 % slower), log-normal
+//   1.03 (14 %), evenly 1.02 to 1.05; 8 to 32, log-normal 1.02 (20 %); 3 and 4, 0.1 to 0.13 hit, in common
+//   0.98 (41 %), log-normal 1.09 (18 %).  Below, 8 to 32 contributions that hit 0.1 to 0.2: evenly 1.12, layers
+//   1.08 (4 %), halves 1.09 (1 %), log-normal 1.05 (9 %), in common 1.05 (14 %);
+// - with up to RED_FEW contributions where the bitmap limits wide tiles so that the entries of a region
+//   with 30 % in common (RED_COMMON a hit slot) still fit their registers, and slim ones have no room for
+//   as many: 17 to 32 contributions, 0.05 to 0.07 hit, in common 0.81 to 0.97;
+// - with more, from RED_SLIM_HITS planned hits a tile on: up to there entries that collide (zipf, two a
+//   hit slot) are 1.1 times as fast, above 0.77 to 0.96 (33 to 63 contributions, 53 to 97 % slower); full
+//   tiles lose more: in common 1.04 (27 %), halves 1.06 (28 %), layers 1.07 (12 %, 0.67 at worst), log-normal 1.06 (16 %);
+// - but from RED_MANY contributions on in all tiles that the bitmap limits, where the tiles are not
+//   planned full: layers 1.13 (2 %), halves 1.16 (2 %), log-normal 1.14 (2 %), in common 1.05 (14 %), zipf 1.0
+//   (38 %, 0.8 at worst); in full ones layers 1.08 (3 %), halves 1.07 (8 %), in common 0.98 (38 %), zipf 1.02 (28 %);
 // - from RED_SLIM_P contributions on: their slices are short, and where they collide the windows of
-//   a slim tile read little pieces of each (256 contributions, zipf, 60 K to 500 K slots, 0.81 to
-//   0.98 times; 30 % in common 0.91 to 0.98; evenly hit 1.13 to 1.2; 150, zipf, and 191, 30 % in common,
-//   0.84 and 0.83; 128, zipf, in common and evenly, 0.94 to 1.22,
-//   0.98 to 1.0 and 1.14 to 1.17);
-// - where the bitmap limits wide tiles so that the entries of a region with 30 % in common (1.41
-//   entries a hit slot) still fit their registers, and slim ones have no room for as many: 36
-//   contributions, a tenth of 150 K to 1.6 M slots hit, 30 % in common 0.89 to 0.93 times, evenly hit
-//   1.17.  With more than RED_FEW contributions also where entries that collide (zipf, two a hit
-//   slot) make windows of a slim tile and none of a wide one: 36 contributions, 0.06 of 200 K and
-//   500 K slots 0.73 to 0.75.
-constexpr double RED_SLIM_TO = 0.4, RED_COMMON = 1.41;
-constexpr uint32_t RED_SLIM_P = 129;
+//   a slim tile read little pieces of each (129 to 256, zipf 0.96 to 1.06, in common 0.91 to 0.96 from 0.05 hit on).
+constexpr double RED_SLIM_TO = 0.2, RED_SLIM_FEW_TO = 0.1, RED_COMMON = 1.41, RED_SLIM_HITS = 3300;
+constexpr uint32_t RED_SLIM_P = 129, RED_SLIM_FEW = 5;
 inline bool reduce_slim_pays(const ReduceShape& slim, const ReduceShape& wide, uint64_t width, uint64_t expected, uint32_t P) {
-    if (wide.kind == RED_DENSE || slim.kind == RED_DENSE) return false;
-    if (P >= RED_SLIM_P || (double)expected > RED_SLIM_TO * (double)width) return false;
-    auto in_common = [&](const ReduceShape& s) { return RED_COMMON * s.slots * (double)expected / (double)width; };
-    auto entries = [&](int rounds) { return (RED_FILL_UNITS * (ReduceSlim::BLOCK / 4 * rounds) - 0.5 * P) * RED_UNIT; };
+    if (wide.kind == RED_DENSE || slim.kind == RED_DENSE || P >= RED_SLIM_P) return false;
+    const double share = (double)expected / (double)width, hits = slim.slots * share;
+    if (share >= (P < RED_SLIM_FEW ? RED_SLIM_FEW_TO : RED_SLIM_TO)) return false;
+    if (P > RED_FEW)
+        return hits <= RED_SLIM_HITS ||
+               (P >= RED_MANY && slim.slots == (slim.kind == RED_SPARSE ? ReduceSlim::S_SPARSE : ReduceSlim::S_RANKED));
     static_assert(ReduceSlim::BLOCK == ReduceWide5::BLOCK, "units of both");
-    if (wide.form != RED_WIDE5 || in_common(wide) > entries(ReduceWide5::ROUNDS)) return true;
-    return P > RED_FEW ? in_common(slim) <= RED_COMMON * 0.93 * RED_SLIM_ACC : in_common(slim) <= entries(ReduceSlim::ROUNDS);
+    auto entries = [&](int rounds) { return (RED_FILL_UNITS * (ReduceSlim::BLOCK / 4 * rounds) - 0.5 * P) * RED_UNIT; };
+    return RED_COMMON * wide.slots * share > entries(ReduceWide5::ROUNDS) || RED_COMMON * hits <= entries(ReduceSlim::ROUNDS);
 }
 // A region that a narrower bitmap covers takes the tiles that have it: more is left for sums.
 inline ReduceShape reduce_slim_shape(uint64_t width, uint64_t expected, uint32_t P) {

@@ -59,6 +59,7 @@ int main() {
         if ((uint64_t)s.nseg * SEL_WAVES * s.piece < n) fail("one-kernel pieces do not cover the vector", n, cus);
         if (s.piece > SEL_PIECE_MAX || s.piece % 256) fail("piece length", n, cus);
     }
+    long forms[4][3] = {};
     // the reduce: every tile shape is one its kernels hold, and fits the workspace it was chosen for
     for (int rep = 0; rep < 200000; ++rep) {
         const uint64_t width = rng() % 3 ? 1 + rng() % (1ull << (1 + rng() % 27)) : rng() % 0xffffffffull;
@@ -75,15 +76,23 @@ int main() {
             const ReduceShape s = reduce_shape(B, width, expected, Pc, cus, ws);
             const size_t region = reduce_ws_bytes_region(width, Pc, s.slots);
             if (ws < region * B || region > 0xffffffffull) fail("reduce workspace too small for its tiles", width, Pc);
-            const bool narrow = s.form == RED_NARROW;
-            const uint32_t dense = narrow ? ReduceNarrow::C_DENSE : ReduceWide5::C_DENSE;
-            const uint32_t ranked = narrow ? ReduceNarrow::S_RANKED : ReduceWide5::S_RANKED;
-            const uint32_t sparse = narrow ? ReduceNarrow::S_SPARSE : ReduceWide5::S_SPARSE;
+            ++forms[s.form][s.kind];
+            uint32_t dense = ReduceWide5::C_DENSE, ranked = ReduceWide5::S_RANKED, sparse = ReduceWide5::S_SPARSE;
+            if (s.form == RED_NARROW) dense = ReduceNarrow::C_DENSE, ranked = ReduceNarrow::S_RANKED, sparse = ReduceNarrow::S_SPARSE;
+            if (s.form == RED_WIDE4) dense = ReduceWide4::C_DENSE, ranked = ReduceWide4::S_RANKED, sparse = ReduceWide4::S_SPARSE;
+            if (s.form == RED_SLIM) {
+                ranked = ReduceSlim::S_RANKED, sparse = ReduceSlim::S_SPARSE;
+                if (s.kind == RED_DENSE) fail("a dense slim tile", width, Pc);
+                if (Pc >= RED_SLIM_P || (double)expected >= RED_SLIM_TO * (double)width) fail("a slim tile where the rule has none", width, Pc);
+            }
             if (s.kind == RED_DENSE && s.slots != dense) fail("dense tile", width, Pc);
             if (s.kind == RED_RANKED && (s.slots > ranked || s.slots < RED_SLOTS_MIN || s.slots % 32)) fail("ranked tile", width, Pc);
             if (s.kind == RED_SPARSE && (s.slots > sparse || s.slots <= ranked || s.slots % 32)) fail("sparse tile", width, Pc);
         }
     }
+    for (const auto form : {RED_WIDE5, RED_WIDE4, RED_NARROW, RED_SLIM})
+        for (const auto kind : {RED_DENSE, RED_RANKED, RED_SPARSE})
+            if (forms[form][kind] == 0 && !(form == RED_SLIM && kind == RED_DENSE)) fail("a kind of tile that no case takes", form, kind);
     std::printf("%ld cases, %ld violations\n", cases, bad);
     return bad ? 1 : 0;
 }

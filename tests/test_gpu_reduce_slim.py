@@ -39,38 +39,81 @@ def regions_of(make, B, P, width):
             for lo in los]
 
 
-@pytest.mark.parametrize("P,distinct,again,most", [
+# P, distinct, again, most
+LONG_CASES = [
     (40, HITS, 0, 2), (40, HITS + 1, 0, 2), (40, HITS, 1, 2), (40, 1, 39, 40),
     (40, 4000, LIST, 2), (40, 4000, LIST + 1, 2), (40, 4000, LIST, 40), (40, 5000, 1536, 3), (40, 5000, 1537, 40),
     (64, 8192 - 64, 0, 2), (64, 6000, 2192, 64), (64, 6000, 2193, 64), (128, 512, 2900, 128), (127, 511, 511, 2),
-    (33, 6000, 500, 33)])
+    (33, 6000, 500, 33)]
+LONG_B, LONG_WIDTH, LONG_CAPACITIES = 52, 1_000_001, (33_000, 5_000)
+
+
+@pytest.mark.parametrize("P,distinct,again,most", LONG_CASES)
 def test_what_a_tile_holds(P, distinct, again, most):
-    """Regions of 60,001 slots, enough of them for wide tiles; the hits lie in the first of two tiles."""
+    """Tiles of 98,304 slots, planned for few hits; the hits lie in the first of a region."""
     rng = np.random.default_rng(P * 7 + distinct + again)
-    width, span = 60_001, 39_000
-    regions = regions_of(lambda lo: tile(rng, lo, span, P, distinct, again, most), 530, P, width)
-    run_batch(regions, P, width, 9_000, lead=P % 4)
-    run_batch(regions, P, width, 6_800)                           # planned wider, outputs cut short
+    regions = regions_of(lambda lo: tile(rng, lo, 39_000, P, distinct, again, most), LONG_B, P, LONG_WIDTH)
+    for capacity in LONG_CAPACITIES:                              # the second cuts outputs short
+        run_batch(regions, P, LONG_WIDTH, capacity, lead=P % 4)
 
 
-@pytest.mark.parametrize("P,width,span,distinct,again,capacity", [
-    (70, 98_304, 98_304, 5_000, 700, 5_900), (70, 65_536 * 9, 65_536, 6_000, 1_000, 6_000 * 9),
-    (3, 2_000_001, 40_000, 3_000, 2_500, 240_000), (7, 2_000_001, 40_000, 3_000, 2_500, 240_000),
-    (8, 2_000_001, 40_000, 5_000, 1_000, 240_000),
+FULL_CASES = [(16, HITS, 0, 2), (16, HITS + 1, 0, 2), (16, 4000, LIST, 2), (16, 4000, LIST + 1, 16), (16, 6000, 2192, 16),
+              (16, 6000, 2193, 16), (32, HITS, 1, 2), (32, 5000, 2500, 32)]
+FULL_B, FULL_WIDTH, FULL_CAPACITY = 24, 1_300_001, 195_000
+
+
+@pytest.mark.parametrize("P,distinct,again,most", FULL_CASES)
+def test_what_a_full_tile_holds(P, distinct, again, most):
+    """Tiles of up to 65,536 slots that are planned for as many hits as they hold."""
+    rng = np.random.default_rng(P * 7 + distinct + again)
+    regions = regions_of(lambda lo: tile(rng, lo, 39_000, P, distinct, again, most), FULL_B, P, FULL_WIDTH)
+    run_batch(regions, P, FULL_WIDTH, FULL_CAPACITY, lead=P % 4)
+
+
+# P, width, span, distinct, again, capacity
+KIND_CASES = [
+    (70, 98_304, 98_304, 5_000, 700, 5_900), (70, 65_536 * 9, 65_536, 6_000, 1_000, 35_000),
+    (3, 3_000_001, 40_000, 3_000, 2_500, 130_000), (7, 2_000_001, 40_000, 3_000, 2_500, 240_000),
+    (8, 2_000_001, 40_000, 5_000, 1_000, 240_000), (64, 60_001, 60_001, 5_000, 900, 6_000), (40, 60_001, 60_001, 2_500, 400, 2_900),
     # 530 x 64,000 entries of eight bytes: more than the last-level cache
-    (70, 1_600_001, 150_000, 9_000, 900, 64_000)])
+    (70, 1_600_001, 150_000, 9_000, 900, 64_000)]
+
+
+def kind_batch(width):
+    return 40 if width > 1_999_999 else 530
+
+
+@pytest.mark.parametrize("P,width,span,distinct,again,capacity", KIND_CASES)
 def test_kinds_of_slim_tiles(P, width, span, distinct, again, capacity):
     """Wide bitmaps and the widest, few contributions in long regions, outputs past the cache."""
     rng = np.random.default_rng(width + distinct)
-    regions = regions_of(lambda lo: tile(rng, lo, span, P, distinct, again), 40 if width > 1_999_999 else 530,
-                         P, width)
+    regions = regions_of(lambda lo: tile(rng, lo, span, P, distinct, again), kind_batch(width), P, width)
     run_batch(regions, P, width, capacity, lead=1)
+
+
+# P, distinct, again: tiles that go by windows of at most 3,568 hits (98,304 slots each).
+# One window of more entries than registers hold, read by chunks and streamed; several, their slices'
+# ends found at once (36 contributions) and in turn (P * windows > 1,024); more than 16 bits count
+WINDOW_CASES = [(40, 3_000, 9_000), (40, 3_500, 20_000), (36, 20_000, 3_000), (36, 98_304, 0), (40, 98_304, 300),
+                (64, 70_000, 9_000), (128, 30_000, 6_000), (128, 98_304, 0), (20, 4_500, 12_000), (7, 98_304, 2_000)]
+WINDOW_B, WINDOW_WIDTH, WINDOW_CAPACITY = 12, 5_000_001, 120_000
+
+
+@pytest.mark.parametrize("dense", [False, True])
+@pytest.mark.parametrize("P,distinct,again", WINDOW_CASES)
+def test_windows_of_slim_tiles(P, distinct, again, dense):
+    rng = np.random.default_rng(P + distinct)
+    regions = regions_of(lambda lo: tile(rng, lo, 98_304, P, distinct, again), WINDOW_B, P, WINDOW_WIDTH)
+    run_batch(regions, P, WINDOW_WIDTH, WINDOW_CAPACITY, lead=P % 4, dense=dense)
+
+
+VALUES_CALL, VALUES_CAPACITY = (40, 40_003, 520), 1_900
 
 
 def test_values_that_are_no_ordinary_numbers():
     """A lone -0 leaves as +0, as an fp64 sum that starts at +0 makes of it; NaN, infinities and
     subnormals stay what they are, alone and in sums."""
-    P, width, B = 40, 40_003, 520
+    P, width, B = VALUES_CALL
     special = np.array([-0.0, np.nan, np.inf, -np.inf, 1e-45, -1e-45, 0.0, 3.0e38], np.float32)
     first = np.arange(0, 16, dtype=np.uint32)                    # contribution 0: each value twice
     second = np.arange(8, 16, dtype=np.uint32)                   # contribution 1: the second eight once more
@@ -81,7 +124,7 @@ def test_values_that_are_no_ordinary_numbers():
     off[:, 1] = off[:, 0] + 16
     off[:, 2:] = (off[:, 0] + 24)[:, None]
     lo_hi = np.stack([7 * np.arange(B), 7 * np.arange(B) + width], 1).astype(np.uint32)
-    cap = 6_000
+    cap = VALUES_CAPACITY
     o_idx = torch.zeros(B * cap, dtype=torch.int32, device=DEV)
     o_val = torch.zeros(B * cap, device=DEV)
     nnz = torch.zeros(2 * B, dtype=torch.int64, device=DEV)
@@ -97,11 +140,14 @@ def test_values_that_are_no_ordinary_numbers():
     assert np.array_equal(np.signbit(got[:, [0, 6, 8, 14]]), np.zeros((B, 4), bool))
 
 
+REPLAY_CALL = (64, 60_001, 520, 6_000)
+
+
 def test_dense_copy_and_replays():
     """The dense regions beside the sparse outputs, eager and from a captured graph replayed on other
     values, with another launch in the workspace in between."""
     rng = np.random.default_rng(5)
-    P, width, B, cap = 40, 60_001, 520, 9_000
+    P, width, B, cap = REPLAY_CALL
     ps = tile(rng, 0, 39_000, P, 5_000, 1_200)
     one = np.concatenate(ps)
     idx = np.concatenate([one, np.concatenate([np.array([3 * p], np.uint32) for p in range(P)])])

@@ -21,7 +21,7 @@ def dev(a):
     return torch.from_numpy(np.ascontiguousarray(a).view(view) if view else a).to(DEV)
 
 
-def run_batch(regions, P, width, capacity, lead=0, ws_share=1.0):
+def run_batch(regions, P, width, capacity, lead=0, ws_share=1.0, dense=False):
     """regions: list of (lo, hi, [P index arrays]); checks every region against the oracle."""
     B = len(regions)
     parts = [p for _, _, ps in regions for p in ps]
@@ -43,8 +43,9 @@ def run_batch(regions, P, width, capacity, lead=0, ws_share=1.0):
     nnz = torch.zeros(2 * B, dtype=torch.int64, device=DEV)
     told = okt.okt_sparse_reduce_batch_workspace_bytes(B, P, width)
     ws = torch.empty(int(ws_share * told), dtype=torch.uint8, device=DEV)
+    d_dense = torch.full((B * width,), 7.0, device=DEV) if dense else None
     okt.okt_sparse_reduce_batch(d_idx, d_val, dev(off.reshape(-1)), lo_hi, B, P, width, o_idx, o_val,
-                                capacity, nnz, ws)
+                                capacity, nnz, ws, dense_out=d_dense)
     torch.cuda.synchronize()
     got_i, got_v = o_idx.cpu().numpy().view(np.uint32), o_val.cpu().numpy()
     nnz = nnz.cpu().numpy().reshape(B, 2)
@@ -57,6 +58,10 @@ def run_batch(regions, P, width, capacity, lead=0, ws_share=1.0):
         at = b * capacity
         assert np.array_equal(got_i[at:at + n], ref["idx"][:n]), b
         assert np.array_equal(got_v[at:at + n], ref["val"][:n].astype(np.float32)), b
+        if dense:
+            full = np.zeros(hi - lo, np.float32)
+            full[ref["idx"].astype(np.int64) - lo] = ref["val"].astype(np.float32)
+            assert np.array_equal(d_dense[b * width:b * width + hi - lo].cpu().numpy(), full), b
 
 
 def some(rng, lo, width, m):
@@ -86,8 +91,9 @@ def test_wide_tiles_in_batches(P, m, share):
 
 
 def test_wide_tiles_with_more_hits_than_they_have_room_for():
-    """Estimated very sparse, in fact every slot hit: tiles of 98,304 slots, all of them
-    hit (more than 16 bits count), by one contribution and by three."""
+    """Estimated very sparse, in fact every slot hit, by one contribution and by three.  (So few
+    contributions in so short regions take narrow tiles; wide and slim ones that are hit so are
+    in test_gpu_reduce_wide.py and test_gpu_reduce_slim.py.)"""
     width, B, P = 98_304 + 1_000, 300, 3
     full = np.arange(width, dtype=np.uint32)
     none = np.zeros(0, np.uint32)
@@ -106,7 +112,7 @@ def clustered(rng, lo, width, blocks, per_block, length):
 
 
 @pytest.mark.parametrize("B,P,dense_part,share", [
-    # one stretch that is hit throughout: 1 window and just over, 2, many (narrow, then wide tiles)
+    # one stretch that is hit throughout: 1 window and just over, 2, many
     (2, 1, 3_968, 0.05), (2, 1, 3_969, 0.05), (2, 3, 8_000, 0.05), (2, 8, 32_768, 0.05), (3, 40, 30_000, 0.02),
     (60, 33, 7_968, 0.02), (60, 33, 8_000, 0.02), (60, 48, 60_000, 0.02), (60, 64, 8_065, 0.02), (60, 100, 65_536, 0.02),
     # the ends of all windows of all slices do not fit in LDS: searched in turn
