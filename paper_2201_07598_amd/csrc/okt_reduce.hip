@@ -484,9 +484,9 @@ __device__ __forceinline__ uint32_t bitmap_prefix(const uint32_t* s_bits, uint16
 // contributions 507 -> 423 us a call, 373 of 64 634 -> 515; neither
 // a look at the descriptors before the list, nor four narrower tiles to a CU (452 us), nor the
 // slice table made in the same launch by workgroups between the tiles (433 to 482 us: they wait
-// for memory in places that tiles could have) makes it any faster.  Stores of outputs beyond
-// the last-level cache go past it: 423 -> 414 us with outputs of 1 GB; with outputs of 120 MB the call
-// gains 2 us and a kernel that reads them loses 9.  A tile with more hits, entries or listed
+// for memory in places that tiles could have), nor stores of the outputs past the last-level cache
+// (930 MB of them 417.9 us without and 419.9 with, 970 MB 508.8 and 510.5) makes it any faster.
+// A tile with more hits, entries or listed
 // entries than there is room for goes by windows, as others do, with fp64 accumulators in all
 // that the bitmap leaves free; those are half as many as in a wide tile, and where regions are
 // hit unevenly that costs more than the third tile to a CU gives.  Which launches that is, and both sides
@@ -518,7 +518,7 @@ __global__ __launch_bounds__(BLOCK, SLIM ? 6 : ROUNDS == 2 ? 8 : 4) void reduce_
     uint32_t hi0, uint32_t P, uint32_t max_width, uint32_t slots,
     uint32_t* __restrict__ idx_out, float* __restrict__ val_out, uint64_t capacity,
     uint64_t* __restrict__ nnz_out, float* __restrict__ dense_out, char* ws,
-    uint32_t ws_region_bytes, uint32_t table_offset, uint32_t past_cache) {
+    uint32_t ws_region_bytes, uint32_t table_offset) {
     constexpr int WAVES = BLOCK / WAVE;
     constexpr bool DENSE = S_MAX == C;            // accumulator = slot, always
     constexpr uint32_t WORDS_MAX = S_MAX / 32;
@@ -980,13 +980,8 @@ __global__ __launch_bounds__(BLOCK, SLIM ? 6 : ROUNDS == 2 ? 8 : 4) void reduce_
             for (int i = 0; i < PER; ++i) {
                 const uint32_t k = k0 + i * BLOCK;
                 if (k < out) {
-                    if (SLIM && past_cache) {
-                        __builtin_nontemporal_store(s_idx[k], to_idx + k);
-                        __builtin_nontemporal_store(x[i], to_val + k);
-                    } else {
-                        to_idx[k] = s_idx[k];
-                        to_val[k] = x[i];
-                    }
+                    to_idx[k] = s_idx[k];
+                    to_val[k] = x[i];
                 }
                 if (dense && k < in_round) dense[s_idx[k] - a] = x[i];
             }
@@ -1237,12 +1232,11 @@ int reduce_launch(const uint32_t* d_idx_cat, const float* d_val_cat,
         return launch_status();
     }
     timing_before(s);
-    const uint32_t past_cache = stream_past_cache(2 * (uint64_t)B * capacity);
     auto launch = [&](auto* tile_kernel, uint32_t block) {
         hipLaunchKernelGGL(tile_kernel, dim3((unsigned)tiles, B), dim3(block), 0, s, d_idx_cat, d_val_cat,
                            d_seg_begin, d_seg_end, seg_stride, d_lo_hi, lo, hi, P, max_width, slots,
                            d_idx_out, d_val_out, capacity, d_nnz_out, d_dense, (char*)d_ws,
-                           (uint32_t)region_bytes, table_offset, past_cache);
+                           (uint32_t)region_bytes, table_offset);
     };
     if (placed) {
         using F = ReduceNarrow;

@@ -1,6 +1,7 @@
 """The slim tiles of the reduce (floats for a slot's first entry, a list for the others) at
 the edges of what they hold: hit slots, listed entries and units up to and one past the limit,
-slots that many contributions share, both kinds of bitmap, outputs written past the cache.
+slots that many contributions share, both kinds of bitmap, room for more outputs than the last-level
+cache holds.
 
 Sums are of dyadic values small enough that fp64 adds them exactly in any order, so the oracle's
 result is the only correct one, bit for bit."""
@@ -85,7 +86,7 @@ def kind_batch(width):
 
 @pytest.mark.parametrize("P,width,span,distinct,again,capacity", KIND_CASES)
 def test_kinds_of_slim_tiles(P, width, span, distinct, again, capacity):
-    """Wide bitmaps and the widest, few contributions in long regions, outputs past the cache."""
+    """Wide bitmaps and the widest, few contributions in long regions, room for many outputs."""
     rng = np.random.default_rng(width + distinct)
     regions = regions_of(lambda lo: tile(rng, lo, span, P, distinct, again), kind_batch(width), P, width)
     run_batch(regions, P, width, capacity, lead=1)
