@@ -28,11 +28,26 @@ def test_edges_of_dense_tiles(B, P, width):
             ps = [np.array([lo + width - 1], np.uint32)] * P
         regions.append((lo, lo + width, ps))
     run_batch(regions, P, width, width, lead=1)
-    run_batch(regions, P, width, max(1, (2 * width) // 3))       # cut short
+    run_batch(regions, P, width, max(1, (2 * width) // 3))       # cut short (two contributions take ranked tiles then)
+    run_batch(regions, P, width, max(1, width - width // 20))    # cut short in dense ones
+
+
+@pytest.mark.parametrize("width", [9_215, 9_216, 9_217, 18_433])
+def test_dense_copy_of_wide_dense_tiles(width):
+    """Tiles of 9,216 slots, in a launch of enough of them."""
+    rng = np.random.default_rng(width)
+    B, P = 530, 70
+    regions = []
+    for b in range(B):
+        ps = [some(rng, 3 * b, width, width // 2) if b in (0, B - 1) else np.array([3 * b + p], np.uint32) for p in range(P)]
+        regions.append((3 * b, 3 * b + width, ps))
+    run_batch(regions, P, width, width, lead=3, dense=True)
+    run_batch(regions, P, width, width // 2, dense=True)         # sparse outputs cut short, dense ones whole
 
 
 @pytest.mark.parametrize("width", [33, 4_097, 9_217])
 def test_dense_copy_of_dense_tiles(width):
+    """One region: tiles of 4,096 slots."""
     rng = np.random.default_rng(width)
     lo, P = 77, 3
     ps = [some(rng, lo, width, width // 2) for _ in range(P)]

@@ -1,13 +1,17 @@
 """Which tiles a call of the reduce takes, asked of the host's rule on the CPU: that the GPU tests
 that are about one kernel run that kernel, and that regions which may be hit unevenly do not take
 the slim tiles where those lose."""
+import itertools
 import os
 import shutil
 import subprocess
 
+import numpy as np
 import pytest
 
+import test_gpu_reduce_dense as dense
 import test_gpu_reduce_slim as slim
+import test_gpu_reduce_tiles as tiles
 import test_gpu_reduce_wide as wide
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -73,3 +77,40 @@ def test_slim_tiles_where_they_gain(forms):
     calls = [(490, 1_597_315, 249_000, 16), (373, 5_250_000, 342_000, 64), (400, 400_000, 12_000, 40), (400, 800_000, 24_000, 100),
              (60, 3_000_001, 120_000, 4), (60, 2_000_001, 380_000, 12)]
     assert [f for f in forms(calls) if not f.startswith("slim")] == []
+
+
+def batches_of(test, module, monkeypatch):
+    """The (B, width, capacity, P) of every batch that a parametrised GPU test would run."""
+    got, none = [], np.zeros(0, np.uint32)
+    monkeypatch.setattr(module, "run_batch",
+                        lambda regions, P, width, capacity, **_: got.append((len(regions), width, capacity, P)))
+    for name in ("some", "clustered"):
+        if hasattr(module, name):
+            monkeypatch.setattr(module, name, lambda *_: none)
+    marks = [m.args for m in getattr(test, "pytestmark", []) if m.name == "parametrize"]
+    for values in itertools.product(*(a[1] for a in marks)):
+        kw = {}
+        for (names, _), v in zip(marks, values):
+            names = names.split(",")
+            kw.update(zip(names, v if len(names) > 1 else [v]))
+        test(**kw)
+    return got
+
+
+@pytest.mark.parametrize("module,test,kernels", [
+    (tiles, "test_wide_tiles_in_batches", {"narrow ranked", "narrow sparse", "slim ranked", "wide4 ranked", "wide4 dense"}),
+    (tiles, "test_wide_tiles_with_more_hits_than_they_have_room_for", {"narrow sparse"}),
+    (tiles, "test_windows_of_a_tile", {"narrow sparse", "narrow dense"}),
+    (dense, "test_edges_of_dense_tiles", {"narrow dense", "narrow ranked", "wide4 dense"}),
+    (dense, "test_dense_copy_of_wide_dense_tiles", {"wide4 dense"})])
+def test_kernels_that_other_tests_run(forms, monkeypatch, module, test, kernels):
+    calls = batches_of(getattr(module, test), module, monkeypatch)
+    assert {" ".join(f.split()[:2]) for f in forms(calls)} == kernels
+
+
+def test_kernels_of_entries_beyond_a_chunk(forms):
+    cases = next(m.args[1] for m in tiles.test_entries_beyond_a_chunk.pytestmark if m.args[0] == "P,units")
+    for P in sorted({P for P, _ in cases}):
+        lone, batch = forms([(1, 900_001, 60_000, P), (36, 900_001, 120_000, P)])
+        assert lone.startswith("narrow sparse")
+        assert batch.startswith("narrow ranked" if P <= 32 else "wide5 ranked" if P < 64 else "wide4 ranked"), (P, batch)
