@@ -343,11 +343,14 @@ inline ReduceShape reduce_least_shape(uint64_t width, uint64_t expected, uint32_
 // quarter is hit eight times as often, log-normal stretches of 10,000 (sigma 1), zipf (exponent 1.1, up to
 // 500 K slots).  Below: median of the times in wide tiles over those in slim ones, and how many of
 // the batches are more than 3 % slower in slim ones.  They are not taken
-// - from RED_SLIM_TO of the slots hit on, nor from RED_SLIM_FEW_TO on with fewer than RED_SLIM_FEW
-//   contributions: 5 to 7 contributions, 0.2 to 0.3 hit, in common 0.97 to 1.00 (40 % slower), log-normal
-//   1.03 (14 %), evenly 1.02 to 1.05; 8 to 32, log-normal 1.02 (20 %); 3 and 4, 0.1 to 0.13 hit, in common
-//   0.98 (41 %), log-normal 1.09 (18 %).  Below, 8 to 32 contributions that hit 0.1 to 0.2: evenly 1.12, layers
-//   1.08 (4 %), halves 1.09 (1 %), log-normal 1.05 (9 %), in common 1.05 (14 %);
+// - from 0.4 of the slots hit on, with fewer than RED_SLIM_EVEN contributions from 0.2 and with fewer than
+//   RED_SLIM_FEW from 0.1 (reduce_slim_to): 16 contributions, 0.4 / 0.5 / 0.6 hit evenly, 1.08 / 1.05 / 1.00;
+//   5 to 7, 0.2 to 0.3 hit, in common 0.97 to 1.00 (40 % slower), log-normal 1.03 (14 %), evenly 1.02 to
+//   1.05; 3 and 4, 0.1 to 0.13 hit, in common 0.98 (41 %), log-normal 1.09 (18 %).  Below, 8 to 32 contributions that
+//   hit 0.3 to 0.4: evenly 1.07, layers 1.06 (7 %), halves 1.05 (6 %), log-normal 1.01 (19 %); 0.2 to 0.3: 1.10,
+//   1.07 (3 %), 1.07 (3 %), 1.03 (19 %), in common 1.05 (13 %); 0.1 to 0.2: 1.12, 1.08 (3 %), 1.10 (1 %), 1.05 (9 %), 1.06
+//   (14 %).  (What is hit is what the capacity says, here 5 % more than it is; callers that leave more room have
+//   narrower tiles, which go by windows less often);
 // - with up to RED_FEW contributions where the bitmap limits wide tiles so that the entries of a region
 //   with 30 % in common (RED_COMMON a hit slot) still fit their registers, and slim ones have no room for
 //   as many: 17 to 32 contributions, 0.05 to 0.07 hit, in common 0.81 to 0.97;
@@ -359,12 +362,13 @@ inline ReduceShape reduce_least_shape(uint64_t width, uint64_t expected, uint32_
 //   (38 %, 0.8 at worst); in full ones layers 1.08 (3 %), halves 1.07 (8 %), in common 0.98 (38 %), zipf 1.02 (28 %);
 // - from RED_SLIM_P contributions on: their slices are short, and where they collide the windows of
 //   a slim tile read little pieces of each (129 to 256, zipf 0.96 to 1.06, in common 0.91 to 0.96 from 0.05 hit on).
-constexpr double RED_SLIM_TO = 0.2, RED_SLIM_FEW_TO = 0.1, RED_COMMON = 1.41, RED_SLIM_HITS = 3300;
+constexpr double RED_COMMON = 1.41, RED_SLIM_HITS = 3300;
 constexpr uint32_t RED_SLIM_P = 129, RED_SLIM_FEW = 5;
+constexpr double reduce_slim_to(uint32_t P) { return P < RED_SLIM_FEW ? 0.1 : P < RED_SLIM_EVEN ? 0.2 : 0.4; }
 inline bool reduce_slim_pays(const ReduceShape& slim, const ReduceShape& wide, uint64_t width, uint64_t expected, uint32_t P) {
     if (wide.kind == RED_DENSE || slim.kind == RED_DENSE || P >= RED_SLIM_P) return false;
     const double share = (double)expected / (double)width, hits = slim.slots * share;
-    if (share >= (P < RED_SLIM_FEW ? RED_SLIM_FEW_TO : RED_SLIM_TO)) return false;
+    if (share >= reduce_slim_to(P)) return false;
     if (P > RED_FEW)
         return hits <= RED_SLIM_HITS ||
                (P >= RED_MANY && slim.slots == (slim.kind == RED_SPARSE ? ReduceSlim::S_SPARSE : ReduceSlim::S_RANKED));

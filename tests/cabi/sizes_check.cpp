@@ -83,7 +83,7 @@ int main() {
             if (s.form == RED_SLIM) {
                 ranked = ReduceSlim::S_RANKED, sparse = ReduceSlim::S_SPARSE;
                 if (s.kind == RED_DENSE) fail("a dense slim tile", width, Pc);
-                if (Pc >= RED_SLIM_P || (double)expected >= RED_SLIM_TO * (double)width) fail("a slim tile where the rule has none", width, Pc);
+                if (Pc >= RED_SLIM_P || (double)expected / (double)width >= reduce_slim_to(Pc)) fail("a slim tile where the rule has none", width, Pc);
             }
             if (s.kind == RED_DENSE && s.slots != dense) fail("dense tile", width, Pc);
             if (s.kind == RED_RANKED && (s.slots > ranked || s.slots < RED_SLOTS_MIN || s.slots % 32)) fail("ranked tile", width, Pc);

@@ -65,8 +65,8 @@ def test_cases_about_wide_tiles_take_them(forms):
     # 64 to 128, planned full (30 % in common 0.92, log-normal stretches 0.93)
     [(400, 150_000, int(s * 150_000), P) for P in (64, 128) for s in (0.1, 0.15, 0.3)],
     [(27, 1_600_000, int(s * 1_600_000), 64) for s in (0.1, 0.2, 0.3)],
-    # up to 32, a good part of the slots hit; very few
-    [(100, 1_600_001, int(s * 1_600_001), P) for P in (6, 16, 32) for s in (0.201, 0.3, 0.39)],
+    # few, a good part of the slots hit
+    [(100, 1_600_001, int(s * 1_600_001), P) for P in (5, 6, 7) for s in (0.201, 0.3, 0.39)],
     [(100, 1_600_001, int(s * 1_600_001), P) for P in (3, 4) for s in (0.101, 0.15)],
 ])
 def test_no_slim_tiles_where_uneven_regions_lose(forms, calls):
@@ -75,7 +75,8 @@ def test_no_slim_tiles_where_uneven_regions_lose(forms, calls):
 
 def test_slim_tiles_where_they_gain(forms):
     calls = [(490, 1_597_315, 249_000, 16), (373, 5_250_000, 342_000, 64), (400, 400_000, 12_000, 40), (400, 800_000, 24_000, 100),
-             (60, 3_000_001, 120_000, 4), (60, 2_000_001, 380_000, 12)]
+             (60, 3_000_001, 120_000, 4), (60, 2_000_001, 380_000, 12),
+             (100, 1_600_001, 460_000, 16), (114, 3_437_500, 1_100_000, 32)]
     assert [f for f in forms(calls) if not f.startswith("slim")] == []
 
 
