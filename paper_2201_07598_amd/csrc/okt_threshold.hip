@@ -214,9 +214,10 @@ constexpr int CNT_U = 4;
 // The counting pass, with the select kernel's one-compare-per-element test.  A workgroup's
 // elements are dealt out to its waves batch by batch, so that it reads one place of the
 // vector at a time: nothing has to be in order here, and sixteen waves with a piece each read
-// sixteen (whole calls, a piece a wave and so: 80 M elements 70.3 and 68.4 us, 133 M 117 and
-// 111, 200 M 164 and 157, below 64 M and at 336 M even; pieces of a half or a quarter, for more
-// workgroups than fit at a time, lose that again: 133 M 113 and 112, 110 M 103 and 99).  Every key at or above the bound is
+// sixteen (whole calls on vectors from memory, a piece a wave and so: 64 M elements 69.4 and 67.6 us,
+// 133 M 119.5 and 113.3, 200 M 167 and 160, 110 M and 336 M even, 14 to 40 M 1 to 2 % less; even as well where
+// the vector was written just before: accumulate, threshold and select of 133 M 491.6 and 491.3; pieces
+// of a half or a quarter, for more workgroups than fit at a time, lose it again).  Every key at or above the bound is
 // a candidate and is copied to `cand`, in any order (per-wave LDS stash; a stash
 // that fills up is flushed with an atomic of its own, the rest of a workgroup
 // with one atomic at the end).
